@@ -176,7 +176,7 @@ struct ScanArgs {
 // N = 2^24).
 __device__ inline u64 quant_one(double v, double m, int K, u64 top, double &z, double &z2, U128 &q2)
 {
-    const double e = det_exp<true>(v - m);
+    const double e = det_exp(v - m);
     if (!(e >= 0.0)) return 0;  // NaN input: the max pass has flagged it
     z += e;
     z2 += e * e;

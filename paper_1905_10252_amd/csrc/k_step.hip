@@ -150,6 +150,30 @@ struct Online {
             e2[k] += ex * xv[k];
         }
     }
+    // Two particles of one coordinate each: their exponentials share the
+    // polynomial's coefficients.  A zero weight (or NaN, flagged elsewhere) and
+    // a weight that moves the reference take the one-by-one form.
+    __device__ void add2(const double (&lw)[2], const double (&xv)[2])
+    {
+        static_assert(DT == 1, "one coordinate");
+        const double hi = m + kOnlineSlack;
+        if (!(lw[0] > -__builtin_huge_val() && lw[1] > -__builtin_huge_val() && lw[0] <= hi &&
+              lw[1] <= hi)) {
+            add(lw[0], &xv[0]);
+            add(lw[1], &xv[1]);
+            return;
+        }
+        const double a[2] = {lw[0] - m, lw[1] - m};
+        double e[2];
+        det_exp_w<2>(a, e);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            e0 += e[h];
+            const double ex = e[h] * xv[h];
+            e1[0] += ex;
+            e2[0] += ex * xv[h];
+        }
+    }
     // Block combine into part = [m_b, sum e, sum e x_k, sum e x_k^2].
     __device__ void finish(double *part)
     {
@@ -220,6 +244,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     Online<DA> on;
     on.init();
     double xv[DA];
+    double mx = -__builtin_huge_val();  // 1-D Gaussian and Student-t: largest weight seen
     // The weight and what follows it, for particle i whose new row is xw
     // (and, with DT > 0, also in xv); acc and acc0 are the quadratic forms of
     // the Gaussian target and of q0.
@@ -229,14 +254,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             if (kInit) logw[i] = lq0;  // combined with log pi by k_reweight
             return;
         }
-        double lpn;
-        if (kKind == SMC_TARGET_GAUSS) {
-            lpn = a.log_norm - 0.5 * acc;
-        } else {
-            const double tt = xw[0] - a.mu;
-            const double w = 1.0 + (tt * tt) * a.inv_nu;
-            lpn = a.log_norm - a.hnu1 * det_log(w);
-        }
+        const double lpn = a.log_norm - 0.5 * acc;  // Gaussian
         const double lw = kInit ? lpn - lq0 : (uni ? a.reset : logw[i]) + (lpn - lp[i]);
         (kOut ? lpo : lp)[i] = lpn;
         logw[i] = lw;
@@ -245,37 +263,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         key = kk > key ? kk : key;
         if (DT > 0) on.add(lw, xv);
     };
-    // Log-target of a 1-D particle of the Gaussian or Student-t target: the
+    // Log-targets of W 1-D particles of the Gaussian or Student-t target: the
     // same operations as tail's, so a value recomputed from a particle equals
-    // the one computed when the particle was proposed, bit for bit.
-    auto lpt1 = [&](double v) {
+    // the one computed when the particle was proposed, bit for bit.  The
+    // previous and new values of a lane's two particles go in together, so
+    // the four logarithms share their coefficients.
+    auto lpt1 = [&](auto &v, auto &lpv) {
+        constexpr int W = sizeof(v) / sizeof(v[0]);
         if (kKind == SMC_TARGET_GAUSS) {
-            const double tt = v - a.mean[0];
-            return a.log_norm - 0.5 * ((tt * tt) * a.prec[0]);
+            const double mn = a.mean[0], pr = a.prec[0];
+#pragma unroll
+            SMC_EACH {
+                const double tt = v[w] - mn;
+                lpv[w] = a.log_norm - 0.5 * ((tt * tt) * pr);
+            }
+        } else {
+            double u[W], lg[W];
+#pragma unroll
+            SMC_EACH {
+                const double tt = v[w] - a.mu;
+                u[w] = 1.0 + (tt * tt) * a.inv_nu;
+            }
+            det_log_w<W, true>(u, lg);
+#pragma unroll
+            SMC_EACH lpv[w] = a.log_norm - a.hnu1 * lg[w];
         }
-        const double tt = v - a.mu;
-        const double w = 1.0 + (tt * tt) * a.inv_nu;
-        return a.log_norm - a.hnu1 * det_log(w);
-    };
-    // tail's weight for such a particle with new value xk, previous weight
-    // lw_old and previous log-target lp_old; returns the weight, lpn the new
-    // log-target.
-    auto weigh1 = [&](double xk, double lw_old, double lp_old, double &lpn) {
-        double lq0 = 0.0;
-        if (kInit) {
-            const double t0 = xk - a.init_mean;
-            lq0 = a.init_log_norm - 0.5 * ((t0 * t0) * a.init_prec);
-        }
-        lpn = lpt1(xk);
-        const double lw = kInit ? lpn - lq0 : lw_old + (lpn - lp_old);
-        bad |= (lw != lw) | (lw == __builtin_huge_val());
-        const u64 kk = okey(lw);
-        key = kk > key ? kk : key;
-        if (DT > 0) {
-            xv[0] = xk;
-            on.add(lw, xv);
-        }
-        return lw;
     };
     constexpr bool kMay1 = kKind != SMC_TARGET_BEARING && DT <= 1;  // d == 1 possible
     if (kMay1 && d == 1) {
@@ -318,52 +330,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
             asm volatile("" ::: "memory");
             double z[2];
-            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)p, 0u, pact, z[0], z[1],
-                             s_xch[tid >> 6]);
+            normal_pairs_wave<1>(a.seed, tag, a.sampler, tt_, (uint32_t)p, 0u, 1, pact, z,
+                                 s_xch[tid >> 6]);
             if (!pact) continue;
-            if (v2) {
-                double lwa = a.reset, lwb = a.reset;
+            if constexpr (kKind != SMC_TARGET_LOGREG) {
+                const bool two = 2 * p + 1 < n;  // false: the lone last particle of an odd n
+                double lw[2] = {a.reset, a.reset};
                 if (!kInit && !uni) {
-                    const f64x2s w = *reinterpret_cast<const f64x2s *>(logw + 2 * p);
-                    lwa = w[0];
-                    lwb = w[1];
-                }
-                double xn0 = 0.0, xn1 = 0.0, lw0 = 0.0, lw1 = 0.0;
-#pragma unroll 1
-                for (int h = 0; h < 2; ++h) {
-                    const double zh = h == 0 ? z[0] : z[1];
-                    const double xh = h == 0 ? xa0 : xa1;
-                    const double xk = kInit ? a.init_mean + a.init_sd * zh : xh + a.rw_sd * zh;
-                    double lpn;
-                    const double lw = weigh1(xk, h == 0 ? lwa : lwb, kInit ? 0.0 : lpt1(xh), lpn);
-                    // the one-workgroup iteration (N <= 2048) reads the cache
-                    if (kInit) lp[2 * p + h] = lpn;
-                    if (h == 0) {
-                        xn0 = xk;
-                        lw0 = lw;
+                    if (v2) {
+                        const f64x2s w = *reinterpret_cast<const f64x2s *>(logw + 2 * p);
+                        lw[0] = w[0];
+                        lw[1] = w[1];
                     } else {
-                        xn1 = xk;
-                        lw1 = lw;
+                        lw[0] = logw[2 * p];
+                        if (two) lw[1] = logw[2 * p + 1];
                     }
                 }
-                *reinterpret_cast<f64x2s *>((kOut ? xo : x) + 2 * p) = f64x2s{xn0, xn1};
-                *reinterpret_cast<f64x2s *>(logw + 2 * p) = f64x2s{lw0, lw1};
-                continue;
-            }
-            if constexpr (kKind != SMC_TARGET_LOGREG) {
-#pragma unroll 1
-                for (int h = 0; h < 2; ++h) {
-                    const i64 i = 2 * p + h;
-                    if (i >= n) break;
-                    const double zh = h == 0 ? z[0] : z[1];
-                    const double xh = h == 0 ? xa0 : xa1;
-                    const double xk = kInit ? a.init_mean + a.init_sd * zh : xh + a.rw_sd * zh;
-                    (kOut ? xo : x)[i] = xk;
-                    const double lw_old = (kInit || uni) ? a.reset : logw[i];
-                    double lpn;
-                    logw[i] = weigh1(xk, lw_old, kInit ? 0.0 : lpt1(xh), lpn);
-                    if (kInit) lp[i] = lpn;
+                const double xh[2] = {xa0, xa1};
+                double xk[2], lpn[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    xk[h] = kInit ? a.init_mean + a.init_sd * z[h] : xh[h] + a.rw_sd * z[h];
+                if (kInit) {
+                    lpt1(xk, lpn);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const double t0 = xk[h] - a.init_mean;
+                        lw[h] = lpn[h] - (a.init_log_norm - 0.5 * ((t0 * t0) * a.init_prec));
+                    }
+                    // the one-workgroup iteration (N <= 2048) reads the cache
+                    lp[2 * p] = lpn[0];
+                    if (two) lp[2 * p + 1] = lpn[1];
+                } else {
+                    const double v4[4] = {xh[0], xh[1], xk[0], xk[1]};
+                    double l4[4];
+                    lpt1(v4, l4);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) lw[h] = lw[h] + (l4[2 + h] - l4[h]);
                 }
+                if (v2) {
+                    *reinterpret_cast<f64x2s *>((kOut ? xo : x) + 2 * p) = f64x2s{xk[0], xk[1]};
+                    *reinterpret_cast<f64x2s *>(logw + 2 * p) = f64x2s{lw[0], lw[1]};
+                } else {
+                    (kOut ? xo : x)[2 * p] = xk[0];
+                    logw[2 * p] = lw[0];
+                    if (two) {
+                        (kOut ? xo : x)[2 * p + 1] = xk[1];
+                        logw[2 * p + 1] = lw[1];
+                    } else {
+                        lw[1] = -__builtin_huge_val();  // no particle: weight zero
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    mx = fmax(mx, lw[h]);
+                    if (!(lw[h] < __builtin_huge_val())) {  // NaN or +inf (never on a sound path)
+                        bad = 1u;
+                        const u64 kk = okey(lw[h]);
+                        key = kk > key ? kk : key;
+                    }
+                }
+                if constexpr (DT == 1) on.add2(lw, xk);
                 continue;
             }
             // logistic regression: the likelihood kernels take its weight
@@ -409,9 +436,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             // coefficients as scalar operands (coef()): 1.5 % faster here;
             // no gain for the other targets, whose uniform values already
             // fill the scalar registers
-            normal_pair_wave<true>(a.seed, tag, a.sampler, tt_, (uint32_t)i, 0u, act, z[0], z[1],
+            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)i, 0u, act, z[0], z[1],
                                    s_xch[tid >> 6]);
-            normal_pair_wave<true>(a.seed, tag, a.sampler, tt_, (uint32_t)i, 1u, act, z[2], z[3],
+            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)i, 1u, act, z[2], z[3],
                                    s_xch[tid >> 6]);
             if (!act) continue;
             double lw;
@@ -432,7 +459,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 xw[1] = n1;
                 xw[2] = n2;
                 xw[3] = n3;
-                const double e = a.obs[t - 1] - det_atan<true>(n2 / n0);
+                const double e = a.obs[t - 1] - det_atan(n2 / n0);
                 lw = (uni ? a.reset : lw0) + (a.obs_log_norm - 0.5 * ((e * e) * a.obs_prec));
             }
             logw[i] = lw;
@@ -468,6 +495,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         tail(i, xw, acc, acc0);
     }
     if (kKind == SMC_TARGET_LOGREG) return;
+    if (kMay1 && d == 1) key = okey(mx) > key ? okey(mx) : key;
     if (!kEst || DT > 0) {
         const u64 bk = block_max_key(key, bad);
         if (kEst) on.finish(is_part + (i64)blockIdx.x * (2 + 2 * DA));

@@ -1,4 +1,6 @@
-// Wave-cooperative standard normals, bit-identical to normal_pair().
+// Wave-cooperative standard normals: for pair `pair` of particle `idx`, the
+// polar method on the uniforms of attempts 0, 1, ... (at most 32) until one is
+// accepted, (0, 0) if none is.
 //
 // The polar method accepts a Philox draw with probability pi/4, so a wave of
 // 64 lanes that retries in lockstep runs about 3.5 attempts (the maximum of 64
@@ -9,7 +11,8 @@
 // lane trying one later attempt of its pair (jobs and results pass through a
 // per-wave LDS buffer).  A pair takes the lowest attempt
 // that accepted, which is the draw the sequential definition takes, and the
-// logarithm runs once per lane at the end.  All 64 lanes must call it in
+// logarithm runs once per lane at the end, for the W pairs of a lane together
+// (their polynomials share the coefficients).  All 64 lanes must call it in
 // convergent control flow; lanes without a pair pass active = false.
 #pragma once
 
@@ -20,36 +23,48 @@
 
 namespace smc {
 
+// k 2^-52 - 1 for the top 53 bits k of the 64-bit word (hi, lo), exact: both
+// parts of k are placed in the low bits of a double whose exponent gives them
+// their weight (2^21 + hi 2^-31, and 1 + (lo >> 11) 2^-52), two exact sums
+// remove the offsets.  No integer conversion, product or scaling.
+__device__ inline double unit_pm1(uint32_t hi, uint32_t lo)
+{
+    const double a = __hiloint2double(0x41400000, (int)hi);
+    const double b = __hiloint2double(0x3FF00000, (int)(lo >> 11));
+    return (a - 2097154.0) + b;
+}
+
 __device__ inline bool polar_uniforms(uint64_t seed, uint32_t tag, uint32_t sampler, uint32_t t,
                                       uint32_t idx, uint32_t sub, double &v1, double &v2)
 {
     const Philox4 w = draw(seed, tag, sampler, t, idx, sub);
-    const uint64_t b1 = ((uint64_t)w.v[1] << 32) | w.v[0];
-    const uint64_t b2 = ((uint64_t)w.v[3] << 32) | w.v[2];
-    v1 = (double)(b1 >> 11) * 0x1p-52 - 1.0;
-    v2 = (double)(b2 >> 11) * 0x1p-52 - 1.0;
+    v1 = unit_pm1(w.v[1], w.v[0]);
+    v2 = unit_pm1(w.v[3], w.v[2]);
     const double s = v1 * v1 + v2 * v2;
     return s > 0.0 && s < 1.0;
 }
 
-// xch: this wave's 64-entry exchange buffer in LDS (16 bytes a lane).  Lanes
-// of one wave read and write it in program order, so no barrier is needed.
-// kSc: the logarithm's coefficients as scalar operands (see coef()).
-template <bool kSc = false>
-__device__ inline void normal_pair_wave(uint64_t seed, uint32_t tag, uint32_t sampler, uint32_t t,
-                                        uint32_t idx, uint32_t pair, bool active, double &z1,
-                                        double &z2, uint4 *xch)
+// The accepted uniforms of one pair per lane; false (and 0, 0) for an idle
+// lane or after 32 rejections.  xch: this wave's 64-entry exchange buffer in
+// LDS (16 bytes a lane).  Lanes of one wave read and write it in program
+// order, so no barrier is needed.
+__device__ inline bool polar_wave(uint64_t seed, uint32_t tag, uint32_t sampler, uint32_t t,
+                                  uint32_t idx, uint32_t pair, bool active, double &v1,
+                                  double &v2, uint4 *xch)
 {
     constexpr uint32_t kAttempts = 32;
     const int lane = (int)__lane_id();
-    double v1 = 0.0, v2 = 0.0;
-    bool ok = active && polar_uniforms(seed, tag, sampler, t, idx, pair << 16, v1, v2);
+    v1 = v2 = 0.0;
+    bool ok = polar_uniforms(seed, tag, sampler, t, idx, pair << 16, v1, v2) && active;
     bool dead = false;         // all attempts rejected: the pair is (0, 0)
     uint32_t next = 1;         // next attempt of this lane's pair
     uint64_t pend = __ballot(active && !ok);
     while (pend) {
         const int r = __popcll(pend);
-        const int L = 64 / r;
+        // floor(64 / r) and floor(lane / L) from FP32 reciprocals of small
+        // integers, half a unit away from every rounding edge: exact
+        const int L = __builtin_amdgcn_readfirstlane(
+            (int)(64.5f * __builtin_amdgcn_rcpf((float)r)));
         const bool own = (pend >> lane) & 1ull;
         const int rank = (int)__builtin_amdgcn_mbcnt_hi(
             (unsigned)(pend >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)pend, 0u));
@@ -57,13 +72,14 @@ __device__ inline void normal_pair_wave(uint64_t seed, uint32_t tag, uint32_t sa
         // pair j (L lanes each) read entry j and try the next L attempts
         if (own) xch[rank] = make_uint4(idx, pair, next, 0u);
         __builtin_amdgcn_wave_barrier();
-        const int j = lane / L, k = lane - j * L;
+        const int j = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)L));
+        const int k = lane - j * L;
         const bool helper = j < r;
-        const uint4 job = helper ? xch[j] : make_uint4(0u, 0u, 0u, 0u);
+        const uint4 job = xch[helper ? j : 0];
         const uint32_t a = job.z + (uint32_t)k;
         double h1 = 0.0, h2 = 0.0;
-        const bool hok = helper && a < kAttempts &&
-                         polar_uniforms(seed, tag, sampler, t, job.x, (job.y << 16) | a, h1, h2);
+        const bool hok = polar_uniforms(seed, tag, sampler, t, job.x, (job.y << 16) | a, h1, h2) &&
+                         helper && a < kAttempts;
         const uint64_t acc = __ballot(hok);
         __builtin_amdgcn_wave_barrier();
         xch[lane] = make_uint4((uint32_t)__double2loint(h1), (uint32_t)__double2hiint(h1),
@@ -83,16 +99,55 @@ __device__ inline void normal_pair_wave(uint64_t seed, uint32_t tag, uint32_t sa
         __builtin_amdgcn_wave_barrier();
         pend = __ballot(own && !ok && !dead);
     }
-    if (ok) {
-        const double s = v1 * v1 + v2 * v2;
-        const double c = (-2.0 * det_log<kSc>(s)) / s;
-        const double f = det_sqrt(c);
-        z1 = v1 * f;
-        z2 = v2 * f;
-    } else {
-        z1 = 0.0;
-        z2 = 0.0;
+    return ok;
+}
+
+// W pairs per lane: pairs pair0, pair0 + 1, ... of particle idx; z[2 q], z[2 q + 1]
+// receive pair pair0 + q.  np (wave-uniform): pairs from np on are skipped.
+// s = v1^2 + v2^2 lies in [2^-104, 1), so the logarithm, quotient and root take
+// the in-range forms.
+template <int W>
+__device__ inline void normal_pairs_wave(uint64_t seed, uint32_t tag, uint32_t sampler,
+                                         uint32_t t, uint32_t idx, uint32_t pair0, int np,
+                                         bool active, double (&z)[2 * W], uint4 *xch)
+{
+    double v1[W], v2[W], s[W], c[W];
+    bool ok[W];
+#pragma unroll
+    SMC_EACH {
+        ok[w] = false;
+        if (w < np)
+            ok[w] = polar_wave(seed, tag, sampler, t, idx, pair0 + (uint32_t)w, active, v1[w],
+                               v2[w], xch);
+        if (!ok[w]) {
+            v1[w] = 0.5;  // any accepted draw: keeps the arithmetic in range
+            v2[w] = 0.0;
+        }
+        s[w] = v1[w] * v1[w] + v2[w] * v2[w];
     }
+    det_log_w<W>(s, c);
+#pragma unroll
+    SMC_EACH c[w] = -2.0 * c[w];
+    det_div_w<W>(c, s, c);
+    det_sqrt_w<W>(c, c);
+#pragma unroll
+    SMC_EACH {
+        z[2 * w] = ok[w] ? v1[w] * c[w] : 0.0;
+        z[2 * w + 1] = ok[w] ? v2[w] * c[w] : 0.0;
+        // keeps the arithmetic here: sunk under the caller's guard it would
+        // leave the coefficients behind, all of them live at once
+        asm volatile("" : "+v"(z[2 * w]), "+v"(z[2 * w + 1]));
+    }
+}
+
+__device__ inline void normal_pair_wave(uint64_t seed, uint32_t tag, uint32_t sampler, uint32_t t,
+                                        uint32_t idx, uint32_t pair, bool active, double &z1,
+                                        double &z2, uint4 *xch)
+{
+    double z[2];
+    normal_pairs_wave<1>(seed, tag, sampler, t, idx, pair, 1, active, z, xch);
+    z1 = z[0];
+    z2 = z[1];
 }
 
 }  // namespace smc
