@@ -152,7 +152,7 @@ hipError_t launch_fold(const Work &w, int par, hipStream_t s)
 __host__ __device__ constexpr int kPad(int i) { return (i & ~15) | ((i ^ (i >> 5)) & 15); }
 constexpr int kScanWaves = kScanThreads / 64;
 constexpr int kScanRow = 2 * kScanThreads;  // elements per striped row
-static_assert(kScanItems % 2 == 0 && 64 % kScanItems == 0, "scan tile shape");
+static_assert(kScanItems % 4 == 0 && 64 % kScanItems == 0, "scan tile shape");
 
 struct ScanArgs {
     const double *lw;   // quantise mode input
@@ -169,35 +169,55 @@ struct ScanArgs {
     int n_tiles;
 };
 
-// Fixed-point weight of one log-weight; accumulates the FP64 and exact sums.
-// The exponential takes its coefficients as scalar operands (coef()): with
-// sixteen of them per thread the vector moves would otherwise be a sixth of
-// the scan's vector instructions (measured: 2 to 3 us less per call at
-// N = 2^24).
-__device__ inline u64 quant_one(double v, double m, int K, u64 top, double &z, double &z2, U128 &q2)
+// Sums of one thread's fixed-point weights squared, q = h 2^26 + l: each part
+// adds up at most kScanItems products below 2^54, so plain 64-bit sums hold
+// them (one multiply-add a part; carries enter once, in total()).
+struct SqSum {
+    u64 ll = 0, hl = 0, hh = 0;
+    __device__ inline void add(u64 q)
+    {
+        const unsigned l = (unsigned)q & 0x3FFFFFFu, h = (unsigned)(q >> 26);
+        ll += (u64)l * l;
+        hl += (u64)h * l;
+        hh += (u64)h * h;
+    }
+    __device__ inline U128 total() const  // ll + hl 2^27 + hh 2^52
+    {
+        const U128 t = add128(U128{hl << 27, hl >> 37}, U128{hh << 52, hh >> 12});
+        return add128(t, ll);
+    }
+};
+static_assert(kScanItems <= 256, "SqSum: products below 2^54");
+
+// Fixed-point weights floor(2^K e), e = exp(l - m) <= 1, of W log-weights, and
+// their FP64 sums.  The integer is cut from the significand of e by one shift
+// (at least 52 - K: e = 1 gives 2^K).  A NaN gives e = 0 (the max pass has
+// flagged it).
+template <int W>
+__device__ inline void quant_w(const double (&v)[W], double m, int K, u64 (&q)[W], double &z,
+                               double &z2, SqSum &q2)
 {
-    const double e = det_exp(v - m);
-    if (!(e >= 0.0)) return 0;  // NaN input: the max pass has flagged it
-    z += e;
-    z2 += e * e;
-    const double f = floor(ldexp(e, K));
-    u64 q = (u64)f;
-    q = q > top ? top : q;
-    // q < 2^53: q = h 2^32 + l, q^2 = l^2 + 2 h l 2^32 + h^2 2^64
-    const unsigned l = (unsigned)q, h = (unsigned)(q >> 32);
-    const u64 ll = (u64)l * l, hl = (u64)h * l, hh = (u64)h * h;
-    const u64 lo1 = q2.lo + ll;
-    const u64 c1 = lo1 < ll ? 1ull : 0ull;
-    const u64 s = hl << 33;
-    const u64 lo2 = lo1 + s;
-    const u64 c2 = lo2 < s ? 1ull : 0ull;
-    q2.lo = lo2;
-    q2.hi += hh + (hl >> 31) + c1 + c2;
-    return q;
+    double a[W], e[W];
+#pragma unroll
+    SMC_EACH a[w] = v[w] - m;
+    det_exp_w<W>(a, e);
+#pragma unroll
+    SMC_EACH {
+        z += e[w];
+        z2 = fma(e[w], e[w], z2);
+        const unsigned hi = (unsigned)__double2hiint(e[w]);
+        int sh = 1075 - K - (int)(hi >> 20);
+        sh = sh > 63 ? 63 : (sh < 52 - K ? 52 - K : sh);
+        const u64 sig = ((u64)((hi & 0xFFFFFu) | 0x100000u) << 32) | (unsigned)__double2loint(e[w]);
+        q[w] = sig >> sh;
+        q2.add(q[w]);
+    }
 }
 
+// Four waves per SIMD: the LDS tile allows no more.
 template <bool kQuant>
-__global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
+__global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
+    ScanArgs a)
 {
     __shared__ u64 sq[kTile];
     __shared__ u64 s_wsum[kScanWaves];
@@ -212,14 +232,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
     const bool full = base + kTile <= n;
 
     double z = 0.0, z2 = 0.0;
-    U128 q2{0, 0};
+    SqSum sq2;
     unsigned bad = 0;
-    u64 q[kScanItems];  // striped: q[2r + h] is element base + kScanRow r + 2 tid + h
+    // striped: a thread's item 2r + h is element base + kScanRow r + 2 tid + h
     if (kQuant) {
         // every wave folds the 64 max slots itself (cached lines; no barrier)
         const double m = okey_inv(wave_max_u64(a.slots_p[lane * kSlotStride]));
         const int K = a.K;
-        const u64 top = 1ull << K;
         double v[kScanItems];
         if (full && a.vec2) {
 #pragma unroll
@@ -237,7 +256,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
             }
         }
 #pragma unroll
-        for (int e = 0; e < kScanItems; ++e) q[e] = quant_one(v[e], m, K, top, z, z2, q2);
+        for (int e = 0; e < kScanItems; e += 4) {
+            const double v4[4] = {v[e], v[e + 1], v[e + 2], v[e + 3]};
+            u64 q4[4];
+            quant_w<4>(v4, m, K, q4, z, z2, sq2);
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                sq[kPad(((e + w) >> 1) * kScanRow + 2 * tid + (w & 1))] = q4[w];
+            // one group's registers at a time: nothing of it is left for later
+            asm volatile("" : "+v"(sq2.ll), "+v"(sq2.hl), "+v"(sq2.hh), "+v"(z), "+v"(z2));
+        }
     } else {
         i64 c[kScanItems];
 #pragma unroll
@@ -249,11 +277,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
         for (int e = 0; e < kScanItems; ++e) {
             const bool ok = c[e] >= 0 && c[e] <= n;
             bad |= ok ? 0u : 1u;
-            q[e] = ok ? (u64)c[e] : 0ull;
+            sq[kPad((e >> 1) * kScanRow + 2 * tid + (e & 1))] = ok ? (u64)c[e] : 0ull;
         }
     }
-#pragma unroll
-    for (int e = 0; e < kScanItems; ++e) sq[kPad((e >> 1) * kScanRow + 2 * tid + (e & 1))] = q[e];
     __syncthreads();
 
     // sequential inclusive scan of this thread's 16 consecutive items
@@ -270,7 +296,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
     if (kQuant) {
         z = wave_sum_f64(z);
         z2 = wave_sum_f64(z2);
-        q2 = wave_sum_u128(q2);
+        const U128 q2 = wave_sum_u128(sq2.total());
         if (lane == 0) {
             s_z[wid] = z;
             s_z2[wid] = z2;
@@ -321,10 +347,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
         }
     }
     __syncthreads();
+    // the striped addresses are formed again here, not kept since the loads
+    int tid2 = 2 * tid;
+    asm volatile("" : "+v"(tid2));
     if (full) {
 #pragma unroll
         for (int r = 0; r < kScanItems / 2; ++r) {
-            const int s0 = r * kScanRow + 2 * tid;
+            const int s0 = r * kScanRow + tid2;
             ulonglong2 v;
             v.x = sq[kPad(s0)];
             v.y = sq[kPad(s0 + 1)];
@@ -333,7 +362,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArgs a)
     } else {
 #pragma unroll
         for (int e = 0; e < kScanItems; ++e) {
-            const int s0 = (e >> 1) * kScanRow + 2 * tid + (e & 1);
+            const int s0 = (e >> 1) * kScanRow + tid2 + (e & 1);
             if (base + s0 < n) a.out[base + s0] = sq[kPad(s0)];
         }
     }
