@@ -24,6 +24,8 @@
 // coarse index for the merge-path searches of the expand kernel.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "../../include/smc.h"
 #include "common.hpp"
 #include "det.hpp"
@@ -369,47 +371,83 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
 }
 
 // Exclusive prefix of the tile totals, in place, by one workgroup of 1024
-// threads (each a contiguous run of tiles); returns the grand total to every
-// thread.
-__device__ inline u64 tile_offsets(u64 *tsum, int n_tiles, u64 *s_w)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int per = (n_tiles + 1023) / 1024;
-    const int t0 = tid * per;
-    u64 run = 0;
-    for (int i = 0; i < per; ++i)
-        if (t0 + i < n_tiles) run += tsum[t0 + i];
-    const u64 incl = wave_incl_scan_u64(run);
-    if (lane == 63) s_w[wid] = incl;
-    __syncthreads();
-    u64 pre = 0, total = 0;
+// threads (each a contiguous run of tiles), in two steps around a barrier: the
+// thread's total and its scan in the wavefront, then the offsets; the second
+// returns the grand total to every thread.  The thread's totals stay in
+// registers in between (up to kRun of them).
+struct TileOffsets {
+    static constexpr int kRun = 4;  // tiles a thread at N = 2^24
+    u64 v[kRun], run, incl;
+    int per, t0;
+
+    __device__ inline void begin(const u64 *tsum, int n_tiles, u64 *s_w)
+    {
+        const int tid = threadIdx.x;
+        per = (n_tiles + 1023) / 1024;
+        t0 = tid * per;
+        run = 0;
+        if (per <= kRun) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        pre += (i < wid) ? s_w[i] : 0;
-        total += s_w[i];
-    }
-    pre += incl - run;
-    for (int i = 0; i < per; ++i)
-        if (t0 + i < n_tiles) {
-            const u64 v = tsum[t0 + i];
-            tsum[t0 + i] = pre;
-            pre += v;
+            for (int i = 0; i < kRun; ++i) {
+                v[i] = i < per && t0 + i < n_tiles ? tsum[t0 + i] : 0ull;
+                run += v[i];
+            }
+        } else {
+            for (int i = 0; i < per; ++i)
+                if (t0 + i < n_tiles) run += tsum[t0 + i];
         }
-    return total;
-}
+        incl = wave_incl_scan_u64(run);
+        if ((tid & 63) == 63) s_w[tid >> 6] = incl;
+    }
+
+    __device__ inline u64 finish(u64 *tsum, int n_tiles, const u64 *s_w) const
+    {
+        const int wid = threadIdx.x >> 6;
+        u64 pre = 0, total = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            pre += (i < wid) ? s_w[i] : 0;
+            total += s_w[i];
+        }
+        pre += incl - run;
+        if (per <= kRun) {
+#pragma unroll
+            for (int i = 0; i < kRun; ++i) {
+                if (i < per && t0 + i < n_tiles) tsum[t0 + i] = pre;
+                pre += v[i];
+            }
+        } else {
+            for (int i = 0; i < per; ++i)
+                if (t0 + i < n_tiles) {
+                    const u64 x = tsum[t0 + i];
+                    tsum[t0 + i] = pre;
+                    pre += x;
+                }
+        }
+        return total;
+    }
+};
 
 // Caller-supplied counts: tile offsets and their total (checked against N by
 // the expand).
 __global__ __launch_bounds__(1024) void k_tile_prefix(Ctrl *ctrl, u64 *tsum, int n_tiles)
 {
     __shared__ u64 s_w[16];
-    const u64 total = tile_offsets(tsum, n_tiles, s_w);
+    TileOffsets to;
+    to.begin(tsum, n_tiles, s_w);
+    __syncthreads();
+    const u64 total = to.finish(tsum, n_tiles, s_w);
     if (threadIdx.x == 0) ctrl->ctotal = total;
 }
 
 // ---------------------------------------------------------------- decision
 // One workgroup: tile offsets; tile partials summed in a fixed order
-// (reproducible FP64); exact integer decision and offset.
+// (reproducible FP64); exact integer decision and offset; with kStats also a
+// sampler iteration's estimates, c_t and recycling.  Bound by latency, so the
+// independent chains (offsets, partials, max slots, block references, the
+// state of the recycling) all start at once and share three barriers: one
+// wavefront decides while the others fold the estimate columns.
+template <bool kStats>
 __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par,
                                                  const TilePart *tpart, u64 *tsum,
                                                  int n_tiles, i64 n, int K, u64 r, int mode,
@@ -418,21 +456,25 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
 {
     __shared__ double s_z[16], s_z2[16];
     __shared__ u64 s_lo[16], s_hi[16];
-    __shared__ u64 s_key, s_w[16];
-    __shared__ unsigned s_badf;
+    __shared__ u64 s_w[16];
+    __shared__ unsigned s_err;
+    __shared__ typename std::conditional<kStats, StatsLds, int>::type s_st;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const u64 S = tile_offsets(tsum, n_tiles, s_w);
+    const RecState rec(ctrl);
+    StepStats<1024> ss;
+    double rec_old = 0.0;
+    if constexpr (kStats) {
+        if (tid < 2 * st.d) rec_old = st.rec_num[tid];
+    }
+    u64 key = 0;
+    unsigned badf = 0;
     if (wid == 0) {
-        u64 *cur = slots + (par & 1) * kSlots * kSlotStride;
+        const u64 *cur = slots + (par & 1) * kSlots * kSlotStride;
         u64 *nxt = slots + ((par & 1) ^ 1) * kSlots * kSlotStride;
-        const u64 key = wave_max_u64(cur[lane * kSlotStride]);
-        const unsigned bad = wave_or((unsigned)cur[lane * kSlotStride + 1]);
+        key = cur[lane * kSlotStride];
+        badf = (unsigned)cur[lane * kSlotStride + 1];
         nxt[lane * kSlotStride] = 0;
         nxt[lane * kSlotStride + 1] = 0;
-        if (lane == 0) {
-            s_key = key;
-            s_badf = bad;
-        }
     }
     double z = 0.0, z2 = 0.0;
     U128 q2{0, 0};
@@ -451,6 +493,9 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
             q2 = add128(q2, U128{p[u].q2lo, p[u].q2hi});
         }
     }
+    TileOffsets to;
+    to.begin(tsum, n_tiles, s_w);
+    if constexpr (kStats) ss.begin(s_st, st.is_part, st.nblk);
     z = wave_sum_f64(z);
     z2 = wave_sum_f64(z2);
     q2 = wave_sum_u128(q2);
@@ -461,71 +506,84 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
         s_hi[wid] = q2.hi;
     }
     __syncthreads();
-    if (tid == 0) {
-        double Z = s_z[0], Z2 = s_z2[0];
-        U128 Q2{s_lo[0], s_hi[0]};
-        for (int i = 1; i < 16; ++i) {
-            Z += s_z[i];
-            Z2 += s_z2[i];
-            Q2 = add128(Q2, U128{s_lo[i], s_hi[i]});
-        }
-        const u64 key = s_key;
-        const double m = okey_inv(key);
-        unsigned err = 0;
-        if (s_badf) err = kErrNonfinite;
-        else if (key <= okey(-__builtin_huge_val())) err = kErrDegenerate;
-        ctrl->mkey = key;
-        ctrl->m = m;
-        ctrl->err_call = err;
-        if (err && !ctrl->err_latch) ctrl->err_latch = err;
-        int resample;
-        if (mode == SMC_MODE_FORCE) {
-            resample = 1;
-        } else if (mode == SMC_MODE_NEVER) {
-            resample = 0;
-        } else {
-            // ess_den * S^2 < ess_num * N * Q2; both sides stay below 2^127
-            const U128 lhs = mul128_small(mul64(S, S), (u64)ess_den);
-            const U128 rhs = mul128_small(mul128_small(Q2, (u64)n), (u64)ess_num);
-            resample = lt128(lhs, rhs) ? 1 : 0;
-        }
-        if (err) resample = 0;
-        const u64 U = mul64(r, S).hi;
-        const double logZ = m + log(Z);
-        const double ess = (Z * Z) / Z2;
-        ctrl->S = S;
-        ctrl->U = U;
-        ctrl->Q2lo = Q2.lo;
-        ctrl->Q2hi = Q2.hi;
-        ctrl->Z = Z;
-        ctrl->Z2 = Z2;
-        ctrl->logZ = logZ;
-        ctrl->ess = ess;
-        ctrl->K = K;
-        ctrl->resample = (unsigned)resample;
-        ctrl->pending = err ? 0 : 1;
-        if (info) {
-            info->m = m;
-            info->logZ = logZ;
-            info->ess = ess;
-            info->Z = Z;
-            info->Z2 = Z2;
-            info->S = S;
-            info->U = U;
-            info->Q2_hi = Q2.hi;
-            info->Q2_lo = Q2.lo;
-            info->K = K;
-            info->resampled = resample;
-            info->err = (int)err;
-            info->pad = 0;
-            info->log_c = 0.0;
+    const u64 S = to.finish(tsum, n_tiles, s_w);
+    if constexpr (kStats) {
+        ss.scale(s_st, st.nblk);
+        __syncthreads();
+    }
+    if (wid == 0) {
+        // the 16 wavefronts' partials, one a lane (entries 16.. are the identity)
+        const bool in = lane < 16;
+        const double Z = wave_sum_f64(in ? s_z[lane & 15] : 0.0);
+        const double Z2 = wave_sum_f64(in ? s_z2[lane & 15] : 0.0);
+        const U128 Q2 = wave_sum_u128(in ? U128{s_lo[lane & 15], s_hi[lane & 15]} : U128{0, 0});
+        key = wave_max_u64(key);
+        badf = wave_or(badf);
+        if (lane == 0) {
+            const double m = okey_inv(key);
+            unsigned err = 0;
+            if (badf) err = kErrNonfinite;
+            else if (key <= okey(-__builtin_huge_val())) err = kErrDegenerate;
+            ctrl->mkey = key;
+            ctrl->m = m;
+            ctrl->err_call = err;
+            if (err && !ctrl->err_latch) ctrl->err_latch = err;
+            int resample;
+            if (mode == SMC_MODE_FORCE) {
+                resample = 1;
+            } else if (mode == SMC_MODE_NEVER) {
+                resample = 0;
+            } else {
+                // ess_den * S^2 < ess_num * N * Q2; both sides stay below 2^127
+                const U128 lhs = mul128_small(mul64(S, S), (u64)ess_den);
+                const U128 rhs = mul128_small(mul128_small(Q2, (u64)n), (u64)ess_num);
+                resample = lt128(lhs, rhs) ? 1 : 0;
+            }
+            if (err) resample = 0;
+            const u64 U = mul64(r, S).hi;
+            const double logZ = m + log(Z);
+            const double ess = (Z * Z) / Z2;
+            ctrl->S = S;
+            ctrl->U = U;
+            ctrl->Q2lo = Q2.lo;
+            ctrl->Q2hi = Q2.hi;
+            ctrl->Z = Z;
+            ctrl->Z2 = Z2;
+            ctrl->logZ = logZ;
+            ctrl->ess = ess;
+            ctrl->K = K;
+            ctrl->resample = (unsigned)resample;
+            ctrl->pending = err ? 0 : 1;
+            // an iteration whose decision found an error (NaN / +inf weight,
+            // all weights zero) leaves c_t, the recycling sums and the
+            // estimates as they were, as it stops at the resampling step
+            double logc = 0.0;
+            if constexpr (kStats)
+                if (!err) logc = recycle(ctrl, rec, logZ, resample != 0, s_st.bc);
+            if (info) {
+                info->m = m;
+                info->logZ = logZ;
+                info->ess = ess;
+                info->Z = Z;
+                info->Z2 = Z2;
+                info->S = S;
+                info->U = U;
+                info->Q2_hi = Q2.hi;
+                info->Q2_lo = Q2.lo;
+                info->K = K;
+                info->resampled = resample;
+                info->err = (int)err;
+                info->pad = 0;
+                info->log_c = logc;
+            }
+            s_err = err;
         }
     }
-    // a sampler iteration's statistics follow the decision in the same
-    // workgroup (they read the log Z and the decision written above)
-    if (st.is_part) {
+    if constexpr (kStats) {
+        ss.columns(s_st, st.is_part, st.nblk, 2 + 2 * st.d);
         __syncthreads();
-        step_stats_block<1024>(ctrl, st.is_part, st.nblk, st.d, st.rec_num, st.est, info, 0);
+        if (tid < 2 * st.d && !s_err)
+            write_estimates(s_st, tid, st.d, rec_old, st.rec_num, st.est);
     }
 }
 
@@ -533,8 +591,9 @@ hipError_t launch_decide(const Work &w, int par, int64_t n, int K, uint64_t r, i
                          int ess_num, int ess_den, void *info, hipStream_t s,
                          const StatsArgs &st)
 {
-    hipLaunchKernelGGL(k_decide, dim3(1), dim3(1024), 0, s, w.ctrl, w.slots, par, w.tpart,
-                       w.tsum, w.n_tiles, (i64)n, K, (u64)r, mode, ess_num, ess_den,
+    auto kern = st.is_part ? k_decide<true> : k_decide<false>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, w.ctrl, w.slots, par, w.tpart, w.tsum,
+                       w.n_tiles, (i64)n, K, (u64)r, mode, ess_num, ess_den,
                        reinterpret_cast<smc_resample_info *>(info), st);
     return hipGetLastError();
 }

@@ -72,45 +72,7 @@ constexpr double kLog2e = 1.4426950408889634;
 constexpr double kLn2 = 0.6931471805599453;
 
 // ------------------------------------------------------------------ partials
-// Per-block sums for the estimates with the block's own max (rescaled later):
-// part = [m_b, sum e, sum e x_k (k < d), sum e x_k^2 (k < d)], e = exp(l - m_b).
-__device__ inline void is_block_finish(i64 n, int d, const double *x, const double *logw, u64 key,
-                                       unsigned bad, u64 *slots_p, double *is_part)
-{
-    __shared__ double s_acc[4][2 + 2 * kMaxDim];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const i64 gtid = (i64)blockIdx.x * 256 + tid, gsz = (i64)gridDim.x * 256;
-    const u64 bk = block_max_key(key, bad);
-    const double mb = okey_inv(bk);
-    const bool live = mb > -__builtin_huge_val() && mb == mb;
-    double e0 = 0.0;
-    for (i64 i = gtid; i < n; i += gsz) e0 += live ? det_exp(logw[i] - mb) : 0.0;
-    e0 = wave_sum_f64(e0);
-    if (lane == 0) s_acc[wid][1] = e0;
-    for (int k = 0; k < d; ++k) {
-        double s1 = 0.0, s2 = 0.0;
-        for (i64 i = gtid; i < n; i += gsz) {
-            const double e = live ? det_exp(logw[i] - mb) : 0.0;
-            const double ex = e * x[i * d + k];
-            s1 += ex;
-            s2 += ex * x[i * d + k];
-        }
-        s1 = wave_sum_f64(s1);
-        s2 = wave_sum_f64(s2);
-        if (lane == 0) {
-            s_acc[wid][2 + k] = s1;
-            s_acc[wid][2 + d + k] = s2;
-        }
-    }
-    __syncthreads();
-    const int ncol = 2 + 2 * d;
-    double *part = is_part + (i64)blockIdx.x * ncol;
-    for (int c = tid; c < ncol; c += 256)
-        part[c] = c == 0 ? mb : ((s_acc[0][c] + s_acc[1][c]) + s_acc[2][c]) + s_acc[3][c];
-    slot_publish(slots_p, bk, bad);
-}
-
-// One-pass variant for small d (the row stays in registers): each thread keeps
+// Estimate sums of the 1-D updates, in one pass: each thread keeps
 // a reference and sums e = exp(l - ref), so the rows are read once; blocks
 // combine the thread references by det_exp rescaling.  The reference is the
 // first finite weight and moves (rescaling the sums) only when a weight exceeds
@@ -119,48 +81,41 @@ __device__ inline void is_block_finish(i64 n, int d, const double *x, const doub
 // maximum, which in a wave of 64 lanes happened on most iterations.
 constexpr double kOnlineSlack = 64.0;
 
-template <int DT>
 struct Online {
-    double m, e0, e1[DT], e2[DT];
+    double m, e0, e1, e2;
     __device__ void init()
     {
         m = -__builtin_huge_val();
-        e0 = 0.0;
-        for (int k = 0; k < DT; ++k) e1[k] = e2[k] = 0.0;
+        e0 = e1 = e2 = 0.0;
     }
-    __device__ void add(double lw, const double *xv)
+    __device__ void add(double lw, double xv)
     {
         if (!(lw > -__builtin_huge_val())) return;  // zero weight, or NaN (flagged elsewhere)
         if (lw > m + kOnlineSlack) {
             if (m > -__builtin_huge_val()) {
                 const double sc = det_exp(m - lw);
                 e0 *= sc;
-                for (int k = 0; k < DT; ++k) {
-                    e1[k] *= sc;
-                    e2[k] *= sc;
-                }
+                e1 *= sc;
+                e2 *= sc;
             }
             m = lw;
         }
         const double e = det_exp(lw - m);
         e0 += e;
-        for (int k = 0; k < DT; ++k) {
-            const double ex = e * xv[k];
-            e1[k] += ex;
-            e2[k] += ex * xv[k];
-        }
+        const double ex = e * xv;
+        e1 += ex;
+        e2 += ex * xv;
     }
-    // Two particles of one coordinate each: their exponentials share the
-    // polynomial's coefficients.  A zero weight (or NaN, flagged elsewhere) and
-    // a weight that moves the reference take the one-by-one form.
+    // Two particles: their exponentials share the polynomial's coefficients.
+    // A zero weight (or NaN) and a weight that moves the reference take the
+    // one-by-one form.
     __device__ void add2(const double (&lw)[2], const double (&xv)[2])
     {
-        static_assert(DT == 1, "one coordinate");
         const double hi = m + kOnlineSlack;
         if (!(lw[0] > -__builtin_huge_val() && lw[1] > -__builtin_huge_val() && lw[0] <= hi &&
               lw[1] <= hi)) {
-            add(lw[0], &xv[0]);
-            add(lw[1], &xv[1]);
+            add(lw[0], xv[0]);
+            add(lw[1], xv[1]);
             return;
         }
         const double a[2] = {lw[0] - m, lw[1] - m};
@@ -170,30 +125,24 @@ struct Online {
         for (int h = 0; h < 2; ++h) {
             e0 += e[h];
             const double ex = e[h] * xv[h];
-            e1[0] += ex;
-            e2[0] += ex * xv[h];
+            e1 += ex;
+            e2 += ex * xv[h];
         }
     }
-    // Block combine into part = [m_b, sum e, sum e x_k, sum e x_k^2].
-    __device__ void finish(double *part)
+    // Block combine into the block's partial row (columns at stride gridDim.x).
+    __device__ void finish(double *is_part)
     {
-        __shared__ double s_m[4], s_acc[4][1 + 2 * DT];
+        __shared__ double s_m[4], s_acc[4][3];
         const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
         const double mw = wave_max_f64(m);
         const double sc = m > -__builtin_huge_val() ? det_exp(m - mw) : 0.0;
-        const double a0 = wave_sum_f64(e0 * sc);
-        double a1[DT], a2[DT];
-        for (int k = 0; k < DT; ++k) {
-            a1[k] = wave_sum_f64(e1[k] * sc);
-            a2[k] = wave_sum_f64(e2[k] * sc);
-        }
+        const double a0 = wave_sum_f64(e0 * sc), a1 = wave_sum_f64(e1 * sc),
+                     a2 = wave_sum_f64(e2 * sc);
         if (lane == 0) {
             s_m[wid] = mw;
             s_acc[wid][0] = a0;
-            for (int k = 0; k < DT; ++k) {
-                s_acc[wid][1 + k] = a1[k];
-                s_acc[wid][1 + DT + k] = a2[k];
-            }
+            s_acc[wid][1] = a1;
+            s_acc[wid][2] = a2;
         }
         __syncthreads();
         if (tid == 0) {
@@ -202,11 +151,12 @@ struct Online {
             double scw[4];
             for (int w = 0; w < 4; ++w)
                 scw[w] = s_m[w] > -__builtin_huge_val() ? det_exp(s_m[w] - mb) : 0.0;
+            double *part = is_part + blockIdx.x;
             part[0] = mb;
-            for (int c = 0; c < 1 + 2 * DT; ++c) {
+            for (int c = 0; c < 3; ++c) {
                 double v = 0.0;
                 for (int w = 0; w < 4; ++w) v += scw[w] * s_acc[w][c];
-                part[1 + c] = v;
+                part[(i64)(1 + c) * gridDim.x] = v;
             }
         }
     }
@@ -214,58 +164,40 @@ struct Online {
 
 // ------------------------------------------------------- proposal + weights
 typedef double f64x2s __attribute__((ext_vector_type(2)));
-// DT > 0: d == DT and the estimate sums are accumulated in one pass; DT == 0:
-// any d, sums in a second pass over the block's particles.  The particle filter
-// takes its estimate after resampling, so its update kernel skips them.
-// kOut: the proposal and its log-target go to xo / lpo (the redistribution
-// then maps them back into x); otherwise they overwrite x / lp in place.
-// At least four waves per SIMD (up to 128 VGPRs): the 1-D Gaussian and
-// Student-t updates need 102-110 VGPRs and the 4-D Gaussian ones 116-119;
-// held to 96 for five waves they spilled 20-92 bytes a lane, and the Student-t
-// iteration at N = 2^24 ran 6 % slower.  The other instances need fewer
-// registers and keep six or seven waves.
-template <int kKind, bool kInit, int DT, bool kOut>
+// The update of one-coordinate particles (Gaussian and Student-t targets, the
+// estimate sums in the same pass) and of the particle filter, which takes its
+// estimate after resampling.  k_rows below is the update of longer rows.
+// kOut: the proposal goes to xo (the redistribution then maps it back into
+// x); otherwise it overwrites x in place.
+template <int kKind, bool kInit, bool kOut>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_is(
     TArgs a, i64 n, uint32_t t, double *__restrict__ x, double *__restrict__ logw,
-    double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo,
-    double *__restrict__ lpo)
+    double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo)
 {
-    constexpr bool kEst = kKind != SMC_TARGET_BEARING;
-    constexpr int DA = DT > 0 ? DT : 1;
+    constexpr bool kFilter = kKind == SMC_TARGET_BEARING;
     __shared__ uint4 s_xch[4][64];  // normal generator exchange, one row per wave
     const int tid = threadIdx.x;
     const i64 gtid = (i64)blockIdx.x * 256 + tid, gsz = (i64)gridDim.x * 256;
-    const int d = DT == 1 ? 1 : a.d;  // DT > 0 is launched only for d == DT
     const bool uni = !kInit && a.uniform && *a.uniform;  // lazy reset: weights are -ln N
     const uint32_t tag = kInit ? (uint32_t)kTagInit : (uint32_t)kTagPropose;
     const uint32_t tt_ = kInit ? 0u : t;
     u64 key = 0;
     unsigned bad = 0;
-    Online<DA> on;
+    double mx = -__builtin_huge_val();  // largest weight seen
+    Online on;
     on.init();
-    double xv[DA];
-    double mx = -__builtin_huge_val();  // 1-D Gaussian and Student-t: largest weight seen
-    // The weight and what follows it, for particle i whose new row is xw
-    // (and, with DT > 0, also in xv); acc and acc0 are the quadratic forms of
-    // the Gaussian target and of q0.
-    auto tail = [&](i64 i, const double *xw, double acc, double acc0) {
-        const double lq0 = kInit ? a.init_log_norm - 0.5 * acc0 : 0.0;
-        if (kKind == SMC_TARGET_LOGREG) {
-            if (kInit) logw[i] = lq0;  // combined with log pi by k_reweight
-            return;
+    // the largest weight, and a flag for NaN or +inf (never on a sound path)
+    auto note = [&](double lw) {
+        mx = fmax(mx, lw);
+        if (!(lw < __builtin_huge_val())) {
+            bad = 1u;
+            const u64 kk = okey(lw);
+            key = kk > key ? kk : key;
         }
-        const double lpn = a.log_norm - 0.5 * acc;  // Gaussian
-        const double lw = kInit ? lpn - lq0 : (uni ? a.reset : logw[i]) + (lpn - lp[i]);
-        (kOut ? lpo : lp)[i] = lpn;
-        logw[i] = lw;
-        bad |= (lw != lw) | (lw == __builtin_huge_val());
-        const u64 kk = okey(lw);
-        key = kk > key ? kk : key;
-        if (DT > 0) on.add(lw, xv);
     };
-    // Log-targets of W 1-D particles of the Gaussian or Student-t target: the
-    // same operations as tail's, so a value recomputed from a particle equals
-    // the one computed when the particle was proposed, bit for bit.  The
+    // Log-targets of W 1-D particles of the Gaussian or Student-t target: always
+    // the same operations, so a value recomputed from a particle equals the one
+    // computed when the particle was proposed, bit for bit.  The
     // previous and new values of a lane's two particles go in together, so
     // the four logarithms share their coefficients.
     auto lpt1 = [&](auto &v, auto &lpv) {
@@ -289,8 +221,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             SMC_EACH lpv[w] = a.log_norm - a.hnu1 * lg[w];
         }
     };
-    constexpr bool kMay1 = kKind != SMC_TARGET_BEARING && DT <= 1;  // d == 1 possible
-    if (kMay1 && d == 1) {
+    if constexpr (!kFilter) {
         // One coordinate a particle: particles 2p and 2p + 1 take the two
         // values of the pair drawn for index p, so each lane draws one pair
         // for two particles (a wave-uniform trip count over the pairs).  The
@@ -301,14 +232,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         // The initial pass still writes it, for the one-workgroup iteration
         // that small populations step with.
         const i64 np = (n + 1) >> 1;
-        // v2 (n even, 16-byte aligned arrays, Gaussian or Student-t target): a
-        // lane moves its two particles' values as one 16-byte access per
+        // v2 (n even, 16-byte aligned arrays): a lane moves its two particles' values as one 16-byte access per
         // array, so every wave instruction uses whole cache lines (about 2 %
         // faster per iteration at N = 2^24); otherwise 8-byte accesses
-        const uintptr_t al = (uintptr_t)x | (uintptr_t)logw | (uintptr_t)lp | (uintptr_t)xo |
-                             (uintptr_t)lpo;
-        const bool v2 = kKind != SMC_TARGET_LOGREG && (n & 1) == 0 && (al & 15) == 0 &&
-                        a.thb == nullptr;
+        const uintptr_t al = (uintptr_t)x | (uintptr_t)logw | (uintptr_t)xo;
+        const bool v2 = (n & 1) == 0 && (al & 15) == 0;
         for (i64 base = gtid - (tid & 63); base < np; base += gsz) {
             const i64 p = base + (tid & 63);
             const bool pact = p < np;
@@ -330,10 +258,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
             asm volatile("" ::: "memory");
             double z[2];
-            normal_pairs_wave<1>(a.seed, tag, a.sampler, tt_, (uint32_t)p, 0u, 1, pact, z,
-                                 s_xch[tid >> 6]);
+            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)p, 0u, pact, z[0], z[1],
+                             s_xch[tid >> 6]);
             if (!pact) continue;
-            if constexpr (kKind != SMC_TARGET_LOGREG) {
+            {
                 const bool two = 2 * p + 1 < n;  // false: the lone last particle of an odd n
                 double lw[2] = {a.reset, a.reset};
                 if (!kInit && !uni) {
@@ -381,51 +309,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                         lw[1] = -__builtin_huge_val();  // no particle: weight zero
                     }
                 }
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    mx = fmax(mx, lw[h]);
-                    if (!(lw[h] < __builtin_huge_val())) {  // NaN or +inf (never on a sound path)
-                        bad = 1u;
-                        const u64 kk = okey(lw[h]);
-                        key = kk > key ? kk : key;
-                    }
-                }
-                if constexpr (DT == 1) on.add2(lw, xk);
-                continue;
-            }
-            // logistic regression: the likelihood kernels take its weight
-#pragma unroll 1
-            for (int h = 0; h < 2; ++h) {
-                const i64 i = 2 * p + h;
-                if (i >= n) break;
-                double *xw = (kOut ? xo : x) + i;
-                const double zh = h == 0 ? z[0] : z[1];
-                const double xh = h == 0 ? xa0 : xa1;
-                const double xk = kInit ? a.init_mean + a.init_sd * zh : xh + a.rw_sd * zh;
-                xw[0] = xk;
-                if (DT > 0) xv[0] = xk;
-                if (a.thb) a.thb[i * a.dp] = to_bf16(xk * kLog2e);
-                double acc = 0.0, acc0 = 0.0;
-                if (kKind == SMC_TARGET_GAUSS) {
-                    const double tt = xk - a.mean[0];
-                    acc = acc + (tt * tt) * a.prec[0];
-                }
-                if (kInit) {
-                    const double t0 = xk - a.init_mean;
-                    acc0 = acc0 + (t0 * t0) * a.init_prec;
-                }
-                tail(i, xw, acc, acc0);
+                note(lw[0]);
+                note(lw[1]);
+                on.add2(lw, xk);
             }
         }
-    }
-    // wave-uniform trip count: the normal generator is wave-cooperative
-    for (i64 base = gtid - (tid & 63); base < (kMay1 && d == 1 ? 0 : n); base += gsz) {
-        const i64 i = base + (tid & 63);
-        const bool act = i < n;
-        double *xi = x + i * d;
-        double *xw = (kOut ? xo : x) + i * d;
-        if (kKind == SMC_TARGET_BEARING) {
-            double z[4];
+    } else {
+        // wave-uniform trip count: the normal generator is wave-cooperative
+        for (i64 base = gtid - (tid & 63); base < n; base += gsz) {
+            const i64 i = base + (tid & 63);
+            const bool act = i < n;
+            double *xi = x + i * 4;
+            double *xw = (kOut ? xo : x) + i * 4;
             // the particle's state and weight are requested before the
             // normals are drawn, so the loads overlap the generator
             const i64 ic = act ? i : 0;
@@ -433,13 +328,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const double s2 = kInit ? 0.0 : x[ic * 4 + 2], s3 = kInit ? 0.0 : x[ic * 4 + 3];
             const double lw0 = (kInit || uni) ? 0.0 : logw[ic];
             asm volatile("" ::: "memory");
-            // coefficients as scalar operands (coef()): 1.5 % faster here;
-            // no gain for the other targets, whose uniform values already
-            // fill the scalar registers
-            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)i, 0u, act, z[0], z[1],
-                                   s_xch[tid >> 6]);
-            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)i, 1u, act, z[2], z[3],
-                                   s_xch[tid >> 6]);
+            const uint32_t idx[2] = {(uint32_t)i, (uint32_t)i}, pair[2] = {0u, 1u};
+            const bool act2[2] = {act, act};
+            double z[4];
+            normal_pairs_wave<2>(a.seed, tag, a.sampler, tt_, idx, pair, 2, act2, z,
+                                 s_xch[tid >> 6]);
             if (!act) continue;
             double lw;
             if (kInit) {
@@ -463,80 +356,328 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 lw = (uni ? a.reset : lw0) + (a.obs_log_norm - 0.5 * ((e * e) * a.obs_prec));
             }
             logw[i] = lw;
-            bad |= (lw != lw) | (lw == __builtin_huge_val());
-            const u64 kk = okey(lw);
-            key = kk > key ? kk : key;
-            continue;
+            note(lw);
         }
-        double acc = 0.0, acc0 = 0.0;
-        for (int k = 0; 2 * k < d; ++k) {
-            double z[2];
-            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)i, (uint32_t)k, act, z[0],
-                             z[1], s_xch[tid >> 6]);
-            if (!act) continue;
-            for (int h = 0; h < 2; ++h) {
-                const int kk = 2 * k + h;
-                if (kk >= d) break;
-                const double xk = kInit ? a.init_mean + a.init_sd * z[h] : xi[kk] + a.rw_sd * z[h];
-                xw[kk] = xk;
-                if (DT > 0 && kk < DT) xv[kk] = xk;
-                if (a.thb) a.thb[i * a.dp + kk] = to_bf16(xk * kLog2e);
-                if (kKind == SMC_TARGET_GAUSS) {
-                    const double tt = xk - a.mean[kk];
-                    acc = acc + (tt * tt) * a.prec[kk];
-                }
-                if (kInit) {
-                    const double t0 = xk - a.init_mean;
-                    acc0 = acc0 + (t0 * t0) * a.init_prec;
+    }
+    key = okey(mx) > key ? okey(mx) : key;
+    const u64 bk = block_max_key(key, bad);
+    if (!kFilter) on.finish(is_part);
+    slot_publish(slots_p, bk, bad);
+}
+
+// ------------------------------------------------ rows of several coordinates
+// Draws the proposal (or x0) of particles [base, base + cnt) with d >= 2
+// coordinates by the whole workgroup: one (particle, pair) a thread, two at a
+// time (the normals share their coefficients), neighbouring threads on
+// neighbouring addresses.  put(p, c, two, v0, v1): coordinates c and, if two,
+// c + 1 of particle base + p.  total: values in x (an odd 1-D population drawn
+// as rows of two ends early).  One thread per particle instead, walking its
+// row, touched a cache line per lane and access and left most of the chip
+// idle below 10^5 particles.
+template <bool kInit, class Put>
+__device__ inline void draw_rows(const TArgs &a, int d, i64 base, int cnt, i64 total, uint32_t t,
+                                 const double *x, uint4 *xch, Put &&put)
+{
+    constexpr int W = 2;
+    const uint32_t tag = kInit ? (uint32_t)kTagInit : (uint32_t)kTagPropose;
+    const int np = (d + 1) >> 1, items = cnt * np, tid = threadIdx.x;
+    const float inv = 1.0f / (float)np;  // quotients below 2^14, half a unit from every edge
+    const bool v2 = (d & 1) == 0 && ((uintptr_t)x & 15) == 0 && (total & 1) == 0;
+    for (int i0 = 0; i0 < items; i0 += 256 * W) {
+        int p[W], c[W];
+        uint32_t idx[W], pair[W];
+        bool act[W], two[W];
+        double x0[W], x1[W], z[2 * W];
+#pragma unroll
+        SMC_EACH {
+            const int it = i0 + 256 * w + tid;
+            act[w] = it < items;
+            p[w] = (int)(((float)(act[w] ? it : 0) + 0.5f) * inv);
+            c[w] = 2 * ((act[w] ? it : 0) - p[w] * np);
+            idx[w] = (uint32_t)(base + p[w]);
+            pair[w] = (uint32_t)c[w] >> 1;
+            const i64 o = (base + p[w]) * d + c[w];
+            two[w] = c[w] + 1 < d && o + 1 < total;
+            x0[w] = x1[w] = 0.0;
+            if (!kInit) {
+                if (v2) {
+                    const f64x2s v = *reinterpret_cast<const f64x2s *>(x + o);
+                    x0[w] = v[0];
+                    x1[w] = v[1];
+                } else {
+                    x0[w] = x[o];
+                    x1[w] = x[two[w] ? o + 1 : o];
                 }
             }
         }
-        if (!act) continue;
-        tail(i, xw, acc, acc0);
+        asm volatile("" ::: "memory");  // the loads overlap the generator
+        normal_pairs_wave<W>(a.seed, tag, a.sampler, kInit ? 0u : t, idx, pair,
+                             i0 + 256 < items ? 2 : 1, act, z, xch + (tid & ~63));
+#pragma unroll
+        SMC_EACH {
+            if (!act[w]) continue;
+            if (kInit)
+                put(p[w], c[w], two[w], a.init_mean + a.init_sd * z[2 * w],
+                    a.init_mean + a.init_sd * z[2 * w + 1]);
+            else
+                put(p[w], c[w], two[w], x0[w] + a.rw_sd * z[2 * w], x1[w] + a.rw_sd * z[2 * w + 1]);
+        }
     }
-    if (kKind == SMC_TARGET_LOGREG) return;
-    if (kMay1 && d == 1) key = okey(mx) > key ? okey(mx) : key;
-    if (!kEst || DT > 0) {
-        const u64 bk = block_max_key(key, bad);
-        if (kEst) on.finish(is_part + (i64)blockIdx.x * (2 + 2 * DA));
-        slot_publish(slots_p, bk, bad);
-        return;
-    }
-    is_block_finish(n, d, kOut ? xo : x, logw, key, bad, slots_p, is_part);
 }
 
-template <bool kInit>
-__global__ __launch_bounds__(256) void k_reweight(i64 n, int d, const double *__restrict__ x,
-                                                  const double *__restrict__ lp_new,
-                                                  double *__restrict__ logw,
-                                                  double *__restrict__ lp, u64 *slots_p,
-                                                  double *is_part, const unsigned *uniform,
-                                                  double reset)
+// Particles of a workgroup of k_rows / k_propose: a power of two with at most
+// 24 KB of rows in LDS (six workgroups on a CU), smaller where the population
+// would otherwise make fewer than two workgroups per CU.
+inline int rows_per_block(int64_t n, int d)
 {
-    const int tid = threadIdx.x;
-    const i64 gtid = (i64)blockIdx.x * 256 + tid, gsz = (i64)gridDim.x * 256;
-    const bool uni = !kInit && uniform && *uniform;
+    const int ds = d | 1;
+    int P = 256;
+    while (P > 32 && P * ds * 8 > 24 * 1024) P >>= 1;
+    while (P > 32 && n < 512ll * P) P >>= 1;
+    return P;
+}
+
+inline int64_t row_chunks(int64_t n, int d)
+{
+    const int P = rows_per_block(n, d);
+    return (n + P - 1) / P;
+}
+
+// Proposal of the logistic regression's particles (its log-target comes from
+// the likelihood kernels, its weights from k_rows).  With d = 1 particles 2p
+// and 2p + 1 take the pair drawn for index p: rows of two values.
+template <bool kInit>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_propose(
+    TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x)
+{
+    __shared__ uint4 s_xch[256];
+    const int dv = a.d == 1 ? 2 : a.d;
+    const i64 rows = a.d == 1 ? (n + 1) >> 1 : n;
+    const i64 base = (i64)blockIdx.x * P;
+    if (base >= rows) return;
+    const int cnt = (int)(rows - base < P ? rows - base : P);
+    draw_rows<kInit>(a, dv, base, cnt, n * a.d, t, x, s_xch,
+                     [&](int p, int c, bool two, double v0, double v1) {
+                         const i64 o = (base + p) * dv + c;
+                         x[o] = v0;
+                         if (two) x[o + 1] = v1;
+                         if (a.thb) {
+                             // particle and column of value o (rows of two: one column)
+                             const i64 i0 = a.d == 1 ? o : base + p;
+                             const int k0 = a.d == 1 ? 0 : c;
+                             a.thb[i0 * a.dp + k0] = to_bf16(v0 * kLog2e);
+                             if (two)
+                                 a.thb[(a.d == 1 ? o + 1 : i0) * a.dp + (a.d == 1 ? 0 : k0 + 1)] =
+                                     to_bf16(v1 * kLog2e);
+                         }
+                     });
+}
+
+// What the weight of a logistic-regression particle needs beside its row.
+struct LrArgs {
+    const double *lpart;  // [msplit][n] partial log-likelihoods
+    int msplit;
+    const double *csum;   // [d] column sums of X (1 - 2 y)
+    double usc, prior_prec;
+    int bf16;
+};
+
+// log pi of a logistic-regression particle from its row (element k at
+// row[k]) and the sum of its partial likelihoods: log_norm - prior_prec
+// |theta|^2 / 2 + lik - usc (theta' . csum), theta' the bf16 copy (it holds
+// theta log2 e) in that precision and theta otherwise.
+__device__ inline double logreg_lp_row(const double *row, int d, double lik, const double *csum,
+                                       const LrArgs &lr, double log_norm)
+{
+    double pr = 0.0, su = 0.0;
+    for (int k = 0; k < d; ++k) {
+        const double v = row[k];
+        pr += v * v;
+        su += (lr.bf16 ? from_bf16(to_bf16(v * kLog2e)) : v) * csum[k];
+    }
+    return log_norm - 0.5 * lr.prior_prec * pr + (lik - lr.usc * su);
+}
+
+// The update of particles with d >= 2 coordinates (any d for the logistic
+// regression): rows drawn (Gaussian) or read (logistic regression) into LDS by
+// the whole workgroup, then one thread per particle for the target and weight,
+// then the estimate sums with threads over (column, share of the particles).
+// Sums are against the workgroup's reference weight, the first chunk's maximum,
+// moved only when a weight exceeds it by kOnlineSlack nats.  Rows are touched
+// once in memory; a second pass over the population for the estimates, with
+// the exponential formed again for every coordinate, took 30 of 50 us at
+// N = 300007, d = 10.  Bound by vector issue of the normals.
+template <int kKind, bool kInit, bool kOut>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows(
+    TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x, double *__restrict__ logw,
+    double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo,
+    double *__restrict__ lpo, LrArgs lr)
+{
+    extern __shared__ double s_dyn[];  // [P][d | 1] rows, [P] exponentials
+    __shared__ uint4 s_buf[256];       // generator exchange, then the last reduction
+    __shared__ double s_par[2][kMaxDim];
+    __shared__ double s_w[4];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int d = a.d, ds = d | 1;
+    double *rows = s_dyn, *s_e = s_dyn + P * ds;
+    const bool uni = !kInit && a.uniform && *a.uniform;  // lazy reset: weights are -ln N
+    const double ninf = -__builtin_huge_val();
+    if (tid < d) {
+        s_par[0][tid] = kKind == SMC_TARGET_GAUSS ? a.mean[tid] : lr.csum[tid];
+        if (kKind == SMC_TARGET_GAUSS) s_par[1][tid] = a.prec[tid];
+    }
+    const int parts = 256 / d, part = tid / d, col = tid - part * d;
+    const float inv = 1.0f / (float)d;
     u64 key = 0;
     unsigned bad = 0;
-    for (i64 i = gtid; i < n; i += gsz) {
-        const double lpn = lp_new[i];
-        const double lw = kInit ? lpn - logw[i] : (uni ? reset : logw[i]) + (lpn - lp[i]);
-        lp[i] = lpn;
-        logw[i] = lw;
-        bad |= (lw != lw) | (lw == __builtin_huge_val());
-        const u64 kk = okey(lw);
-        key = kk > key ? kk : key;
+    double ref = ninf, e0 = 0.0, s1 = 0.0, s2 = 0.0;
+    for (i64 base = (i64)blockIdx.x * P; base < n; base += (i64)gridDim.x * P) {
+        const int cnt = (int)(n - base < P ? n - base : P);
+        const i64 i = base + tid;
+        const bool act = tid < cnt;
+        double lw_old = 0.0, lp_old = 0.0, lik = 0.0;
+        if (act && !kInit) {
+            lw_old = uni ? a.reset : logw[i];
+            lp_old = lp[i];
+        }
+        if (kKind == SMC_TARGET_GAUSS) {
+            draw_rows<kInit>(a, d, base, cnt, n * d, t, x, s_buf,
+                             [&](int p, int c, bool two, double v0, double v1) {
+                                 const i64 o = (base + p) * d + c;
+                                 (kOut ? xo : x)[o] = v0;
+                                 rows[p * ds + c] = v0;
+                                 if (two) {
+                                     (kOut ? xo : x)[o + 1] = v1;
+                                     rows[p * ds + c + 1] = v1;
+                                 }
+                             });
+        } else {
+            if (act)
+                for (int j = 0; j < lr.msplit; ++j) lik += lr.lpart[(i64)j * n + i];
+            constexpr int U = 4;
+            for (int q0 = tid; q0 < cnt * d; q0 += 256 * U) {
+                double v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = q0 + 256 * u;
+                    v[u] = x[base * d + (q < cnt * d ? q : q0)];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = q0 + 256 * u;
+                    const int p = (int)(((float)q + 0.5f) * inv);
+                    if (q < cnt * d) rows[p * ds + (q - p * d)] = v[u];
+                }
+            }
+        }
+        __syncthreads();
+        double lw = ninf;
+        if (act) {
+            const double *row = rows + tid * ds;
+            double acc = 0.0, acc0 = 0.0, lpn;
+            if (kKind == SMC_TARGET_GAUSS || kInit) {
+                for (int k = 0; k < d; ++k) {
+                    if (kKind == SMC_TARGET_GAUSS) {
+                        const double tt = row[k] - s_par[0][k];
+                        acc = acc + (tt * tt) * s_par[1][k];
+                    }
+                    if (kInit) {
+                        const double t0 = row[k] - a.init_mean;
+                        acc0 = acc0 + (t0 * t0) * a.init_prec;
+                    }
+                }
+            }
+            if (kKind == SMC_TARGET_GAUSS) lpn = a.log_norm - 0.5 * acc;
+            else lpn = logreg_lp_row(row, d, lik, s_par[0], lr, a.log_norm);
+            lw = kInit ? lpn - (a.init_log_norm - 0.5 * acc0) : lw_old + (lpn - lp_old);
+            (kOut ? lpo : lp)[i] = lpn;
+            logw[i] = lw;
+            bad |= !(lw < __builtin_huge_val());  // NaN or +inf
+            const u64 kk = okey(lw);
+            key = kk > key ? kk : key;
+        }
+        const double wm = wave_max_f64(lw);
+        if (lane == 0) s_w[wid] = wm;
+        __syncthreads();
+        const double cm = fmax(fmax(s_w[0], s_w[1]), fmax(s_w[2], s_w[3]));
+        if (ref == ninf ? cm > ninf : cm > ref + kOnlineSlack) {  // uniform over the workgroup
+            const double sc = ref == ninf ? 0.0 : det_exp(ref - cm);
+            e0 *= sc;
+            s1 *= sc;
+            s2 *= sc;
+            ref = cm;
+        }
+        const double e = lw > ninf ? det_exp(lw - ref) : 0.0;
+        e0 += e;
+        if (act) s_e[tid] = e;
+        __syncthreads();
+        if (part < parts) {
+            for (int p = part; p < cnt; p += parts) {
+                const double ep = s_e[p];
+                const double xv = ep != 0.0 ? rows[p * ds + col] : 0.0;
+                const double ex = ep * xv;
+                s1 += ex;
+                s2 += ex * xv;
+            }
+        }
+        __syncthreads();  // the next chunk overwrites the rows
     }
-    is_block_finish(n, d, x, logw, key, bad, slots_p, is_part);
+    double *red = reinterpret_cast<double *>(s_buf);  // [2][256]
+    red[tid] = s1;
+    red[256 + tid] = s2;
+    const double we = wave_sum_f64(e0);
+    if (lane == 0) s_w[wid] = we;
+    __syncthreads();
+    double *out = is_part + blockIdx.x;
+    if (tid < 2 * d) {
+        const int c = tid < d ? tid : 256 + (tid - d);
+        double v = 0.0;
+        for (int q = 0; q < parts; ++q) v += red[c + q * d];
+        out[(i64)(2 + tid) * gridDim.x] = v;
+    }
+    if (tid == 0) {
+        out[0] = ref;
+        out[gridDim.x] = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
+    }
+    const u64 bk = block_max_key(key, bad);
+    slot_publish(slots_p, bk, bad);
 }
 
 // -------------------------------------------- estimates, c_t and recycling
-template <int NT>
-__global__ __launch_bounds__(NT) void k_step_stats(Ctrl *ctrl, const double *is_part, int nblk,
-                                                   int d, double *rec_num, double *est,
-                                                   smc_resample_info *info, int init)
+// One workgroup: the statistics of the initialisation (init: log sum w_0,
+// cleared recycling sums) or of a filter iteration.
+__global__ __launch_bounds__(1024) void k_step_stats(Ctrl *ctrl, const double *is_part, int nblk,
+                                                     int d, double *rec_num, double *est,
+                                                     smc_resample_info *info, int init)
 {
-    step_stats_block<NT>(ctrl, is_part, nblk, d, rec_num, est, info, init);
+    __shared__ StatsLds s_st;
+    const int tid = threadIdx.x;
+    const RecState rec(ctrl);
+    const unsigned err = init ? 0u : ctrl->err_call, resampled = ctrl->resample;
+    const double logZ = ctrl->logZ;
+    const double rec_old = !init && tid < 2 * d ? rec_num[tid] : 0.0;
+    StepStats<1024> ss;
+    ss.begin(s_st, is_part, nblk);
+    __syncthreads();
+    const double m = ss.scale(s_st, nblk);
+    if (tid == 0 && !init && !err) {
+        const double logc = recycle(ctrl, rec, logZ, resampled != 0, s_st.bc);
+        if (info) info->log_c = logc;
+    }
+    __syncthreads();
+    ss.columns(s_st, is_part, nblk, 2 + 2 * d);
+    __syncthreads();
+    if (init) {
+        if (tid == 0) {
+            ctrl->logZ_prev = m + log(s_st.col[1]);
+            ctrl->lc_max = -__builtin_huge_val();
+            ctrl->rec_den = 0.0;
+            ctrl->rec_steps = 0;
+        }
+        if (tid < 2 * d) rec_num[tid] = 0.0;
+        return;
+    }
+    if (tid < 2 * d && !err) write_estimates(s_st, tid, d, rec_old, rec_num, est);
 }
 
 // uniform (lazy reset): instead of writing logw, mark the weights uniform.
@@ -581,9 +722,9 @@ __global__ __launch_bounds__(256) void k_reset_est(const Ctrl *ctrl, i64 n, int 
         if (lp_scr)
             for (i64 i = gtid; i < n; i += gsz) lp[i] = lp_scr[i];
         if (DT > 0 && tid == 0) {  // no estimate for a failed step
-            double *part = is_part + (i64)blockIdx.x * (2 + 2 * DT);
+            double *part = is_part + blockIdx.x;
             part[0] = -__builtin_huge_val();
-            for (int c = 1; c < 2 + 2 * DT; ++c) part[c] = 0.0;
+            for (int c = 1; c < 2 + 2 * DT; ++c) part[(i64)c * gridDim.x] = 0.0;
         }
         return;
     }
@@ -604,7 +745,7 @@ __global__ __launch_bounds__(256) void k_reset_est(const Ctrl *ctrl, i64 n, int 
         if (tid < kEstCols) {
             double v = 0.0;
             for (i64 g = blockIdx.x; g < nseg; g += gridDim.x) v += epart[g * kEstCols + tid];
-            is_part[(i64)blockIdx.x * kEstCols + tid] = tid == 0 ? reset : v;
+            is_part[(i64)tid * gridDim.x + blockIdx.x] = tid == 0 ? reset : v;
         }
         return;
     }
@@ -640,9 +781,9 @@ __global__ __launch_bounds__(256) void k_reset_est(const Ctrl *ctrl, i64 n, int 
         }
     }
     __syncthreads();
-    double *part = is_part + (i64)blockIdx.x * (2 + 2 * DA);
+    double *part = is_part + blockIdx.x;
     for (int c = tid; c < 2 + 2 * DA; c += 256)
-        part[c] = c == 0 ? m : ((s_acc[0][c - 1] + s_acc[1][c - 1]) + s_acc[2][c - 1]) +
+        part[(i64)c * gridDim.x] = c == 0 ? m : ((s_acc[0][c - 1] + s_acc[1][c - 1]) + s_acc[2][c - 1]) +
                                    s_acc[3][c - 1];
 }
 
@@ -684,9 +825,9 @@ __global__ __launch_bounds__(256) void k_post_est(const Ctrl *ctrl, i64 n, int d
         }
     }
     __syncthreads();
-    double *part = is_part + (i64)blockIdx.x * (2 + 2 * DT);
+    double *part = is_part + blockIdx.x;
     for (int c = tid; c < 2 + 2 * DT; c += 256)
-        part[c] = c == 0 ? m : ((s_acc[0][c - 1] + s_acc[1][c - 1]) + s_acc[2][c - 1]) +
+        part[(i64)c * gridDim.x] = c == 0 ? m : ((s_acc[0][c - 1] + s_acc[1][c - 1]) + s_acc[2][c - 1]) +
                                    s_acc[3][c - 1];
 }
 
@@ -1287,25 +1428,15 @@ __global__ __launch_bounds__(256) void k_xs_colsum(const unsigned short *xs, i64
     if (tid == 0) csum[k] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// log pi = log_norm - prior_prec |theta|^2 / 2 + the partial likelihoods
-// - usc (theta' . csum), where theta' is the bf16 copy thb when given (it holds
-// theta log2 e) and theta otherwise.
-__global__ __launch_bounds__(256) void k_logreg_sum(const double *theta, i64 n, int d,
-                                                    const double *lpart, int msplit,
-                                                    double log_norm, double prior_prec,
-                                                    const unsigned short *thb, int dp,
-                                                    const double *csum, double usc, double *lp)
+// log pi at caller points (smc_log_target) from the partial likelihoods.
+__global__ __launch_bounds__(256) void k_logreg_sum(const double *theta, i64 n, int d, LrArgs lr,
+                                                    double log_norm, double *lp)
 {
     const i64 gtid = (i64)blockIdx.x * 256 + threadIdx.x, gsz = (i64)gridDim.x * 256;
     for (i64 i = gtid; i < n; i += gsz) {
-        double pr = 0.0;
-        for (int k = 0; k < d; ++k) pr += theta[i * d + k] * theta[i * d + k];
-        double s = 0.0;
-        for (int j = 0; j < msplit; ++j) s += lpart[(i64)j * n + i];
-        double su = 0.0;
-        for (int k = 0; k < d; ++k)
-            su += (thb ? from_bf16(thb[i * dp + k]) : theta[i * d + k]) * csum[k];
-        lp[i] = log_norm - 0.5 * prior_prec * pr + (s - usc * su);
+        double lik = 0.0;
+        for (int j = 0; j < lr.msplit; ++j) lik += lr.lpart[(i64)j * n + i];
+        lp[i] = logreg_lp_row(theta + i * d, d, lik, lr.csum, lr, log_norm);
     }
 }
 
@@ -1384,9 +1515,15 @@ bool is_bf16(const smc_config &c)
     return c.target == SMC_TARGET_LOGREG && c.loglik_precision == SMC_PREC_BF16;
 }
 
-// log pi at x[n][d] into lp (the likelihood kernels of the costly target).
-hipError_t logreg_lp(const smc_config &c, const Work &w, const double *x, int64_t n, double *lp,
-                     bool theta_ready, hipStream_t s)
+LrArgs lr_args(const smc_config &c, const Work &w)
+{
+    const bool bf = is_bf16(c);
+    return LrArgs{w.lpart, kLogregSplit, w.csum, bf ? 0.5 * kLn2 : 0.5, c.prior_prec, bf ? 1 : 0};
+}
+
+// Partial log-likelihoods at x[n][d] into lpart.
+hipError_t logreg_lik(const smc_config &c, const Work &w, const double *x, int64_t n,
+                      bool theta_ready, hipStream_t s)
 {
     if (c.target != SMC_TARGET_LOGREG || !w.lpart || !w.csum || (is_bf16(c) && (!w.xs || !w.thb)) ||
         (!is_bf16(c) && !w.xf))
@@ -1416,24 +1553,35 @@ hipError_t logreg_lp(const smc_config &c, const Work &w, const double *x, int64_
         default: hipLaunchKernelGGL(k_logreg_f64<16>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, c.m_rows, w.mpad, w.lpart); break;
         }
     }
-    const bool bf = is_bf16(c);
-    hipLaunchKernelGGL(k_logreg_sum, dim3(grid_for(n)), dim3(256), 0, s, x, (i64)n, c.d, w.lpart,
-                       msplit, c.log_norm, c.prior_prec, bf ? w.thb : nullptr, w.dp, w.csum,
-                       bf ? 0.5 * kLn2 : 0.5, lp);
     return hipGetLastError();
 }
 
-template <int kKind, bool kInit, int DT>
+// out: the proposal goes to the workspace copy x_scr.
+template <int kKind, bool kInit>
 void launch_is_k(dim3 g, hipStream_t s, const TArgs &a, i64 n, uint32_t t, double *x, double *logw,
                  const Work &w, u64 *sp, bool out)
 {
     if (!kInit && out)
-        hipLaunchKernelGGL((k_is<kKind, false, DT, true>), g, dim3(256), 0, s, a, n, t, x, logw,
-                           w.lp, sp, w.is_part, w.x_scr, w.lp_scr);
+        hipLaunchKernelGGL((k_is<kKind, false, true>), g, dim3(256), 0, s, a, n, t, x, logw, w.lp,
+                           sp, w.is_part, w.x_scr);
     else
-        hipLaunchKernelGGL((k_is<kKind, kInit, DT, false>), g, dim3(256), 0, s, a, n, t, x, logw,
-                           w.lp, sp, w.is_part, (double *)nullptr,
-                           (double *)nullptr);
+        hipLaunchKernelGGL((k_is<kKind, kInit, false>), g, dim3(256), 0, s, a, n, t, x, logw, w.lp,
+                           sp, w.is_part, (double *)nullptr);
+}
+
+// The same for rows of several coordinates; out: also the log-targets.
+template <int kKind, bool kInit>
+void launch_rows_k(dim3 g, hipStream_t s, const TArgs &a, i64 n, uint32_t t, double *x,
+                   double *logw, const Work &w, u64 *sp, bool out, const LrArgs &lr)
+{
+    const int P = rows_per_block(n, a.d);
+    const size_t lds = (size_t)P * ((a.d | 1) + 1) * sizeof(double);
+    if (!kInit && out)
+        hipLaunchKernelGGL((k_rows<kKind, false, true>), g, dim3(256), lds, s, a, n, t, P, x, logw,
+                           w.lp, sp, w.is_part, w.x_scr, w.lp_scr, lr);
+    else
+        hipLaunchKernelGGL((k_rows<kKind, kInit, false>), g, dim3(256), lds, s, a, n, t, P, x,
+                           logw, w.lp, sp, w.is_part, (double *)nullptr, (double *)nullptr, lr);
 }
 
 // out: the proposal goes to the workspace copies (x_scr, lp_scr).
@@ -1447,24 +1595,25 @@ hipError_t launch_is(const smc_config &c, const Work &w, int par, uint32_t t, do
     u64 *sp = w.slots + (par & 1) * kSlots * kSlotStride;
     switch (c.target) {
     case SMC_TARGET_GAUSS:
-        if (c.d == 1) launch_is_k<SMC_TARGET_GAUSS, kInit, 1>(g, s, a, n, t, x, logw, w, sp, out);
-        else if (c.d == 4)
-            launch_is_k<SMC_TARGET_GAUSS, kInit, 4>(g, s, a, n, t, x, logw, w, sp, out);
-        else launch_is_k<SMC_TARGET_GAUSS, kInit, 0>(g, s, a, n, t, x, logw, w, sp, out);
+        if (c.d == 1) launch_is_k<SMC_TARGET_GAUSS, kInit>(g, s, a, n, t, x, logw, w, sp, out);
+        else launch_rows_k<SMC_TARGET_GAUSS, kInit>(g, s, a, n, t, x, logw, w, sp, out, LrArgs{});
         break;
     case SMC_TARGET_STUDENT:
-        launch_is_k<SMC_TARGET_STUDENT, kInit, 1>(g, s, a, n, t, x, logw, w, sp, out);
+        launch_is_k<SMC_TARGET_STUDENT, kInit>(g, s, a, n, t, x, logw, w, sp, out);
         break;
     case SMC_TARGET_BEARING:
-        launch_is_k<SMC_TARGET_BEARING, kInit, 4>(g, s, a, n, t, x, logw, w, sp, out);
+        launch_is_k<SMC_TARGET_BEARING, kInit>(g, s, a, n, t, x, logw, w, sp, out);
         break;
-    case SMC_TARGET_LOGREG:
-        launch_is_k<SMC_TARGET_LOGREG, kInit, 0>(g, s, a, n, t, x, logw, w, sp, false);
+    case SMC_TARGET_LOGREG: {
+        const int P = rows_per_block(n, c.d);
+        hipLaunchKernelGGL(k_propose<kInit>, dim3((unsigned)row_chunks(n, c.d)), dim3(256), 0, s,
+                           a, n, t, P, x);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-        if (logreg_lp(c, w, x, n, w.lp_new, true, s) != hipSuccess) return hipErrorLaunchFailure;
-        hipLaunchKernelGGL(k_reweight<kInit>, g, dim3(256), 0, s, n, c.d, x, w.lp_new, logw,
-                           w.lp, sp, w.is_part, a.uniform, a.reset);
+        if (logreg_lik(c, w, x, n, true, s) != hipSuccess) return hipErrorLaunchFailure;
+        launch_rows_k<SMC_TARGET_LOGREG, kInit>(g, s, a, n, t, x, logw, w, sp, false,
+                                                lr_args(c, w));
         break;
+    }
     default:
         return hipErrorInvalidValue;
     }
@@ -1473,11 +1622,11 @@ hipError_t launch_is(const smc_config &c, const Work &w, int par, uint32_t t, do
     return kInit ? launch_fold(w, par, s) : hipSuccess;
 }
 
-template <int kKind, int DT>
+template <int kKind>
 int resident_blocks()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_is<kKind, false, DT, false>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_is<kKind, false, false>, 256, 0) !=
         hipSuccess)
         return 0;
     return nb;
@@ -1487,20 +1636,20 @@ int resident_blocks()
 
 int sampler_grid(const smc_config &c)
 {
+    // rows of several coordinates: one workgroup per chunk of rows
+    if (c.target == SMC_TARGET_LOGREG || (c.target == SMC_TARGET_GAUSS && c.d > 1)) {
+        const int64_t g = row_chunks(c.n, c.d);
+        return (int)(g < kIsBlocks ? g : kIsBlocks);
+    }
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
     int per_cu = 0;
     switch (c.target) {
-    case SMC_TARGET_GAUSS:
-        per_cu = c.d == 1 ? resident_blocks<SMC_TARGET_GAUSS, 1>()
-                 : c.d == 4 ? resident_blocks<SMC_TARGET_GAUSS, 4>()
-                            : resident_blocks<SMC_TARGET_GAUSS, 0>();
-        break;
-    case SMC_TARGET_STUDENT: per_cu = resident_blocks<SMC_TARGET_STUDENT, 1>(); break;
-    case SMC_TARGET_BEARING: per_cu = resident_blocks<SMC_TARGET_BEARING, 4>(); break;
-    case SMC_TARGET_LOGREG: per_cu = resident_blocks<SMC_TARGET_LOGREG, 0>(); break;
+    case SMC_TARGET_GAUSS: per_cu = resident_blocks<SMC_TARGET_GAUSS>(); break;
+    case SMC_TARGET_STUDENT: per_cu = resident_blocks<SMC_TARGET_STUDENT>(); break;
+    case SMC_TARGET_BEARING: per_cu = resident_blocks<SMC_TARGET_BEARING>(); break;
     default: return 0;
     }
     if (per_cu < 1) return 0;
@@ -1535,7 +1684,7 @@ smc_status step_init(const smc_config &c, const Work &w, int par, double *x, dou
     if (c.target == SMC_TARGET_BEARING)  // equal initial weights: sums from the common reference
         hipLaunchKernelGGL(k_post_est<4>, dim3(w.is_grid), dim3(256), 0, s, w.ctrl, (i64)c.n,
                            c.d, x, logw, -std::log((double)c.n), w.is_part);
-    hipLaunchKernelGGL(k_step_stats<1024>, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part, w.is_grid,
+    hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part, w.is_grid,
                        c.d, w.rec_num, (double *)nullptr, (smc_resample_info *)nullptr, 1);
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
@@ -1626,7 +1775,7 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
                                c.d, x, w.x_scr, (double *)nullptr, (const double *)nullptr,
                                logw, reset, w.is_part, (const double *)ep,
                                (i64)expand_segments(n), uni);
-            hipLaunchKernelGGL(k_step_stats<1024>, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part,
+            hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part,
                                w.is_grid, c.d, w.rec_num, est, info, 0);
         } else {
             hipLaunchKernelGGL(k_reset_est<0>, dim3(w.is_grid), dim3(256), 0, s, w.ctrl, (i64)n,
@@ -1664,7 +1813,10 @@ smc_status step_log_target(const smc_config &c, const Work &w, const double *x, 
 {
     if (n > c.n) return SMC_E_ARG;
     if (c.target == SMC_TARGET_LOGREG) {
-        return logreg_lp(c, w, x, n, lp, false, s) == hipSuccess ? SMC_OK : SMC_E_DEVICE;
+        if (logreg_lik(c, w, x, n, false, s) != hipSuccess) return SMC_E_DEVICE;
+        hipLaunchKernelGGL(k_logreg_sum, dim3(grid_for(n)), dim3(256), 0, s, x, (i64)n, c.d,
+                           lr_args(c, w), c.log_norm, lp);
+        return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
     }
     const TArgs a = targs(c, w, false);
     hipLaunchKernelGGL(k_lp_cheap, dim3(grid_for(n)), dim3(256), 0, s, a, (i64)n, x, lp);

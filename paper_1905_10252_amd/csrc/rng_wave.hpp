@@ -102,14 +102,15 @@ __device__ inline bool polar_wave(uint64_t seed, uint32_t tag, uint32_t sampler,
     return ok;
 }
 
-// W pairs per lane: pairs pair0, pair0 + 1, ... of particle idx; z[2 q], z[2 q + 1]
-// receive pair pair0 + q.  np (wave-uniform): pairs from np on are skipped.
+// W pairs per lane: pair[q] of particle idx[q] gives z[2 q], z[2 q + 1].  np
+// (wave-uniform): pairs from np on are skipped (their z are 0).
 // s = v1^2 + v2^2 lies in [2^-104, 1), so the logarithm, quotient and root take
 // the in-range forms.
 template <int W>
 __device__ inline void normal_pairs_wave(uint64_t seed, uint32_t tag, uint32_t sampler,
-                                         uint32_t t, uint32_t idx, uint32_t pair0, int np,
-                                         bool active, double (&z)[2 * W], uint4 *xch)
+                                         uint32_t t, const uint32_t (&idx)[W],
+                                         const uint32_t (&pair)[W], int np,
+                                         const bool (&active)[W], double (&z)[2 * W], uint4 *xch)
 {
     double v1[W], v2[W], s[W], c[W];
     bool ok[W];
@@ -117,8 +118,8 @@ __device__ inline void normal_pairs_wave(uint64_t seed, uint32_t tag, uint32_t s
     SMC_EACH {
         ok[w] = false;
         if (w < np)
-            ok[w] = polar_wave(seed, tag, sampler, t, idx, pair0 + (uint32_t)w, active, v1[w],
-                               v2[w], xch);
+            ok[w] = polar_wave(seed, tag, sampler, t, idx[w], pair[w], active[w], v1[w], v2[w],
+                               xch);
         if (!ok[w]) {
             v1[w] = 0.5;  // any accepted draw: keeps the arithmetic in range
             v2[w] = 0.0;
@@ -144,8 +145,10 @@ __device__ inline void normal_pair_wave(uint64_t seed, uint32_t tag, uint32_t sa
                                         uint32_t idx, uint32_t pair, bool active, double &z1,
                                         double &z2, uint4 *xch)
 {
+    const uint32_t i[1] = {idx}, p[1] = {pair};
+    const bool act[1] = {active};
     double z[2];
-    normal_pairs_wave<1>(seed, tag, sampler, t, idx, pair, 1, active, z, xch);
+    normal_pairs_wave<1>(seed, tag, sampler, t, i, p, 1, act, z, xch);
     z1 = z[0];
     z2 = z[1];
 }

@@ -1,5 +1,12 @@
-// The sampler's per-iteration statistics as a block-level routine, shared by
-// the statistics kernel and the fused decision kernel.
+// The sampler's per-iteration statistics as steps of one workgroup, shared by
+// the statistics kernel and the decision kernel (which interleaves them with
+// its own steps, so that both wait for memory and barriers together).
+//
+// Every block of the update leaves one row of partial sums, stored by columns
+// (column c of block b at part[c nblk + b]: the folding wavefronts read whole
+// cache lines; stored by rows, the reads of 22 columns alone took 9 us):
+// the block's reference weight, sum e, sum e x_k (k < d), sum e x_k^2, with e
+// relative to the reference.  A block without weight carries -inf and zeros.
 #pragma once
 
 #include "../../include/smc.h"
@@ -11,124 +18,130 @@ namespace smc {
 
 constexpr int kStatsMaxDim = 64;
 
-// Estimates of eq. estimation_at_t, c_t (eq. normconst) and the recycling
-// sums (eq. recycling) from the per-block partials of the update, by one
-// workgroup of NT threads (sums in a fixed order for a given NT).
+// LDS of the statistics.
+struct StatsLds {
+    double sc[kIsBlocks];                 // scale of each block's sums
+    double col[2 + 2 * kStatsMaxDim];     // folded columns
+    double mk[16];
+    double bc[4];                         // scale and weight of eq. recycling, its denominator
+};
+
 template <int NT>
-__device__ inline void step_stats_block(Ctrl *ctrl, const double *is_part, int nblk, int d,
-                                        double *rec_num, double *est, smc_resample_info *info,
-                                        int init)
-{
-    constexpr int NW = NT / 64;
-    __shared__ double s_col[2 + 2 * kStatsMaxDim];
-    __shared__ double s_red[NW][2 + 2 * kStatsMaxDim];
-    __shared__ double s_sc, s_wgt, s_den;
-    __shared__ u64 s_mk[NW];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int ncol = 2 + 2 * d;
-    // reference: the largest block reference (blocks with no weight carry -inf)
-    u64 mk = 0;
-    for (int b = tid; b < nblk; b += NT) {
-        const u64 k = okey(is_part[(i64)b * ncol]);
-        mk = k > mk ? k : mk;
+struct StepStats {
+    static constexpr int NW = NT / 64;
+    static constexpr int kPer = (kIsBlocks + NT - 1) / NT;
+    static_assert(NW <= 16, "wave totals");
+    double mb[kPer];
+
+    // References of this thread's blocks; their maximum per wavefront into LDS.
+    __device__ void begin(StatsLds &L, const double *part, int nblk)
+    {
+        const int tid = threadIdx.x;
+        double m = -__builtin_huge_val();
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int b = tid + NT * j;
+            mb[j] = b < nblk ? part[b] : -__builtin_huge_val();
+            m = fmax(m, mb[j]);
+        }
+        m = wave_max_f64(m);
+        if ((tid & 63) == 0) L.mk[tid >> 6] = m;
     }
-    mk = wave_max_u64(mk);
-    if ((tid & 63) == 0) s_mk[tid >> 6] = mk;
-    __syncthreads();
-    for (int i = 1; i < NW; ++i) mk = s_mk[i] > mk ? s_mk[i] : mk;
-    mk = s_mk[0] > mk ? s_mk[0] : mk;
-    const double m = okey_inv(mk);
-    // thread tid folds blocks tid, tid + NT, ... (nblk <= kIsBlocks), then a
-    // fixed-order wave and block sum per column
-    constexpr int kPer = (kIsBlocks + NT - 1) / NT;
-    double sc[kPer];
-    for (int j = 0; j < kPer; ++j) {
-        const int b = tid + NT * j;
-        const double mb = b < nblk ? is_part[(i64)b * ncol] : -__builtin_huge_val();
-        sc[j] = mb > -__builtin_huge_val() ? det_exp(mb - m) : 0.0;
+
+    // After a barrier: the scale of every block against the largest reference,
+    // which it returns.
+    __device__ double scale(StatsLds &L, int nblk)
+    {
+        const int tid = threadIdx.x;
+        double m = L.mk[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmax(m, L.mk[w]);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int b = tid + NT * j;
+            if (b < nblk) L.sc[b] = mb[j] > -__builtin_huge_val() ? det_exp(mb[j] - m) : 0.0;
+        }
+        return m;
     }
-    // four columns at a time: their loads are all issued before the first
-    // sum waits on them (the per-column sums and their order are unchanged)
-    constexpr int CU = 4;
-    for (int c0 = 1; c0 < ncol; c0 += CU) {
-        double v[CU][kPer];
-#pragma unroll
-        for (int q = 0; q < CU; ++q)
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                const int b = tid + NT * j;
-                v[q][j] = (c0 + q < ncol && b < nblk && sc[j] != 0.0)
-                              ? is_part[(i64)b * ncol + c0 + q]
-                              : 0.0;
-            }
-#pragma unroll
-        for (int q = 0; q < CU; ++q) {
-            if (c0 + q >= ncol) break;
+
+    // After another barrier: column c is folded by one wavefront, lanes over
+    // the blocks (a fixed order), eight loads in flight.  Column 1 goes to the
+    // second wavefront: the first has other work in the decision kernel.
+    __device__ void columns(StatsLds &L, const double *part, int nblk, int ncol)
+    {
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        for (int c = 1 + (wid + NW - 1) % NW; c < ncol; c += NW) {
+            const double *pc = part + (i64)c * nblk;
             double acc = 0.0;
-            for (int j = 0; j < kPer; ++j) {
-                const int b = tid + NT * j;
-                if (b < nblk && sc[j] != 0.0) acc += sc[j] * v[q][j];
+            constexpr int U = 8;
+            for (int b0 = lane; b0 < nblk; b0 += 64 * U) {
+                double v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int b = b0 + 64 * u;
+                    v[u] = pc[b < nblk ? b : b0];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int b = b0 + 64 * u;
+                    const double s = b < nblk ? L.sc[b] : 0.0;
+                    acc += s != 0.0 ? s * v[u] : 0.0;
+                }
             }
             acc = wave_sum_f64(acc);
-            if (lane == 0) s_red[wid][c0 + q] = acc;
+            if (lane == 0) L.col[c] = acc;
         }
     }
-    __syncthreads();
-    for (int c = 1 + tid; c < ncol; c += NT) {
-        double v = s_red[0][c];
-        for (int w = 1; w < NW; ++w) v += s_red[w][c];
-        s_col[c] = v;
+};
+
+// The control block's part of c_t and recycling, read before it is needed.
+struct RecState {
+    double logZ_prev, lc_max, rec_den;
+    int rec_steps;
+    __device__ explicit RecState(const Ctrl *c)
+        : logZ_prev(c->logZ_prev), lc_max(c->lc_max), rec_den(c->rec_den), rec_steps(c->rec_steps)
+    {
     }
-    __syncthreads();
-    const double E0 = s_col[1];
-    if (init) {
-        if (tid == 0) {
-            ctrl->logZ_prev = m + log(E0);
-            ctrl->lc_max = -__builtin_huge_val();
-            ctrl->rec_den = 0.0;
-            ctrl->rec_steps = 0;
-        }
-        for (int c = tid; c < 2 * d; c += NT) rec_num[c] = 0.0;
-        return;
+};
+
+// c_t (eq. normconst) and the recycling weights (eq. recycling), by one
+// thread of an iteration without error; returns log c_t and leaves
+// bc = (scale of the old sums, weight of this iteration, their denominator).
+__device__ inline double recycle(Ctrl *ctrl, const RecState &r, double logZ, bool resampled,
+                                 double *bc)
+{
+    const double logc = logZ - r.logZ_prev;
+    double sc = 1.0, den = r.rec_den, lc_max = r.lc_max;
+    if (logc > lc_max) {
+        sc = r.rec_steps ? exp(lc_max - logc) : 0.0;
+        den *= sc;
+        lc_max = logc;
+        ctrl->lc_max = lc_max;
     }
-    // an iteration whose decision found an error (NaN / +inf weight, all
-    // weights zero) leaves c_t, the recycling sums and the estimates as they
-    // were, as the iteration stops at the resampling step
-    __shared__ unsigned s_err;
-    if (tid == 0) s_err = ctrl->err_call;
-    __syncthreads();
-    if (s_err) return;
-    if (tid == 0) {
-        const double logc = ctrl->logZ - ctrl->logZ_prev;
-        double sc = 1.0;
-        double den = ctrl->rec_den;
-        if (logc > ctrl->lc_max) {
-            sc = ctrl->rec_steps ? exp(ctrl->lc_max - logc) : 0.0;
-            den *= sc;
-            ctrl->lc_max = logc;
-        }
-        const double wgt = exp(logc - ctrl->lc_max);
-        den += wgt;
-        ctrl->rec_den = den;
-        ctrl->rec_steps += 1;
-        ctrl->log_c = logc;
-        ctrl->logZ_prev = ctrl->resample ? 0.0 : ctrl->logZ;
-        s_sc = sc;
-        s_wgt = wgt;
-        s_den = den;
-        if (info) info->log_c = logc;
-    }
-    __syncthreads();
-    for (int k = tid; k < 2 * d; k += NT) {
-        const double f = s_col[2 + k] / E0;
-        const double num = rec_num[k] * s_sc + s_wgt * f;
-        rec_num[k] = num;
-        if (est) {
-            est[k] = f;
-            est[2 * d + k] = num / s_den;
-        }
-    }
+    const double wgt = exp(logc - lc_max);
+    den += wgt;
+    ctrl->rec_den = den;
+    ctrl->rec_steps = r.rec_steps + 1;
+    ctrl->log_c = logc;
+    ctrl->logZ_prev = resampled ? 0.0 : logZ;
+    bc[0] = sc;
+    bc[1] = wgt;
+    bc[2] = den;
+    return logc;
 }
 
+// Estimates f_t (eq. estimation_at_t) and the recycled ones; threads k < 2 d,
+// rec_old = rec_num[k].
+__device__ inline void write_estimates(const StatsLds &L, int k, int d, double rec_old,
+                                       double *rec_num, double *est)
+{
+    const double f = L.col[2 + k] / L.col[1];
+    const double num = rec_old * L.bc[0] + L.bc[1] * f;
+    rec_num[k] = num;
+    if (est) {
+        est[k] = f;
+        est[2 * d + k] = num / L.bc[2];
+    }
+}
 
 }  // namespace smc
