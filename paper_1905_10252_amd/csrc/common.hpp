@@ -152,6 +152,24 @@ __device__ inline u64 wave_scan_u64(u64 v, u64 fill, Op op)
     return v;
 }
 
+// The same for 32-bit maxima (identity 0).
+template <int CTRL, int ROW_MASK>
+__device__ inline unsigned dpp_max_u32(unsigned v)
+{
+    const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
+    return o > v ? o : v;
+}
+
+__device__ inline unsigned wave_scan_max_u32(unsigned v)
+{
+    v = dpp_max_u32<0x111, 0xF>(v);
+    v = dpp_max_u32<0x112, 0xF>(v);
+    v = dpp_max_u32<0x114, 0xF>(v);
+    v = dpp_max_u32<0x118, 0xF>(v);
+    v = dpp_max_u32<0x142, 0xA>(v);
+    return dpp_max_u32<0x143, 0xC>(v);
+}
+
 __device__ inline u64 wave_max_u64(u64 v)
 {
     return lane63_u64(wave_scan_u64(v, 0ull, [](u64 a, u64 b) { return b > a ? b : a; }));

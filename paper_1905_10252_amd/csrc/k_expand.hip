@@ -5,9 +5,9 @@
 // the output order is exactly that of the sequential redistribute.  Copies per
 // source range from 0 to N, so a source-parallel copy is unbalanced; instead
 // the merge of the two sorted sequences (A_j + j over sources, p over outputs)
-// is cut into equal segments of kSegLen merge steps (merge path).  Every
+// is cut into equal segments of up to kSegLen merge steps (merge path).  Every
 // workgroup owns one segment: a few sources and a few outputs, never more than
-// kSegLen in total, whatever the weights.
+// the segment's length in total, whatever the weights.
 //
 // A_j is computed from the fixed-point prefix as floor((N S_j + U) / S), or is
 // the prefix of caller-supplied counts, or j + 1 when the ESS rule decided not
@@ -21,6 +21,7 @@
 
 #include "../../include/smc.h"
 #include "common.hpp"
+#include "det.hpp"
 #include "kernels.hpp"
 
 namespace smc {
@@ -201,142 +202,154 @@ struct VecT<4> {
     typedef unsigned T;
 };
 
+// Values of a filter row (four FP64 values) that the threads of the row-summing
+// copy add up: each thread's chunks of VEC bytes all sit in the same place of
+// a row (the lane stride is a multiple of the row's chunks), so it keeps the
+// sums and the sums of squares of that place, each weighted by w.
+template <int VEC>
+struct RowAcc {
+    static constexpr int NV = VEC / 8 > 0 ? VEC / 8 : 1;  // values a chunk
+    double s[NV], q[NV], e;
+    __device__ void init()
+    {
+        e = 0.0;
+        for (int i = 0; i < NV; ++i) s[i] = q[i] = 0.0;
+    }
+    __device__ void add(const u32x4 &v, double w)
+    {
+        one(0, __hiloint2double((int)v.y, (int)v.x), w);
+        one(NV - 1, __hiloint2double((int)v.w, (int)v.z), w);
+    }
+    __device__ void add(const u32x2 &v, double w)
+    {
+        one(0, __hiloint2double((int)v.y, (int)v.x), w);
+    }
+    __device__ void one(int i, double x, double w)
+    {
+        const double wx = w * x;
+        s[i] += wx;
+        q[i] += wx * x;
+    }
+};
+
 // Copies np rows [p0, p0 + np) of dst from rows sAnc[] of src, VEC bytes per
-// lane access; consecutive lanes write consecutive addresses.  The bulk of the
-// stores is non-temporal: the new population is not read again by this call,
-// and keeping it out of the caches spares the next resample the write-back
-// of a cache full of dirty rows (about 5 us per call at N = 2^24 on MI355X).
+// lane access; consecutive lanes write consecutive addresses.  A thread's
+// chunks are 256 apart, so its (row, column) moves by a constant step and one
+// carry (a division per chunk, for rows that are no power of two, cost as much
+// as the copy).
+// kNtStore: the stores are non-temporal: a large new population is not read
+// again by this call, and keeping it out of the caches spares the next
+// resample the write-back of a cache full of dirty rows (about 5 us per call
+// at N = 2^24 on MI355X).  One that the caches hold is written through them.
 // kNtLoad: the source rows are read non-temporally too.  A segment whose
 // outputs are mostly distinct sources reads each line about once; streaming
 // those lines past the caches measured 48 us faster per call at N = 2^24,
 // s = 0.5 (HBM read requests are whole 128-byte lines either way).  Where a
 // few sources fill many outputs (heavy degeneracy) the cached reads are
 // faster, the same lines serving the whole segment.
-// kSum (VEC = 16, rows of four FP64 values): the thread also adds up the two
-// values of every chunk it copies, and their squares, into acc; its chunks all
-// sit in the same half of a row (the lane stride is a multiple of two chunks).
-__device__ inline void add_chunk(const u32x4 &v, double *acc)
+// kSum (rows of four FP64 values): also adds up the rows; lw (nullable): each
+// row weighted by exp(lw - m), otherwise by one.
+// kPow2: a row's chunks are a power of two up to 256, so a thread's column is
+// fixed.
+template <int VEC, bool kPow2, bool kSum, bool kNtLoad, bool kNtStore>
+__device__ inline void copy_chunks(const unsigned char *__restrict__ src,
+                                   unsigned char *__restrict__ dst, int row_bytes, int cpr,
+                                   const unsigned *sAnc, i64 p0, int total, RowAcc<VEC> *acc,
+                                   const double *lw, double m)
 {
-    const double lo = __hiloint2double((int)v.y, (int)v.x);
-    const double hi = __hiloint2double((int)v.w, (int)v.z);
-    acc[0] += lo;
-    acc[1] += hi;
-    acc[2] += lo * lo;
-    acc[3] += hi * hi;
-}
-
-template <int VEC, bool kSum = false, bool kNtLoad = false>
-__device__ inline void copy_rows(const unsigned char *__restrict__ src,
-                                 unsigned char *__restrict__ dst, int row_bytes, int cpr_shift,
-                                 const unsigned *sAnc, i64 p0, int np, double *acc = nullptr)
-{
-    static_assert(!kSum || VEC == 16, "row sums take 16-byte chunks");
+    static_assert(!kSum || VEC >= 8, "row sums take FP64 values");
     typedef typename VecT<VEC>::T V;
-    const int cpr = row_bytes / VEC;
-    const int total = np * cpr;
-    const int tid = threadIdx.x;
-    constexpr int U = 4;
-    int c = tid;
+    const int dr = kExpandThreads / cpr, dc = kExpandThreads - dr * cpr;
+    int r = (int)threadIdx.x / cpr, col = (int)threadIdx.x - r * cpr;
+    constexpr int U = VEC == 4 ? 8 : 4;  // loads in flight a thread
+    V *d = reinterpret_cast<V *>(dst + p0 * (i64)row_bytes);
+    auto load = [&]() {  // the chunk at (r, col), then on to the thread's next
+        const V *sp = reinterpret_cast<const V *>(src + (i64)sAnc[r] * row_bytes) + col;
+        const V v = kNtLoad ? __builtin_nontemporal_load(sp) : *sp;
+        r += dr;
+        if (!kPow2) {
+            col += dc;
+            if (col >= cpr) {
+                col -= cpr;
+                ++r;
+            }
+        }
+        return v;
+    };
+    auto store = [&](const V &v, int c, int row) {
+        if (kNtStore) __builtin_nontemporal_store(v, d + c);
+        else d[c] = v;
+        if constexpr (kSum) {
+            const double w = lw ? det_exp(lw[p0 + row] - m) : 1.0;
+            if (threadIdx.x % (32 / VEC) == 0) acc->e += w;
+            acc->add(v, w);
+        }
+    };
+    int c = threadIdx.x;
     for (; c + (U - 1) * kExpandThreads < total; c += U * kExpandThreads) {
         V v[U];
-        i64 doff[U];
+        int row[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int cc = c + u * kExpandThreads;
-            int r, col;
-            if (cpr_shift >= 0) {
-                r = cc >> cpr_shift;
-                col = cc & (cpr - 1);
-            } else {
-                r = cc / cpr;
-                col = cc - r * cpr;
-            }
-            const V *sp = reinterpret_cast<const V *>(src + (i64)sAnc[r] * row_bytes + col * VEC);
-            v[u] = kNtLoad ? __builtin_nontemporal_load(sp) : *sp;
-            doff[u] = (p0 + r) * (i64)row_bytes + col * VEC;
+            row[u] = r;
+            v[u] = load();
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) __builtin_nontemporal_store(v[u], reinterpret_cast<V *>(dst + doff[u]));
-        if constexpr (kSum) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) add_chunk(v[u], acc);
-        }
+        for (int u = 0; u < U; ++u) store(v[u], c + u * kExpandThreads, row[u]);
     }
     for (; c < total; c += kExpandThreads) {
-        int r, col;
-        if (cpr_shift >= 0) {
-            r = c >> cpr_shift;
-            col = c & (cpr - 1);
-        } else {
-            r = c / cpr;
-            col = c - r * cpr;
-        }
-        const V v = *reinterpret_cast<const V *>(src + (i64)sAnc[r] * row_bytes + col * VEC);
-        *reinterpret_cast<V *>(dst + (p0 + r) * (i64)row_bytes + col * VEC) = v;
-        if constexpr (kSum) add_chunk(v, acc);
+        const int row = r;
+        store(load(), c, row);
     }
 }
 
-// Rows of 8 bytes with an 8-byte side row each (a 1-D sampler's particle and
-// its cached log-target): both copies in one loop, twice the loads in flight;
-// kNtLoad as in copy_rows.
-template <bool kNtLoad>
-__device__ inline void copy_rows_8x2(const unsigned char *__restrict__ src,
-                                     unsigned char *__restrict__ dst,
-                                     const unsigned char *__restrict__ src2,
-                                     unsigned char *__restrict__ dst2, const unsigned *sAnc,
-                                     i64 p0, int np)
+template <int VEC, bool kSum, bool kNtLoad, bool kNtStore>
+__device__ inline void copy_rows(const unsigned char *__restrict__ src,
+                                 unsigned char *__restrict__ dst, int row_bytes,
+                                 const unsigned *sAnc, i64 p0, int np,
+                                 RowAcc<VEC> *acc = nullptr, const double *lw = nullptr,
+                                 double m = 0.0)
 {
-    typedef unsigned long long V;
-    const V *s1 = reinterpret_cast<const V *>(src), *s2 = reinterpret_cast<const V *>(src2);
-    V *d1 = reinterpret_cast<V *>(dst) + p0, *d2 = reinterpret_cast<V *>(dst2) + p0;
-    constexpr int U = 4;
-    int r = threadIdx.x;
-    for (; r + (U - 1) * kExpandThreads < np; r += U * kExpandThreads) {
-        V v[U], w[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned j = sAnc[r + u * kExpandThreads];
-            v[u] = kNtLoad ? __builtin_nontemporal_load(s1 + j) : s1[j];
-            w[u] = kNtLoad ? __builtin_nontemporal_load(s2 + j) : s2[j];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            __builtin_nontemporal_store(v[u], d1 + r + u * kExpandThreads);
-            __builtin_nontemporal_store(w[u], d2 + r + u * kExpandThreads);
-        }
-    }
-    for (; r < np; r += kExpandThreads) {
-        const unsigned j = sAnc[r];
-        d1[r] = s1[j];
-        d2[r] = s2[j];
-    }
+    const int cpr = row_bytes / VEC;
+    if (kSum || ((cpr & (cpr - 1)) == 0 && cpr <= kExpandThreads))
+        copy_chunks<VEC, true, kSum, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0,
+                                                        np * cpr, acc, lw, m);
+    else
+        copy_chunks<VEC, false, kSum, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0,
+                                                         np * cpr, acc, lw, m);
 }
 
-// Sums of the rows one workgroup wrote (rows of four FP64 values, two 16-byte
-// chunks each): lanes of equal parity hold the same half of a row; their sums
-// are combined in a fixed order and written in the filter's estimate layout
-// (column 0 unused here, 1 the row count, 2 + k the sum of value k, 6 + k the
-// sum of its square).
-__device__ inline void store_row_sums(double *acc, int np, double *out)
+// Sums of the rows one workgroup wrote: lanes of equal index modulo the row's
+// chunks hold the same place of a row; their sums are combined in a fixed order
+// and written in the filter's estimate columns (column c of this workgroup at
+// out[c stride]: 0 the reference weight, 1 the sum of the weights, 2 + k the
+// sum of value k, 6 + k the sum of its square).
+template <int VEC>
+__device__ inline void store_row_sums(RowAcc<VEC> &acc, double ref, double *out, i64 stride)
 {
-    __shared__ double s_acc[kExpandThreads / 64][2][4];
+    constexpr int NC = 32 / VEC, NV = RowAcc<VEC>::NV, NW = kExpandThreads / 64;
+    __shared__ double s_acc[NW][NC][2 * NV + 1];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    double v[2 * NV + 1];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        for (int o = 2; o < 64; o <<= 1) acc[k] += __shfl_xor(acc[k], o, 64);
-    if (lane < 2)
-        for (int k = 0; k < 4; ++k) s_acc[wid][lane][k] = acc[k];
+    for (int i = 0; i < NV; ++i) {
+        v[i] = acc.s[i];
+        v[NV + i] = acc.q[i];
+    }
+    v[2 * NV] = acc.e;
+#pragma unroll
+    for (int i = 0; i < 2 * NV + 1; ++i)
+        for (int o = NC; o < 64; o <<= 1) v[i] += __shfl_xor(v[i], o, 64);
+    if (lane < NC)
+        for (int i = 0; i < 2 * NV + 1; ++i) s_acc[wid][lane][i] = v[i];
     __syncthreads();
     if (tid < kEstCols) {
-        double v = tid == 1 ? (double)np : 0.0;
-        if (tid >= 2) {
-            const int k = (tid - 2) & 3;                  // value k = 2 h + half
-            const int j = (tid >= 6 ? 2 : 0) + (k & 1);   // its sum, or its square's
-            v = s_acc[0][k >> 1][j];
-            for (int w = 1; w < kExpandThreads / 64; ++w) v += s_acc[w][k >> 1][j];
-        }
-        out[tid] = v;
+        const int k = (tid - 2) & 3;  // value
+        const int ch = tid < 2 ? 0 : k / NV;
+        const int i = tid < 2 ? 2 * NV : (tid >= 6 ? NV : 0) + k % NV;
+        double t = s_acc[0][ch][i];
+        for (int w = 1; w < NW; ++w) t += s_acc[w][ch][i];
+        out[tid * stride] = tid == 0 ? ref : t;
     }
 }
 
@@ -349,32 +362,42 @@ struct ExpandArgs {
     int count_mode;
     const unsigned char *x;
     unsigned char *xo;
-    int row_bytes, cpr_shift;
-    const unsigned char *aux;
+    int row_bytes;
+    const unsigned char *aux;  // 8-byte side rows (a sampler's cached log-target), nullable
     unsigned char *auxo;
-    int aux_bytes, aux_shift;
     i64 *nc_out;
     i64 *anc_out;
-    int skip_identity;  // when the decision is "no resample", write nothing
-    double *est_part;   // kSum: [segments][kEstCols] sums of the rows written
+    ExpandMode mode;
+    double *logw;       // a resampling iteration's weights, set to `reset` (nullable) ...
+    double reset;
+    unsigned *uniform;  // ... or marked uniform here instead (lazy reset, nullable)
+    double *est_part;   // kSum: [kEstCols][segments] sums of the rows written
+    int stream;         // the new rows are written past the caches
 };
 
-template <int VEC, bool kSum = false>
+// SEG: merge steps of one workgroup.
+template <int VEC, int SEG, bool kSum>
 __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
 {
-    __shared__ unsigned sA[kSegLen + 1];
-    __shared__ __attribute__((aligned(16))) unsigned sAnc[kSegLen];
+    __shared__ unsigned sA[SEG + 1];
+    __shared__ __attribute__((aligned(16))) unsigned sAnc[SEG];
     __shared__ i64 s_j[2];
-    __shared__ u64 s_wmax[kExpandThreads / 64];
+    __shared__ unsigned s_wmax[kExpandThreads / 64];
     const int tid = threadIdx.x, wid = tid >> 6;
     AFun f;
-    if (!make_afun(a.ctrl, a.pref, a.tpre, a.n, a.count_mode, f, blockIdx.x == 0 && tid == 0))
-        return;
-    if (a.skip_identity && f.mode == 0) return;
+    bool failed = false;
+    if (!make_afun(a.ctrl, a.pref, a.tpre, a.n, a.count_mode, f, blockIdx.x == 0 && tid == 0)) {
+        // an iteration that found an error resamples nothing: its proposal
+        // still has to reach the caller's array
+        if (a.mode != ExpandMode::kForward) return;
+        failed = true;
+        f.mode = 0;
+    }
+    if (a.mode == ExpandMode::kIfResampled && f.mode == 0) return;
 
     const i64 n = a.n;
-    const i64 k0 = (i64)blockIdx.x * kSegLen;
-    const i64 k1 = (k0 + kSegLen < 2 * n) ? k0 + kSegLen : 2 * n;
+    const i64 k0 = (i64)blockIdx.x * SEG;
+    const i64 k1 = (k0 + SEG < 2 * n) ? k0 + SEG : 2 * n;
     if (wid < 2) {
         const i64 k = wid == 0 ? k0 : k1;
         const i64 lo = k - n > 0 ? k - n : 0;
@@ -387,21 +410,36 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     const i64 p0 = k0 - j0;
     const int ns = (int)(j1 - j0), np = (int)((k1 - j1) - p0);
 
-    // sources j0 - 1 .. j1 - 1 (at most kSegLen + 1 < 4096) lie in at most two
-    // tiles: their offsets are read once
-    const i64 ta = (j0 > 0 ? j0 - 1 : 0) >> kTileShift;
-    const i64 ntl = (n + kTile - 1) >> kTileShift;
-    const u64 off_a = f.mode ? f.tpre[ta] : 0ull;
-    const u64 off_b = (f.mode && ta + 1 < ntl) ? f.tpre[ta + 1] : 0ull;
-    for (int i = tid; i <= ns; i += kExpandThreads) {
-        const i64 j = j0 - 1 + i;
-        if (j < 0) {
-            sA[i] = 0u;
-            continue;
+    // Alg 4 reset of the outputs this segment owns (a pass of its own took 21 us
+    // and a launch at N = 2^24)
+    if (f.mode == 1 && a.logw) {
+        if (a.uniform) {
+            if (blockIdx.x == 0 && tid == 0) *a.uniform = 1u;
+        } else {
+            for (int r = tid; r < np; r += kExpandThreads) a.logw[p0 + r] = a.reset;
         }
-        const u64 sj = f.mode ? a.pref[j] + ((j >> kTileShift) == ta ? off_a : off_b) : 0ull;
-        sA[i] = f.A_of(j, sj);
     }
+
+    // From here on in 32 bits: sources, outputs and A are below 2^31.
+    const unsigned p0u = (unsigned)p0, j0u = (unsigned)j0;
+    if (f.mode == 0) {
+        for (int i = tid; i <= ns; i += kExpandThreads) sA[i] = j0u + (unsigned)i;
+    } else {
+        // sA[i] is A of source j0 - 1 + i; these sources (at most SEG + 1 < 4096)
+        // lie in at most two tiles, whose offsets are read once
+        const int skip = j0 == 0 ? 1 : 0;  // A before the first source is 0
+        const i64 jb = j0 - 1 + skip;
+        const i64 ta = jb >> kTileShift;
+        const i64 ntl = (n + kTile - 1) >> kTileShift;
+        const u64 off_a = f.tpre[ta];
+        const u64 off_b = ta + 1 < ntl ? f.tpre[ta + 1] : 0ull;
+        const int ib = (int)(((ta + 1) << kTileShift) - jb);  // first source of the second tile
+        const u64 *pj = a.pref + jb;
+        if (skip && tid == 0) sA[0] = 0u;
+        for (int i = tid; i <= ns - skip; i += kExpandThreads)
+            sA[i + skip] = f.A_of(0, pj[i] + (i < ib ? off_a : off_b));
+    }
+    for (int r = tid; r < np; r += kExpandThreads) sAnc[r] = 0u;
     __syncthreads();
     if (a.nc_out)
         for (int i = tid; i < ns; i += kExpandThreads)
@@ -413,90 +451,86 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     // the rest of its source's outputs.  Local source ns (source j1) owns
     // whatever follows sA[ns].  Marks land on distinct outputs (sources with
     // copies start at distinct outputs) and output p0 always holds one.
-    for (int r = tid; r < np; r += kExpandThreads) sAnc[r] = 0u;
-    __syncthreads();
     for (int t = tid; t <= ns; t += kExpandThreads) {
-        const i64 lo = sA[t];
-        const i64 hi = t < ns ? (i64)sA[t + 1] : INT64_MAX;
-        if (hi > lo && hi > p0) {
-            const i64 st = (lo > p0 ? lo : p0) - p0;
-            if (st < np) sAnc[st] = (unsigned)(t + 1);
+        const unsigned lo = sA[t], hi = t < ns ? sA[t + 1] : 0xFFFFFFFFu;
+        if (hi > lo && hi > p0u) {
+            const unsigned st = lo > p0u ? lo - p0u : 0u;
+            if (st < (unsigned)np) sAnc[st] = (unsigned)(t + 1);
         }
     }
     __syncthreads();
     {
-        constexpr int E = kSegLen / kExpandThreads;  // outputs per thread, contiguous
-        static_assert(E == 8, "two 16-byte LDS reads per thread");
+        constexpr int E = SEG / kExpandThreads;  // outputs per thread, contiguous
+        static_assert(E >= 1 && E * kExpandThreads == SEG, "whole outputs a thread");
         const int lane = tid & 63;
         // entries past np are stale; they reach only positions past np
-        const uint4 q0 = reinterpret_cast<const uint4 *>(sAnc)[2 * tid];
-        const uint4 q1 = reinterpret_cast<const uint4 *>(sAnc)[2 * tid + 1];
-        unsigned v[E] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-        unsigned run = 0u;
+        unsigned v[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            run = v[e] > run ? v[e] : run;
-            v[e] = run;
-        }
-        const u64 incl = wave_scan_u64((u64)run, 0ull, [](u64 x, u64 y) { return y > x ? y : x; });
+        for (int e = 0; e < E; ++e) v[e] = sAnc[tid * E + e];
+#pragma unroll
+        for (int e = 1; e < E; ++e) v[e] = v[e] > v[e - 1] ? v[e] : v[e - 1];
+        const unsigned incl = wave_scan_max_u32(v[E - 1]);
         if (lane == 63) s_wmax[wid] = incl;
-        u64 carry = (u64)__shfl_up((long long)incl, 1, 64);
-        carry = lane ? carry : 0ull;
+        unsigned carry = (unsigned)__shfl_up((int)incl, 1, 64);
+        carry = lane ? carry : 0u;
         __syncthreads();
         for (int w = 0; w < wid; ++w) carry = s_wmax[w] > carry ? s_wmax[w] : carry;
+        const unsigned last = (unsigned)n - 1u;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int r = tid * E + e;
-            if (r < np) {
-                const unsigned m = v[e] > (unsigned)carry ? v[e] : (unsigned)carry;
-                i64 anc = j0 + (i64)m - 1;
-                anc = anc < n ? anc : n - 1;
-                sAnc[r] = (unsigned)anc;
-                if (a.anc_out) a.anc_out[p0 + r] = anc;
-            }
+            unsigned anc = j0u + (v[e] > carry ? v[e] : carry) - 1u;
+            anc = anc < last ? anc : last;  // entries past np: any valid source
+            sAnc[tid * E + e] = anc;
+        }
+        if (a.anc_out) {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (tid * E + e < np) a.anc_out[p0 + tid * E + e] = (i64)sAnc[tid * E + e];
         }
     }
     __syncthreads();
+    const bool distinct = np < 2 * ns;  // fewer than two outputs per source in this segment
     if constexpr (kSum) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (np < 2 * ns)
-            copy_rows<VEC, true, true>(a.x, a.xo, a.row_bytes, a.cpr_shift, sAnc, p0, np, acc);
+        RowAcc<VEC> acc;
+        acc.init();
+        // the filter's mean of the new population: equal weights when it
+        // resampled, the current ones against the exact max otherwise
+        const double *lw = f.mode == 0 && !failed ? a.logw : nullptr;
+        const double m = lw ? a.ctrl->m : a.reset;
+        if (a.stream && distinct)
+            copy_rows<VEC, true, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
+        else if (a.stream)
+            copy_rows<VEC, true, false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
         else
-            copy_rows<VEC, true>(a.x, a.xo, a.row_bytes, a.cpr_shift, sAnc, p0, np, acc);
-        store_row_sums(acc, np, a.est_part + (i64)blockIdx.x * kEstCols);
-    } else if (VEC == 8 && a.row_bytes == 8 && a.aux && a.aux_bytes == 8) {
-        if (np < 2 * ns) copy_rows_8x2<true>(a.x, a.xo, a.aux, a.auxo, sAnc, p0, np);
-        else copy_rows_8x2<false>(a.x, a.xo, a.aux, a.auxo, sAnc, p0, np);
-        return;
-    } else if (np < 2 * ns) {
-        // fewer than two outputs per source in this segment
-        copy_rows<VEC, false, true>(a.x, a.xo, a.row_bytes, a.cpr_shift, sAnc, p0, np);
+            copy_rows<VEC, true, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
+        store_row_sums(acc, failed ? -__builtin_huge_val() : m, a.est_part + blockIdx.x,
+                       gridDim.x);
+    } else if (a.stream && distinct) {
+        copy_rows<VEC, false, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+    } else if (a.stream) {
+        copy_rows<VEC, false, false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else {
-        copy_rows<VEC>(a.x, a.xo, a.row_bytes, a.cpr_shift, sAnc, p0, np);
+        copy_rows<VEC, false, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     }
-    if (a.aux) {
-        if (np < 2 * ns)
-            copy_rows<8, false, true>(a.aux, a.auxo, a.aux_bytes, a.aux_shift, sAnc, p0, np);
-        else
-            copy_rows<8>(a.aux, a.auxo, a.aux_bytes, a.aux_shift, sAnc, p0, np);
-    }
+    if (a.aux) copy_rows<8, false, false, false>(a.aux, a.auxo, 8, sAnc, p0, np);
 }
 
-static int shift_of(int v)
+template <int VEC, bool kSum>
+static void launch_expand_seg(int seg, int64_t n, hipStream_t s, const ExpandArgs &a)
 {
-    if (v <= 0 || (v & (v - 1))) return -1;
-    int s = 0;
-    while ((1 << s) < v) ++s;
-    return s;
+    const dim3 g((unsigned)((2 * n + seg - 1) / seg)), b(kExpandThreads);
+    switch (seg) {
+    case 256: hipLaunchKernelGGL((k_expand<VEC, 256, kSum>), g, b, 0, s, a); break;
+    case 512: hipLaunchKernelGGL((k_expand<VEC, 512, kSum>), g, b, 0, s, a); break;
+    case 1024: hipLaunchKernelGGL((k_expand<VEC, 1024, kSum>), g, b, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_expand<VEC, kSegLen, kSum>), g, b, 0, s, a); break;
+    }
 }
 
 hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x, void *x_out,
-                         int row_bytes, const void *aux, void *aux_out, int aux_bytes,
-                         int64_t *ncopies_out, int64_t *anc_out, hipStream_t s,
-                         bool skip_identity, double *est_part)
+                         int row_bytes, hipStream_t s, const ExpandOut &o)
 {
     ExpandArgs a;
-    a.skip_identity = skip_identity ? 1 : 0;
     a.n = n;
     a.pref = w.pref;
     a.pref64 = w.pref64;
@@ -506,29 +540,28 @@ hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x
     a.x = reinterpret_cast<const unsigned char *>(x);
     a.xo = reinterpret_cast<unsigned char *>(x_out);
     a.row_bytes = row_bytes;
-    a.aux = reinterpret_cast<const unsigned char *>(aux);
-    a.auxo = reinterpret_cast<unsigned char *>(aux_out);
-    a.aux_bytes = aux_bytes;
-    a.aux_shift = shift_of(aux_bytes / 8);
-    a.nc_out = reinterpret_cast<i64 *>(ncopies_out);
-    a.anc_out = reinterpret_cast<i64 *>(anc_out);
-    a.est_part = est_part;
+    a.aux = reinterpret_cast<const unsigned char *>(o.aux);
+    a.auxo = reinterpret_cast<unsigned char *>(o.aux_out);
+    a.nc_out = reinterpret_cast<i64 *>(o.ncopies);
+    a.anc_out = reinterpret_cast<i64 *>(o.anc);
+    a.mode = o.mode;
+    a.logw = o.logw;
+    a.reset = o.reset;
+    a.uniform = o.uniform;
+    a.est_part = o.est_part;
+    a.stream = n * (int64_t)row_bytes >= kStreamBytes;
     const uintptr_t al = (uintptr_t)x | (uintptr_t)x_out | (uintptr_t)row_bytes;
-    const int64_t segs = expand_segments(n);
-    if (est_part) {
-        if ((al & 15) != 0 || row_bytes != 32) return hipErrorInvalidValue;
-        a.cpr_shift = 1;
-        hipLaunchKernelGGL((k_expand<16, true>), dim3((unsigned)segs), dim3(kExpandThreads), 0, s,
-                           a);
+    const int seg = expand_seg_len(n);
+    if (o.est_part) {
+        if ((al & 7) != 0 || row_bytes != 32) return hipErrorInvalidValue;
+        if ((al & 15) == 0) launch_expand_seg<16, true>(seg, n, s, a);
+        else launch_expand_seg<8, true>(seg, n, s, a);
     } else if ((al & 15) == 0) {
-        a.cpr_shift = shift_of(row_bytes / 16);
-        hipLaunchKernelGGL(k_expand<16>, dim3((unsigned)segs), dim3(kExpandThreads), 0, s, a);
+        launch_expand_seg<16, false>(seg, n, s, a);
     } else if ((al & 7) == 0) {
-        a.cpr_shift = shift_of(row_bytes / 8);
-        hipLaunchKernelGGL(k_expand<8>, dim3((unsigned)segs), dim3(kExpandThreads), 0, s, a);
+        launch_expand_seg<8, false>(seg, n, s, a);
     } else {
-        a.cpr_shift = shift_of(row_bytes / 4);
-        hipLaunchKernelGGL(k_expand<4>, dim3((unsigned)segs), dim3(kExpandThreads), 0, s, a);
+        launch_expand_seg<4, false>(seg, n, s, a);
     }
     return hipGetLastError();
 }

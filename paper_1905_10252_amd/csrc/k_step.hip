@@ -1,19 +1,16 @@
 // Sampler kernels of Alg 2 (SMC sampler with recycling), random-walk proposal
 // and backward kernel L = q (so the incremental weight is pi(x_t)/pi(x_{t-1}),
 // eq. smcs_drawing_weights):
-//   k_is<target, init>  draws x0 ~ q0 or x_t = x_{t-1} + rw_sd z, evaluates the
-//                       cheap targets, updates the log-weights, and leaves per
-//                       block estimate sums (block-local max) and the grid max.
-//   k_reweight<init>    the weight update for targets whose log-density comes
-//                       from a separate likelihood kernel.
+//   k_is<target, init>  one-coordinate particles: draws x0 ~ q0 or
+//                       x_t = x_{t-1} + rw_sd z, evaluates the target, updates
+//                       the log-weights, and leaves per block estimate sums
+//                       (against a block reference) and the grid max.
+//   k_rows              the same for rows of several coordinates, and the
+//                       weight update of the logistic regression after its
+//                       proposal (k_propose) and likelihood kernels.
 //   k_step_stats        estimates f_t (eq. estimation_at_t), c_t
 //                       (eq. normconst) and the recycled estimate
 //                       (eq. recycling).
-//   k_copyback          after an in-place update and redistribute: particles
-//                       and cached log-target back in place, weights reset to
-//                       1/N (Alg 4 Reset).
-//   k_reset_est         after a redistribution straight into x: the reset,
-//                       and for the filter the post-resampling sums.
 //   k_is<BEARING>       one SIR particle-filter update (Alg 1, Sec. 5.2.2):
 //                       constant-velocity transition as proposal, bearing
 //                       likelihood as weight; the expand then adds up the rows
@@ -167,9 +164,15 @@ typedef double f64x2s __attribute__((ext_vector_type(2)));
 // The update of one-coordinate particles (Gaussian and Student-t targets, the
 // estimate sums in the same pass) and of the particle filter, which takes its
 // estimate after resampling.  k_rows below is the update of longer rows.
-// kOut: the proposal goes to xo (the redistribution then maps it back into
-// x); otherwise it overwrites x in place.
-template <int kKind, bool kInit, bool kOut>
+// Where the proposal goes.  kToCopy: to the workspace copy xo; the
+// redistribution then maps it into x.  kToBoth: to x, and to xo as well, from
+// which a resampling redistribution writes x; an iteration that keeps its
+// weights is then done (the second store rides under the arithmetic; mapping x
+// into a copy and back instead took another pass over the rows each way).
+// kInPlace: to x alone.
+enum Dst { kInPlace, kToCopy, kToBoth };
+
+template <int kKind, bool kInit, Dst kDst>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_is(
     TArgs a, i64 n, uint32_t t, double *__restrict__ x, double *__restrict__ logw,
     double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo)
@@ -297,13 +300,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                     for (int h = 0; h < 2; ++h) lw[h] = lw[h] + (l4[2 + h] - l4[h]);
                 }
                 if (v2) {
-                    *reinterpret_cast<f64x2s *>((kOut ? xo : x) + 2 * p) = f64x2s{xk[0], xk[1]};
+                    if (kDst != kToCopy)
+                        *reinterpret_cast<f64x2s *>(x + 2 * p) = f64x2s{xk[0], xk[1]};
+                    if (kDst != kInPlace)
+                        *reinterpret_cast<f64x2s *>(xo + 2 * p) = f64x2s{xk[0], xk[1]};
                     *reinterpret_cast<f64x2s *>(logw + 2 * p) = f64x2s{lw[0], lw[1]};
                 } else {
-                    (kOut ? xo : x)[2 * p] = xk[0];
+                    if (kDst != kToCopy) x[2 * p] = xk[0];
+                    if (kDst != kInPlace) xo[2 * p] = xk[0];
                     logw[2 * p] = lw[0];
                     if (two) {
-                        (kOut ? xo : x)[2 * p + 1] = xk[1];
+                        if (kDst != kToCopy) x[2 * p + 1] = xk[1];
+                        if (kDst != kInPlace) xo[2 * p + 1] = xk[1];
                         logw[2 * p + 1] = lw[1];
                     } else {
                         lw[1] = -__builtin_huge_val();  // no particle: weight zero
@@ -320,7 +328,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const i64 i = base + (tid & 63);
             const bool act = i < n;
             double *xi = x + i * 4;
-            double *xw = (kOut ? xo : x) + i * 4;
+            double *xw = (kDst == kToCopy ? xo : x) + i * 4;
             // the particle's state and weight are requested before the
             // normals are drawn, so the loads overlap the generator
             const i64 ic = act ? i : 0;
@@ -444,11 +452,12 @@ inline int64_t row_chunks(int64_t n, int d)
 }
 
 // Proposal of the logistic regression's particles (its log-target comes from
-// the likelihood kernels, its weights from k_rows).  With d = 1 particles 2p
+// the likelihood kernels, its weights from k_rows), to x and (xo not NULL) to
+// the workspace copy.  With d = 1 particles 2p
 // and 2p + 1 take the pair drawn for index p: rows of two values.
 template <bool kInit>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_propose(
-    TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x)
+    TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x, double *__restrict__ xo)
 {
     __shared__ uint4 s_xch[256];
     const int dv = a.d == 1 ? 2 : a.d;
@@ -461,6 +470,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                          const i64 o = (base + p) * dv + c;
                          x[o] = v0;
                          if (two) x[o + 1] = v1;
+                         if (xo) {
+                             xo[o] = v0;
+                             if (two) xo[o + 1] = v1;
+                         }
                          if (a.thb) {
                              // particle and column of value o (rows of two: one column)
                              const i64 i0 = a.d == 1 ? o : base + p;
@@ -507,7 +520,7 @@ __device__ inline double logreg_lp_row(const double *row, int d, double lik, con
 // once in memory; a second pass over the population for the estimates, with
 // the exponential formed again for every coordinate, took 30 of 50 us at
 // N = 300007, d = 10.  Bound by vector issue of the normals.
-template <int kKind, bool kInit, bool kOut>
+template <int kKind, bool kInit, Dst kDst>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows(
     TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x, double *__restrict__ logw,
     double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo,
@@ -544,11 +557,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             draw_rows<kInit>(a, d, base, cnt, n * d, t, x, s_buf,
                              [&](int p, int c, bool two, double v0, double v1) {
                                  const i64 o = (base + p) * d + c;
-                                 (kOut ? xo : x)[o] = v0;
                                  rows[p * ds + c] = v0;
-                                 if (two) {
-                                     (kOut ? xo : x)[o + 1] = v1;
-                                     rows[p * ds + c + 1] = v1;
+                                 if (two) rows[p * ds + c + 1] = v1;
+                                 if (kDst != kToCopy) {
+                                     x[o] = v0;
+                                     if (two) x[o + 1] = v1;
+                                 }
+                                 if (kDst != kInPlace) {
+                                     xo[o] = v0;
+                                     if (two) xo[o + 1] = v1;
                                  }
                              });
         } else {
@@ -590,7 +607,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             if (kKind == SMC_TARGET_GAUSS) lpn = a.log_norm - 0.5 * acc;
             else lpn = logreg_lp_row(row, d, lik, s_par[0], lr, a.log_norm);
             lw = kInit ? lpn - (a.init_log_norm - 0.5 * acc0) : lw_old + (lpn - lp_old);
-            (kOut ? lpo : lp)[i] = lpn;
+            if (kDst != kToCopy) lp[i] = lpn;
+            if (kDst != kInPlace) lpo[i] = lpn;
             logw[i] = lw;
             bad |= !(lw < __builtin_huge_val());  // NaN or +inf
             const u64 kk = okey(lw);
@@ -680,116 +698,25 @@ __global__ __launch_bounds__(1024) void k_step_stats(Ctrl *ctrl, const double *i
     if (tid < 2 * d && !err) write_estimates(s_st, tid, d, rec_old, rec_num, est);
 }
 
-// uniform (lazy reset): instead of writing logw, mark the weights uniform.
-__global__ __launch_bounds__(256) void k_copyback(Ctrl *ctrl, i64 n, int d, double *x,
-                                                  const double *x_scr, double *lp,
-                                                  const double *lp_scr, double *logw,
-                                                  double reset, unsigned *uniform)
+// The filter's row sums of more than kIsBlocks expand workgroups, gathered
+// into kFoldBlocks rows (workgroup b adds segments b, b + kFoldBlocks, ... of
+// each column, in that order; all of them carry the same reference).
+constexpr int kFoldBlocks = 256;
+
+__global__ __launch_bounds__(64) void k_fold_rows(const double *epart, i64 nseg, double *is_part)
 {
-    if (!ctrl->resample || ctrl->err_call) return;
-    const i64 gtid = (i64)blockIdx.x * 256 + threadIdx.x, gsz = (i64)gridDim.x * 256;
-    for (i64 i = gtid; i < n * d; i += gsz) x[i] = x_scr[i];
-    for (i64 i = gtid; i < n; i += gsz) {
-        if (lp_scr) lp[i] = lp_scr[i];
-        if (!uniform) logw[i] = reset;
-    }
-    if (uniform && gtid == 0) *uniform = 1u;
+    const int c = threadIdx.x;
+    if (c >= kEstCols) return;
+    const double *col = epart + c * nseg;
+    double v = 0.0;
+    if (c == 0) v = col[blockIdx.x];
+    else
+        for (i64 g = blockIdx.x; g < nseg; g += kFoldBlocks) v += col[g];
+    is_part[c * kFoldBlocks + blockIdx.x] = v;
 }
 
-// After a redistribution straight into x: weights reset to 1/N when it
-// resampled; with DT > 0 (the particle filter) also the post-resampling sums
-// of Alg 1: when resampled, the equal-weight sums the expand formed from the
-// rows it wrote (epart, one row per expand workgroup; NULL when x was not
-// 16-byte aligned for it), gathered into block b's row from workgroups
-// b, b + grid, ... in that order; else read from x, with equal weights when
-// resampled and the current ones against the exact max otherwise.  A step that found an error
-// redistributes nothing: the proposal (and its log-target) is copied into
-// place instead, as the in-place update would have left it.
-template <int DT>
-__global__ __launch_bounds__(256) void k_reset_est(const Ctrl *ctrl, i64 n, int d,
-                                                   double *__restrict__ x,
-                                                   const double *__restrict__ x_scr,
-                                                   double *__restrict__ lp,
-                                                   const double *__restrict__ lp_scr,
-                                                   double *__restrict__ logw, double reset,
-                                                   double *is_part, const double *epart,
-                                                   i64 nseg, unsigned *uniform)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const i64 gtid = (i64)blockIdx.x * 256 + tid, gsz = (i64)gridDim.x * 256;
-    if (ctrl->err_call) {
-        for (i64 e = gtid; e < n * d; e += gsz) x[e] = x_scr[e];
-        if (lp_scr)
-            for (i64 i = gtid; i < n; i += gsz) lp[i] = lp_scr[i];
-        if (DT > 0 && tid == 0) {  // no estimate for a failed step
-            double *part = is_part + blockIdx.x;
-            part[0] = -__builtin_huge_val();
-            for (int c = 1; c < 2 + 2 * DT; ++c) part[(i64)c * gridDim.x] = 0.0;
-        }
-        return;
-    }
-    const bool rs = ctrl->resample;
-    // lazy reset: the weights are marked uniform instead of written
-    const bool wr = rs && !uniform;
-    if (rs && uniform && gtid == 0) *uniform = 1u;
-    if (DT == 0) {
-        if (wr)
-            for (i64 i = gtid; i < n; i += gsz) logw[i] = reset;
-        return;
-    }
-    constexpr int DA = DT > 0 ? DT : 1;
-    if (rs && epart) {
-        static_assert(DT == 0 || 2 + 2 * DA == kEstCols, "filter row layout");
-        if (wr)
-            for (i64 i = gtid; i < n; i += gsz) logw[i] = reset;
-        if (tid < kEstCols) {
-            double v = 0.0;
-            for (i64 g = blockIdx.x; g < nseg; g += gridDim.x) v += epart[g * kEstCols + tid];
-            is_part[(i64)tid * gridDim.x + blockIdx.x] = tid == 0 ? reset : v;
-        }
-        return;
-    }
-    __shared__ double s_acc[4][1 + 2 * DA];
-    const double m = rs ? reset : ctrl->m;
-    double e0 = 0.0, e1[DA], e2[DA];
-    for (int k = 0; k < DA; ++k) e1[k] = e2[k] = 0.0;
-    for (i64 i = gtid; i < n; i += gsz) {
-        double e = 1.0;
-        if (rs) {
-            if (wr) logw[i] = reset;
-        } else {
-            e = det_exp(logw[i] - m);
-        }
-        e0 += e;
-        for (int k = 0; k < DA; ++k) {
-            const double xk = x[i * DA + k];
-            const double ex = e * xk;
-            e1[k] += ex;
-            e2[k] += ex * xk;
-        }
-    }
-    e0 = wave_sum_f64(e0);
-    for (int k = 0; k < DA; ++k) {
-        e1[k] = wave_sum_f64(e1[k]);
-        e2[k] = wave_sum_f64(e2[k]);
-    }
-    if (lane == 0) {
-        s_acc[wid][0] = e0;
-        for (int k = 0; k < DA; ++k) {
-            s_acc[wid][1 + k] = e1[k];
-            s_acc[wid][1 + DA + k] = e2[k];
-        }
-    }
-    __syncthreads();
-    double *part = is_part + blockIdx.x;
-    for (int c = tid; c < 2 + 2 * DA; c += 256)
-        part[(i64)c * gridDim.x] = c == 0 ? m : ((s_acc[0][c - 1] + s_acc[1][c - 1]) + s_acc[2][c - 1]) +
-                                   s_acc[3][c - 1];
-}
-
-// Weighted sums of the population after resampling (Alg 1 takes its mean
-// after the resampling step), in the block-partial layout of is_block_finish
-// with one common reference weight.
+// Weighted sums of the initial population, one partial row per block with one
+// common reference weight.
 template <int DT>
 __global__ __launch_bounds__(256) void k_post_est(const Ctrl *ctrl, i64 n, int d,
                                                   const double *__restrict__ x,
@@ -1556,38 +1483,38 @@ hipError_t logreg_lik(const smc_config &c, const Work &w, const double *x, int64
     return hipGetLastError();
 }
 
-// out: the proposal goes to the workspace copy x_scr.
 template <int kKind, bool kInit>
 void launch_is_k(dim3 g, hipStream_t s, const TArgs &a, i64 n, uint32_t t, double *x, double *logw,
-                 const Work &w, u64 *sp, bool out)
+                 const Work &w, u64 *sp, Dst dst)
 {
-    if (!kInit && out)
-        hipLaunchKernelGGL((k_is<kKind, false, true>), g, dim3(256), 0, s, a, n, t, x, logw, w.lp,
-                           sp, w.is_part, w.x_scr);
-    else
-        hipLaunchKernelGGL((k_is<kKind, kInit, false>), g, dim3(256), 0, s, a, n, t, x, logw, w.lp,
-                           sp, w.is_part, (double *)nullptr);
+    auto kern = k_is<kKind, kInit, kInPlace>;
+    if constexpr (!kInit) {
+        if (dst == kToCopy) kern = k_is<kKind, false, kToCopy>;
+        if constexpr (kKind != SMC_TARGET_BEARING)
+            if (dst == kToBoth) kern = k_is<kKind, false, kToBoth>;
+    }
+    hipLaunchKernelGGL(kern, g, dim3(256), 0, s, a, n, t, x, logw, w.lp, sp, w.is_part, w.x_scr);
 }
 
-// The same for rows of several coordinates; out: also the log-targets.
+// The same for rows of several coordinates, with their log-targets.
 template <int kKind, bool kInit>
 void launch_rows_k(dim3 g, hipStream_t s, const TArgs &a, i64 n, uint32_t t, double *x,
-                   double *logw, const Work &w, u64 *sp, bool out, const LrArgs &lr)
+                   double *logw, const Work &w, u64 *sp, Dst dst, const LrArgs &lr)
 {
     const int P = rows_per_block(n, a.d);
     const size_t lds = (size_t)P * ((a.d | 1) + 1) * sizeof(double);
-    if (!kInit && out)
-        hipLaunchKernelGGL((k_rows<kKind, false, true>), g, dim3(256), lds, s, a, n, t, P, x, logw,
-                           w.lp, sp, w.is_part, w.x_scr, w.lp_scr, lr);
-    else
-        hipLaunchKernelGGL((k_rows<kKind, kInit, false>), g, dim3(256), lds, s, a, n, t, P, x,
-                           logw, w.lp, sp, w.is_part, (double *)nullptr, (double *)nullptr, lr);
+    auto kern = k_rows<kKind, kInit, kInPlace>;
+    if constexpr (!kInit) {
+        if (dst == kToCopy) kern = k_rows<kKind, false, kToCopy>;
+        if (dst == kToBoth) kern = k_rows<kKind, false, kToBoth>;
+    }
+    hipLaunchKernelGGL(kern, g, dim3(256), lds, s, a, n, t, P, x, logw, w.lp, sp, w.is_part,
+                       w.x_scr, w.lp_scr, lr);
 }
 
-// out: the proposal goes to the workspace copies (x_scr, lp_scr).
 template <bool kInit>
 hipError_t launch_is(const smc_config &c, const Work &w, int par, uint32_t t, double *x,
-                     double *logw, hipStream_t s, bool out = false)
+                     double *logw, hipStream_t s, Dst out = kInPlace)
 {
     const TArgs a = targs(c, w, is_bf16(c));
     const dim3 g(w.is_grid);
@@ -1607,10 +1534,10 @@ hipError_t launch_is(const smc_config &c, const Work &w, int par, uint32_t t, do
     case SMC_TARGET_LOGREG: {
         const int P = rows_per_block(n, c.d);
         hipLaunchKernelGGL(k_propose<kInit>, dim3((unsigned)row_chunks(n, c.d)), dim3(256), 0, s,
-                           a, n, t, P, x);
+                           a, n, t, P, x, out == kInPlace ? nullptr : w.x_scr);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         if (logreg_lik(c, w, x, n, true, s) != hipSuccess) return hipErrorLaunchFailure;
-        launch_rows_k<SMC_TARGET_LOGREG, kInit>(g, s, a, n, t, x, logw, w, sp, false,
+        launch_rows_k<SMC_TARGET_LOGREG, kInit>(g, s, a, n, t, x, logw, w, sp, out,
                                                 lr_args(c, w));
         break;
     }
@@ -1626,7 +1553,7 @@ template <int kKind>
 int resident_blocks()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_is<kKind, false, false>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_is<kKind, false, kInPlace>, 256, 0) !=
         hipSuccess)
         return 0;
     return nb;
@@ -1733,15 +1660,18 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     if (small_path(c)) return small_step(c, w, K, par, t, x, logw, info, est, s);
     const int64_t n = c.n;
     const bool pf = c.target == SMC_TARGET_BEARING;
-    // With resampling forced every iteration the proposal goes to the
-    // workspace copy and the redistribution writes straight into x (an
-    // identity copy if the step found an error or kept the weights): no copy
-    // back.  The particle filter always takes this path (its weights collapse
-    // almost every update, and the expand forms its post-resampling sums from
-    // the rows it writes).  With the ESS rule a sampler is updated in place,
-    // and only resampling steps move rows.
+    // Resampling forced every iteration, and the particle filter (its weights
+    // collapse almost every update, and the expand forms its post-resampling
+    // sums from the rows it writes): the proposal goes to the workspace copy
+    // and the redistribution writes x (an identity copy if the step found an
+    // error or kept the weights).  ESS rule: to both, and a resampling
+    // redistribution overwrites x.  The logistic regression reads its proposal
+    // back from x and so always writes it there.
     const bool fwd = (c.mode == SMC_MODE_FORCE && c.target != SMC_TARGET_LOGREG) || pf;
-    if (launch_is<false>(c, w, par, t, x, logw, s, fwd) != hipSuccess) return SMC_E_DEVICE;
+    const bool keep = c.mode == SMC_MODE_NEVER && !pf;
+    if (launch_is<false>(c, w, par, t, x, logw, s,
+                         fwd ? kToCopy : keep ? kInPlace : kToBoth) != hipSuccess)
+        return SMC_E_DEVICE;
     if (launch_quant_scan(w, logw, n, K, par, s, c.lazy_reset != 0) != hipSuccess)
         return SMC_E_DEVICE;
     const uint64_t r = resample_word(c.seed, c.sampler_id, t);
@@ -1757,38 +1687,30 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     }
     if (launch_decide(w, par, n, K, r, c.mode, c.ess_num, c.ess_den, info, s, st) != hipSuccess)
         return SMC_E_DEVICE;
-    const double reset = -std::log((double)n);
-    unsigned *uni = c.lazy_reset ? &w.ctrl->uniform : nullptr;
+    if (keep) return SMC_OK;
+    ExpandOut o;
+    o.mode = fwd ? ExpandMode::kForward : ExpandMode::kIfResampled;
+    o.logw = logw;
+    o.reset = -std::log((double)n);
+    o.uniform = c.lazy_reset ? &w.ctrl->uniform : nullptr;
     // the particle filter and the 1-D Gaussian and Student-t samplers carry no
     // cached log-target
-    const bool lpc = !pf && !(c.d == 1 && (c.target == SMC_TARGET_GAUSS ||
-                                           c.target == SMC_TARGET_STUDENT));
-    double *lp = lpc ? w.lp : nullptr, *lp_scr = lpc ? w.lp_scr : nullptr;
-    if (fwd) {
-        // the filter's row sums ride on 16-byte chunks of its 32-byte rows
-        double *ep = (pf && ((uintptr_t)x & 15) == 0) ? w.epart : nullptr;
-        if (launch_expand(w, n, 0, w.x_scr, x, c.d * 8, lp_scr, lp, 8, nullptr, nullptr, s,
-                          false, ep) != hipSuccess)
-            return SMC_E_DEVICE;
-        if (pf) {  // Alg 1 takes the mean after resampling
-            hipLaunchKernelGGL(k_reset_est<4>, dim3(w.is_grid), dim3(256), 0, s, w.ctrl, (i64)n,
-                               c.d, x, w.x_scr, (double *)nullptr, (const double *)nullptr,
-                               logw, reset, w.is_part, (const double *)ep,
-                               (i64)expand_segments(n), uni);
-            hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part,
-                               w.is_grid, c.d, w.rec_num, est, info, 0);
-        } else {
-            hipLaunchKernelGGL(k_reset_est<0>, dim3(w.is_grid), dim3(256), 0, s, w.ctrl, (i64)n,
-                               c.d, x, w.x_scr, lp, lp_scr, logw, reset, w.is_part,
-                               (const double *)nullptr, (i64)0, uni);
-        }
-        return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
+    if (!pf && !(c.d == 1 && (c.target == SMC_TARGET_GAUSS || c.target == SMC_TARGET_STUDENT))) {
+        o.aux = w.lp_scr;
+        o.aux_out = w.lp;
     }
-    if (launch_expand(w, n, 0, x, w.x_scr, c.d * 8, lp, lp_scr, 8, nullptr, nullptr, s, true) !=
-        hipSuccess)
-        return SMC_E_DEVICE;
-    hipLaunchKernelGGL(k_copyback, dim3(grid_for(n * c.d)), dim3(256), 0, s, w.ctrl, (i64)n, c.d,
-                       x, w.x_scr, lp, lp_scr, logw, reset, uni);
+    o.est_part = pf ? w.epart : nullptr;
+    if (launch_expand(w, n, 0, w.x_scr, x, c.d * 8, s, o) != hipSuccess) return SMC_E_DEVICE;
+    if (pf) {  // Alg 1 takes the mean after resampling
+        const int64_t nseg = expand_segments(n);
+        const bool fold = nseg > kIsBlocks;
+        if (fold)
+            hipLaunchKernelGGL(k_fold_rows, dim3(kFoldBlocks), dim3(64), 0, s, w.epart, (i64)nseg,
+                               w.is_part);
+        hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl,
+                           fold ? w.is_part : w.epart, fold ? kFoldBlocks : (int)nseg, c.d,
+                           w.rec_num, est, info, 0);
+    }
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 

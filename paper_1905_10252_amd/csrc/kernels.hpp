@@ -17,7 +17,10 @@ static_assert(kTile == 1 << kTileShift, "tile size");
 constexpr int kMaxBlocks = 1024;                  // grid of the max / reweight passes
 constexpr int kIsBlocks = 2048;                   // max grid of the sampler kernels
 constexpr int kExpandThreads = 256;
-constexpr int kSegLen = 2048;                     // merge-path steps per expand workgroup
+constexpr int kSegLen = 2048;                     // most merge-path steps per expand workgroup
+// Populations from this size on are written past the caches by the expand
+// (half of the 256 MB memory-side cache).
+constexpr int64_t kStreamBytes = 128ll << 20;
 // Largest row of smc_redistribute: a segment's 32-bit chunk count
 // (kSegLen rows of row_bytes / 4 chunks) then stays below 2^31.
 constexpr int kMaxRowBytes = 1 << 20;
@@ -46,7 +49,7 @@ struct Work {
     double *lp_scr;     // [n]
     double *is_part;    // [kIsBlocks * (2 + 2d)] per-block estimate sums
     double *rec_num;    // [2d] recycled estimate sums
-    double *epart;      // particle filter: [expand segments][kEstCols] row sums of the
+    double *epart;      // particle filter: [kEstCols][expand segments] row sums of the
                         // redistributed rows (NULL otherwise)
     // logistic regression (NULL otherwise)
     unsigned short *xs;   // [mpad][dp] bf16 rows of X times (1 - 2 y)
@@ -98,12 +101,42 @@ hipError_t launch_weights(const Work &w, const double *lw, int64_t n, double *ou
 hipError_t launch_count_scan(const Work &w, const int64_t *ncopies, int64_t n, hipStream_t s);
 hipError_t launch_ncopies(const Work &w, int64_t n, int count_mode, int64_t *ncopies,
                           hipStream_t s);
-// est_part (nullable; rows of four FP64 values only): per workgroup, the
-// count, sums and sums of squares of the rows it wrote, kEstCols doubles.
+
+// Merge-path steps of an expand workgroup: kSegLen where that makes eight
+// workgroups per CU (one residency), shorter segments below, so that a small
+// population still spreads over the chip.
+inline int expand_seg_len(int64_t n)
+{
+    int seg = kSegLen;
+    while (seg > 256 && 2 * n < 2048ll * seg) seg >>= 1;
+    return seg;
+}
+inline int64_t expand_segments(int64_t n)
+{
+    const int seg = expand_seg_len(n);
+    return (2 * n + seg - 1) / seg;
+}
+
+// What the expand does when the decision kept the weights: kCopy writes the
+// identity; kIfResampled writes nothing; kForward (a sampler iteration whose
+// proposal waits in the workspace copy) writes the identity, also when the
+// iteration found an error.
+enum class ExpandMode { kCopy, kIfResampled, kForward };
+
+// The expand's optional outputs (all nullable).
+struct ExpandOut {
+    ExpandMode mode = ExpandMode::kCopy;
+    int64_t *ncopies = nullptr, *anc = nullptr;
+    const void *aux = nullptr;  // 8-byte side rows copied along
+    void *aux_out = nullptr;
+    double *logw = nullptr;     // weights set to `reset` where the decision resampled,
+    double reset = 0.0;         //   or the flag `uniform` set instead (lazy reset)
+    unsigned *uniform = nullptr;
+    // rows of four FP64 values only: per workgroup the weighted sums of the
+    // rows it wrote, kEstCols columns of expand_segments(n)
+    double *est_part = nullptr;
+};
 hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x, void *x_out,
-                         int row_bytes, const void *aux, void *aux_out, int aux_bytes,
-                         int64_t *ncopies_out, int64_t *anc_out, hipStream_t s,
-                         bool skip_identity, double *est_part = nullptr);
-inline int64_t expand_segments(int64_t n) { return (2 * n + kSegLen - 1) / kSegLen; }
+                         int row_bytes, hipStream_t s, const ExpandOut &o);
 
 }  // namespace smc

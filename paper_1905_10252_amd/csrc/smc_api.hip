@@ -331,8 +331,10 @@ smc_status smc_redistribute(smc_ctx *ctx, const int64_t *ncopies, const void *x,
         ctx->pending = false;
         count_mode = 1;
     }
-    if (launch_expand(w, n, count_mode, x, x_out, row_bytes, nullptr, nullptr, 0, ncopies_out, anc,
-                      s, false) != hipSuccess)
+    ExpandOut o;
+    o.ncopies = ncopies_out;
+    o.anc = anc;
+    if (launch_expand(w, n, count_mode, x, x_out, row_bytes, s, o) != hipSuccess)
         return SMC_E_DEVICE;
     return SMC_OK;
 }
