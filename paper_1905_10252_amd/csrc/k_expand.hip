@@ -45,11 +45,12 @@ struct AFun {
     i64 n;
     const u64 *pref;  // tile-local inclusive prefix
     const u64 *tpre;  // exclusive prefix of the tile totals
+    int tsh;          // log2 of the tile size
     int mode;  // 0: identity, 1: systematic from S_j, 2: caller counts (A_j = prefix)
     u64 S, U;
     double nS, uS;  // N / S and U / S
 
-    __device__ inline u64 at(i64 j) const { return pref[j] + tpre[j >> kTileShift]; }
+    __device__ inline u64 at(i64 j) const { return pref[j] + tpre[j >> tsh]; }
 
     // A_j + j < k, given the prefix value pj of source j
     __device__ inline bool pred_at(i64 j, u64 pj, i64 k) const
@@ -138,7 +139,7 @@ __device__ inline i64 wave_search(const AFun &f, const u64 *pref64, i64 k, i64 l
     i64 g = glo;
     if (ghi > glo) {
         auto ps = [&](i64 gg) {
-            return f.pred_at(gg * 64 + 63, pref64[gg] + f.tpre[gg >> (kTileShift - 6)], k);
+            return f.pred_at(gg * 64 + 63, pref64[gg] + f.tpre[gg >> (f.tsh - 6)], k);
         };
         g = wave_first_false(ps, glo, ghi);
     }
@@ -151,12 +152,13 @@ __device__ inline i64 wave_search(const AFun &f, const u64 *pref64, i64 k, i64 l
 }
 
 // Chooses the A function of this call; false if nothing may be written.
-__device__ inline bool make_afun(const Ctrl *ctrl, const u64 *pref, const u64 *tpre, i64 n,
-                                 int count_mode, AFun &f, bool report)
+__device__ inline bool make_afun(const Ctrl *ctrl, const u64 *pref, const u64 *tpre, int tsh,
+                                 i64 n, int count_mode, AFun &f, bool report)
 {
     f.n = n;
     f.pref = pref;
     f.tpre = tpre;
+    f.tsh = tsh;
     f.S = 1;
     f.U = 0;
     f.nS = 0.0;
@@ -303,6 +305,62 @@ __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
     }
 }
 
+// Rows of at least 16 bytes whose size or address is no multiple of 16: 16-byte
+// accesses at 4-byte alignment (which the memory pipeline takes), the last
+// one of a row moved back to end with it, so that it repeats a few bytes of the
+// one before.  Rows of 28 bytes then move in two accesses instead of seven.
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+template <bool kNtLoad, bool kNtStore>
+__device__ inline void copy_ragged(const unsigned char *__restrict__ src,
+                                   unsigned char *__restrict__ dst, int row_bytes,
+                                   const unsigned *sAnc, i64 p0, int np)
+{
+    const int cpr = (row_bytes + 15) >> 4, total = np * cpr;
+    const int dr = kExpandThreads / cpr, dc = kExpandThreads - dr * cpr;
+    int r = (int)threadIdx.x / cpr, col = (int)threadIdx.x - r * cpr;
+    constexpr int U = 4;
+    unsigned char *d = dst + p0 * (i64)row_bytes;
+    auto next = [&](int &row, int &off) {
+        row = r;
+        off = 16 * col < row_bytes - 16 ? 16 * col : row_bytes - 16;
+        r += dr;
+        col += dc;
+        if (col >= cpr) {
+            col -= cpr;
+            ++r;
+        }
+    };
+    auto load = [&](int row, int off) -> u32x4 {
+        const u32x4_a4 *sp =
+            reinterpret_cast<const u32x4_a4 *>(src + (i64)sAnc[row] * row_bytes + off);
+        if (kNtLoad) return __builtin_nontemporal_load(sp);
+        return *sp;
+    };
+    auto store = [&](const u32x4 &v, int row, int off) {
+        u32x4_a4 *dp = reinterpret_cast<u32x4_a4 *>(d + (i64)row * row_bytes + off);
+        if (kNtStore) __builtin_nontemporal_store(v, dp);
+        else *dp = v;
+    };
+    int c = threadIdx.x;
+    for (; c + (U - 1) * kExpandThreads < total; c += U * kExpandThreads) {
+        u32x4 v[U];
+        int row[U], off[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            next(row[u], off[u]);
+            v[u] = load(row[u], off[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) store(v[u], row[u], off[u]);
+    }
+    for (; c < total; c += kExpandThreads) {
+        int row, off;
+        next(row, off);
+        store(load(row, off), row, off);
+    }
+}
+
 template <int VEC, bool kSum, bool kNtLoad, bool kNtStore>
 __device__ inline void copy_rows(const unsigned char *__restrict__ src,
                                  unsigned char *__restrict__ dst, int row_bytes,
@@ -359,7 +417,7 @@ struct ExpandArgs {
     const u64 *pref64;
     const u64 *tpre;
     const Ctrl *ctrl;
-    int count_mode;
+    int tsh, count_mode;
     const unsigned char *x;
     unsigned char *xo;
     int row_bytes;
@@ -376,7 +434,8 @@ struct ExpandArgs {
 };
 
 // SEG: merge steps of one workgroup.
-template <int VEC, int SEG, bool kSum>
+// kRagged: rows for copy_ragged (VEC does not matter then).
+template <int VEC, int SEG, bool kSum, bool kRagged>
 __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
 {
     __shared__ unsigned sA[SEG + 1];
@@ -386,7 +445,8 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     const int tid = threadIdx.x, wid = tid >> 6;
     AFun f;
     bool failed = false;
-    if (!make_afun(a.ctrl, a.pref, a.tpre, a.n, a.count_mode, f, blockIdx.x == 0 && tid == 0)) {
+    if (!make_afun(a.ctrl, a.pref, a.tpre, a.tsh, a.n, a.count_mode, f,
+                   blockIdx.x == 0 && tid == 0)) {
         // an iteration that found an error resamples nothing: its proposal
         // still has to reach the caller's array
         if (a.mode != ExpandMode::kForward) return;
@@ -425,15 +485,16 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     if (f.mode == 0) {
         for (int i = tid; i <= ns; i += kExpandThreads) sA[i] = j0u + (unsigned)i;
     } else {
-        // sA[i] is A of source j0 - 1 + i; these sources (at most SEG + 1 < 4096)
-        // lie in at most two tiles, whose offsets are read once
+        // sA[i] is A of source j0 - 1 + i; these sources (at most SEG + 1)
+        // lie in at most two tiles (the segment length sees to it), whose offsets
+        // are read once
         const int skip = j0 == 0 ? 1 : 0;  // A before the first source is 0
         const i64 jb = j0 - 1 + skip;
-        const i64 ta = jb >> kTileShift;
-        const i64 ntl = (n + kTile - 1) >> kTileShift;
+        const i64 ta = jb >> f.tsh;
+        const i64 ntl = (n + (1ll << f.tsh) - 1) >> f.tsh;
         const u64 off_a = f.tpre[ta];
         const u64 off_b = ta + 1 < ntl ? f.tpre[ta + 1] : 0ull;
-        const int ib = (int)(((ta + 1) << kTileShift) - jb);  // first source of the second tile
+        const int ib = (int)(((ta + 1) << f.tsh) - jb);  // first source of the second tile
         const u64 *pj = a.pref + jb;
         if (skip && tid == 0) sA[0] = 0u;
         for (int i = tid; i <= ns - skip; i += kExpandThreads)
@@ -505,6 +566,13 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
             copy_rows<VEC, true, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
         store_row_sums(acc, failed ? -__builtin_huge_val() : m, a.est_part + blockIdx.x,
                        gridDim.x);
+    } else if constexpr (kRagged) {
+        if (a.stream && distinct)
+            copy_ragged<true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        else if (a.stream)
+            copy_ragged<false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        else
+            copy_ragged<false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream && distinct) {
         copy_rows<VEC, false, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream) {
@@ -515,15 +583,15 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     if (a.aux) copy_rows<8, false, false, false>(a.aux, a.auxo, 8, sAnc, p0, np);
 }
 
-template <int VEC, bool kSum>
+template <int VEC, bool kSum, bool kRagged = false>
 static void launch_expand_seg(int seg, int64_t n, hipStream_t s, const ExpandArgs &a)
 {
     const dim3 g((unsigned)((2 * n + seg - 1) / seg)), b(kExpandThreads);
     switch (seg) {
-    case 256: hipLaunchKernelGGL((k_expand<VEC, 256, kSum>), g, b, 0, s, a); break;
-    case 512: hipLaunchKernelGGL((k_expand<VEC, 512, kSum>), g, b, 0, s, a); break;
-    case 1024: hipLaunchKernelGGL((k_expand<VEC, 1024, kSum>), g, b, 0, s, a); break;
-    default: hipLaunchKernelGGL((k_expand<VEC, kSegLen, kSum>), g, b, 0, s, a); break;
+    case 256: hipLaunchKernelGGL((k_expand<VEC, 256, kSum, kRagged>), g, b, 0, s, a); break;
+    case 512: hipLaunchKernelGGL((k_expand<VEC, 512, kSum, kRagged>), g, b, 0, s, a); break;
+    case 1024: hipLaunchKernelGGL((k_expand<VEC, 1024, kSum, kRagged>), g, b, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_expand<VEC, kSegLen, kSum, kRagged>), g, b, 0, s, a); break;
     }
 }
 
@@ -536,6 +604,7 @@ hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x
     a.pref64 = w.pref64;
     a.tpre = w.tsum;
     a.ctrl = w.ctrl;
+    a.tsh = w.tile_shift;
     a.count_mode = count_mode;
     a.x = reinterpret_cast<const unsigned char *>(x);
     a.xo = reinterpret_cast<unsigned char *>(x_out);
@@ -558,6 +627,8 @@ hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x
         else launch_expand_seg<8, true>(seg, n, s, a);
     } else if ((al & 15) == 0) {
         launch_expand_seg<16, false>(seg, n, s, a);
+    } else if (row_bytes >= 16) {
+        launch_expand_seg<16, false, true>(seg, n, s, a);
     } else if ((al & 7) == 0) {
         launch_expand_seg<8, false>(seg, n, s, a);
     } else {
@@ -576,11 +647,11 @@ constexpr int kNcItems = 4;
 typedef u64 u64x2_t __attribute__((ext_vector_type(2)));
 
 __global__ __launch_bounds__(256) void k_ncopies(const Ctrl *ctrl, const u64 *pref,
-                                                 const u64 *tpre, i64 n, int count_mode, int vec,
-                                                 i64 *nc)
+                                                 const u64 *tpre, int tsh, i64 n, int count_mode,
+                                                 int vec, i64 *nc)
 {
     AFun f;
-    if (!make_afun(ctrl, pref, tpre, n, count_mode, f, false)) return;
+    if (!make_afun(ctrl, pref, tpre, tsh, n, count_mode, f, false)) return;
     const int lane = threadIdx.x & 63;
     const i64 step = (i64)gridDim.x * 256 * kNcItems;
     // the trip count is uniform over a wavefront (its lanes exchange A)
@@ -590,7 +661,7 @@ __global__ __launch_bounds__(256) void k_ncopies(const Ctrl *ctrl, const u64 *pr
         if (f.mode == 0) {
             for (int e = 0; e < kNcItems; ++e) s[e] = 0;
         } else {
-            const u64 off = f.tpre[w0 >> kTileShift];  // a wavefront's run lies in one tile
+            const u64 off = f.tpre[w0 >> f.tsh];  // a wavefront's run lies in one tile
             if (j0 + kNcItems <= n) {
 #pragma unroll
                 for (int e = 0; e < kNcItems; e += 2) {
@@ -612,7 +683,8 @@ __global__ __launch_bounds__(256) void k_ncopies(const Ctrl *ctrl, const u64 *pr
             if (w0 > 0) {
                 u64 sp = 0;
                 if (f.mode)
-                    sp = f.tpre[w0 >> kTileShift] + ((w0 & (kTile - 1)) ? pref[w0 - 1] : 0ull);
+                    sp = f.tpre[w0 >> f.tsh] +
+                         ((w0 & ((1ll << f.tsh) - 1)) ? pref[w0 - 1] : 0ull);
                 prev = f.A_of(w0 - 1, sp);
             }
         }
@@ -634,7 +706,7 @@ __global__ __launch_bounds__(256) void k_ncopies(const Ctrl *ctrl, const u64 *pr
         }
     }
 }
-static_assert(kTile % (64 * kNcItems) == 0, "a wavefront's run lies in one tile");
+static_assert((1 << kTileShiftSmall) % (64 * kNcItems) == 0, "a wavefront's run lies in one tile");
 
 hipError_t launch_ncopies(const Work &w, int64_t n, int count_mode, int64_t *ncopies,
                           hipStream_t s)
@@ -642,7 +714,7 @@ hipError_t launch_ncopies(const Work &w, int64_t n, int count_mode, int64_t *nco
     int64_t blocks = (n + 256 * kNcItems - 1) / (256 * kNcItems);
     blocks = blocks > 4096 ? 4096 : blocks;
     hipLaunchKernelGGL(k_ncopies, dim3((unsigned)blocks), dim3(256), 0, s, w.ctrl, w.pref, w.tsum,
-                       (i64)n, count_mode, ((uintptr_t)ncopies & 15) == 0,
+                       w.tile_shift, (i64)n, count_mode, ((uintptr_t)ncopies & 15) == 0,
                        reinterpret_cast<i64 *>(ncopies));
     return hipGetLastError();
 }

@@ -7,7 +7,7 @@
 //                  q_i = min(2^K, floor(2^K det_exp(l_i - m))), FP64 sums for
 //                  log-sum-exp and ESS (eq. normalise, eq. neff), the exact
 //                  sum of q_i^2, and the prefix sums of q within each tile of
-//                  4096 weights, plus the tile's total.
+//                  4096 or 1024 weights, plus the tile's total.
 //   k_scan<false>  the same tile scan over caller-supplied int64 ncopies.
 //   k_decide       the exclusive prefix of the tile totals (so that the
 //                  inclusive prefix S_j of the Cumulative Sum of MVR is the
@@ -138,9 +138,9 @@ hipError_t launch_fold(const Work &w, int par, hipStream_t s)
 }
 
 // ------------------------------------------------------------ tile scan
-// Tile = kScanThreads threads x kScanItems items; tile t is workgroup t.
+// Tile = kScanThreads threads x kItems items; tile t is workgroup t.
 // Global loads and stores are coalesced 16-byte accesses over rows of
-// 2 kScanThreads elements; an LDS transpose gives each thread kScanItems
+// 2 kScanThreads elements; an LDS transpose gives each thread kItems
 // consecutive items for the sequential part of the scan.  Entry i of the
 // transpose sits at slot (i ^ (i >> 5)) & 15 of its 16-entry block (a
 // bijection): in both the striped and the per-thread accesses at most two
@@ -154,7 +154,6 @@ hipError_t launch_fold(const Work &w, int par, hipStream_t s)
 __host__ __device__ constexpr int kPad(int i) { return (i & ~15) | ((i ^ (i >> 5)) & 15); }
 constexpr int kScanWaves = kScanThreads / 64;
 constexpr int kScanRow = 2 * kScanThreads;  // elements per striped row
-static_assert(kScanItems % 4 == 0 && 64 % kScanItems == 0, "scan tile shape");
 
 struct ScanArgs {
     const double *lw;   // quantise mode input
@@ -172,7 +171,7 @@ struct ScanArgs {
 };
 
 // Sums of one thread's fixed-point weights squared, q = h 2^26 + l: each part
-// adds up at most kScanItems products below 2^54, so plain 64-bit sums hold
+// adds up at most 16 products below 2^54, so plain 64-bit sums hold
 // them (one multiply-add a part; carries enter once, in total()).
 struct SqSum {
     u64 ll = 0, hl = 0, hh = 0;
@@ -189,7 +188,6 @@ struct SqSum {
         return add128(t, ll);
     }
 };
-static_assert(kScanItems <= 256, "SqSum: products below 2^54");
 
 // Fixed-point weights floor(2^K e), e = exp(l - m) <= 1, of W log-weights, and
 // their FP64 sums.  The integer is cut from the significand of e by one shift
@@ -216,11 +214,13 @@ __device__ inline void quant_w(const double (&v)[W], double m, int K, u64 (&q)[W
     }
 }
 
-// Four waves per SIMD: the LDS tile allows no more.
-template <bool kQuant>
+// Four waves per SIMD: the LDS of a 4096-element tile allows no more.
+template <bool kQuant, int kItems>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
     ScanArgs a)
 {
+    static_assert(kItems % 4 == 0 && 64 % kItems == 0 && kItems <= 16, "scan tile shape");
+    constexpr int kTile = kScanThreads * kItems;
     __shared__ u64 sq[kTile];
     __shared__ u64 s_wsum[kScanWaves];
     __shared__ double s_z[kScanWaves], s_z2[kScanWaves];
@@ -241,10 +241,10 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
         // every wave folds the 64 max slots itself (cached lines; no barrier)
         const double m = okey_inv(wave_max_u64(a.slots_p[lane * kSlotStride]));
         const int K = a.K;
-        double v[kScanItems];
+        double v[kItems];
         if (full && a.vec2) {
 #pragma unroll
-            for (int r = 0; r < kScanItems / 2; ++r) {
+            for (int r = 0; r < kItems / 2; ++r) {
                 const f64x2_t t = __builtin_nontemporal_load(
                     reinterpret_cast<const f64x2_t *>(a.lw + base + r * kScanRow + 2 * tid));
                 v[2 * r] = t.x;
@@ -252,13 +252,13 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < kScanItems; ++e) {
+            for (int e = 0; e < kItems; ++e) {
                 const i64 i = base + (e >> 1) * kScanRow + 2 * tid + (e & 1);
                 v[e] = i < n ? a.lw[i] : -__builtin_huge_val();
             }
         }
 #pragma unroll
-        for (int e = 0; e < kScanItems; e += 4) {
+        for (int e = 0; e < kItems; e += 4) {
             const double v4[4] = {v[e], v[e + 1], v[e + 2], v[e + 3]};
             u64 q4[4];
             quant_w<4>(v4, m, K, q4, z, z2, sq2);
@@ -269,14 +269,14 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
             asm volatile("" : "+v"(sq2.ll), "+v"(sq2.hl), "+v"(sq2.hh), "+v"(z), "+v"(z2));
         }
     } else {
-        i64 c[kScanItems];
+        i64 c[kItems];
 #pragma unroll
-        for (int e = 0; e < kScanItems; ++e) {
+        for (int e = 0; e < kItems; ++e) {
             const i64 i = base + (e >> 1) * kScanRow + 2 * tid + (e & 1);
             c[e] = i < n ? a.nc[i] : 0;
         }
 #pragma unroll
-        for (int e = 0; e < kScanItems; ++e) {
+        for (int e = 0; e < kItems; ++e) {
             const bool ok = c[e] >= 0 && c[e] <= n;
             bad |= ok ? 0u : 1u;
             sq[kPad((e >> 1) * kScanRow + 2 * tid + (e & 1))] = ok ? (u64)c[e] : 0ull;
@@ -285,11 +285,11 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
     __syncthreads();
 
     // sequential inclusive scan of this thread's 16 consecutive items
-    u64 loc[kScanItems];
+    u64 loc[kItems];
     u64 run = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        run += sq[kPad(tid * kScanItems + j)];
+    for (int j = 0; j < kItems; ++j) {
+        run += sq[kPad(tid * kItems + j)];
         loc[j] = run;
     }
     const u64 incl = wave_incl_scan_u64(run);
@@ -319,11 +319,11 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
     // each thread rewrites only the 16 entries it read above
     const u64 pre = wpre + incl - run;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) sq[kPad(tid * kScanItems + j)] = pre + loc[j];
+    for (int j = 0; j < kItems; ++j) sq[kPad(tid * kItems + j)] = pre + loc[j];
     // every 64th prefix value (item 64g + 63 is the last item of its thread)
-    if (((tid + 1) * kScanItems) % 64 == 0) {
-        const i64 gi = base + tid * kScanItems + (kScanItems - 1);
-        if (gi < n) a.out64[gi >> 6] = pre + loc[kScanItems - 1];
+    if (((tid + 1) * kItems) % 64 == 0) {
+        const i64 gi = base + tid * kItems + (kItems - 1);
+        if (gi < n) a.out64[gi >> 6] = pre + loc[kItems - 1];
     }
     if (tid == 0) {
         if (a.uniform && tile == 0) *a.uniform = 0u;
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
         } else {
             unsigned b = 0;
             for (int i = 0; i < kScanWaves; ++i) b |= s_bad[i];
-            if (b) atomicOr(&a.ctrl->ncopy_bad, 1u);
+            a.tpart[tile].q2lo = b;  // collected by k_tile_prefix
         }
     }
     __syncthreads();
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
     asm volatile("" : "+v"(tid2));
     if (full) {
 #pragma unroll
-        for (int r = 0; r < kScanItems / 2; ++r) {
+        for (int r = 0; r < kItems / 2; ++r) {
             const int s0 = r * kScanRow + tid2;
             ulonglong2 v;
             v.x = sq[kPad(s0)];
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
         }
     } else {
 #pragma unroll
-        for (int e = 0; e < kScanItems; ++e) {
+        for (int e = 0; e < kItems; ++e) {
             const int s0 = (e >> 1) * kScanRow + tid2 + (e & 1);
             if (base + s0 < n) a.out[base + s0] = sq[kPad(s0)];
         }
@@ -428,16 +428,24 @@ struct TileOffsets {
     }
 };
 
-// Caller-supplied counts: tile offsets and their total (checked against N by
-// the expand).
-__global__ __launch_bounds__(1024) void k_tile_prefix(Ctrl *ctrl, u64 *tsum, int n_tiles)
+// Caller-supplied counts: tile offsets, their total (checked against N by the
+// expand) and the tiles' flags for an invalid count; the call's other flags.
+__global__ __launch_bounds__(1024) void k_tile_prefix(Ctrl *ctrl, u64 *tsum,
+                                                      const TilePart *tpart, int n_tiles)
 {
     __shared__ u64 s_w[16];
     TileOffsets to;
     to.begin(tsum, n_tiles, s_w);
-    __syncthreads();
+    int bad = 0;
+    for (int t = threadIdx.x; t < n_tiles; t += 1024) bad |= tpart[t].q2lo != 0;
+    bad = __syncthreads_or(bad);
     const u64 total = to.finish(tsum, n_tiles, s_w);
-    if (threadIdx.x == 0) ctrl->ctotal = total;
+    if (threadIdx.x == 0) {
+        ctrl->ctotal = total;
+        ctrl->ncopy_bad = bad ? 1u : 0u;
+        ctrl->err_call = 0;
+        ctrl->pending = 0;
+    }
 }
 
 // ---------------------------------------------------------------- decision
@@ -615,7 +623,8 @@ hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, 
     a.out64 = w.pref64;
     a.slots_p = w.slots + (par & 1) * kSlots * kSlotStride;
     a.n_tiles = w.n_tiles;
-    hipLaunchKernelGGL(k_scan<true>, dim3(w.n_tiles), dim3(kScanThreads), 0, s, a);
+    auto kern = w.tile_shift == kTileShift ? k_scan<true, 16> : k_scan<true, 4>;
+    hipLaunchKernelGGL(kern, dim3(w.n_tiles), dim3(kScanThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -638,20 +647,6 @@ hipError_t launch_weights(const Work &w, const double *lw, int64_t n, double *ou
     return hipGetLastError();
 }
 
-// Resets the per-call flags before a scan of caller-supplied counts.
-__global__ void k_clear_scan(Ctrl *ctrl)
-{
-    ctrl->ncopy_bad = 0;
-    ctrl->err_call = 0;
-    ctrl->pending = 0;
-}
-
-hipError_t launch_clear_scan(const Work &w, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_clear_scan, dim3(1), dim3(1), 0, s, w.ctrl);
-    return hipGetLastError();
-}
-
 hipError_t launch_count_scan(const Work &w, const int64_t *ncopies, int64_t n, hipStream_t s)
 {
     ScanArgs a;
@@ -668,9 +663,11 @@ hipError_t launch_count_scan(const Work &w, const int64_t *ncopies, int64_t n, h
     a.out64 = w.pref64;
     a.slots_p = nullptr;
     a.n_tiles = w.n_tiles;
-    hipLaunchKernelGGL(k_scan<false>, dim3(w.n_tiles), dim3(kScanThreads), 0, s, a);
+    auto kern = w.tile_shift == kTileShift ? k_scan<false, 16> : k_scan<false, 4>;
+    hipLaunchKernelGGL(kern, dim3(w.n_tiles), dim3(kScanThreads), 0, s, a);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    hipLaunchKernelGGL(k_tile_prefix, dim3(1), dim3(1024), 0, s, w.ctrl, w.tsum, w.n_tiles);
+    hipLaunchKernelGGL(k_tile_prefix, dim3(1), dim3(1024), 0, s, w.ctrl, w.tsum, w.tpart,
+                       w.n_tiles);
     return hipGetLastError();
 }
 

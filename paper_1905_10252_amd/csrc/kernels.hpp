@@ -10,10 +10,14 @@
 namespace smc {
 
 constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kTile = kScanThreads * kScanItems;  // 4096 elements per scan tile
-constexpr int kTileShift = 12;
-static_assert(kTile == 1 << kTileShift, "tile size");
+// Scan tiles: 4096 elements (16 a thread) for large populations; below
+// kSmallTileN tiles of 1024, so that the tiles cover the chip (at N = 2^17, 32
+// tiles of 4096 took 5.9 us, a chain of 16 exponentials a thread).
+constexpr int kTileShift = 12, kTileShiftSmall = 10;
+constexpr int64_t kSmallTileN = 1 << 20;
+static_assert(kScanThreads * 16 == 1 << kTileShift && kScanThreads * 4 == 1 << kTileShiftSmall,
+              "tile sizes");
+inline int tile_shift_of(int64_t n) { return n < kSmallTileN ? kTileShiftSmall : kTileShift; }
 constexpr int kMaxBlocks = 1024;                  // grid of the max / reweight passes
 constexpr int kIsBlocks = 2048;                   // max grid of the sampler kernels
 constexpr int kExpandThreads = 256;
@@ -26,7 +30,7 @@ constexpr int64_t kStreamBytes = 128ll << 20;
 constexpr int kMaxRowBytes = 1 << 20;
 static_assert((long long)kSegLen * (kMaxRowBytes / 4) < (1ll << 31), "expand chunk count");
 constexpr int kEstCols = 10;                      // 2 + 2 d sums of a filter row (d = 4)
-static_assert(kSegLen + 1 <= kTile, "an expand segment spans at most two scan tiles");
+static_assert(kSegLen + 1 <= 1 << kTileShift, "an expand segment spans at most two scan tiles");
 constexpr int kLogregSplit = 8;                   // row blocks of the likelihood contraction
 
 struct TilePart {
@@ -59,16 +63,20 @@ struct Work {
     double *lpart;        // [kLogregSplit][n] partial log-likelihoods
     int64_t mpad, npad;
     int dp;
-    int n_tiles;
+    int n_tiles, tile_shift;
     int is_grid;        // blocks of the sampler kernels (rows of is_part)
 };
 
 // FP64 likelihood: MFMA k-steps of four columns, d padded to a power of two.
 inline int lr_ks(int d) { return d <= 4 ? 1 : d <= 8 ? 2 : d <= 16 ? 4 : d <= 32 ? 8 : 16; }
-inline int n_tiles_of(int64_t n) { return (int)((n + kTile - 1) / kTile); }
+inline int n_tiles_of(int64_t n)
+{
+    const int sh = tile_shift_of(n);
+    return (int)((n + (1ll << sh) - 1) >> sh);
+}
 inline int max_blocks_of(int64_t n)
 {
-    int64_t b = (n + 2 * 256 * 8 - 1) / (2 * 256 * 8);
+    int64_t b = (n + 1023) / 1024;  // one round of loads a thread, up to kMaxBlocks
     return (int)(b < 1 ? 1 : (b > kMaxBlocks ? kMaxBlocks : b));
 }
 
@@ -95,7 +103,6 @@ struct StatsArgs {
 hipError_t launch_decide(const Work &w, int par, int64_t n, int K, uint64_t r, int mode,
                          int ess_num, int ess_den, void *info, hipStream_t s,
                          const StatsArgs &st = StatsArgs());
-hipError_t launch_clear_scan(const Work &w, hipStream_t s);
 // Normalised weights exp(l_i - m) / Z from the last decision.
 hipError_t launch_weights(const Work &w, const double *lw, int64_t n, double *out, hipStream_t s);
 hipError_t launch_count_scan(const Work &w, const int64_t *ncopies, int64_t n, hipStream_t s);
@@ -109,8 +116,10 @@ inline int expand_seg_len(int64_t n)
 {
     int seg = kSegLen;
     while (seg > 256 && 2 * n < 2048ll * seg) seg >>= 1;
-    return seg;
+    return seg;  // at most 512 for n < kSmallTileN: two small tiles hold a segment
 }
+static_assert(2 * kSmallTileN <= 2048ll * 1024 && 512 + 1 <= 1 << kTileShiftSmall,
+              "an expand segment spans at most two small tiles");
 inline int64_t expand_segments(int64_t n)
 {
     const int seg = expand_seg_len(n);

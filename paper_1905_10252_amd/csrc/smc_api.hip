@@ -23,7 +23,8 @@ using namespace smc;
 // workspace), in a fixed device array, one copy per GPU, held until the
 // process ends (about 8.6 MB).
 static constexpr size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
-static constexpr size_t kNaTiles = ((size_t)SMC_NOALLOC_MAX_N + kTile - 1) / kTile;
+static constexpr size_t kNaTiles = (size_t)SMC_NOALLOC_MAX_N >> kTileShiftSmall;
+static_assert(SMC_NOALLOC_MAX_N <= kSmallTileN, "tiles of the largest call");
 static constexpr size_t kNaCtrl = 0;
 static constexpr size_t kNaSlots = kNaCtrl + al256(sizeof(Ctrl));
 static constexpr size_t kNaTsum = kNaSlots + al256(8 * (size_t)kSlotWords);
@@ -211,6 +212,7 @@ smc_status smc_init(smc_ctx **h_out, const smc_config *h_cfg, void *workspace,
     w.pref = reinterpret_cast<u64 *>(b + L.pref);
     w.pref64 = reinterpret_cast<u64 *>(b + L.pref64);
     w.n_tiles = n_tiles_of(h_cfg->n);
+    w.tile_shift = tile_shift_of(h_cfg->n);
     const bool samp = h_cfg->target != SMC_TARGET_NONE;
     w.lp = samp ? reinterpret_cast<double *>(b + L.lp) : nullptr;
     w.lp_new = samp ? reinterpret_cast<double *>(b + L.lp_new) : nullptr;
@@ -286,6 +288,7 @@ smc_status smc_resample_noalloc(const double *logw, int64_t n, uint64_t r, int32
     w.pref = reinterpret_cast<u64 *>(b + kNaPref);
     w.pref64 = reinterpret_cast<u64 *>(b + kNaPref64);
     w.n_tiles = n_tiles_of(n);
+    w.tile_shift = tile_shift_of(n);
     int c = 0;
     while ((1LL << c) < n) ++c;
     const int K = 61 - c < 52 ? 61 - c : 52;
@@ -326,7 +329,6 @@ smc_status smc_redistribute(smc_ctx *ctx, const int64_t *ncopies, const void *x,
     hipStream_t s = S(stream);
     int count_mode = 0;
     if (ncopies) {
-        if (launch_clear_scan(w, s) != hipSuccess) return SMC_E_DEVICE;
         if (launch_count_scan(w, ncopies, n, s) != hipSuccess) return SMC_E_DEVICE;
         ctx->pending = false;
         count_mode = 1;
