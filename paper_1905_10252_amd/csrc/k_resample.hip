@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "../../include/smc.h"
+#include "afun.hpp"
 #include "common.hpp"
 #include "det.hpp"
 #include "kernels.hpp"
@@ -449,6 +450,83 @@ __global__ __launch_bounds__(1024) void k_tile_prefix(Ctrl *ctrl, u64 *tsum,
 }
 
 // ---------------------------------------------------------------- decision
+struct Decision {
+    u64 key, S, U;
+    U128 Q2;
+    double m, logZ, ess, Z, Z2;
+    unsigned err;
+    bool resample;
+};
+
+// The error of the call, the exact integer ESS rule of Alg 2 and the
+// systematic offset, from the max key and the sums.
+__device__ inline Decision decide(u64 key, unsigned bad, u64 S, double Z, double Z2, U128 Q2,
+                                  i64 n, u64 r, int mode, int ess_num, int ess_den)
+{
+    Decision d;
+    d.key = key;
+    d.m = okey_inv(key);
+    d.err = 0;
+    if (bad) d.err = kErrNonfinite;
+    else if (key <= okey(-__builtin_huge_val())) d.err = kErrDegenerate;
+    if (mode == SMC_MODE_FORCE) {
+        d.resample = true;
+    } else if (mode == SMC_MODE_NEVER) {
+        d.resample = false;
+    } else {
+        // ess_den * S^2 < ess_num * N * Q2; both sides stay below 2^127
+        const U128 lhs = mul128_small(mul64(S, S), (u64)ess_den);
+        const U128 rhs = mul128_small(mul128_small(Q2, (u64)n), (u64)ess_num);
+        d.resample = lt128(lhs, rhs);
+    }
+    if (d.err) d.resample = false;
+    d.S = S;
+    d.U = mul64(r, S).hi;
+    d.Q2 = Q2;
+    d.Z = Z;
+    d.Z2 = Z2;
+    d.logZ = d.m + log(Z);
+    d.ess = (Z * Z) / Z2;
+    return d;
+}
+
+// The control block and the caller's record, by one thread.
+__device__ inline void store_decision(const Decision &d, int K, double log_c, Ctrl *ctrl,
+                                      smc_resample_info *info)
+{
+    ctrl->mkey = d.key;
+    ctrl->m = d.m;
+    ctrl->err_call = d.err;
+    if (d.err && !ctrl->err_latch) ctrl->err_latch = d.err;
+    ctrl->S = d.S;
+    ctrl->U = d.U;
+    ctrl->Q2lo = d.Q2.lo;
+    ctrl->Q2hi = d.Q2.hi;
+    ctrl->Z = d.Z;
+    ctrl->Z2 = d.Z2;
+    ctrl->logZ = d.logZ;
+    ctrl->ess = d.ess;
+    ctrl->K = K;
+    ctrl->resample = d.resample ? 1u : 0u;
+    ctrl->pending = d.err ? 0 : 1;
+    if (info) {
+        info->m = d.m;
+        info->logZ = d.logZ;
+        info->ess = d.ess;
+        info->Z = d.Z;
+        info->Z2 = d.Z2;
+        info->S = d.S;
+        info->U = d.U;
+        info->Q2_hi = d.Q2.hi;
+        info->Q2_lo = d.Q2.lo;
+        info->K = K;
+        info->resampled = d.resample ? 1 : 0;
+        info->err = (int)d.err;
+        info->pad = 0;
+        info->log_c = log_c;
+    }
+}
+
 // One workgroup: tile offsets; tile partials summed in a fixed order
 // (reproducible FP64); exact integer decision and offset; with kStats also a
 // sampler iteration's estimates, c_t and recycling.  Bound by latency, so the
@@ -528,63 +606,15 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
         key = wave_max_u64(key);
         badf = wave_or(badf);
         if (lane == 0) {
-            const double m = okey_inv(key);
-            unsigned err = 0;
-            if (badf) err = kErrNonfinite;
-            else if (key <= okey(-__builtin_huge_val())) err = kErrDegenerate;
-            ctrl->mkey = key;
-            ctrl->m = m;
-            ctrl->err_call = err;
-            if (err && !ctrl->err_latch) ctrl->err_latch = err;
-            int resample;
-            if (mode == SMC_MODE_FORCE) {
-                resample = 1;
-            } else if (mode == SMC_MODE_NEVER) {
-                resample = 0;
-            } else {
-                // ess_den * S^2 < ess_num * N * Q2; both sides stay below 2^127
-                const U128 lhs = mul128_small(mul64(S, S), (u64)ess_den);
-                const U128 rhs = mul128_small(mul128_small(Q2, (u64)n), (u64)ess_num);
-                resample = lt128(lhs, rhs) ? 1 : 0;
-            }
-            if (err) resample = 0;
-            const u64 U = mul64(r, S).hi;
-            const double logZ = m + log(Z);
-            const double ess = (Z * Z) / Z2;
-            ctrl->S = S;
-            ctrl->U = U;
-            ctrl->Q2lo = Q2.lo;
-            ctrl->Q2hi = Q2.hi;
-            ctrl->Z = Z;
-            ctrl->Z2 = Z2;
-            ctrl->logZ = logZ;
-            ctrl->ess = ess;
-            ctrl->K = K;
-            ctrl->resample = (unsigned)resample;
-            ctrl->pending = err ? 0 : 1;
+            const Decision dec = decide(key, badf, S, Z, Z2, Q2, n, r, mode, ess_num, ess_den);
             // an iteration whose decision found an error (NaN / +inf weight,
             // all weights zero) leaves c_t, the recycling sums and the
             // estimates as they were, as it stops at the resampling step
             double logc = 0.0;
             if constexpr (kStats)
-                if (!err) logc = recycle(ctrl, rec, logZ, resample != 0, s_st.bc);
-            if (info) {
-                info->m = m;
-                info->logZ = logZ;
-                info->ess = ess;
-                info->Z = Z;
-                info->Z2 = Z2;
-                info->S = S;
-                info->U = U;
-                info->Q2_hi = Q2.hi;
-                info->Q2_lo = Q2.lo;
-                info->K = K;
-                info->resampled = resample;
-                info->err = (int)err;
-                info->pad = 0;
-                info->log_c = logc;
-            }
-            s_err = err;
+                if (!dec.err) logc = recycle(ctrl, rec, dec.logZ, dec.resample, s_st.bc);
+            store_decision(dec, K, logc, ctrl, info);
+            s_err = dec.err;
         }
     }
     if constexpr (kStats) {
@@ -603,6 +633,131 @@ hipError_t launch_decide(const Work &w, int par, int64_t n, int K, uint64_t r, i
     hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, w.ctrl, w.slots, par, w.tpart, w.tsum,
                        w.n_tiles, (i64)n, K, (u64)r, mode, ess_num, ess_den,
                        reinterpret_cast<smc_resample_info *>(info), st);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------- one-workgroup resampling
+// The whole of smc_resample for at most kSmallResample weights in one launch:
+// max, fixed-point weights, their prefix, the sums, the decision and the copy
+// counts.  Four launches of one or two workgroups each spent 12 us at
+// N = 1000, nearly all of it launch and memory latency; here the weights stay
+// in registers (kPer consecutive ones a thread, at most 1024 threads) and two
+// barriers separate the three phases.  The same integers; the FP64 sums are
+// taken in thread order.  The prefix is stored whole (every tile's offset 0)
+// for the expand that may follow.
+template <int kPer>
+__global__ __launch_bounds__(1024) void k_small_resample(
+    const double *__restrict__ lw, i64 n, int K, u64 r, int mode, int ess_num, int ess_den,
+    Ctrl *ctrl, u64 *slots_other, u64 *tsum, int n_tiles, u64 *pref, u64 *pref64, i64 *nc,
+    smc_resample_info *info)
+{
+    static_assert(kPer % 4 == 0, "weights in groups of four");
+    __shared__ u64 s_key[16], s_wsum[16], s_lo[16], s_hi[16];
+    __shared__ unsigned s_bad[16];
+    __shared__ double s_z[16], s_z2[16];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
+    const int i0 = tid * kPer, ni = (int)n;
+    const double ninf = -__builtin_huge_val();
+    // the next call's max slots start clear, as after a decision
+    if (slots_other && wid == nw - 1) {
+        slots_other[lane * kSlotStride] = 0;
+        slots_other[lane * kSlotStride + 1] = 0;
+    }
+    for (int t = tid; t < n_tiles; t += blockDim.x) tsum[t] = 0;
+    double v[kPer];
+    u64 key = 0;
+    unsigned bad = 0;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) v[e] = i0 + e < ni ? lw[i0 + e] : ninf;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        bad |= !(v[e] < __builtin_huge_val());
+        const u64 k = okey(v[e]);
+        key = k > key ? k : key;
+    }
+    key = wave_max_u64(key);
+    bad = wave_or(bad);
+    if (lane == 0) {
+        s_key[wid] = key;
+        s_bad[wid] = bad;
+    }
+    __syncthreads();
+    key = s_key[0];
+    bad = s_bad[0];
+    for (int w = 1; w < nw; ++w) {
+        key = s_key[w] > key ? s_key[w] : key;
+        bad |= s_bad[w];
+    }
+    const double m = okey_inv(key);
+    double z = 0.0, z2 = 0.0;
+    SqSum sq;
+    u64 loc[kPer], run = 0;
+#pragma unroll
+    for (int e = 0; e < kPer; e += 4) {
+        const double v4[4] = {v[e], v[e + 1], v[e + 2], v[e + 3]};
+        u64 q4[4];
+        quant_w<4>(v4, m, K, q4, z, z2, sq);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            run += q4[w];
+            loc[e + w] = run;
+        }
+    }
+    const u64 incl = wave_incl_scan_u64(run);
+    z = wave_sum_f64(z);
+    z2 = wave_sum_f64(z2);
+    const U128 q2 = wave_sum_u128(sq.total());
+    if (lane == 63) s_wsum[wid] = incl;
+    if (lane == 0) {
+        s_z[wid] = z;
+        s_z2[wid] = z2;
+        s_lo[wid] = q2.lo;
+        s_hi[wid] = q2.hi;
+    }
+    __syncthreads();
+    u64 pre = incl - run, S = 0;
+    for (int w = 0; w < nw; ++w) {
+        pre += w < wid ? s_wsum[w] : 0ull;
+        S += s_wsum[w];
+    }
+    // every wavefront forms the decision itself: no third barrier
+    const bool in = lane < nw;
+    const double Z = wave_sum_f64(in ? s_z[lane & 15] : 0.0);
+    const double Z2 = wave_sum_f64(in ? s_z2[lane & 15] : 0.0);
+    const U128 Q2 = wave_sum_u128(in ? U128{s_lo[lane & 15], s_hi[lane & 15]} : U128{0, 0});
+    const Decision dec = decide(key, bad, S, Z, Z2, Q2, n, r, mode, ess_num, ess_den);
+    if (tid == 0) store_decision(dec, K, 0.0, ctrl, info);
+    AFun f;
+    f.n = n;
+    f.mode = 0;
+    if (dec.resample) f.set_systematic(S, dec.U);
+    unsigned prev = i0 > 0 ? f.A_of(i0 - 1, pre) : 0u;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        if (i0 + e >= ni) break;
+        const u64 s = pre + loc[e];
+        pref[i0 + e] = s;
+        if (((i0 + e) & 63) == 63) pref64[(i0 + e) >> 6] = s;
+        if (nc && !dec.err) {
+            const unsigned a = f.A_of(i0 + e, s);
+            nc[i0 + e] = (i64)(a - prev);
+            prev = a;
+        }
+    }
+}
+
+hipError_t launch_small_resample(const Work &w, const double *lw, int64_t n, int K, uint64_t r,
+                                 int mode, int ess_num, int ess_den, int par, bool slots,
+                                 int64_t *ncopies, void *info, hipStream_t s)
+{
+    auto kern = n <= 4096 ? k_small_resample<4> : k_small_resample<8>;
+    const int64_t per = n <= 4096 ? 4 : 8;
+    const int64_t waves = (n + 64 * per - 1) / (64 * per);
+    hipLaunchKernelGGL(kern, dim3(1), dim3((unsigned)(64 * waves)), 0, s, lw, (i64)n, K, (u64)r,
+                       mode, ess_num, ess_den, w.ctrl,
+                       slots ? w.slots + ((par & 1) ^ 1) * kSlots * kSlotStride : (u64 *)nullptr,
+                       w.tsum, w.n_tiles, w.pref, w.pref64, reinterpret_cast<i64 *>(ncopies),
+                       reinterpret_cast<smc_resample_info *>(info));
     return hipGetLastError();
 }
 

@@ -105,6 +105,13 @@ hipError_t launch_decide(const Work &w, int par, int64_t n, int K, uint64_t r, i
                          const StatsArgs &st = StatsArgs());
 // Normalised weights exp(l_i - m) / Z from the last decision.
 hipError_t launch_weights(const Work &w, const double *lw, int64_t n, double *out, hipStream_t s);
+// smc_resample in one launch, for n <= kSmallResample (one workgroup; above, the
+// separate passes spread over the chip); slots: also clears the max slots of
+// the parity after par.
+constexpr int64_t kSmallResample = 8192;
+hipError_t launch_small_resample(const Work &w, const double *lw, int64_t n, int K, uint64_t r,
+                                 int mode, int ess_num, int ess_den, int par, bool slots,
+                                 int64_t *ncopies, void *info, hipStream_t s);
 hipError_t launch_count_scan(const Work &w, const int64_t *ncopies, int64_t n, hipStream_t s);
 hipError_t launch_ncopies(const Work &w, int64_t n, int count_mode, int64_t *ncopies,
                           hipStream_t s);

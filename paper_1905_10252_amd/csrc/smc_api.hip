@@ -258,6 +258,13 @@ smc_status smc_resample(smc_ctx *ctx, const double *logw, int64_t n, uint64_t r,
     hipStream_t s = S(stream);
     const int par = ctx->par;
     ctx->par ^= 1;
+    if (n <= kSmallResample) {
+        if (launch_small_resample(w, logw, n, ctx->K, r, mode, ctx->cfg.ess_num, ctx->cfg.ess_den,
+                                  par, true, ncopies, info, s) != hipSuccess)
+            return SMC_E_DEVICE;
+        ctx->pending = true;
+        return SMC_OK;
+    }
     if (launch_max(w, logw, n, par, s) != hipSuccess) return SMC_E_DEVICE;
     if (launch_quant_scan(w, logw, n, ctx->K, par, s) != hipSuccess) return SMC_E_DEVICE;
     if (launch_decide(w, par, n, ctx->K, r, mode, ctx->cfg.ess_num, ctx->cfg.ess_den, info, s) !=
@@ -293,6 +300,11 @@ smc_status smc_resample_noalloc(const double *logw, int64_t n, uint64_t r, int32
     while ((1LL << c) < n) ++c;
     const int K = 61 - c < 52 ? 61 - c : 52;
     hipStream_t s = S(stream);
+    if (n <= kSmallResample)  // reads nothing that an earlier call left
+        return launch_small_resample(w, logw, n, K, r, mode, ess_num, ess_den, 0, false, ncopies,
+                                     info, s) == hipSuccess
+                   ? SMC_OK
+                   : SMC_E_DEVICE;
     // the last call's control block and max slots are cleared by a kernel
     // (no memset node if the caller captures the stream); parity 0 always
     if (launch_init_ctrl(w, s) != hipSuccess) return SMC_E_DEVICE;
