@@ -1158,7 +1158,7 @@ __global__ __launch_bounds__(256) void k_lp_cheap(TArgs a, i64 n, const double *
 // --------------------------------------------- logistic regression, FP64
 // With s_m = 1 - 2 y_m and u = s_m z_m, y_m z_m - softplus(z_m) = -softplus(u),
 // and softplus(u) = (u + |u|) / 2 + log1p(e^(-|u|)).  The kernel sums |u| and
-// the logs of products of 64 factors 1 + e^(-|u|) in (1, 2] (at most 2^64);
+// the logs of products of 512 factors 1 + e^(-|u|) in (1, 2];
 // the sum of u over all rows, theta . (sum_m s_m x_m), is added once per
 // particle by k_logreg_sum.
 //
@@ -1174,18 +1174,87 @@ __global__ __launch_bounds__(256) void k_lp_cheap(TArgs a, i64 n, const double *
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2v __attribute__((ext_vector_type(2)));
 
-__device__ inline void softplus_acc64(double u, double &sa, double &prod)
+// The FP64 matrix and vector instructions share one pipe on this chip: the
+// 8 MFMAs of a D = 32 tile (512 cycles a SIMD) and its 4 x 22 vector
+// instructions took 981 cycles together, so the epilogue counts in full.  Its
+// exponential: with a = |u| <= 700 and k = rint(a 2048 / ln 2),
+// e^-a = 2^(-k / 2048) e^-r, |r| <= ln 2 / 4096, the first factor from a table of
+// 2048 values (exact to 0.5 ulp, in LDS) and an exponent shift in 32-bit
+// arithmetic, the second 1 - r + r^2 / 2 - r^3 / 6 with the r^4 term folded into
+// r^2 (off by at most 4.3e-18; the constant enters as 1 + e^-a, whose rounding
+// is 1.1e-16).  Nine FP64 instructions an element instead of nineteen.  The
+// clamp of a (in its high word: infinities and NaN too) keeps the exponent in
+// range; e^-700 adds nothing to 1.
+constexpr int kExpBits = 11, kExpN = 1 << kExpBits;
+static_assert(kExpN == kExpTabN, "table size");
+
+__device__ inline void softplus_acc64(double u, const double *tab, double &sa, double &prod)
 {
-    const double au = fabs(u);
-    prod = fma(prod, exp(-au), prod);
-    sa += au;
+    const double magic = 0x1.8p52;  // its last place is 1: adding it rounds to an integer
+    const unsigned uh = (unsigned)__double2hiint(u) & 0x7FFFFFFFu;
+    const double ac = __hiloint2double((int)(uh < 0x4085E000u ? uh : 0x4085E000u),
+                                       __double2loint(u));
+    const double kd = fma(ac, 0x1.71547652b82fep+11, magic);
+    const int k = __double2loint(kd);
+    const double r = fma(kd - magic, -0x1.62e42fefa39efp-12, ac);
+    const double t0 = tab[k & (kExpN - 1)];
+    const double t = __hiloint2double(
+        __double2hiint(t0) - (int)(((unsigned)k << (20 - kExpBits)) & 0xFFF00000u),
+        __double2loint(t0));
+    const double q = fma(fma(r, -0x1.5555555555555p-3, 0x1.0000000a3fea0p-1), r, -1.0) * r;
+    prod = fma(prod, fma(t, q, t), prod);
+    sa += fabs(u);
+}
+
+// The table of 2^(-j / 2048): products of double-double powers, rounded once.
+__device__ inline void two_prod(double a, double b, double &p, double &e)
+{
+    p = a * b;
+    e = fma(a, b, -p);
+}
+
+__global__ __launch_bounds__(256) void k_exp_table(double *tab)
+{
+    const double pw[kExpBits][2] = {
+        {0x1.ffd3a565efb65p-1, -0x1.54441c5aeb90fp-57},  // 2^(-1/2048)
+        {0x1.ffa74ea381efcp-1, 0x1.0bd3b9f8ae013p-56},   // 2^(-2/2048)
+        {0x1.ff4eaca4391b6p-1, -0x1.2e60c5e4b7047p-56},
+        {0x1.fe9d96b2a23d9p-1, 0x1.4a6037442fde3p-57},
+        {0x1.fd3c22b8f71f1p-1, 0x1.2eb74966579e7p-58},
+        {0x1.fa7c1819e90d8p-1, 0x1.74853f3a5931ep-56},
+        {0x1.f50765b6e4540p-1, 0x1.9d3e12dd8a18bp-55},
+        {0x1.ea4afa2a490dap-1, -0x1.e9c23179c2893p-55},
+        {0x1.d5818dcfba487p-1, 0x1.2ed02d75b3707p-56},
+        {0x1.ae89f995ad3adp-1, 0x1.7a1cd345dcc81p-55},
+        {0x1.6a09e667f3bcdp-1, -0x1.bdd3413b26456p-55},  // 2^(-1024/2048)
+    };
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= kExpN) return;
+    double hi = 1.0, lo = 0.0;
+#pragma unroll
+    for (int i = 0; i < kExpBits; ++i) {
+        if (!((j >> i) & 1)) continue;
+        double p, e;
+        two_prod(hi, pw[i][0], p, e);
+        e += hi * pw[i][1] + lo * pw[i][0];
+        hi = p + e;
+        lo = e - (hi - p);
+    }
+    tab[j] = hi;
 }
 
 template <int KS>
 __global__ __launch_bounds__(256) void k_logreg_f64(const double *__restrict__ theta, i64 n, int d,
-                                                    const double *__restrict__ xf, i64 m_rows,
+                                                    const double *__restrict__ xf,
+                                                    const double *__restrict__ etab, i64 m_rows,
                                                     i64 mpad, double *__restrict__ lpart)
 {
+    __shared__ double s_tab[kExpN];
+#pragma unroll
+    for (int i = 0; i < kExpN / 512; ++i)
+        reinterpret_cast<f64x2v *>(s_tab)[256 * i + threadIdx.x] =
+            reinterpret_cast<const f64x2v *>(etab)[256 * i + threadIdx.x];
+    __syncthreads();
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const i64 p0 = ((i64)blockIdx.x * 4 + wid) * 16;
     if (p0 >= n) return;
@@ -1220,8 +1289,8 @@ __global__ __launch_bounds__(256) void k_logreg_f64(const double *__restrict__ t
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) softplus_acc64(acc[v], sa, prod);
-        if (++cnt == 16) {
+        for (int v = 0; v < 4; ++v) softplus_acc64(acc[v], s_tab, sa, prod);
+        if (++cnt == 128) {  // 512 factors in (1, 2]: at most 2^512
             lg += log(prod);
             prod = 1.0;
             cnt = 0;
@@ -1453,7 +1522,7 @@ hipError_t logreg_lik(const smc_config &c, const Work &w, const double *x, int64
                       bool theta_ready, hipStream_t s)
 {
     if (c.target != SMC_TARGET_LOGREG || !w.lpart || !w.csum || (is_bf16(c) && (!w.xs || !w.thb)) ||
-        (!is_bf16(c) && !w.xf))
+        (!is_bf16(c) && (!w.xf || !w.etab)))
         return hipErrorInvalidValue;
     const int msplit = kLogregSplit;
     if (is_bf16(c)) {
@@ -1473,11 +1542,15 @@ hipError_t logreg_lik(const smc_config &c, const Work &w, const double *x, int64
         const dim3 grid((unsigned)((n + 63) / 64), msplit);
         const double *xf = w.xf;
         switch (lr_ks(c.d)) {
-        case 1: hipLaunchKernelGGL(k_logreg_f64<1>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, c.m_rows, w.mpad, w.lpart); break;
-        case 2: hipLaunchKernelGGL(k_logreg_f64<2>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, c.m_rows, w.mpad, w.lpart); break;
-        case 4: hipLaunchKernelGGL(k_logreg_f64<4>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, c.m_rows, w.mpad, w.lpart); break;
-        case 8: hipLaunchKernelGGL(k_logreg_f64<8>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, c.m_rows, w.mpad, w.lpart); break;
-        default: hipLaunchKernelGGL(k_logreg_f64<16>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, c.m_rows, w.mpad, w.lpart); break;
+#define SMC_LR64_CASE(KS)                                                                      \
+    case KS:                                                                                   \
+        hipLaunchKernelGGL(k_logreg_f64<KS>, grid, dim3(256), 0, s, x, (i64)n, c.d, xf, w.etab, \
+                           c.m_rows, w.mpad, w.lpart);                                         \
+        break;
+            SMC_LR64_CASE(1) SMC_LR64_CASE(2) SMC_LR64_CASE(4) SMC_LR64_CASE(6) SMC_LR64_CASE(8)
+            SMC_LR64_CASE(10) SMC_LR64_CASE(12) SMC_LR64_CASE(14) SMC_LR64_CASE(16)
+#undef SMC_LR64_CASE
+        default: return hipErrorInvalidValue;
         }
     }
     return hipGetLastError();
@@ -1603,6 +1676,7 @@ smc_status step_init(const smc_config &c, const Work &w, int par, double *x, dou
         hipLaunchKernelGGL(k_prep_xf, dim3(grid_for(w.mpad * 4 * ks)), dim3(256), 0, s,
                            reinterpret_cast<const double *>(c.X), c.y, (i64)c.m_rows, c.d,
                            (i64)w.mpad, ks, w.xf);
+        hipLaunchKernelGGL(k_exp_table, dim3(kExpN / 256), dim3(256), 0, s, w.etab);
         hipLaunchKernelGGL(k_x_colsum, dim3(c.d), dim3(256), 0, s,
                            reinterpret_cast<const double *>(c.X), c.y, (i64)c.m_rows, c.d, w.csum);
         if (hipGetLastError() != hipSuccess) return SMC_E_DEVICE;

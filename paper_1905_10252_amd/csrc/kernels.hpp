@@ -60,6 +60,7 @@ struct Work {
     unsigned short *thb;  // [npad][dp] bf16 copy of the particles times log2 e
     double *csum;         // [dp] column sums of X (1 - 2 y) (of xs for BF16)
     double *xf;           // FP64: [mpad / 16][64][lr_ks(d)] X (1 - 2 y) in MFMA operand order
+    double *etab;         // FP64: [kExpTabN] powers 2^(-j / kExpTabN)
     double *lpart;        // [kLogregSplit][n] partial log-likelihoods
     int64_t mpad, npad;
     int dp;
@@ -67,8 +68,11 @@ struct Work {
     int is_grid;        // blocks of the sampler kernels (rows of is_part)
 };
 
-// FP64 likelihood: MFMA k-steps of four columns, d padded to a power of two.
-inline int lr_ks(int d) { return d <= 4 ? 1 : d <= 8 ? 2 : d <= 16 ? 4 : d <= 32 ? 8 : 16; }
+// FP64 likelihood: MFMA k-steps of four columns, one or an even number (a
+// lane's operands of a tile are read 16 bytes at a time).
+inline int lr_ks(int d) { return d <= 4 ? 1 : (d + 7) / 8 * 2; }
+// Entries of the FP64 likelihood's table of powers of two.
+constexpr int kExpTabN = 2048;
 inline int n_tiles_of(int64_t n)
 {
     const int sh = tile_shift_of(n);
