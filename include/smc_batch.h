@@ -105,9 +105,9 @@ smc_status smc_batch_step(smc_batch *b, smc_resample_info *info, double *est, vo
 smc_status smc_batch_particles(smc_batch *b, int32_t slot, double **h_x, double **h_lp,
                                void *stream);
 
-/* Coordinate pairs per proposal work unit (a unit is 256 particles times
- * `pairs` pairs of coordinates; 1 <= pairs <= 8, default 8).  A tuning knob:
- * results do not depend on it. */
+/* Once the coordinate pairs per proposal work unit (1 <= pairs <= 8).  The
+ * proposal spreads (particle, pair) items over the lanes by itself now; the
+ * call checks its argument and changes nothing. */
 smc_status smc_batch_set_group(smc_batch *b, int32_t pairs, void *stream);
 
 /* Occupancy the target kernel of smc_batch_step (the log-density and

@@ -6,7 +6,7 @@
 // precision U^T U.  One step is one sequence of launches for all samplers:
 //
 //   k_bprop     per chunk of 256 particles of every sampler: the random-walk
-//               proposal in place (normals generated wave-cooperatively).
+//               proposal in place, (particle, pair) items over the lanes.
 //   k_bquad<DB> per chunk of samplers whose dimension falls in the bucket
 //               (DB - 8, DB]: |U (x - mean)|^2 with U staged in LDS and the row
 //               in registers, weight update, chunk max key and estimate sums
@@ -57,7 +57,7 @@ __host__ __device__ constexpr int kBPad(int i) { return (i & ~15) | ((i ^ (i >> 
 typedef double f64x2b_t __attribute__((ext_vector_type(2)));
 constexpr int kBChunk = 256;           // particles of an update / expand / copy workgroup
 constexpr int kChunksPerTile = kBTile / kBChunk;
-constexpr int kMaxGroup = 8;           // coordinate pairs of a proposal unit (16 columns of LDS)
+constexpr int kMaxGroup = 8;           // range of smc_batch_set_group
 constexpr int kBSpin = 1 << 22;        // lookback poll bound
 constexpr int kBuckets = 8;            // dimension buckets (8b, 8b + 8]
 constexpr int kBMaxCap = 4096;
@@ -118,7 +118,6 @@ struct BTabs {
     int *act;         // [cap] attached slots, ascending
     int *tile_pref;   // [cap + 1] tile prefix over act
     int *chunk_pref;  // [cap + 1] expand-chunk prefix over act
-    int *unit_pref;   // [cap + 1] proposal-unit prefix over act (chunk x pair group)
     int *bact;        // [kBuckets][cap]
     int *btile_pref;  // [kBuckets][cap + 1] chunk prefix over bact
 };
@@ -148,7 +147,6 @@ __device__ inline double row16_sum(double v)
     return v;
 }
 
-// Position of block b in a prefix table: slot and index within the slot.
 // Rows [0, cnt) x columns [0, w) of a row-major block (row stride d, w <= 16)
 // into LDS as whole lines: 16 lanes a row, 16 rows per pass.  Every load of a
 // thread is issued before the first wait (its address is clamped into the
@@ -172,6 +170,7 @@ __device__ inline void stage_rows(double (*sx)[CW], const GLB(double) *xb, int d
     }
 }
 
+// Position of block b in a prefix table: slot and index within the slot.
 __device__ inline bool locate(const int *pref, const int *act, int nact, int b, int &slot,
                               int &local)
 {
@@ -217,14 +216,9 @@ __global__ void k_bslots_clear(BSlot *slots, int cap)
 
 // Tables of the attached slots in slot order; thread t owns a contiguous
 // range of slots, counts are combined by a block scan.
-__device__ __host__ inline int units_of(int nchunk, int d, int G)
+__global__ __launch_bounds__(256) void k_btables(const BSlot *slots, int cap, BTabs tb)
 {
-    return nchunk * (((d + 1) / 2 + G - 1) / G);
-}
-
-__global__ __launch_bounds__(256) void k_btables(const BSlot *slots, int cap, int G, BTabs tb)
-{
-    constexpr int NV = 4 + 2 * kBuckets;  // act, tiles, chunks, bucket counts, bucket chunks, units
+    constexpr int NV = 3 + 2 * kBuckets;  // act, tiles, chunks, bucket counts, bucket chunks
     __shared__ int s_v[NV][256];
     const int tid = threadIdx.x;
     const int per = (cap + 255) / 256;
@@ -239,7 +233,6 @@ __global__ __launch_bounds__(256) void k_btables(const BSlot *slots, int cap, in
         v[2] += slots[s].nchunk;
         v[3 + b] += 1;
         v[3 + kBuckets + b] += slots[s].nchunk;
-        v[3 + 2 * kBuckets] += units_of(slots[s].nchunk, slots[s].d, G);
     }
     for (int q = 0; q < NV; ++q) s_v[q][tid] = v[q];
     __syncthreads();
@@ -258,7 +251,6 @@ __global__ __launch_bounds__(256) void k_btables(const BSlot *slots, int cap, in
         tb.act[off[0]] = s;
         tb.tile_pref[off[0]] = off[1];
         tb.chunk_pref[off[0]] = off[2];
-        tb.unit_pref[off[0]] = off[3 + 2 * kBuckets];
         tb.bact[b * cap + off[3 + b]] = s;
         tb.btile_pref[b * (cap + 1) + off[3 + b]] = off[3 + kBuckets + b];
         off[0] += 1;
@@ -266,14 +258,12 @@ __global__ __launch_bounds__(256) void k_btables(const BSlot *slots, int cap, in
         off[2] += slots[s].nchunk;
         off[3 + b] += 1;
         off[3 + kBuckets + b] += slots[s].nchunk;
-        off[3 + 2 * kBuckets] += units_of(slots[s].nchunk, slots[s].d, G);
     }
     if (tid == 255) {
         const int na = s_v[0][255];
         tb.n_act[0] = na;
         tb.tile_pref[na] = s_v[1][255];
         tb.chunk_pref[na] = s_v[2][255];
-        tb.unit_pref[na] = s_v[3 + 2 * kBuckets][255];
         for (int b = 0; b < kBuckets; ++b) {
             const int nb = s_v[3 + b][255];
             tb.n_act[1 + b] = nb;
@@ -283,119 +273,82 @@ __global__ __launch_bounds__(256) void k_btables(const BSlot *slots, int cap, in
 }
 
 // ---------------------------------------------------------------- proposal
-// One workgroup per chunk of 256 particles (one per thread), every sampler in
-// one launch (single >= 0: the chunks of that slot only).  Draws the proposal
-// (or x0 ~ q0) in place; at initialisation also leaves the quadratic term of
-// log q0 in lp_scr.  Kept apart from the target so that its register use, and
-// with it the occupancy of the normal generation, does not depend on d.
-// CW: row stride of the step's LDS staging block, at least 2 G + 1 doubles.
-template <bool kInit, int CW = 17>
-__global__ __launch_bounds__(256) void k_bprop(const BSlot *slots, const int *n_act,
-                                               const int *act_list, const int *unit_pref, int G,
-                                               int single)
+// x0 ~ q0 of the chunks of slot `slot`, one particle a thread, and the
+// quadratic term of log q0 (summed over the row in order) in lp_scr.  With one
+// coordinate a particle, particles 2p and 2p + 1 take the two values of the
+// pair drawn for index p: one pair a lane of the chunk's first two wavefronts.
+__global__ __launch_bounds__(256) void k_bdraw0(const BSlot *slots, int slot)
 {
     const int tid = threadIdx.x;
-    int slot, unit;
-    if (single >= 0) {
-        slot = single;
-        unit = blockIdx.x;
-    } else if (!locate(unit_pref, act_list, n_act[0], blockIdx.x, slot, unit)) {
-        return;
-    }
     // a local copy: stores through the sampler's arrays cannot alias it
     const BSlot S = slots[__builtin_amdgcn_readfirstlane(slot)];
     const i64 n = S.n;
-    const int d = S.d;
-    // a unit is one chunk of 256 particles and a group of G coordinate pairs
-    // (all pairs at initialisation, where log q0 sums over the whole row)
+    const int d = S.d, chunk = blockIdx.x;
     __shared__ uint4 s_xch[4][64];  // normal generator exchange, one row per wave
-    const int npair = (d + 1) / 2;
-    const int ng = kInit ? 1 : (npair + G - 1) / G;
-    const int chunk = unit / ng, grp = unit - chunk * ng;
-    const int kp0 = kInit ? 0 : grp * G;
-    const int kp1 = kInit ? npair : (kp0 + G < npair ? kp0 + G : npair);
-    if (tid == 0 && grp == 0 && (chunk % kChunksPerTile) == 0) S.status[chunk / kChunksPerTile] = 0;
-    const uint32_t t = kInit ? 0u : S.ctrl->t;
-    const uint32_t tag = kInit ? (uint32_t)kTagInit : (uint32_t)kTagPropose;
-    if (d == 1) {
-        // One coordinate a particle: particles 2p and 2p + 1 take the two
-        // values of the pair drawn for index p; the chunk's (at most 128)
-        // pairs go to its first two wavefronts, one pair a lane.
-        if (tid >= kBChunk / 2) return;  // whole wavefronts
-        const i64 p = (i64)chunk * (kBChunk / 2) + tid;
-        const i64 i0 = 2 * p;
-        const bool pact = i0 < n;
-        double z[2];
-        normal_pair_wave(S.seed, tag, S.sampler, t, (uint32_t)p, 0u, pact, z[0], z[1],
-                         s_xch[tid >> 6]);
-        if (!pact) return;
-        GLB(double) *xr = glb(kInit ? S.x : (S.ctrl->cur ? S.x_scr : S.x));
-        for (int h = 0; h < 2; ++h) {
-            const i64 i = i0 + h;
-            if (i >= n) break;
-            const double zh = h == 0 ? z[0] : z[1];
-            if (kInit) {
-                const double xk = S.init_mean + S.init_sd * zh;
-                xr[i] = xk;
-                const double t0 = xk - S.init_mean;
-                glb(S.lp_scr)[i] = 0.0 + (t0 * t0) * S.init_prec;
-            } else {
-                xr[i] = xr[i] + S.rw_sd * zh;
-            }
-        }
-        return;
-    }
-    const i64 i = (i64)chunk * kBChunk + tid;
+    const bool one = d == 1;
+    if (one && tid >= kBChunk / 2) return;  // whole wavefronts
+    const i64 p = (i64)chunk * (one ? kBChunk / 2 : kBChunk) + tid;  // counter index
+    const i64 i = one ? 2 * p : p;                                   // first particle
     const bool act = i < n;
     GLB(double) *xi = glb(S.x) + i * d;
+    const int nv = one ? (i + 1 < n ? 2 : 1) : d;  // values drawn by this thread
     double acc0 = 0.0;
-    if (!kInit) {
-        // Step: the unit's block of rows [base, base + cnt) x columns
-        // [k0, k0 + w), w <= 16, moves between HBM and LDS as whole 128-byte
-        // lines (16 lanes per row); each thread then updates its own row in
-        // LDS.  Strided per-thread row accesses would touch 64 lines per
-        // wave instruction.
-        __shared__ double sx[kBChunk][CW];
-        const int k0 = 2 * kp0, w = (2 * kp1 < d ? 2 * kp1 : d) - k0;
-        const i64 base = (i64)chunk * kBChunk;
-        const int cnt = (int)((n - base) < kBChunk ? (n - base) : kBChunk);
-        const int lc = tid & 15, lr = tid >> 4;
-        GLB(double) *xb = glb(S.ctrl->cur ? S.x_scr : S.x) + base * d + k0;
-        stage_rows(sx, xb, d, cnt, w);
-        __syncthreads();
-        for (int k2 = kp0; k2 < kp1; ++k2) {
-            double z[2];
-            normal_pair_wave(S.seed, tag, S.sampler, t, (uint32_t)i, (uint32_t)k2, act, z[0],
-                             z[1], s_xch[tid >> 6]);
-            const int c = 2 * k2 - k0;
-            if (act) {
-                sx[tid][c] = sx[tid][c] + S.rw_sd * z[0];
-                if (c + 1 < w) sx[tid][c + 1] = sx[tid][c + 1] + S.rw_sd * z[1];
-            }
-        }
-        __syncthreads();
-        for (int r = lr; r < cnt; r += 16)
-            if (lc < w) xb[(i64)r * d + lc] = sx[r][lc];
-        return;
-    }
-    // Initialisation (whole rows, all pairs; log q0 sums over the row)
-    for (int k2 = kp0; k2 < kp1; ++k2) {
-        const int k0 = 2 * k2;
+    for (int k0 = 0; k0 < (one ? 2 : d); k0 += 2) {
         double z[2];
-        normal_pair_wave(S.seed, tag, S.sampler, t, (uint32_t)i, (uint32_t)k2, act, z[0], z[1],
-                         s_xch[tid >> 6]);
-        if (act) {
-            for (int h = 0; h < 2; ++h) {
-                const int kk = k0 + h;
-                if (kk >= d) break;
-                const double xk = S.init_mean + S.init_sd * z[h];
-                xi[kk] = xk;
-                const double t0 = xk - S.init_mean;
-                acc0 = acc0 + (t0 * t0) * S.init_prec;
-            }
+        normal_pair_wave(S.seed, kTagInit, S.sampler, 0u, (uint32_t)p, (uint32_t)k0 >> 1, act,
+                         z[0], z[1], s_xch[tid >> 6]);
+        if (!act) continue;
+        for (int h = 0; h < 2; ++h) {
+            if (k0 + h >= nv) break;
+            const double xk = S.init_mean + S.init_sd * (h == 0 ? z[0] : z[1]);
+            xi[k0 + h] = xk;
+            const double t0 = xk - S.init_mean;
+            acc0 = (one ? 0.0 : acc0) + (t0 * t0) * S.init_prec;
+            if (one) glb(S.lp_scr)[i + h] = acc0;
         }
     }
-    if (kInit && act) glb(S.lp_scr)[i] = acc0;
+    if (!one && act) glb(S.lp_scr)[i] = acc0;
+}
+
+// The random-walk proposal in place, one workgroup per chunk of 256 particles of
+// every sampler in one launch (draw_rows: items spread over the lanes, rows
+// touched in whole lines).  The first workgroup of a tile also clears the
+// tile's lookback word.  Bound by vector issue (95 % busy, 260 vector
+// instructions per pair of normals and wavefront): 614 -> 478 us on the
+// 256-sampler workload against units of 256 particles times 8 pairs through an
+// LDS block, each pair's rejections resolved at once.  The same drawing inside
+// the target kernels, which saves a read of the rows, was slower: their
+// registers leave three wavefronts a SIMD to hide the generator's latencies.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k_bprop(
+    const BSlot *slots, const int *n_act, const int *act, const int *chunk_pref)
+{
+    __shared__ uint32_t s_queue[4][kDrawQueue];
+    __shared__ double s_draw[4][kDrawBlock][2];
+    int slot, chunk;
+    if (!locate(chunk_pref, act, n_act[0], blockIdx.x, slot, chunk)) return;
+    // a local copy: stores through the sampler's arrays cannot alias it
+    const BSlot S = slots[__builtin_amdgcn_readfirstlane(slot)];
+    const i64 base = (i64)chunk * kBChunk;
+    const int cnt = (int)(S.n - base < kBChunk ? S.n - base : kBChunk);
+    if (threadIdx.x == 0 && chunk % kChunksPerTile == 0) S.status[chunk / kChunksPerTile] = 0;
+    GLB(double) *x = glb(S.ctrl->cur ? S.x_scr : S.x);
+    GLB(double) *xb = x + base * S.d;
+    // one coordinate: rows of two particles, which share a pair
+    const bool one = S.d == 1;
+    const int d = one ? 2 : S.d;
+    draw_rows<false, kDrawBlock>(
+        RowDraw{S.seed, S.sampler, 0.0, S.rw_sd}, d, one ? base >> 1 : base,
+        one ? (cnt + 1) >> 1 : cnt, S.n * S.d, S.ctrl->t, x, ((uintptr_t)x & 15) == 0, s_queue,
+        [&](int it) { return s_draw[threadIdx.x >> 6][it % kDrawBlock]; },
+        [&](int p, int c, bool two, bool vec, double v0, double v1) {
+            const int o = p * d + c;
+            if (vec) {
+                *(GLB(f64x2b_t) *)(xb + o) = f64x2b_t{v0, v1};
+            } else {
+                xb[o] = v0;
+                if (two) xb[o + 1] = v1;
+            }
+        });
 }
 
 // ------------------------------------------------------ target + weights
@@ -1290,7 +1243,7 @@ SamplerLayout sampler_layout(int64_t n, int d)
 }
 
 struct BatchLayout {
-    size_t slots, n_act, act, tile_pref, chunk_pref, unit_pref, bact, btile_pref, total;
+    size_t slots, n_act, act, tile_pref, chunk_pref, bact, btile_pref, total;
 };
 
 BatchLayout batch_layout(int cap)
@@ -1307,7 +1260,6 @@ BatchLayout batch_layout(int cap)
     L.act = take(4 * (size_t)cap);
     L.tile_pref = take(4 * (size_t)(cap + 1));
     L.chunk_pref = take(4 * (size_t)(cap + 1));
-    L.unit_pref = take(4 * (size_t)(cap + 1));
     L.bact = take(4 * (size_t)kBuckets * cap);
     L.btile_pref = take(4 * (size_t)kBuckets * (cap + 1));
     L.total = off;
@@ -1341,8 +1293,6 @@ struct smc_batch {
     std::vector<BSlot> h_slots;
     // host mirror of the tables (grid sizes)
     int n_act, total_tiles, total_chunks;
-    int64_t total_units;
-    int G;  // coordinate pairs per proposal unit
     int quad_waves[kBuckets];  // occupancy aim of k_bquad per dimension bucket
     int btiles[kBuckets];
     // graph of one step for the current membership and output pointers
@@ -1363,7 +1313,6 @@ inline hipStream_t HS(void *s) { return reinterpret_cast<hipStream_t>(s); }
 void mirror_update(smc_batch *b)
 {
     b->n_act = b->total_tiles = b->total_chunks = 0;
-    b->total_units = 0;
     for (int q = 0; q < kBuckets; ++q) b->btiles[q] = 0;
     for (int s = 0; s < b->cap; ++s) {
         const BSlot &v = b->h_slots[s];
@@ -1371,7 +1320,6 @@ void mirror_update(smc_batch *b)
         b->n_act += 1;
         b->total_tiles += v.ntile;
         b->total_chunks += v.nchunk;
-        b->total_units += units_of(v.nchunk, v.d, b->G);
         b->btiles[v.bucket] += v.nchunk;
     }
     b->version += 1;
@@ -1381,7 +1329,7 @@ void mirror_update(smc_batch *b)
 hipError_t launch_tables(smc_batch *b, hipStream_t s)
 {
     hipLaunchKernelGGL(k_btables, dim3(1), dim3(256), 0, s, (const BSlot *)b->d_slots, b->cap,
-                       b->G, b->tabs);
+                       b->tabs);
     return hipGetLastError();
 }
 
@@ -1446,18 +1394,8 @@ hipError_t enqueue_step(smc_batch *b, smc_resample_info *info, double *est, hipS
 {
     const BSlot *sl = b->d_slots;
     const BTabs &t = b->tabs;
-    // the staging block is sized for the unit (2 G columns, one of padding):
-    // at 5 or 6 pairs its LDS lets 6 or 5 workgroups share a CU instead of 4
-    // (and the kernel needs 73 or 81 VGPRs instead of 97)
-    if (b->G <= 5)
-        hipLaunchKernelGGL((k_bprop<false, 11>), dim3((unsigned)b->total_units), dim3(256), 0, s, sl,
-                           t.n_act, t.act, t.unit_pref, b->G, -1);
-    else if (b->G == 6)
-        hipLaunchKernelGGL((k_bprop<false, 13>), dim3((unsigned)b->total_units), dim3(256), 0, s, sl,
-                           t.n_act, t.act, t.unit_pref, b->G, -1);
-    else
-        hipLaunchKernelGGL((k_bprop<false, 17>), dim3((unsigned)b->total_units), dim3(256), 0, s, sl,
-                           t.n_act, t.act, t.unit_pref, b->G, -1);
+    hipLaunchKernelGGL(k_bprop, dim3(b->total_chunks), dim3(256), 0, s, sl, t.n_act, t.act,
+                       t.chunk_pref);
     for (int q = 0; q < kBuckets; ++q)
         if (b->btiles[q] > 0) launch_quad_bucket<false>(q, dim3(b->btiles[q]), s, b, -1);
     hipLaunchKernelGGL(k_bscan, dim3(b->total_tiles), dim3(256), 0, s, sl, t.n_act, t.act,
@@ -1509,13 +1447,11 @@ smc_status smc_batch_create(smc_batch **h_out, int32_t capacity, void *ws, size_
     b->tabs.act = reinterpret_cast<int *>(b->ws + L.act);
     b->tabs.tile_pref = reinterpret_cast<int *>(b->ws + L.tile_pref);
     b->tabs.chunk_pref = reinterpret_cast<int *>(b->ws + L.chunk_pref);
-    b->tabs.unit_pref = reinterpret_cast<int *>(b->ws + L.unit_pref);
     b->tabs.bact = reinterpret_cast<int *>(b->ws + L.bact);
     b->tabs.btile_pref = reinterpret_cast<int *>(b->ws + L.btile_pref);
     b->h_slots.assign((size_t)capacity, BSlot());
     for (auto &v : b->h_slots) v.n = 0;
     b->graph_on = true;
-    b->G = 8;
     for (int q = 0; q < kBuckets; ++q) b->quad_waves[q] = default_quad_waves(q);
     b->graph = nullptr;
     b->exec = nullptr;
@@ -1550,8 +1486,7 @@ smc_status smc_batch_attach(smc_batch *b, int32_t slot, const smc_batch_sampler 
     const SamplerLayout L = sampler_layout(h_s->n, h_s->d);
     if (h_s->ws_bytes < L.total) return SMC_E_NOMEM;
     const int64_t nt = ntile_of(h_s->n), nc = nchunk_of(h_s->n);
-    if ((int64_t)b->total_tiles + nt > 0x7fffffff || (int64_t)b->total_chunks + nc > 0x7fffffff ||
-        b->total_units + units_of((int)nc, h_s->d, 1) > 0x7fffffff)
+    if ((int64_t)b->total_tiles + nt > 0x7fffffff || (int64_t)b->total_chunks + nc > 0x7fffffff)
         return SMC_E_UNSUPPORTED;
     unsigned char *w = reinterpret_cast<unsigned char *>(h_s->ws);
     BSlot v;
@@ -1597,8 +1532,7 @@ smc_status smc_batch_attach(smc_batch *b, int32_t slot, const smc_batch_sampler 
     const hipStream_t s = HS(stream);
     hipLaunchKernelGGL(k_bslot_set, dim3(1), dim3(1), 0, s, v, b->d_slots + slot);
     hipLaunchKernelGGL(k_bpad, dim3(4), dim3(256), 0, s, (const BSlot *)b->d_slots, slot);
-    hipLaunchKernelGGL(k_bprop<true>, dim3(v.nchunk), dim3(256), 0, s, (const BSlot *)b->d_slots,
-                       b->tabs.n_act, b->tabs.act, b->tabs.unit_pref, b->G, slot);
+    hipLaunchKernelGGL(k_bdraw0, dim3(v.nchunk), dim3(256), 0, s, (const BSlot *)b->d_slots, slot);
     launch_quad_bucket<true>(v.bucket, dim3(v.nchunk), s, b, slot);
     hipLaunchKernelGGL(k_binit, dim3(1), dim3(64), 0, s, (const BSlot *)b->d_slots, slot);
     if (hipGetLastError() != hipSuccess) return SMC_E_DEVICE;
@@ -1677,11 +1611,9 @@ smc_status smc_batch_particles(smc_batch *b, int32_t slot, double **h_x, double 
 
 smc_status smc_batch_set_group(smc_batch *b, int32_t pairs, void *stream)
 {
-    if (!b || pairs < 1 || pairs > kMaxGroup) return SMC_E_ARG;
-    if (pairs == b->G) return SMC_OK;
-    b->G = pairs;
-    mirror_update(b);
-    return launch_tables(b, HS(stream)) == hipSuccess ? SMC_OK : SMC_E_DEVICE;
+    // the proposal has no unit size any more; the range is still checked
+    (void)stream;
+    return b && pairs >= 1 && pairs <= kMaxGroup ? SMC_OK : SMC_E_ARG;
 }
 
 smc_status smc_batch_set_bucket_waves(smc_batch *b, int32_t bucket, int32_t waves)

@@ -374,71 +374,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 // ------------------------------------------------ rows of several coordinates
-// Draws the proposal (or x0) of particles [base, base + cnt) with d >= 2
-// coordinates by the whole workgroup: one (particle, pair) a thread, two at a
-// time (the normals share their coefficients), neighbouring threads on
-// neighbouring addresses.  put(p, c, two, v0, v1): coordinates c and, if two,
-// c + 1 of particle base + p.  total: values in x (an odd 1-D population drawn
-// as rows of two ends early).  One thread per particle instead, walking its
-// row, touched a cache line per lane and access and left most of the chip
-// idle below 10^5 particles.
-template <bool kInit, class Put>
-__device__ inline void draw_rows(const TArgs &a, int d, i64 base, int cnt, i64 total, uint32_t t,
-                                 const double *x, uint4 *xch, Put &&put)
+// Coordinates c and, if two, c + 1 of a row at dst (vec: 16-byte aligned; the
+// workspace copy is aligned wherever x is).
+__device__ inline void put_pair(double *dst, bool two, bool vec, double v0, double v1)
 {
-    constexpr int W = 2;
-    const uint32_t tag = kInit ? (uint32_t)kTagInit : (uint32_t)kTagPropose;
-    const int np = (d + 1) >> 1, items = cnt * np, tid = threadIdx.x;
-    const float inv = 1.0f / (float)np;  // quotients below 2^14, half a unit from every edge
-    const bool v2 = (d & 1) == 0 && ((uintptr_t)x & 15) == 0 && (total & 1) == 0;
-    for (int i0 = 0; i0 < items; i0 += 256 * W) {
-        int p[W], c[W];
-        uint32_t idx[W], pair[W];
-        bool act[W], two[W];
-        double x0[W], x1[W], z[2 * W];
-#pragma unroll
-        SMC_EACH {
-            const int it = i0 + 256 * w + tid;
-            act[w] = it < items;
-            p[w] = (int)(((float)(act[w] ? it : 0) + 0.5f) * inv);
-            c[w] = 2 * ((act[w] ? it : 0) - p[w] * np);
-            idx[w] = (uint32_t)(base + p[w]);
-            pair[w] = (uint32_t)c[w] >> 1;
-            const i64 o = (base + p[w]) * d + c[w];
-            two[w] = c[w] + 1 < d && o + 1 < total;
-            x0[w] = x1[w] = 0.0;
-            if (!kInit) {
-                if (v2) {
-                    const f64x2s v = *reinterpret_cast<const f64x2s *>(x + o);
-                    x0[w] = v[0];
-                    x1[w] = v[1];
-                } else {
-                    x0[w] = x[o];
-                    x1[w] = x[two[w] ? o + 1 : o];
-                }
-            }
-        }
-        asm volatile("" ::: "memory");  // the loads overlap the generator
-        normal_pairs_wave<W>(a.seed, tag, a.sampler, kInit ? 0u : t, idx, pair,
-                             i0 + 256 < items ? 2 : 1, act, z, xch + (tid & ~63));
-#pragma unroll
-        SMC_EACH {
-            if (!act[w]) continue;
-            if (kInit)
-                put(p[w], c[w], two[w], a.init_mean + a.init_sd * z[2 * w],
-                    a.init_mean + a.init_sd * z[2 * w + 1]);
-            else
-                put(p[w], c[w], two[w], x0[w] + a.rw_sd * z[2 * w], x1[w] + a.rw_sd * z[2 * w + 1]);
-        }
+    if (vec) {
+        *reinterpret_cast<f64x2s *>(dst) = f64x2s{v0, v1};
+    } else {
+        dst[0] = v0;
+        if (two) dst[1] = v1;
     }
+}
+
+// The proposal (or x0) of particles [base, base + cnt): see draw_rows.
+template <bool kInit, int kMaxBlock, class Slot, class Put>
+__device__ inline void draw_rows(const TArgs &a, int d, i64 base, int cnt, i64 total, uint32_t t,
+                                 const double *x, uint32_t (&queue)[4][kDrawQueue], Slot &&slot,
+                                 Put &&put)
+{
+    draw_rows<kInit, kMaxBlock>(RowDraw{a.seed, a.sampler, kInit ? a.init_mean : 0.0,
+                             kInit ? a.init_sd : a.rw_sd},
+                     d, base, cnt, total, t, x, (((uintptr_t)x & 15) == 0), queue, slot, put);
 }
 
 // Particles of a workgroup of k_rows / k_propose: a power of two with at most
 // 24 KB of rows in LDS (six workgroups on a CU), smaller where the population
 // would otherwise make fewer than two workgroups per CU.
+__host__ __device__ inline int row_stride(int d) { return ((d + 1) | 1); }  // odd, whole pairs
 inline int rows_per_block(int64_t n, int d)
 {
-    const int ds = d | 1;
+    const int ds = row_stride(d);
     int P = 256;
     while (P > 32 && P * ds * 8 > 24 * 1024) P >>= 1;
     while (P > 32 && n < 512ll * P) P >>= 1;
@@ -459,21 +424,20 @@ template <bool kInit>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_propose(
     TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x, double *__restrict__ xo)
 {
-    __shared__ uint4 s_xch[256];
+    __shared__ uint32_t s_queue[4][kDrawQueue];
+    __shared__ double s_draw[4][kDrawBlock][2];
+    const int tid = threadIdx.x;
     const int dv = a.d == 1 ? 2 : a.d;
     const i64 rows = a.d == 1 ? (n + 1) >> 1 : n;
     const i64 base = (i64)blockIdx.x * P;
     if (base >= rows) return;
     const int cnt = (int)(rows - base < P ? rows - base : P);
-    draw_rows<kInit>(a, dv, base, cnt, n * a.d, t, x, s_xch,
-                     [&](int p, int c, bool two, double v0, double v1) {
+    draw_rows<kInit, kDrawBlock>(a, dv, base, cnt, n * a.d, t, x, s_queue,
+                     [&](int it) { return s_draw[tid >> 6][it % kDrawBlock]; },
+                     [&](int p, int c, bool two, bool vec, double v0, double v1) {
                          const i64 o = (base + p) * dv + c;
-                         x[o] = v0;
-                         if (two) x[o + 1] = v1;
-                         if (xo) {
-                             xo[o] = v0;
-                             if (two) xo[o + 1] = v1;
-                         }
+                         put_pair(x + o, two, vec, v0, v1);
+                         if (xo) put_pair(xo + o, two, vec, v0, v1);
                          if (a.thb) {
                              // particle and column of value o (rows of two: one column)
                              const i64 i0 = a.d == 1 ? o : base + p;
@@ -526,12 +490,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo,
     double *__restrict__ lpo, LrArgs lr)
 {
-    extern __shared__ double s_dyn[];  // [P][d | 1] rows, [P] exponentials
-    __shared__ uint4 s_buf[256];       // generator exchange, then the last reduction
+    extern __shared__ double s_dyn[];  // [P][row_stride(d)] rows, [P] exponentials
+    __shared__ uint32_t s_queue[4][kDrawQueue];
+    __shared__ double s_red[2][256];
     __shared__ double s_par[2][kMaxDim];
     __shared__ double s_w[4];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int d = a.d, ds = d | 1;
+    const int d = a.d, ds = row_stride(d);
     double *rows = s_dyn, *s_e = s_dyn + P * ds;
     const bool uni = !kInit && a.uniform && *a.uniform;  // lazy reset: weights are -ln N
     const double ninf = -__builtin_huge_val();
@@ -554,19 +519,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             lp_old = lp[i];
         }
         if (kKind == SMC_TARGET_GAUSS) {
-            draw_rows<kInit>(a, d, base, cnt, n * d, t, x, s_buf,
-                             [&](int p, int c, bool two, double v0, double v1) {
+            // the uniforms wait where the row's values will be
+            const int np = (d + 1) >> 1;
+            const float invp = 1.0f / (float)np;
+            draw_rows<kInit, 4096>(a, d, base, cnt, n * d, t, x, s_queue,
+                             [&](int it) {
+                                 const int p = (int)(((float)it + 0.5f) * invp);
+                                 return rows + p * ds + 2 * (it - p * np);
+                             },
+                             [&](int p, int c, bool two, bool vec, double v0, double v1) {
                                  const i64 o = (base + p) * d + c;
                                  rows[p * ds + c] = v0;
                                  if (two) rows[p * ds + c + 1] = v1;
-                                 if (kDst != kToCopy) {
-                                     x[o] = v0;
-                                     if (two) x[o + 1] = v1;
-                                 }
-                                 if (kDst != kInPlace) {
-                                     xo[o] = v0;
-                                     if (two) xo[o + 1] = v1;
-                                 }
+                                 if (kDst != kToCopy) put_pair(x + o, two, vec, v0, v1);
+                                 if (kDst != kInPlace) put_pair(xo + o, two, vec, v0, v1);
                              });
         } else {
             if (act)
@@ -640,17 +606,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         }
         __syncthreads();  // the next chunk overwrites the rows
     }
-    double *red = reinterpret_cast<double *>(s_buf);  // [2][256]
-    red[tid] = s1;
-    red[256 + tid] = s2;
+    s_red[0][tid] = s1;
+    s_red[1][tid] = s2;
     const double we = wave_sum_f64(e0);
     if (lane == 0) s_w[wid] = we;
     __syncthreads();
     double *out = is_part + blockIdx.x;
     if (tid < 2 * d) {
-        const int c = tid < d ? tid : 256 + (tid - d);
+        const double *red = tid < d ? s_red[0] + tid : s_red[1] + (tid - d);
         double v = 0.0;
-        for (int q = 0; q < parts; ++q) v += red[c + q * d];
+        for (int q = 0; q < parts; ++q) v += red[q * d];
         out[(i64)(2 + tid) * gridDim.x] = v;
     }
     if (tid == 0) {
@@ -1575,7 +1540,7 @@ void launch_rows_k(dim3 g, hipStream_t s, const TArgs &a, i64 n, uint32_t t, dou
                    double *logw, const Work &w, u64 *sp, Dst dst, const LrArgs &lr)
 {
     const int P = rows_per_block(n, a.d);
-    const size_t lds = (size_t)P * ((a.d | 1) + 1) * sizeof(double);
+    const size_t lds = (size_t)P * (row_stride(a.d) + 1) * sizeof(double);
     auto kern = k_rows<kKind, kInit, kInPlace>;
     if constexpr (!kInit) {
         if (dst == kToCopy) kern = k_rows<kKind, false, kToCopy>;

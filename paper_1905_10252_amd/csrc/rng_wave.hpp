@@ -153,4 +153,174 @@ __device__ inline void normal_pair_wave(uint64_t seed, uint32_t tag, uint32_t sa
     z2 = z[1];
 }
 
+// What the rows of a population are drawn from.
+struct RowDraw {
+    uint64_t seed;
+    uint32_t sampler;
+    double mean, sd;  // x0 ~ N(mean, sd^2 I); a step adds sd z to the row
+};
+
+typedef double f64x2r __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) double gdouble;
+__device__ const f64x2r *vec_of(const double *);
+__device__ const __attribute__((address_space(1))) f64x2r *vec_of(const gdouble *);
+
+// Draws the proposal (kInit: x0) of particles [base, base + cnt) with d >= 2
+// coordinates by the whole workgroup of 256 threads: items (particle, pair),
+// neighbouring threads on neighbouring addresses.  put(p, c, two, vec, v0, v1):
+// coordinates c and, if two, c + 1 of particle base + p; vec: both there, and
+// 16-byte aligned in x.  total: values in x (an odd 1-D population drawn as
+// rows of two ends early).  vec: x is 16-byte aligned.  cnt times the row's
+// pairs is at most 2^14.  slot(it): where two doubles of item `it` wait in LDS.
+//
+// Nothing ties an item to a lane here, so the rejected ones are not resolved
+// where they arose.  A wavefront takes a block of up to kMaxBlock items: it tries
+// 64 new ones at a time, leaves the accepted uniforms in their slots and queues
+// the others in LDS with their next attempt; a queue of 64 makes a trial of its
+// own, and the last ones share the wavefront, floor(64 / pending) lanes trying
+// consecutive attempts of each (the lowest accepted counts).  A block of 512
+// takes about 11 trials; resolving every 64 items at once took 16.5, with an
+// exchange of results each.  The logarithms and roots then run on whole
+// wavefronts, two items a lane, and rows are read and written in whole lines
+// (finishing each item where it was accepted scattered a fifth of the stores:
+// 630 us against 380 without them, 256-sampler workload).  Bound by vector
+// issue.
+constexpr int kDrawBlock = 256;  // where the items wait in a buffer of their own
+constexpr int kDrawQueue = 128;  // entries a wavefront: fewer than 64 before a trial
+
+template <bool kInit, int kMaxBlock, class Ptr, class Slot, class Put>
+__device__ inline void draw_rows(const RowDraw &g, int d, long long base, int cnt,
+                                 long long total, uint32_t t, Ptr x, bool vec,
+                                 uint32_t (&queue)[4][kDrawQueue], Slot &&slot, Put &&put)
+{
+    constexpr uint32_t kAttempts = 32;
+    const uint32_t tag = kInit ? (uint32_t)kTagInit : (uint32_t)kTagPropose;
+    const int np = (d + 1) >> 1, items = cnt * np;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float inv = 1.0f / (float)np;  // quotients below 2^14, half a unit from every edge
+    const bool v2 = vec && (d & 1) == 0 && (total & 1) == 0;
+    const Ptr xb = x + base * d;
+    const long long left = total - base * d;  // values from here to the end of x
+    const int lim = left < (1 << 30) ? (int)left : 1 << 30;
+    uint32_t *q = queue[wid];
+    int blk = (items + 255) / 256 * 64;  // an equal share, in whole wavefronts
+    blk = blk < kMaxBlock ? blk : kMaxBlock;
+    for (int it0 = wid * blk; it0 < items; it0 += 4 * blk) {
+        const int m = items - it0 < blk ? items - it0 : blk;
+        int qn = 0;
+        // posts `e` of the lanes in `again` to the queue
+        auto post = [&](bool again, uint32_t e) {
+            const uint64_t mask = __ballot(again);
+            __builtin_amdgcn_wave_barrier();
+            if (again)
+                q[qn + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u))] =
+                    e;
+            qn += __popcll(mask);
+            __builtin_amdgcn_wave_barrier();
+            asm volatile("" ::: "memory");
+        };
+        // up to 64 queued items, L consecutive attempts of each
+        auto queued = [&]() {
+            const int n = qn < 64 ? qn : 64;
+            qn -= n;
+            // floor(64 / n) and floor(lane / L) from FP32 reciprocals of small
+            // integers, half a unit away from every edge: exact
+            const int L = __builtin_amdgcn_readfirstlane(
+                (int)(64.5f * __builtin_amdgcn_rcpf((float)n)));
+            const int j = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)L));
+            const int k = lane - j * L;
+            const uint32_t e = q[qn + (j < n ? j : 0)];
+            const uint32_t it = e & 0xFFFFu, first = e >> 16, attempt = first + (uint32_t)k;
+            const int p = (int)(((float)it + 0.5f) * inv);
+            const uint32_t pair = it - (uint32_t)(p * np);
+            double v1, w1;
+            const bool ok = polar_uniforms(g.seed, tag, g.sampler, kInit ? 0u : t,
+                                           (uint32_t)(base + p), (pair << 16) | attempt, v1, w1) &&
+                            j < n && attempt < kAttempts;
+            const uint64_t acc = __ballot(ok);
+            // accepted attempts of this lane's item, lowest first
+            const uint64_t seg = (acc >> ((j * L) & 63)) & (L == 64 ? ~0ull : (1ull << L) - 1ull);
+            const bool lost = j < n && k == 0 && seg == 0ull;
+            const bool again = lost && first + (uint32_t)L < kAttempts;
+            if (ok && (seg & ((1ull << k) - 1ull)) == 0ull) {
+                double *s = slot((int)it);
+                s[0] = v1;
+                s[1] = w1;
+            } else if (lost && !again) {  // every attempt rejected: the pair is (0, 0)
+                double *s = slot((int)it);
+                s[0] = s[1] = 0.0;
+            }
+            post(again, it | ((first + (uint32_t)L) << 16));
+        };
+        for (int next = 0; next < m; next += 64) {
+            const bool act = next + lane < m;
+            const int it = it0 + next + (act ? lane : 0);
+            const int p = (int)(((float)it + 0.5f) * inv);
+            const uint32_t pair = (uint32_t)(it - p * np);
+            double v1, w1;
+            const bool ok = polar_uniforms(g.seed, tag, g.sampler, kInit ? 0u : t,
+                                           (uint32_t)(base + p), pair << 16, v1, w1);
+            if (ok && act) {
+                double *s = slot(it);
+                s[0] = v1;
+                s[1] = w1;
+            }
+            post(act && !ok, (uint32_t)it | (1u << 16));
+            if (qn >= 64) queued();
+        }
+        while (qn > 0) queued();
+        constexpr int W = 2;
+        for (int i0 = 0; i0 < m; i0 += 64 * W) {
+            int p[W], c[W];
+            bool act[W], two[W];
+            double x0[W], x1[W], v1[W], w1[W], s[W], f[W];
+#pragma unroll
+            SMC_EACH {
+                act[w] = i0 + 64 * w + lane < m;
+                const int it = it0 + (act[w] ? i0 + 64 * w + lane : 0);
+                p[w] = (int)(((float)it + 0.5f) * inv);
+                c[w] = 2 * (it - p[w] * np);
+                const int o = p[w] * d + c[w];
+                two[w] = c[w] + 1 < d && o + 1 < lim;
+                const double *sl = slot(it);
+                v1[w] = sl[0];
+                w1[w] = sl[1];
+                x0[w] = x1[w] = 0.0;
+                if (!kInit) {
+                    if (v2) {
+                        const f64x2r v = *(decltype(vec_of(xb)))(xb + o);
+                        x0[w] = v[0];
+                        x1[w] = v[1];
+                    } else {
+                        x0[w] = xb[o];
+                        x1[w] = xb[two[w] ? o + 1 : o];
+                    }
+                }
+            }
+            asm volatile("" ::: "memory");  // all requested before the first use
+#pragma unroll
+            SMC_EACH s[w] = v1[w] * v1[w] + w1[w] * w1[w];
+            if (__any(!(s[0] > 0.0 && s[1] > 0.0))) {  // a pair of (0, 0): any value in range
+#pragma unroll
+                SMC_EACH s[w] = s[w] > 0.0 ? s[w] : 0.25;
+            }
+            det_log_w<W>(s, f);
+#pragma unroll
+            SMC_EACH f[w] = -2.0 * f[w];
+            det_div_w<W>(f, s, f);
+            det_sqrt_w<W>(f, f);
+#pragma unroll
+            SMC_EACH {
+                if (!act[w]) continue;
+                const double z0 = v1[w] * f[w], z1 = w1[w] * f[w];
+                if (kInit) put(p[w], c[w], two[w], v2, g.mean + g.sd * z0, g.mean + g.sd * z1);
+                else put(p[w], c[w], two[w], v2, x0[w] + g.sd * z0, x1[w] + g.sd * z1);
+            }
+            asm volatile("" ::: "memory");
+        }
+        __builtin_amdgcn_wave_barrier();  // the slots are free for the next block
+    }
+}
+
 }  // namespace smc
