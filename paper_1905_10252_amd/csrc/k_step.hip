@@ -24,7 +24,9 @@
 #include <cmath>
 
 #include "../../include/smc.h"
+#include "afun.hpp"
 #include "common.hpp"
+#include "decide.hpp"
 #include "det.hpp"
 #include "kernels.hpp"
 #include "reduce.hpp"
@@ -725,115 +727,114 @@ __global__ __launch_bounds__(256) void k_post_est(const Ctrl *ctrl, i64 n, int d
 
 
 // ------------------------------------------------- small-N fused iteration
-// One workgroup of 1024 threads runs a whole iteration of Alg 2 for N <= 2048
-// particles of a cheap target (Gaussian d <= 16, Student-t): proposal and
-// weights, exact max, fixed-point weights and their inclusive prefix in LDS,
-// FP64 sums, estimates, the integer decision, c_t and recycling, then the
-// redistribution (ancestor by binary search on the LDS prefix) and reset.
-// Same arithmetic per particle and same integers as the multi-kernel path;
-// only the order of the FP64 sums differs.  It keeps the control block as
-// the multi-kernel path does and clears the other parity's max slots.
-constexpr int kSmallN = 2048, kSmallD = 16, kSmallT = 1024, kSmallI = kSmallN / kSmallT;
+// One workgroup runs a whole iteration of Alg 2 for at most kSmallN particles
+// of a cheap target with up to kSmallD coordinates, two consecutive particles
+// a thread and only as many wavefronts as that takes: proposal and weights;
+// after a barrier the fixed-point weights, their prefix and every sum; after
+// another the integer decision, c_t and recycling, which every thread forms
+// for itself from the wavefronts' totals; when it resamples, the sources mark
+// their first outputs in LDS and a max-scan over the outputs carries the marks
+// (two more barriers; a binary search per output took eleven dependent LDS
+// reads).  Rows wait in LDS, and each particle is stored once.  Same arithmetic
+// per particle and same integers as the multi-kernel path; only the order of
+// the FP64 sums differs.  It keeps the control block as the multi-kernel path
+// does and clears the other parity's max slots.  Bound by latency: 7.2 us a
+// call at N = 1024 with one coordinate (1024 threads whatever N, a search per
+// output and six barriers: 10.1).
+constexpr int kSmallN = 2048, kSmallD = 8;
+constexpr int kSmallPairs = 3072;  // most (particle, pair) items
+constexpr int kSmallRows = 2 * kSmallPairs;  // row values in LDS
 
-template <int CTRL>
-__device__ inline double sdpp_f64(double v)
+template <int kKind, int kDim, int kMaxN>  // kDim: largest d (1, 4 or 8)
+__global__ __launch_bounds__(kMaxN / 2) void k_small_step(TArgs a, i64 n, uint32_t t, int K, int mode,
+                                                        int ess_num, int ess_den,
+                                                        double *__restrict__ x,
+                                                        double *__restrict__ logw,
+                                                        double *__restrict__ lp, Ctrl *ctrl,
+                                                        u64 *slots_other, double *rec_num,
+                                                        smc_resample_info *info, double *est,
+                                                        double reset)
 {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-// sum of each 16-lane row, in the row's last lane (DPP only, no LDS trips)
-__device__ inline double srow16(double v)
-{
-    v += sdpp_f64<0x111>(v);
-    v += sdpp_f64<0x112>(v);
-    v += sdpp_f64<0x114>(v);
-    v += sdpp_f64<0x118>(v);
-    return v;
-}
-
-// One whole iteration t of a population of at most kSmallN particles by one
-// workgroup of kSmallT threads.  kD1 (d = 1): each thread keeps its items'
-// new coordinate and log-target in registers, and the redistribution gathers
-// them from LDS (no scratch rows in global memory).
-template <int kKind, bool kD1>
-__device__ __forceinline__ void small_iteration(const TArgs &a, i64 n, uint32_t t, int K,
-                                                int mode, int ess_num, int ess_den,
-                                                double *__restrict__ x,
-                                                double *__restrict__ logw,
-                                                double *__restrict__ lp,
-                                                double *__restrict__ x_scr,
-                                                double *__restrict__ lp_scr, Ctrl *ctrl,
-                                                double *rec_num, smc_resample_info *info,
-                                                double *est, double reset)
-{
-    constexpr int NW = kSmallT / 64;  // waves of the block
-    __shared__ double s_e[kSmallN];
-    __shared__ u64 s_S[kSmallN];
-    __shared__ double s_col[NW][2 * kSmallD];
+    constexpr int NW = kMaxN / 128, DM = kDim;
+    constexpr bool kD1 = kDim == 1;
+    __shared__ double s_x[kD1 ? kMaxN : kSmallRows], s_lp[kMaxN];
+    __shared__ unsigned s_mark[kMaxN];
     __shared__ uint4 s_xch[NW][64];
-    __shared__ double s_tot[2 * kSmallD];
-    __shared__ double s_z[16], s_z2[16];
-    __shared__ u64 s_key[16], s_wsum[16], s_lo[16], s_hi[16];
-    __shared__ unsigned s_bad[16];
-    __shared__ double s_bc[4];
-    __shared__ u64 s_bu[4];
-    __shared__ double s_lpv[kD1 ? kSmallN : 1];
-    constexpr int DM = kD1 ? 1 : kSmallD;  // coordinates a thread handles
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int d = kD1 ? 1 : a.d;
+    __shared__ double s_col[2 * DM][NW], s_z[NW], s_z2[NW];
+    __shared__ u64 s_key[NW], s_wsum[NW], s_lo[NW], s_hi[NW];
+    __shared__ unsigned s_bad[NW], s_wmax[NW];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
+    const int d = kD1 ? 1 : a.d, ni = (int)n, i0 = 2 * tid;
+    const double ninf = -__builtin_huge_val();
+    const bool act[2] = {i0 < ni, i0 + 1 < ni};
+    const RecState rec(ctrl);
+    const double rec_old = tid < 2 * d ? rec_num[tid] : 0.0;
     const u64 r = resample_word(a.seed, a.sampler, t);
-    double xr[kSmallI], lpr[kSmallI];  // kD1: the items' new x and log-target
 
-    // proposal and weights (items tid + 1024 j; with d = 1 items 2 tid + j,
-    // the two particles that share the pair drawn for index tid)
-    static_assert(kSmallI == 2, "one pair per thread covers its two 1-D items");
+    // the thread's particles, requested before the normals are drawn
+    double xr[2][DM], lw[2], lp_old[2], lpn[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int i = act[j] ? i0 + j : 0;
+#pragma unroll
+        for (int k = 0; k < DM; ++k) xr[j][k] = k < d ? x[i * d + k] : 0.0;
+        lw[j] = logw[i];
+        lp_old[j] = lp[i];
+    }
+    for (int k = tid; k < kSlots * kSlotStride; k += blockDim.x) slots_other[k] = 0;
+    s_mark[i0] = 0u;
+    s_mark[i0 + 1] = 0u;
+    asm volatile("" ::: "memory");
+    if constexpr (kD1) {
+        double z[2];
+        normal_pair_wave(a.seed, kTagPropose, a.sampler, t, (uint32_t)tid, 0u, act[0], z[0], z[1],
+                         s_xch[wid]);
+        xr[0][0] = xr[0][0] + a.rw_sd * z[0];
+        xr[1][0] = xr[1][0] + a.rw_sd * z[1];
+    } else {
+        for (int q = 0; 2 * q < d; ++q) {
+            const uint32_t idx[2] = {(uint32_t)i0, (uint32_t)(i0 + 1)};
+            const uint32_t pair[2] = {(uint32_t)q, (uint32_t)q};
+            double z[4];
+            normal_pairs_wave<2>(a.seed, kTagPropose, a.sampler, t, idx, pair, 2, act, z,
+                                 s_xch[wid]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int k = 0; k < DM; ++k)
+                    if (k >> 1 == q && k < d) xr[j][k] = xr[j][k] + a.rw_sd * z[2 * j + (k & 1)];
+        }
+    }
+    if (kKind == SMC_TARGET_GAUSS) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            double acc = 0.0;
+#pragma unroll
+            for (int k = 0; k < DM; ++k)
+                if (k < d) {
+                    const double tt = xr[j][k] - a.mean[k];
+                    acc = acc + (tt * tt) * a.prec[k];
+                }
+            lpn[j] = a.log_norm - 0.5 * acc;
+        }
+    } else {
+        double u[2], lg[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const double tt = xr[j][0] - a.mu;
+            u[j] = 1.0 + (tt * tt) * a.inv_nu;
+        }
+        det_log_w<2, true>(u, lg);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) lpn[j] = a.log_norm - a.hnu1 * lg[j];
+    }
     u64 key = 0;
     unsigned bad = 0;
-    double zp[2] = {0.0, 0.0};
-    if (kD1)
-        normal_pair_wave(a.seed, kTagPropose, a.sampler, t, (uint32_t)tid, 0u, 2 * (i64)tid < n,
-                         zp[0], zp[1], s_xch[wid]);
-    for (int j = 0; j < kSmallI; ++j) {
-        const i64 i = kD1 ? 2 * (i64)tid + j : tid + (i64)kSmallT * j;
-        const bool act = i < n;
-        double *xi = x + i * d;
-        double acc = 0.0;
-        for (int k = 0; 2 * k < d; ++k) {
-            double z[2] = {zp[j == 0 ? 0 : 1], 0.0};
-            if (!kD1)
-                normal_pair_wave(a.seed, kTagPropose, a.sampler, t, (uint32_t)i, (uint32_t)k, act,
-                                 z[0], z[1], s_xch[wid]);
-            if (!act) continue;
-            for (int h = 0; h < 2; ++h) {
-                const int kk = 2 * k + h;
-                if (kk >= d) break;
-                const double xk = xi[kk] + a.rw_sd * z[h];
-                xi[kk] = xk;
-                if (kD1) xr[j] = xk;
-                if (kKind == SMC_TARGET_GAUSS) {
-                    const double tt = xk - a.mean[kk];
-                    acc = acc + (tt * tt) * a.prec[kk];
-                }
-            }
-        }
-        if (!act) continue;
-        double lpn;
-        if (kKind == SMC_TARGET_GAUSS) {
-            lpn = a.log_norm - 0.5 * acc;
-        } else {
-            const double tt = xi[0] - a.mu;
-            lpn = a.log_norm - a.hnu1 * det_log(1.0 + (tt * tt) * a.inv_nu);
-        }
-        const double lw = logw[i] + (lpn - lp[i]);
-        lp[i] = lpn;
-        if (kD1) lpr[j] = lpn;
-        logw[i] = lw;
-        s_e[i] = lw;
-        bad |= (lw != lw) | (lw == __builtin_huge_val());
-        const u64 kk = okey(lw);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        lw[j] = act[j] ? lw[j] + (lpn[j] - lp_old[j]) : ninf;
+        bad |= !(lw[j] < __builtin_huge_val());  // NaN or +inf
+        const u64 kk = okey(lw[j]);
         key = kk > key ? kk : key;
     }
     key = wave_max_u64(key);
@@ -843,261 +844,135 @@ __device__ __forceinline__ void small_iteration(const TArgs &a, i64 n, uint32_t 
         s_bad[wid] = bad;
     }
     __syncthreads();
-    key = s_key[0];
-    bad = s_bad[0];
-    for (int w = 1; w < 16; ++w) {
-        key = s_key[w] > key ? s_key[w] : key;
-        bad |= s_bad[w];
-    }
+    key = wave_max_u64(lane < nw ? s_key[lane & (NW - 1)] : 0ull);
+    bad = wave_or(lane < nw ? s_bad[lane & (NW - 1)] : 0u);
     const double m = okey_inv(key);
 
-    // fixed-point weights of consecutive items per thread, FP64 sums, prefix
-    const u64 top = 1ull << K;
-    double z = 0.0, z2 = 0.0;
-    U128 q2{0, 0};
-    u64 loc[kSmallI];
-    u64 run = 0;
-    for (int j = 0; j < kSmallI; ++j) {
-        const i64 i = (i64)tid * kSmallI + j;
-        u64 q = 0;
-        double e = 0.0;
-        if (i < n) {
-            e = det_exp(s_e[i] - m);  // s_e holds l_i here, e_i after this loop
-            if (e >= 0.0) {
-                z += e;
-                z2 += e * e;
-                q = (u64)floor(ldexp(e, K));
-                q = q > top ? top : q;
-                q2 = add128(q2, mul64(q, q));
-            } else {
-                e = 0.0;
-            }
-        }
-        run += q;
-        loc[j] = run;
-        if (i < n) s_e[i] = e;  // the thread's own items: no hazard
-    }
-    const u64 incl = wave_incl_scan_u64(run);
-    if (lane == 63) s_wsum[wid] = incl;
+    // fixed-point weights, their prefix, the FP64 sums, the estimate sums
+    const double v[2] = {lw[0], lw[1]};
+    double z = 0.0, z2 = 0.0, e[2];
+    SqSum sq;
+    u64 q[2];
+    quant_w<2>(v, m, K, q, z, z2, sq, e);
+    const u64 run = q[0] + q[1], incl = wave_incl_scan_u64(run);
     z = wave_sum_f64(z);
     z2 = wave_sum_f64(z2);
-    q2 = wave_sum_u128(q2);
-    __syncthreads();
-    u64 wpre = 0;
-    for (int w = 0; w < wid; ++w) wpre += s_wsum[w];
-    const u64 pre = wpre + incl - run;
-    for (int j = 0; j < kSmallI; ++j) {
-        const i64 i = (i64)tid * kSmallI + j;
-        if (i < n) s_S[i] = pre + loc[j];
+    const U128 q2 = wave_sum_u128(sq.total());
+    double c1[DM], c2[DM];
+#pragma unroll
+    for (int k = 0; k < DM; ++k) {
+        c1[k] = c2[k] = 0.0;
+        if (k >= d) continue;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const double ex = act[j] ? e[j] * xr[j][k] : 0.0;
+            c1[k] += ex;
+            c2[k] += ex * xr[j][k];
+        }
+        c1[k] = wave_sum_f64(c1[k]);
+        c2[k] = wave_sum_f64(c2[k]);
     }
+    if (lane == 63) s_wsum[wid] = incl;
     if (lane == 0) {
         s_z[wid] = z;
         s_z2[wid] = z2;
         s_lo[wid] = q2.lo;
         s_hi[wid] = q2.hi;
-    }
-    __syncthreads();
-
-    // estimate sums: a DPP sum per 16-lane row, rows in order
-    {
-        double s1[DM], s2[DM];
-        for (int k = 0; k < DM; ++k) s1[k] = s2[k] = 0.0;
-        for (int j = 0; j < kSmallI; ++j) {
-            const i64 i = kD1 ? 2 * (i64)tid + j : tid + (i64)kSmallT * j;
-            if (i >= n) continue;
-            const double e = s_e[i];
 #pragma unroll
-            for (int k = 0; k < DM; ++k) {
-                if (k < d) {
-                    const double xv = kD1 ? xr[j] : x[i * d + k];
-                    const double ex = e * xv;
-                    s1[k] += ex;
-                    s2[k] += ex * xv;
-                }
-            }
-        }
-        // a DPP sum per 16-lane row, then the wave's four rows in order
-#pragma unroll
-        for (int k = 0; k < DM; ++k) {
+        for (int k = 0; k < DM; ++k)
             if (k < d) {
-                const double a1 = srow16(s1[k]), a2 = srow16(s2[k]);
-                const double w1 = ((lane_f64(a1, 15) + lane_f64(a1, 31)) + lane_f64(a1, 47)) +
-                                  lane_f64(a1, 63);
-                const double w2 = ((lane_f64(a2, 15) + lane_f64(a2, 31)) + lane_f64(a2, 47)) +
-                                  lane_f64(a2, 63);
-                if (lane == 0) {
-                    s_col[wid][k] = w1;
-                    s_col[wid][kSmallD + k] = w2;
-                }
+                s_col[k][wid] = c1[k];
+                s_col[d + k][wid] = c2[k];
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        if (act[j]) {
+#pragma unroll
+            for (int k = 0; k < DM; ++k)
+                if (k < d) s_x[(i0 + j) * d + k] = xr[j][k];
+            s_lp[i0 + j] = lpn[j];
+        }
+    __syncthreads();
+
+    // decision, c_t and recycling, by every thread from the wavefronts' totals
+    const bool in = lane < nw;
+    const u64 wincl = wave_incl_scan_u64(in ? s_wsum[lane & (NW - 1)] : 0ull);
+    const u64 S = lane63_u64(wincl);
+    const u64 wpre = wid ? (u64)__shfl((long long)wincl, wid - 1, 64) : 0ull;
+    const double Z = wave_sum_f64(in ? s_z[lane & (NW - 1)] : 0.0);
+    const double Z2 = wave_sum_f64(in ? s_z2[lane & (NW - 1)] : 0.0);
+    const U128 Q2 =
+        wave_sum_u128(in ? U128{s_lo[lane & (NW - 1)], s_hi[lane & (NW - 1)]} : U128{0, 0});
+    const Decision dec = decide(key, bad, S, Z, Z2, Q2, n, r, mode, ess_num, ess_den);
+    if (wid == 0) {  // 2 d <= 16 estimate threads, all in the first wavefront
+        double bc[3] = {1.0, 0.0, 0.0}, logc = 0.0;
+        RecNext nx;
+        if (!dec.err) logc = recycle_step(rec, dec.logZ, bc, nx);
+        if (tid == 0) {
+            store_decision(dec, K, logc, ctrl, info);
+            ctrl->pending = 0;
+            if (!dec.err) store_recycling(nx, logc, dec.logZ, dec.resample, ctrl);
+        }
+        if (tid < 2 * d && !dec.err) {
+            double tot = 0.0;
+            for (int w = 0; w < nw; ++w) tot += s_col[tid][w];
+            const double f = tot / Z;
+            const double num = rec_old * bc[0] + bc[1] * f;
+            rec_num[tid] = num;
+            if (est) {
+                est[tid] = f;
+                est[2 * d + tid] = num / bc[2];
             }
         }
     }
-    __syncthreads();
-    if (kD1) {
-        // s_e is free now (the decision below does not read it)
-        for (int j = 0; j < kSmallI; ++j) {
-            const i64 i = 2 * (i64)tid + j;
-            if (i < n) {
-                s_e[i] = xr[j];
-                s_lpv[i] = lpr[j];
+    if (!dec.resample) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (act[j]) {
+#pragma unroll
+                for (int k = 0; k < DM; ++k)
+                    if (k < d) x[(i0 + j) * d + k] = xr[j][k];
+                lp[i0 + j] = lpn[j];
+                logw[i0 + j] = lw[j];
             }
-        }
+        return;
     }
-    if (tid < 2 * d) {
-        const int c = tid < d ? tid : kSmallD + (tid - d);
-        double acc = 0.0;
-        for (int w = 0; w < NW; ++w) acc += s_col[w][c];
-        s_tot[tid] = acc;
+
+    // redistribution: source j's copies start at output A_{j-1}
+    AFun f;
+    f.n = n;
+    f.set_systematic(S, dec.U);
+    const u64 pre = wpre + incl - run;
+    unsigned a0 = i0 > 0 ? f.A_of(0, pre) : 0u;
+    u64 sj = pre;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (!act[j]) break;
+        sj += q[j];
+        const unsigned a1 = f.A_of(0, sj);
+        if (a1 > a0) s_mark[a0] = (unsigned)(i0 + j + 1);
+        a0 = a1;
     }
     __syncthreads();
-
-    // decision, offset, log Z, ESS, c_t and recycling (one thread)
-    if (tid == 0) {
-        double Z = s_z[0], Z2 = s_z2[0];
-        U128 Q2{s_lo[0], s_hi[0]};
-        for (int w = 1; w < 16; ++w) {
-            Z += s_z[w];
-            Z2 += s_z2[w];
-            Q2 = add128(Q2, U128{s_lo[w], s_hi[w]});
-        }
-        const u64 S = s_S[n - 1];
-        unsigned err = 0;
-        if (bad) err = kErrNonfinite;
-        else if (key <= okey(-__builtin_huge_val())) err = kErrDegenerate;
-        int resample;
-        if (mode == SMC_MODE_FORCE) {
-            resample = 1;
-        } else if (mode == SMC_MODE_NEVER) {
-            resample = 0;
-        } else {
-            const U128 lhs = mul128_small(mul64(S, S), (u64)ess_den);
-            const U128 rhs = mul128_small(mul128_small(Q2, (u64)n), (u64)ess_num);
-            resample = lt128(lhs, rhs) ? 1 : 0;
-        }
-        if (err) resample = 0;
-        const u64 U = mul64(r, S).hi;
-        const double logZ = m + log(Z);
-        const double ess = (Z * Z) / Z2;
-        ctrl->mkey = key;
-        ctrl->m = m;
-        ctrl->err_call = err;
-        if (err && !ctrl->err_latch) ctrl->err_latch = err;
-        ctrl->S = S;
-        ctrl->U = U;
-        ctrl->Q2lo = Q2.lo;
-        ctrl->Q2hi = Q2.hi;
-        ctrl->Z = Z;
-        ctrl->Z2 = Z2;
-        ctrl->logZ = logZ;
-        ctrl->ess = ess;
-        ctrl->K = K;
-        ctrl->resample = (unsigned)resample;
-        ctrl->pending = 0;
-        // c_t and the recycling sums; an iteration that found an error leaves
-        // them (and the estimates) unchanged
-        double logc = 0.0, sc = 1.0, wgt = 0.0, den = ctrl->rec_den;
-        if (!err) {
-            logc = logZ - ctrl->logZ_prev;
-            if (logc > ctrl->lc_max) {
-                sc = ctrl->rec_steps ? exp(ctrl->lc_max - logc) : 0.0;
-                den *= sc;
-                ctrl->lc_max = logc;
-            }
-            wgt = exp(logc - ctrl->lc_max);
-            den += wgt;
-            ctrl->rec_den = den;
-            ctrl->rec_steps += 1;
-            ctrl->log_c = logc;
-            ctrl->logZ_prev = resample ? 0.0 : logZ;
-        }
-        if (info) {
-            info->m = m;
-            info->logZ = logZ;
-            info->ess = ess;
-            info->Z = Z;
-            info->Z2 = Z2;
-            info->S = S;
-            info->U = U;
-            info->Q2_hi = Q2.hi;
-            info->Q2_lo = Q2.lo;
-            info->K = K;
-            info->resampled = resample;
-            info->err = (int)err;
-            info->pad = 0;
-            info->log_c = logc;
-        }
-        s_bc[0] = sc;
-        s_bc[1] = wgt;
-        s_bc[2] = den;
-        s_bc[3] = Z;
-        s_bu[0] = S;
-        s_bu[1] = U;
-        s_bu[2] = (u64)resample;
-        s_bu[3] = (u64)err;
-    }
+    unsigned mk[2] = {s_mark[i0], s_mark[i0 + 1]};
+    mk[1] = mk[1] > mk[0] ? mk[1] : mk[0];
+    const unsigned minc = wave_scan_max_u32(mk[1]);
+    if (lane == 63) s_wmax[wid] = minc;
+    unsigned carry = (unsigned)__shfl_up((int)minc, 1, 64);
+    carry = lane ? carry : 0u;
     __syncthreads();
-    if (tid < 2 * d && !s_bu[3]) {
-        const double f = s_tot[tid] / s_bc[3];
-        const double num = rec_num[tid] * s_bc[0] + s_bc[1] * f;
-        rec_num[tid] = num;
-        if (est) {
-            est[tid] = f;
-            est[2 * d + tid] = num / s_bc[2];
-        }
+    for (int w = 0; w < wid; ++w) carry = s_wmax[w] > carry ? s_wmax[w] : carry;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (!act[j]) continue;
+        const int src = (int)(mk[j] > carry ? mk[j] : carry) - 1;
+#pragma unroll
+        for (int k = 0; k < DM; ++k)
+            if (k < d) x[(i0 + j) * d + k] = s_x[src * d + k];
+        lp[i0 + j] = s_lp[src];
+        logw[i0 + j] = reset;
     }
-    if (!s_bu[2]) return;
-
-    // redistribution: output p takes row anc(p), the first j with
-    // N S_j + U >= (p + 1) S; staged in the scratch rows, then back in place
-    // (kD1: gathered from LDS straight into place)
-    const u64 S = s_bu[0], U = s_bu[1];
-    for (int j = 0; j < kSmallI; ++j) {
-        const i64 p = tid + (i64)kSmallT * j;
-        if (p >= n) continue;
-        const U128 rhs = mul64((u64)(p + 1), S);
-        i64 lo = 0, hi = n - 1;
-        while (lo < hi) {
-            const i64 mid = (lo + hi) >> 1;
-            if (lt128(add128(mul64((u64)n, s_S[mid]), U), rhs)) lo = mid + 1;
-            else hi = mid;
-        }
-        if (kD1) {
-            x[p] = s_e[lo];
-            lp[p] = s_lpv[lo];
-            logw[p] = reset;
-        } else {
-            for (int k = 0; k < d; ++k) x_scr[p * d + k] = x[lo * d + k];
-            lp_scr[p] = lp[lo];
-        }
-    }
-    if (kD1) return;
-    __syncthreads();
-    for (int j = 0; j < kSmallI; ++j) {
-        const i64 p = tid + (i64)kSmallT * j;
-        if (p >= n) continue;
-        for (int k = 0; k < d; ++k) x[p * d + k] = x_scr[p * d + k];
-        lp[p] = lp_scr[p];
-        logw[p] = reset;
-    }
-}
-
-// One iteration in one launch.  slots: the other parity's max slots are
-// cleared for the call that follows.
-template <int kKind, bool kD1>
-__global__ __launch_bounds__(1024) void k_small_step(TArgs a, i64 n, uint32_t t, int K, int mode,
-                                                     int ess_num, int ess_den,
-                                                     double *__restrict__ x,
-                                                     double *__restrict__ logw,
-                                                     double *__restrict__ lp,
-                                                     double *__restrict__ x_scr,
-                                                     double *__restrict__ lp_scr, Ctrl *ctrl,
-                                                     u64 *slots_other, double *rec_num,
-                                                     smc_resample_info *info, double *est,
-                                                     double reset)
-{
-    for (int k = threadIdx.x; k < kSlots * kSlotStride; k += kSmallT) slots_other[k] = 0;
-    small_iteration<kKind, kD1>(a, n, t, K, mode, ess_num, ess_den, x, logw, lp, x_scr, lp_scr,
-                                ctrl, rec_num, info, est, reset);
 }
 
 // ------------------------------------------------------ cheap log-targets
@@ -1655,10 +1530,17 @@ smc_status step_init(const smc_config &c, const Work &w, int par, double *x, dou
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
+// The one-workgroup iteration where it is the faster one.  Against the separate
+// kernels' 22.5 to 23.5 us (18.5 with one coordinate) at these sizes it takes
+// 6.1 us at N = 256, 7.2 at 1024 and 10.4 at 2048 with one coordinate, 14.8 at
+// N = 2048 with two, 19.2 at 1536 with four, 20.4 at 1024 with six, 20.6 at 512 and
+// 25.0 at 640 with eight; the draws of one compute unit set the line.
 bool small_path(const smc_config &c)
 {
-    return c.n <= kSmallN && c.d <= kSmallD &&
-           (c.target == SMC_TARGET_GAUSS || c.target == SMC_TARGET_STUDENT);
+    if (c.n > kSmallN) return false;
+    if (c.target == SMC_TARGET_STUDENT) return true;
+    if (c.target != SMC_TARGET_GAUSS || c.d > kSmallD) return false;
+    return c.d == 1 || c.n * ((c.d + 1) / 2) <= (c.d <= 6 ? kSmallPairs : 2048);
 }
 
 // Small population: the whole iteration in one workgroup and one launch.
@@ -1670,13 +1552,14 @@ smc_status small_step(const smc_config &c, const Work &w, int K, int par, uint32
     const double reset = -std::log((double)n);
     u64 *other = w.slots + ((par & 1) ^ 1) * kSlots * kSlotStride;
     auto kern = c.target == SMC_TARGET_GAUSS
-                    ? (c.d == 1 ? k_small_step<SMC_TARGET_GAUSS, true>
-                                : k_small_step<SMC_TARGET_GAUSS, false>)
-                    : (c.d == 1 ? k_small_step<SMC_TARGET_STUDENT, true>
-                                : k_small_step<SMC_TARGET_STUDENT, false>);
-    hipLaunchKernelGGL(kern, dim3(1), dim3(kSmallT), 0, s, a, (i64)n, t, K, c.mode, c.ess_num,
-                       c.ess_den, x, logw, w.lp, w.x_scr, w.lp_scr, w.ctrl, other, w.rec_num, info,
-                       est, reset);
+                    ? (c.d == 1   ? k_small_step<SMC_TARGET_GAUSS, 1, kSmallN>
+                       : c.d <= 4 ? k_small_step<SMC_TARGET_GAUSS, 4, kSmallN>
+                                  : k_small_step<SMC_TARGET_GAUSS, 8, 1024>)
+                    : k_small_step<SMC_TARGET_STUDENT, 1, kSmallN>;
+    static_assert(kSmallPairs / 3 <= 1024, "rows of five and more coordinates");
+    hipLaunchKernelGGL(kern, dim3(1), dim3((unsigned)((n + 127) / 128 * 64)), 0, s, a, (i64)n, t,
+                       K, c.mode, c.ess_num, c.ess_den, x, logw, w.lp, w.ctrl, other, w.rec_num,
+                       info, est, reset);
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
@@ -1731,7 +1614,8 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     o.mode = fwd ? ExpandMode::kForward : ExpandMode::kIfResampled;
     o.logw = logw;
     o.reset = -std::log((double)n);
-    o.uniform = c.lazy_reset ? &w.ctrl->uniform : nullptr;
+    // populations of at most kSmallN particles always write their weights
+    o.uniform = c.lazy_reset && n > kSmallN ? &w.ctrl->uniform : nullptr;
     // the particle filter and the 1-D Gaussian and Student-t samplers carry no
     // cached log-target
     if (!pf && !(c.d == 1 && (c.target == SMC_TARGET_GAUSS || c.target == SMC_TARGET_STUDENT))) {

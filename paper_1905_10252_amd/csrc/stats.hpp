@@ -104,11 +104,15 @@ struct RecState {
     }
 };
 
-// c_t (eq. normconst) and the recycling weights (eq. recycling), by one
-// thread of an iteration without error; returns log c_t and leaves
-// bc = (scale of the old sums, weight of this iteration, their denominator).
-__device__ inline double recycle(Ctrl *ctrl, const RecState &r, double logZ, bool resampled,
-                                 double *bc)
+// c_t (eq. normconst) and the recycling weights (eq. recycling) of an iteration
+// without error; returns log c_t, leaves bc = (scale of the old sums, weight of
+// this iteration, their denominator) and the state to store.
+struct RecNext {
+    double lc_max, rec_den;
+    int rec_steps;
+};
+
+__device__ inline double recycle_step(const RecState &r, double logZ, double *bc, RecNext &nx)
 {
     const double logc = logZ - r.logZ_prev;
     double sc = 1.0, den = r.rec_den, lc_max = r.lc_max;
@@ -116,17 +120,35 @@ __device__ inline double recycle(Ctrl *ctrl, const RecState &r, double logZ, boo
         sc = r.rec_steps ? exp(lc_max - logc) : 0.0;
         den *= sc;
         lc_max = logc;
-        ctrl->lc_max = lc_max;
     }
     const double wgt = exp(logc - lc_max);
     den += wgt;
-    ctrl->rec_den = den;
-    ctrl->rec_steps = r.rec_steps + 1;
-    ctrl->log_c = logc;
-    ctrl->logZ_prev = resampled ? 0.0 : logZ;
+    nx.lc_max = lc_max;
+    nx.rec_den = den;
+    nx.rec_steps = r.rec_steps + 1;
     bc[0] = sc;
     bc[1] = wgt;
     bc[2] = den;
+    return logc;
+}
+
+__device__ inline void store_recycling(const RecNext &nx, double logc, double logZ, bool resampled,
+                                       Ctrl *ctrl)
+{
+    ctrl->lc_max = nx.lc_max;
+    ctrl->rec_den = nx.rec_den;
+    ctrl->rec_steps = nx.rec_steps;
+    ctrl->log_c = logc;
+    ctrl->logZ_prev = resampled ? 0.0 : logZ;
+}
+
+// Both by one thread.
+__device__ inline double recycle(Ctrl *ctrl, const RecState &r, double logZ, bool resampled,
+                                 double *bc)
+{
+    RecNext nx;
+    const double logc = recycle_step(r, logZ, bc, nx);
+    store_recycling(nx, logc, logZ, resampled, ctrl);
     return logc;
 }
 
