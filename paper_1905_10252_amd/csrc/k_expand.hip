@@ -12,8 +12,8 @@
 // A_j is computed from the fixed-point prefix as floor((N S_j + U) / S), or is
 // the prefix of caller-supplied counts, or j + 1 when the ESS rule decided not
 // to resample.  A prefix value is the scan's tile-local value plus the offset
-// of its tile of 4096.  The segment boundaries are found by a 64-ary search
-// run by one wavefront; the test A_j + j < k is evaluated as
+// of its tile.  The segment boundaries are found by a 64-ary search run by one
+// wavefront; the test A_j + j < k is evaluated in FP64 and, next to equality, as
 // N S_j + U < (k - j) S in 128-bit integers (no division).  Inside a segment
 // the outputs find their sources without a search: each source with copies
 // marks its first output, and a max-scan over the outputs carries the marks.
@@ -24,62 +24,9 @@
 #include "common.hpp"
 #include "det.hpp"
 #include "kernels.hpp"
+#include "segment.hpp"
 
 namespace smc {
-
-// First index in [lo, hi) where a predicate that is true on a prefix turns
-// false (hi if none), by rounds of 64 probes, one per lane.
-template <class P>
-__device__ inline i64 wave_first_false(const P &pred, i64 lo, i64 hi)
-{
-    const int lane = threadIdx.x & 63;
-    while (hi > lo) {
-        const i64 len = hi - lo;
-        const i64 stride = (len + 63) / 64;
-        const i64 pos = lo + (i64)lane * stride;
-        const bool t = pos < hi ? pred(pos) : false;
-        const int c = __popcll(__ballot(t));
-        if (c == 0) {
-            hi = lo;
-            break;
-        }
-        const i64 nlo = lo + (i64)(c - 1) * stride + 1;
-        i64 nhi = lo + (i64)c * stride;
-        if (nhi > hi) nhi = hi;
-        lo = nlo;
-        hi = nhi;
-    }
-    return lo;
-}
-
-// j(k) = #{j : A_j + j < k}, the number of sources consumed after k merge
-// steps, known to lie in [lo, hi].  The test is monotone in j, so it is first
-// searched on the sampled prefix values S_{64g+63} (a small array that stays
-// in cache), then among the 64 consecutive sources of one group.
-__device__ inline i64 wave_search(const AFun &f, const u64 *pref64, i64 k, i64 lo, i64 hi)
-{
-    if (f.mode == 0) {
-        auto p = [&](i64 j) { return f.pred(j, k); };
-        return wave_first_false(p, lo, hi);
-    }
-    const i64 G = f.n >> 6;  // full groups, each with a sample
-    const i64 glo = lo >> 6;
-    i64 ghi = (hi >> 6) + 1;
-    ghi = ghi < G ? ghi : G;
-    i64 g = glo;
-    if (ghi > glo) {
-        auto ps = [&](i64 gg) {
-            return f.pred_at(gg * 64 + 63, pref64[gg] + f.tpre[gg >> (f.tsh - 6)], k);
-        };
-        g = wave_first_false(ps, glo, ghi);
-    }
-    i64 lo2 = g * 64 > lo ? g * 64 : lo;
-    lo2 = lo2 < hi ? lo2 : hi;
-    i64 hi2 = g * 64 + 64 < hi ? g * 64 + 64 : hi;
-    hi2 = hi2 > lo2 ? hi2 : lo2;
-    auto p = [&](i64 j) { return f.pred(j, k); };
-    return wave_first_false(p, lo2, hi2);
-}
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
@@ -333,11 +280,9 @@ struct ExpandArgs {
 template <int VEC, int SEG, bool kSum, bool kRagged>
 __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
 {
-    __shared__ unsigned sA[SEG + 1];
-    __shared__ __attribute__((aligned(16))) unsigned sAnc[SEG];
-    __shared__ i64 s_j[2];
-    __shared__ unsigned s_wmax[kExpandThreads / 64];
-    const int tid = threadIdx.x, wid = tid >> 6;
+    __shared__ SegLds<SEG> s_seg;
+    unsigned *const sAnc = s_seg.anc;
+    const int tid = threadIdx.x;
     AFun f;
     bool failed = false;
     if (!make_afun(a.ctrl, a.pref, a.tpre, a.tsh, a.n, a.count_mode, f,
@@ -350,20 +295,9 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     }
     if (a.mode == ExpandMode::kIfResampled && f.mode == 0) return;
 
-    const i64 n = a.n;
-    const i64 k0 = (i64)blockIdx.x * SEG;
-    const i64 k1 = (k0 + SEG < 2 * n) ? k0 + SEG : 2 * n;
-    if (wid < 2) {
-        const i64 k = wid == 0 ? k0 : k1;
-        const i64 lo = k - n > 0 ? k - n : 0;
-        const i64 hi = k < n ? k : n;
-        const i64 j = wave_search(f, a.pref64, k, lo, hi);
-        if ((tid & 63) == 0) s_j[wid] = j;
-    }
-    __syncthreads();
-    const i64 j0 = s_j[0], j1 = s_j[1];
-    const i64 p0 = k0 - j0;
-    const int ns = (int)(j1 - j0), np = (int)((k1 - j1) - p0);
+    const Segment g = segment_cut<SEG>(f, a.pref64, s_seg);
+    const i64 p0 = g.p0;
+    const int ns = g.ns, np = g.np;
 
     // Alg 4 reset of the outputs this segment owns (a pass of its own took 21 us
     // and a launch at N = 2^24)
@@ -375,76 +309,12 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
         }
     }
 
-    // From here on in 32 bits: sources, outputs and A are below 2^31.
-    const unsigned p0u = (unsigned)p0, j0u = (unsigned)j0;
-    if (f.mode == 0) {
-        for (int i = tid; i <= ns; i += kExpandThreads) sA[i] = j0u + (unsigned)i;
-    } else {
-        // sA[i] is A of source j0 - 1 + i; these sources (at most SEG + 1)
-        // lie in at most two tiles (the segment length sees to it), whose offsets
-        // are read once
-        const int skip = j0 == 0 ? 1 : 0;  // A before the first source is 0
-        const i64 jb = j0 - 1 + skip;
-        const i64 ta = jb >> f.tsh;
-        const i64 ntl = (n + (1ll << f.tsh) - 1) >> f.tsh;
-        const u64 off_a = f.tpre[ta];
-        const u64 off_b = ta + 1 < ntl ? f.tpre[ta + 1] : 0ull;
-        const int ib = (int)(((ta + 1) << f.tsh) - jb);  // first source of the second tile
-        const u64 *pj = a.pref + jb;
-        if (skip && tid == 0) sA[0] = 0u;
-        for (int i = tid; i <= ns - skip; i += kExpandThreads)
-            sA[i + skip] = f.A_of(0, pj[i] + (i < ib ? off_a : off_b));
-    }
-    for (int r = tid; r < np; r += kExpandThreads) sAnc[r] = 0u;
-    __syncthreads();
+    segment_map<SEG>(f, g, s_seg);
     if (a.nc_out)
         for (int i = tid; i < ns; i += kExpandThreads)
-            a.nc_out[j0 + i] = (i64)sA[i + 1] - (i64)sA[i];
-    // Output p comes from local source t, the first with sA[1 + t] > p, so
-    // sA[t] <= p < sA[1 + t] (sA[0] <= p0 by the merge-path cut).  Each source
-    // with copies marks the first of its outputs inside the segment with
-    // t + 1; an inclusive max-scan over the outputs carries every mark over
-    // the rest of its source's outputs.  Local source ns (source j1) owns
-    // whatever follows sA[ns].  Marks land on distinct outputs (sources with
-    // copies start at distinct outputs) and output p0 always holds one.
-    for (int t = tid; t <= ns; t += kExpandThreads) {
-        const unsigned lo = sA[t], hi = t < ns ? sA[t + 1] : 0xFFFFFFFFu;
-        if (hi > lo && hi > p0u) {
-            const unsigned st = lo > p0u ? lo - p0u : 0u;
-            if (st < (unsigned)np) sAnc[st] = (unsigned)(t + 1);
-        }
-    }
-    __syncthreads();
-    {
-        constexpr int E = SEG / kExpandThreads;  // outputs per thread, contiguous
-        static_assert(E >= 1 && E * kExpandThreads == SEG, "whole outputs a thread");
-        const int lane = tid & 63;
-        // entries past np are stale; they reach only positions past np
-        unsigned v[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = sAnc[tid * E + e];
-#pragma unroll
-        for (int e = 1; e < E; ++e) v[e] = v[e] > v[e - 1] ? v[e] : v[e - 1];
-        const unsigned incl = wave_scan_max_u32(v[E - 1]);
-        if (lane == 63) s_wmax[wid] = incl;
-        unsigned carry = (unsigned)__shfl_up((int)incl, 1, 64);
-        carry = lane ? carry : 0u;
-        __syncthreads();
-        for (int w = 0; w < wid; ++w) carry = s_wmax[w] > carry ? s_wmax[w] : carry;
-        const unsigned last = (unsigned)n - 1u;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            unsigned anc = j0u + (v[e] > carry ? v[e] : carry) - 1u;
-            anc = anc < last ? anc : last;  // entries past np: any valid source
-            sAnc[tid * E + e] = anc;
-        }
-        if (a.anc_out) {
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                if (tid * E + e < np) a.anc_out[p0 + tid * E + e] = (i64)sAnc[tid * E + e];
-        }
-    }
-    __syncthreads();
+            a.nc_out[g.j0 + i] = (i64)s_seg.A[i + 1] - (i64)s_seg.A[i];
+    if (a.anc_out)
+        for (int r = tid; r < np; r += kExpandThreads) a.anc_out[p0 + r] = (i64)sAnc[r];
     const bool distinct = np < 2 * ns;  // fewer than two outputs per source in this segment
     if constexpr (kSum) {
         RowAcc<VEC> acc;

@@ -170,10 +170,11 @@ struct ScanArgs {
     const u64 *slots_p; // max slots of this call's parity (quantise mode)
     unsigned *uniform;  // lazy-reset flag to clear (nullable)
     int n_tiles;
+    StatsArgs tail;     // kTail: the filter iteration before
 };
 
 // Four waves per SIMD: the LDS of a 4096-element tile allows no more.
-template <bool kQuant, int kItems>
+template <bool kQuant, int kItems, bool kTail = false>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
     ScanArgs a)
 {
@@ -187,7 +188,15 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
 
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const i64 n = a.n;
-    const unsigned tile = blockIdx.x;
+    if constexpr (kTail) {  // the first workgroup, so that it ends with the others
+        if (blockIdx.x == 0) {
+            filter_stats<kScanThreads>(a.ctrl, a.tail.is_part, a.tail.nblk, a.tail.d,
+                                       a.tail.rec_num, a.tail.est,
+                                       reinterpret_cast<smc_resample_info *>(a.tail.info));
+            return;
+        }
+    }
+    const unsigned tile = blockIdx.x - (kTail ? 1u : 0u);
     const i64 base = (i64)tile * kTile;
     const bool full = base + kTile <= n;
 
@@ -642,7 +651,7 @@ hipError_t launch_small_resample(const Work &w, const double *lw, int64_t n, int
 }
 
 hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, int par,
-                             hipStream_t s, bool clear_uniform)
+                             hipStream_t s, bool clear_uniform, const StatsArgs &tail)
 {
     ScanArgs a;
     a.uniform = clear_uniform ? &w.ctrl->uniform : nullptr;
@@ -658,8 +667,11 @@ hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, 
     a.out64 = w.pref64;
     a.slots_p = w.slots + (par & 1) * kSlots * kSlotStride;
     a.n_tiles = w.n_tiles;
-    auto kern = w.tile_shift == kTileShift ? k_scan<true, 16> : k_scan<true, 4>;
-    hipLaunchKernelGGL(kern, dim3(w.n_tiles), dim3(kScanThreads), 0, s, a);
+    a.tail = tail;
+    const bool big = w.tile_shift == kTileShift, stats = tail.is_part != nullptr;
+    auto kern = stats ? (big ? k_scan<true, 16, true> : k_scan<true, 4, true>)
+                      : (big ? k_scan<true, 16> : k_scan<true, 4>);
+    hipLaunchKernelGGL(kern, dim3(w.n_tiles + stats), dim3(kScanThreads), 0, s, a);
     return hipGetLastError();
 }
 

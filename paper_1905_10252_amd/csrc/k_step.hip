@@ -10,11 +10,15 @@
 //                       proposal (k_propose) and likelihood kernels.
 //   k_step_stats        estimates f_t (eq. estimation_at_t), c_t
 //                       (eq. normconst) and the recycled estimate
-//                       (eq. recycling).
+//                       (eq. recycling) of a filter iteration (the other
+//                       targets': k_decide).
 //   k_is<BEARING>       one SIR particle-filter update (Alg 1, Sec. 5.2.2):
 //                       constant-velocity transition as proposal, bearing
 //                       likelihood as weight; the expand then adds up the rows
 //                       it writes for the mean of the resampled population.
+//   k_filter_step       inside a call of several iterations: that expand and the
+//                       next update in one pass.
+//   k_small_step        a whole iteration of a small population.
 //   k_logreg_f64 / k_logreg_bf16 + k_logreg_sum
 //                       Bayesian logistic regression log-likelihood
 //                       sum_m [y_m z_m - softplus(z_m)], z = X theta, in FP64 or
@@ -31,6 +35,7 @@
 #include "kernels.hpp"
 #include "reduce.hpp"
 #include "rng_wave.hpp"
+#include "segment.hpp"
 #include "stats.hpp"
 #include "step.hpp"
 
@@ -173,6 +178,26 @@ typedef double f64x2s __attribute__((ext_vector_type(2)));
 // into a copy and back instead took another pass over the rows each way).
 // kInPlace: to x alone.
 enum Dst { kInPlace, kToCopy, kToBoth };
+
+// The particle filter's transition of one state and its weight.
+__device__ inline double bearing_move(const TArgs &a, uint32_t t, const double (&s)[4],
+                                      const double (&z)[4], double lw, double *xw)
+{
+    const double v0 = a.l11 * z[0];
+    const double v1 = a.l21 * z[0] + a.l22 * z[1];
+    const double v2 = a.l11 * z[2];
+    const double v3 = a.l21 * z[2] + a.l22 * z[3];
+    const double n0 = (s[0] + a.delta * s[1]) + v0;
+    const double n1 = s[1] + v1;
+    const double n2 = (s[2] + a.delta * s[3]) + v2;
+    const double n3 = s[3] + v3;
+    xw[0] = n0;
+    xw[1] = n1;
+    xw[2] = n2;
+    xw[3] = n3;
+    const double e = a.obs[t - 1] - det_atan(n2 / n0);
+    return lw + (a.obs_log_norm - 0.5 * ((e * e) * a.obs_prec));
+}
 
 template <int kKind, bool kInit, Dst kDst>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_is(
@@ -350,20 +375,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 lw = a.reset;
                 lp[i] = 0.0;
             } else {
-                const double v0 = a.l11 * z[0];
-                const double v1 = a.l21 * z[0] + a.l22 * z[1];
-                const double v2 = a.l11 * z[2];
-                const double v3 = a.l21 * z[2] + a.l22 * z[3];
-                const double n0 = (s0 + a.delta * s1) + v0;
-                const double n1 = s1 + v1;
-                const double n2 = (s2 + a.delta * s3) + v2;
-                const double n3 = s3 + v3;
-                xw[0] = n0;
-                xw[1] = n1;
-                xw[2] = n2;
-                xw[3] = n3;
-                const double e = a.obs[t - 1] - det_atan(n2 / n0);
-                lw = (uni ? a.reset : lw0) + (a.obs_log_norm - 0.5 * ((e * e) * a.obs_prec));
+                const double st[4] = {s0, s1, s2, s3};
+                lw = bearing_move(a, t, st, z, uni ? a.reset : lw0, xw);
             }
             logw[i] = lw;
             note(lw);
@@ -373,6 +386,124 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const u64 bk = block_max_key(key, bad);
     if (!kFilter) on.finish(is_part);
     slot_publish(slots_p, bk, bad);
+}
+
+// Between two iterations of the particle filter in one call: the redistribution
+// of the one and the update of the next (step t) in one pass over the rows.  Each
+// workgroup takes a segment of the merge path; a particle is read from its
+// source's row, counted in the mean of the resampled population, moved, weighted
+// and written once.  The population in between is never stored: 64 bytes a
+// particle less, and a launch (35.0 us at N = 2^20; redistribution 21.6 us and
+// update 25.7 us as kernels of their own).  Bound by vector issue, the normals
+// foremost.  An iteration that kept its weights or found an error moves each
+// particle from its own row, as the separate kernels do.
+struct FilterArgs {
+    i64 n;
+    uint32_t t;
+    const u64 *pref, *pref64, *tpre;
+    const Ctrl *ctrl;
+    int tsh;
+    const double *x;  // the proposals of the iteration before
+    double *xo;       // these
+    double *logw;
+    u64 *slots_p;
+    double *est_part;  // [kEstCols][segments]
+};
+
+template <int SEG>
+__global__ __launch_bounds__(kExpandThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+k_filter_step(TArgs a, FilterArgs g)
+{
+    constexpr int NW = kExpandThreads / 64;
+    union Lds {
+        struct {
+            SegLds<SEG> seg;
+            uint4 xch[NW][64];
+        } m;
+        double red[8][kExpandThreads];
+    };
+    __shared__ Lds L;
+    __shared__ double s_e[NW];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    AFun f;
+    bool failed = false;
+    if (!make_afun(g.ctrl, g.pref, g.tpre, g.tsh, g.n, 0, f, false)) {
+        failed = true;
+        f.mode = 0;
+    }
+    const Segment sg = segment_cut<SEG>(f, g.pref64, L.m.seg);
+    segment_map<SEG>(f, sg, L.m.seg);
+    const int np = sg.np;
+    const bool kept = f.mode == 0;  // the weights of the iteration before still stand
+    const double m = kept && !failed ? g.ctrl->m : a.reset;
+    double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0}, se = 0.0;
+    double mx = -__builtin_huge_val();
+    u64 key = 0;
+    unsigned bad = 0;
+    // wave-uniform trip count; the wavefronts of neighbouring segments start
+    // apart, so that the SIMDs share the remainders
+    for (int r0 = ((wid + (int)blockIdx.x) & (NW - 1)) * 64; r0 < np; r0 += kExpandThreads) {
+        const int r = r0 + lane;
+        const bool act = r < np;
+        const i64 i = sg.p0 + r;
+        const double *xs = g.x + (i64)L.m.seg.anc[act ? r : 0] * 4;
+        const double st[4] = {xs[0], xs[1], xs[2], xs[3]};
+        double lw = kept && act ? g.logw[i] : a.reset;
+        asm volatile("" ::: "memory");
+        const uint32_t idx[2] = {(uint32_t)i, (uint32_t)i}, pair[2] = {0u, 1u};
+        const bool act2[2] = {act, act};
+        double z[4];
+        normal_pairs_wave<2>(a.seed, kTagPropose, a.sampler, g.t, idx, pair, 2, act2, z,
+                             L.m.xch[wid]);
+        if (!act) continue;
+        const double w = kept && !failed ? det_exp(lw - m) : 1.0;
+        se += w;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double wx = w * st[k];
+            s1[k] += wx;
+            s2[k] += wx * st[k];
+        }
+        double nx[4];
+        lw = bearing_move(a, g.t, st, z, lw, nx);
+        double *xw = g.xo + i * 4;
+        xw[0] = nx[0];
+        xw[1] = nx[1];
+        xw[2] = nx[2];
+        xw[3] = nx[3];
+        g.logw[i] = lw;
+        mx = fmax(mx, lw);
+        if (!(lw < __builtin_huge_val())) {  // NaN or +inf
+            bad = 1u;
+            const u64 kk = okey(lw);
+            key = kk > key ? kk : key;
+        }
+    }
+    key = okey(mx) > key ? okey(mx) : key;
+    se = wave_sum_f64(se);
+    __syncthreads();  // the map is done with
+    if (lane == 0) s_e[wid] = se;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        L.red[k][tid] = s1[k];
+        L.red[4 + k][tid] = s2[k];
+    }
+    const u64 bk = block_max_key(key, bad);
+    __syncthreads();
+    {
+        const int c = tid >> 5, l = tid & 31;  // 32 threads a column
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k < kExpandThreads / 32; ++k) v += L.red[c][32 * k + l];
+        for (int o = 16; o; o >>= 1) v += __shfl_xor(v, o, 64);
+        double *out = g.est_part + blockIdx.x;
+        if (l == 0) out[(i64)(2 + c) * gridDim.x] = v;
+        if (tid == 0) {
+            out[0] = failed ? -__builtin_huge_val() : m;
+            out[gridDim.x] = (s_e[0] + s_e[1]) + (s_e[2] + s_e[3]);
+        }
+    }
+    slot_publish(g.slots_p, bk, bad);
 }
 
 // ------------------------------------------------ rows of several coordinates
@@ -629,40 +760,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 // -------------------------------------------- estimates, c_t and recycling
-// One workgroup: the statistics of the initialisation (init: log sum w_0,
-// cleared recycling sums) or of a filter iteration.
+// One workgroup: the statistics of a filter iteration ...
 __global__ __launch_bounds__(1024) void k_step_stats(Ctrl *ctrl, const double *is_part, int nblk,
                                                      int d, double *rec_num, double *est,
-                                                     smc_resample_info *info, int init)
+                                                     smc_resample_info *info)
+{
+    filter_stats<1024>(ctrl, is_part, nblk, d, rec_num, est, info);
+}
+
+// ... and of an initialisation: log sum w_0, cleared recycling sums.
+__global__ __launch_bounds__(1024) void k_init_stats(Ctrl *ctrl, const double *is_part, int nblk,
+                                                     int d, double *rec_num)
 {
     __shared__ StatsLds s_st;
     const int tid = threadIdx.x;
-    const RecState rec(ctrl);
-    const unsigned err = init ? 0u : ctrl->err_call, resampled = ctrl->resample;
-    const double logZ = ctrl->logZ;
-    const double rec_old = !init && tid < 2 * d ? rec_num[tid] : 0.0;
     StepStats<1024> ss;
     ss.begin(s_st, is_part, nblk);
     __syncthreads();
     const double m = ss.scale(s_st, nblk);
-    if (tid == 0 && !init && !err) {
-        const double logc = recycle(ctrl, rec, logZ, resampled != 0, s_st.bc);
-        if (info) info->log_c = logc;
-    }
     __syncthreads();
-    ss.columns(s_st, is_part, nblk, 2 + 2 * d);
+    ss.columns(s_st, is_part, nblk, 2);
     __syncthreads();
-    if (init) {
-        if (tid == 0) {
-            ctrl->logZ_prev = m + log(s_st.col[1]);
-            ctrl->lc_max = -__builtin_huge_val();
-            ctrl->rec_den = 0.0;
-            ctrl->rec_steps = 0;
-        }
-        if (tid < 2 * d) rec_num[tid] = 0.0;
-        return;
+    if (tid == 0) {
+        ctrl->logZ_prev = m + log(s_st.col[1]);
+        ctrl->lc_max = -__builtin_huge_val();
+        ctrl->rec_den = 0.0;
+        ctrl->rec_steps = 0;
     }
-    if (tid < 2 * d && !err) write_estimates(s_st, tid, d, rec_old, rec_num, est);
+    if (tid < 2 * d) rec_num[tid] = 0.0;
 }
 
 // The filter's row sums of more than kIsBlocks expand workgroups, gathered
@@ -1525,8 +1650,8 @@ smc_status step_init(const smc_config &c, const Work &w, int par, double *x, dou
     if (c.target == SMC_TARGET_BEARING)  // equal initial weights: sums from the common reference
         hipLaunchKernelGGL(k_post_est<4>, dim3(w.is_grid), dim3(256), 0, s, w.ctrl, (i64)c.n,
                            c.d, x, logw, -std::log((double)c.n), w.is_part);
-    hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part, w.is_grid,
-                       c.d, w.rec_num, (double *)nullptr, (smc_resample_info *)nullptr, 1);
+    hipLaunchKernelGGL(k_init_stats, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part, w.is_grid,
+                       c.d, w.rec_num);
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
@@ -1563,10 +1688,114 @@ smc_status small_step(const smc_config &c, const Work &w, int K, int par, uint32
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
+// The filter's row sums of an iteration (nseg rows), in at most kIsBlocks rows.
+static StatsArgs filter_sums(const smc_config &c, const Work &w, int64_t nseg, double *est,
+                             smc_resample_info *info, hipStream_t s)
+{
+    const bool fold = nseg > kIsBlocks;
+    if (fold)
+        hipLaunchKernelGGL(k_fold_rows, dim3(kFoldBlocks), dim3(64), 0, s, w.epart, (i64)nseg,
+                           w.is_part);
+    StatsArgs st;
+    st.is_part = fold ? w.is_part : w.epart;
+    st.nblk = fold ? kFoldBlocks : (int)nseg;
+    st.d = c.d;
+    st.rec_num = w.rec_num;
+    st.est = est;
+    st.info = info;
+    return st;
+}
+
+// Where a resampling iteration's weights go.
+static void reset_weights(const smc_config &c, const Work &w, double *logw, ExpandOut &o)
+{
+    o.logw = logw;
+    o.reset = -std::log((double)c.n);
+    // populations of at most kSmallN particles always write their weights
+    o.uniform = c.lazy_reset && c.n > kSmallN ? &w.ctrl->uniform : nullptr;
+}
+
+// The end of a filter iteration: the redistribution into x, and the mean, which
+// Alg 1 takes after resampling.
+static smc_status filter_finish(const smc_config &c, const Work &w, double *x, double *logw,
+                                double *est, smc_resample_info *info, hipStream_t s)
+{
+    ExpandOut o;
+    o.mode = ExpandMode::kForward;
+    reset_weights(c, w, logw, o);
+    o.est_part = w.epart;
+    if (launch_expand(w, c.n, 0, w.x_scr, x, c.d * 8, s, o) != hipSuccess) return SMC_E_DEVICE;
+    const StatsArgs st = filter_sums(c, w, expand_segments(c.n), est, info, s);
+    hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, st.is_part, st.nblk, c.d,
+                       w.rec_num, est, info);
+    return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
+}
+
+static hipError_t launch_filter_step(const smc_config &c, const Work &w, int par, uint32_t t,
+                                     const double *x, double *xo, double *logw, hipStream_t s)
+{
+    FilterArgs g;
+    g.n = c.n;
+    g.t = t;
+    g.pref = w.pref;
+    g.pref64 = w.pref64;
+    g.tpre = w.tsum;
+    g.ctrl = w.ctrl;
+    g.tsh = w.tile_shift;
+    g.x = x;
+    g.xo = xo;
+    g.logw = logw;
+    g.slots_p = w.slots + (par & 1) * kSlots * kSlotStride;
+    g.est_part = w.epart;
+    const int seg = filter_seg_len(c.n);
+    auto kern = seg == 256    ? k_filter_step<256>
+                : seg == 512  ? k_filter_step<512>
+                : seg == 1024 ? k_filter_step<1024>
+                              : k_filter_step<kSegLen>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)filter_segments(c.n)), dim3(kExpandThreads), 0, s,
+                       targs(c, w, false), g);
+    return hipGetLastError();
+}
+
+// Several iterations of the particle filter: the rows go back and forth between x
+// and the workspace copy, so that the last proposals end in the copy and the
+// redistribution writes x.
+static smc_status filter_run_n(const smc_config &c, const Work &w, int K, int par0, uint32_t t0,
+                               int nsteps, double *x, double *logw, smc_resample_info *info,
+                               double *est, hipStream_t s)
+{
+    StatsArgs tail;  // of the iteration before: formed beside the next one's scan
+    for (int i = 0; i < nsteps; ++i) {
+        const int par = par0 ^ (i & 1);
+        const uint32_t t = t0 + (uint32_t)i;
+        const bool to_copy = ((nsteps - 1 - i) & 1) == 0;
+        if (i == 0) {
+            if (launch_is<false>(c, w, par, t, x, logw, s, to_copy ? kToCopy : kInPlace) !=
+                hipSuccess)
+                return SMC_E_DEVICE;
+        } else {
+            double *from = to_copy ? x : w.x_scr, *to = to_copy ? w.x_scr : x;
+            if (launch_filter_step(c, w, par, t, from, to, logw, s) != hipSuccess)
+                return SMC_E_DEVICE;
+            tail = filter_sums(c, w, filter_segments(c.n), est ? est + (int64_t)(i - 1) * 4 * c.d : nullptr,
+                               info ? info + (i - 1) : nullptr, s);
+        }
+        if (launch_quant_scan(w, logw, c.n, K, par, s, c.lazy_reset != 0, tail) != hipSuccess)
+            return SMC_E_DEVICE;
+        if (launch_decide(w, par, c.n, K, resample_word(c.seed, c.sampler_id, t), c.mode,
+                          c.ess_num, c.ess_den, info ? info + i : nullptr, s) != hipSuccess)
+            return SMC_E_DEVICE;
+    }
+    return filter_finish(c, w, x, logw, est ? est + (int64_t)(nsteps - 1) * 4 * c.d : nullptr,
+                         info ? info + (nsteps - 1) : nullptr, s);
+}
+
 smc_status step_run_n(const smc_config &c, const Work &w, int K, int par0, uint32_t t0,
                       int nsteps, double *x, double *logw, smc_resample_info *info, double *est,
                       hipStream_t s)
 {
+    if (c.target == SMC_TARGET_BEARING && nsteps > 1)
+        return filter_run_n(c, w, K, par0, t0, nsteps, x, logw, info, est, s);
     for (int i = 0; i < nsteps; ++i) {
         const smc_status st = step_run(c, w, K, par0 ^ (i & 1), t0 + (uint32_t)i, x, logw,
                                        info ? info + i : nullptr,
@@ -1610,31 +1839,16 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     if (launch_decide(w, par, n, K, r, c.mode, c.ess_num, c.ess_den, info, s, st) != hipSuccess)
         return SMC_E_DEVICE;
     if (keep) return SMC_OK;
+    if (pf) return filter_finish(c, w, x, logw, est, info, s);
     ExpandOut o;
     o.mode = fwd ? ExpandMode::kForward : ExpandMode::kIfResampled;
-    o.logw = logw;
-    o.reset = -std::log((double)n);
-    // populations of at most kSmallN particles always write their weights
-    o.uniform = c.lazy_reset && n > kSmallN ? &w.ctrl->uniform : nullptr;
-    // the particle filter and the 1-D Gaussian and Student-t samplers carry no
-    // cached log-target
-    if (!pf && !(c.d == 1 && (c.target == SMC_TARGET_GAUSS || c.target == SMC_TARGET_STUDENT))) {
+    reset_weights(c, w, logw, o);
+    // the 1-D Gaussian and Student-t samplers carry no cached log-target
+    if (!(c.d == 1 && (c.target == SMC_TARGET_GAUSS || c.target == SMC_TARGET_STUDENT))) {
         o.aux = w.lp_scr;
         o.aux_out = w.lp;
     }
-    o.est_part = pf ? w.epart : nullptr;
-    if (launch_expand(w, n, 0, w.x_scr, x, c.d * 8, s, o) != hipSuccess) return SMC_E_DEVICE;
-    if (pf) {  // Alg 1 takes the mean after resampling
-        const int64_t nseg = expand_segments(n);
-        const bool fold = nseg > kIsBlocks;
-        if (fold)
-            hipLaunchKernelGGL(k_fold_rows, dim3(kFoldBlocks), dim3(64), 0, s, w.epart, (i64)nseg,
-                               w.is_part);
-        hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl,
-                           fold ? w.is_part : w.epart, fold ? kFoldBlocks : (int)nseg, c.d,
-                           w.rec_num, est, info, 0);
-    }
-    return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
+    return launch_expand(w, n, 0, w.x_scr, x, c.d * 8, s, o) == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
 __global__ __launch_bounds__(256) void k_sync_weights(const Ctrl *ctrl, i64 n, double *logw,

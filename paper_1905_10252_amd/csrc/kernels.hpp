@@ -30,7 +30,6 @@ constexpr int64_t kStreamBytes = 128ll << 20;
 constexpr int kMaxRowBytes = 1 << 20;
 static_assert((long long)kSegLen * (kMaxRowBytes / 4) < (1ll << 31), "expand chunk count");
 constexpr int kEstCols = 10;                      // 2 + 2 d sums of a filter row (d = 4)
-static_assert(kSegLen + 1 <= 1 << kTileShift, "an expand segment spans at most two scan tiles");
 constexpr int kLogregSplit = 8;                   // row blocks of the likelihood contraction
 
 struct TilePart {
@@ -89,18 +88,23 @@ hipError_t launch_init_ctrl(const Work &w, hipStream_t s);
 // Max pass into the slots of parity par, then the fold of those slots.
 hipError_t launch_max(const Work &w, const double *lw, int64_t n, int par, hipStream_t s);
 hipError_t launch_fold(const Work &w, int par, hipStream_t s);
-// Quantise + scan; reads the max slots of parity par.
-// clear_uniform: also clears the lazy-reset flag (an iteration's scan runs
-// after the kernels that read it).
-hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, int par,
-                             hipStream_t s, bool clear_uniform = false);
 // A sampler iteration's statistics, computed by the decision's workgroup
 // right after the decision (is_part NULL: none).
 struct StatsArgs {
     const double *is_part = nullptr;
     int nblk = 0, d = 0;
     double *rec_num = nullptr, *est = nullptr;
+    void *info = nullptr;  // a filter iteration's smc_resample_info
 };
+
+// Quantise + scan; reads the max slots of parity par.
+// clear_uniform: also clears the lazy-reset flag (an iteration's scan runs
+// after the kernels that read it).  tail: the statistics of the filter iteration
+// before, formed by a workgroup of their own beside the scan (6 us as a kernel
+// of its own).
+hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, int par,
+                             hipStream_t s, bool clear_uniform = false,
+                             const StatsArgs &tail = StatsArgs());
 
 // Error and decision of the call from the max slots of parity par and the
 // scan; info is a device smc_resample_info (nullable).
@@ -127,13 +131,26 @@ inline int expand_seg_len(int64_t n)
 {
     int seg = kSegLen;
     while (seg > 256 && 2 * n < 2048ll * seg) seg >>= 1;
-    return seg;  // at most 512 for n < kSmallTileN: two small tiles hold a segment
+    return seg;
 }
-static_assert(2 * kSmallTileN <= 2048ll * 1024 && 512 + 1 <= 1 << kTileShiftSmall,
-              "an expand segment spans at most two small tiles");
 inline int64_t expand_segments(int64_t n)
 {
     const int seg = expand_seg_len(n);
+    return (2 * n + seg - 1) / seg;
+}
+
+// The same for the filter's fused iteration, whose workgroups hold their CU longer:
+// four per CU (N = 2^20: 34.4 us with 2048 steps, 38.6 with 1024; N = 2^19: 24.6,
+// 22.7 with 1024, 25.3 with 512; N = 2^17: 13.0 with 512, 12.8 with 256).
+inline int filter_seg_len(int64_t n)
+{
+    int seg = kSegLen;
+    while (seg > 256 && 2 * n < 1024ll * seg) seg >>= 1;
+    return seg;
+}
+inline int64_t filter_segments(int64_t n)  // at most expand_segments(n): they share epart
+{
+    const int seg = filter_seg_len(n);
     return (2 * n + seg - 1) / seg;
 }
 

@@ -166,4 +166,57 @@ __device__ inline void write_estimates(const StatsLds &L, int k, int d, double r
     }
 }
 
+// The statistics of a filter iteration, whose weights, decision and log Z are in
+// the control block, by one workgroup of NT threads.  The rows of `part` all carry
+// the same reference, so their sums are added as they are: a wavefront takes a
+// column, lanes over the rows, every load of a trip in flight.
+template <int NT>
+__device__ inline void filter_stats(Ctrl *ctrl, const double *part, int nblk, int d,
+                                    double *rec_num, double *est, smc_resample_info *info)
+{
+    constexpr int NW = NT / 64;
+    __shared__ double s_col[kEstCols], s_bc[3];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const RecState rec(ctrl);
+    const unsigned err = ctrl->err_call, resampled = ctrl->resample;
+    const double logZ = ctrl->logZ;
+    const double rec_old = tid < 2 * d ? rec_num[tid] : 0.0;
+    if (err) return;
+    for (int c = 1 + wid; c < 2 + 2 * d; c += NW) {
+        const double *pc = part + (i64)c * nblk;
+        double acc = 0.0;
+        constexpr int U = 16;
+        for (int b0 = lane; b0 < nblk; b0 += 64 * U) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int b = b0 + 64 * u;
+                v[u] = pc[b < nblk ? b : b0];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc += b0 + 64 * u < nblk ? v[u] : 0.0;
+        }
+        acc = wave_sum_f64(acc);
+        if (lane == 0) s_col[c] = acc;
+    }
+    if (tid == 0) {
+        double bc[3];
+        RecNext nx;
+        const double logc = recycle_step(rec, logZ, bc, nx);
+        store_recycling(nx, logc, logZ, resampled != 0, ctrl);
+        if (info) info->log_c = logc;
+        for (int i = 0; i < 3; ++i) s_bc[i] = bc[i];
+    }
+    __syncthreads();
+    if (tid < 2 * d) {
+        const double f = s_col[2 + tid] / s_col[1];
+        const double num = rec_old * s_bc[0] + s_bc[1] * f;
+        rec_num[tid] = num;
+        if (est) {
+            est[tid] = f;
+            est[2 * d + tid] = num / s_bc[2];
+        }
+    }
+}
+
 }  // namespace smc
