@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(256) void k_logreg_f64(const double *__restrict__ t
     const i64 t1 = t0 + per < tiles ? t0 + per : tiles;
     double sa = 0.0, lg = 0.0, prod = 1.0;
     int cnt = 0;
-    for (i64 tt = t0; tt < t1; ++tt) {
+    auto contract = [&](i64 tt) {
         const double *ap = xf + (tt * 64 + lane) * KS;
         double a[KS];
         if constexpr (KS == 1) {
@@ -1253,6 +1253,11 @@ __global__ __launch_bounds__(256) void k_logreg_f64(const double *__restrict__ t
         f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+        return acc;
+    };
+    const i64 whole = m_rows / 16 < t1 ? m_rows / 16 : t1;
+    for (i64 tt = t0; tt < whole; ++tt) {
+        const f64x4 acc = contract(tt);
 #pragma unroll
         for (int v = 0; v < 4; ++v) softplus_acc64(acc[v], s_tab, sa, prod);
         if (++cnt == 128) {  // 512 factors in (1, 2]: at most 2^512
@@ -1261,13 +1266,20 @@ __global__ __launch_bounds__(256) void k_logreg_f64(const double *__restrict__ t
             cnt = 0;
         }
     }
+    // A last tile with rows beyond M: those add nothing.  The row of each
+    // accumulator comes from a product of its own (row index times one).
+    if (t0 <= whole && whole < t1 && m_rows > whole * 16) {
+        const f64x4 acc = contract(whole);
+        const double ri = kq == 0 ? (double)col : 0.0, one = kq == 0 ? 1.0 : 0.0;
+        f64x4 row = {0.0, 0.0, 0.0, 0.0};
+        row = __builtin_amdgcn_mfma_f64_16x16x4f64(ri, one, row, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (whole * 16 + (i64)row[v] < m_rows) softplus_acc64(acc[v], s_tab, sa, prod);
+    }
     double sp = 0.5 * sa + (lg + log(prod));
     sp += __shfl_xor(sp, 16, kWave);
     sp += __shfl_xor(sp, 32, kWave);
-    // Rows of the last tile beyond M are zero: u = 0 there, and each added a
-    // factor of exactly 2 (and nothing to |u|), whichever lane held it.
-    const i64 lo = t0 * 16 > m_rows ? t0 * 16 : m_rows, hi = t1 * 16;
-    if (hi > lo) sp -= (double)(hi - lo) * kLn2;
     if (lane < 16 && p < n) lpart[(i64)blockIdx.y * n + p] = -sp;
 }
 

@@ -260,3 +260,24 @@ def test_logreg_f64_operand_widths(smc, dev, d, m_rows):
         bound = 2.0 ** -53 * (m_rows + 4 * d + 16) * (mag + np.abs(want).astype(np.float64))
         assert (np.abs(lp - want.astype(np.float64)) <= bound).all(), (d, m_rows, n)
 
+
+def test_logreg_f64_single_terms(smc, dev):
+    """One row, one feature: softplus over the range of its exponential, the table's
+    grid points and its clamp included."""
+    import torch
+    u = np.concatenate([np.linspace(-60, 60, 4001), np.geomspace(1e-320, 1e308, 3000),
+                        -np.geomspace(1e-320, 1e5, 3000), np.arange(4096) * math.log(2) / 2048,
+                        (np.arange(4096) + 0.5) * math.log(2) / 2048, [0.0, -0.0, 699.999,
+                                                                       700.0, 700.001, 745.2]])
+    # a wide prior keeps the quadratic term small; its part is taken out exactly
+    g = smc.Sampler(u.size, 1, "logreg", X=np.ones((1, 1)), y=np.zeros(1), prior_var=1e300,
+                    precision="f64", log_norm=0.0, device=dev)
+    lp = g.log_target(torch.from_numpy(u.reshape(-1, 1)).to(dev)).cpu().numpy()
+    ul = u.astype(np.longdouble)
+    prior = np.where(np.abs(u) < 1e100, 0.0, 0.5e-300 * ul * ul)
+    want = -(np.maximum(ul, 0) + np.log1p(np.exp(-np.abs(ul)))) - prior
+    small = np.abs(u) < 1e100
+    err = np.abs(lp[small] - want[small].astype(np.float64))
+    # (u + |u|) / 2 and the logarithm: a few roundings of values up to |u| + 1
+    assert (err <= 2.0 ** -52 * 4 * (1.0 + np.abs(u[small]))).all()
+    assert np.isfinite(lp[small]).all()
