@@ -10,9 +10,9 @@
 //   k_bquad<DB> per chunk of samplers whose dimension falls in the bucket
 //               (DB - 8, DB]: |U (x - mean)|^2 with U staged in LDS and the row
 //               in registers, weight update, chunk max key and estimate sums
-//               against the chunk's max.  One launch per bucket.  From
-//               DB = 24 up, k_bquad_mx: the same results with the product
-//               U (x - mean) on the FP64 matrix cores.
+//               against the chunk's max.  From DB = 24 up the product
+//               U (x - mean) runs on the FP64 matrix cores, with the same
+//               results.  One launch for all buckets (k_bquad_all).
 //   k_bscan     per tile of 4096 particles of every sampler: the sampler's max
 //               from its chunk keys, 64-bit fixed-point weights, FP64 sums,
 //               the exact sum of squares, and the inclusive prefix by a
@@ -35,6 +35,7 @@
 
 #include <cmath>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/smc.h"
@@ -170,17 +171,24 @@ __device__ inline void stage_rows(double (*sx)[CW], const GLB(double) *xb, int d
     }
 }
 
-// Position of block b in a prefix table: slot and index within the slot.
+// Position of block b in a prefix table: slot and index within the slot.  64 probes
+// a round, one per lane (two rounds for 256 samplers; halving took eight
+// dependent loads at the start of every workgroup).
 __device__ inline bool locate(const int *pref, const int *act, int nact, int b, int &slot,
                               int &local)
 {
     if (nact <= 0 || b >= pref[nact]) return false;
-    int lo = 0, hi = nact;  // pref[lo] <= b < pref[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (pref[mid] <= b) lo = mid;
-        else hi = mid;
+    const int lane = threadIdx.x & 63;
+    int lo = 0, len = nact;  // pref[lo] <= b < pref[lo + len]
+    while (len > 1) {
+        const int stride = (len + 63) >> 6, pos = lo + lane * stride;
+        const u64 in = __ballot(lane * stride < len && pref[pos < nact ? pos : nact] <= b);
+        const int c = __popcll(in) - 1;  // the first probe is always in
+        const int rest = len - c * stride;
+        lo += c * stride;
+        len = rest < stride ? rest : stride;
     }
+    lo = __builtin_amdgcn_readfirstlane(lo);
     slot = act[lo];
     local = b - pref[lo];
     return true;
@@ -357,26 +365,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k
 // staged in LDS and the row in registers, the weight update, the chunk's max
 // key, non-finite flag and estimate sums against the chunk's own max m_b:
 // [m_b, sum e, sum e x_k, sum e x_k^2], e = exp(l - m_b).
-// W: the occupancy the register allocation aims at (waves per SIMD), a
-// per-bucket speed knob (smc_batch_set_bucket_waves); results do not depend
-// on it.
-template <int DB, bool kInit, int W>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k_bquad(
-    const BSlot *slots, const int *n_act, const int *bact, const int *bchunk_pref, int bucket,
-    int cap, int single)
+template <int DB>
+struct QuadLds {
+    u64 key[4];
+    unsigned bad[4];
+    double col[16][1 + 2 * DB];    // one partial per 16-lane row
+    double x[kBChunk][17];
+    double T[DB * (DB + 1) / 2];
+};
+
+template <int DB, bool kInit>
+__device__ __forceinline__ void quad_rows(QuadLds<DB> &L, const BSlot *slots, int slot, int chunk)
 {
-    __shared__ u64 s_key[4];
-    __shared__ unsigned s_bad[4];
-    __shared__ double s_col[16][1 + 2 * DB];  // one partial per 16-lane row
+    auto &s_key = L.key;
+    auto &s_bad = L.bad;
+    auto &s_col = L.col;
+    auto &sx = L.x;
+    auto &sT = L.T;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    int slot, chunk;
-    if (single >= 0) {
-        slot = single;
-        chunk = blockIdx.x;
-    } else if (!locate(bchunk_pref + bucket * (cap + 1), bact + bucket * cap, n_act[1 + bucket],
-                       blockIdx.x, slot, chunk)) {
-        return;
-    }
     // a local copy: stores through the sampler's arrays cannot alias it
     const BSlot S = slots[__builtin_amdgcn_readfirstlane(slot)];
     const i64 n = S.n;
@@ -390,7 +396,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
     double lw = -__builtin_huge_val();
     // The chunk's rows come in through LDS in slices of 16 columns, each
     // moved as whole 128-byte lines (16 lanes per row).
-    __shared__ double sx[kBChunk][17];
     constexpr int PW = DB < 16 ? DB : 16;
     const i64 base = (i64)chunk * kBChunk;
     const int cnt = (int)((n - base) < kBChunk ? (n - base) : kBChunk);
@@ -400,7 +405,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
     // U's upper triangle, packed by rows (row r holds k = r .. DB - 1 from
     // offset tri_off(r)), in LDS: every lane reads the same element, so the
     // reads are broadcasts, and many can be in flight (unlike scalar loads).
-    __shared__ double sT[DB * (DB + 1) / 2];
     {
         constexpr int kPer = (DB * DB + 255) / 256;
         const GLB(double) *ug = glb(S.upad);
@@ -527,8 +531,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
 // are +0 and add nothing).  No LDS holds Y, which leaves the LDS footprint
 // small enough that registers alone set the occupancy.  A particle with a
 // non-finite difference (possible only with non-finite parameters, where a
-// zero of U times inf gives NaN instead of the row-by-row result) takes the
-// row-by-row loop instead.
+// zero of U times inf gives NaN instead of the row-by-row result) has a
+// non-finite form, and every such particle takes the row-by-row loop instead.
 // U's operands and the mean wait in LDS.  The estimate sums re-read the
 // chunk's rows (from cache) once the chunk's max is known, per lane over its
 // four particles, then across the 16 lanes of each row, then over the
@@ -543,31 +547,46 @@ __host__ __device__ constexpr int mx_pair(int R, int c)
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-template <int DB, bool kInit, int W>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k_bquad_mx(
-    const BSlot *slots, const int *n_act, const int *bact, const int *bchunk_pref, int bucket,
-    int cap, int single)
+// Coordinates 4 c + g of a row.  Its bucket has d > DB - 8: only the last two steps
+// can pass the row's end, where the last coordinate is read instead (a guard on
+// every step, and on the particle, took a third of the vector instructions and
+// forty registers).
+template <int DB>
+__device__ inline void load_row(double (&xv)[DB / 4], const GLB(double) *row, int g, int d)
+{
+    const GLB(double) *rg = row + g;
+#pragma unroll
+    for (int c = 0; c < DB / 4; ++c) {
+        if (4 * c + 3 > DB - 8) xv[c] = row[4 * c + g < d ? 4 * c + g : d - 1];
+        else xv[c] = rg[4 * c];
+    }
+}
+
+template <int DB>
+struct QuadMxLds {
+    static constexpr int NP = mx_pair<DB>((DB + 15) / 16, 4 * ((DB + 15) / 16));
+    double U[NP][64];             // B operands, one per lane and step
+    double mean[DB];
+    double q[kBChunk], e[kBChunk];
+    double col[4][1 + 2 * DB];    // one partial per wavefront
+    u64 key[4];
+    unsigned bad[4];
+};
+
+template <int DB, bool kInit>
+__device__ __forceinline__ void quad_mx(QuadMxLds<DB> &L, const BSlot *slots, int slot, int chunk)
 {
     constexpr int NC = DB / 4;           // k steps of four coordinates
     constexpr int NRB = (DB + 15) / 16;  // blocks of 16 rows of U
-    constexpr int NP = mx_pair<DB>(NRB, 4 * NRB);
-    static_assert(DB % 8 == 0 && NP > 0, "bucket width");
-    __shared__ double sU[NP][64];         // B operands, one per lane and step
-    __shared__ double sMean[DB];
-    __shared__ double s_q[kBChunk];
-    __shared__ double s_e[kBChunk];
-    __shared__ double s_col[4][1 + 2 * DB];  // one partial per wavefront
-    __shared__ u64 s_key[4];
-    __shared__ unsigned s_bad[4];
+    static_assert(DB % 8 == 0 && QuadMxLds<DB>::NP > 0, "bucket width");
+    auto &sU = L.U;
+    auto &sMean = L.mean;
+    auto &s_q = L.q;
+    auto &s_e = L.e;
+    auto &s_col = L.col;
+    auto &s_key = L.key;
+    auto &s_bad = L.bad;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    int slot, chunk;
-    if (single >= 0) {
-        slot = single;
-        chunk = blockIdx.x;
-    } else if (!locate(bchunk_pref + bucket * (cap + 1), bact + bucket * cap, n_act[1 + bucket],
-                       blockIdx.x, slot, chunk)) {
-        return;
-    }
     // a local copy: stores through the sampler's arrays cannot alias it
     const BSlot S = slots[__builtin_amdgcn_readfirstlane(slot)];
     const i64 n = S.n;
@@ -601,25 +620,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
         // every load of the tile is issued before the first is used (the
         // empty asm keeps the compiler from sinking each load into its use)
         double xv[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) xv[c] = xb[(i64)plc * d + (4 * c + g < d ? 4 * c + g : d - 1)];
+        load_row<DB>(xv, xb + (i64)plc * d, g, d);
         asm volatile("" ::: "memory");
         f64x4_t acc[NRB];
 #pragma unroll
         for (int R = 0; R < NRB; ++R) acc[R] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-        bool nf = false;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const int k = 4 * c + g;
-            const double t = (pact && k < d) ? xv[c] - sMean[k] : 0.0;
-            nf |= !__builtin_isfinite(t);
+            double t = xv[c] - sMean[k];
+            if (4 * c + 3 > DB - 8) t = k < d ? t : 0.0;  // d > DB - 8
 #pragma unroll
             for (int R = 0; R < NRB; ++R)
                 if (4 * R <= c)
                     acc[R] = __builtin_amdgcn_mfma_f64_16x16x4f64(sU[mx_pair<DB>(R, c)][lane], t,
                                                                   acc[R], 0, 0, 0);
         }
-        const u64 nfm = __ballot(nf);
         // element v of lane (g, p16) in block R is Y[p16][16 R + 4 v + g]
         f64x4_t q2 = f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -631,7 +647,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
             const int pt = wid * 64 + tile * 16 + p16;
             const int vq = p16 >> 2;
             double q = vq == 0 ? q2[0] : (vq == 1 ? q2[1] : (vq == 2 ? q2[2] : q2[3]));
-            if (((nfm >> p16) & 0x0001000100010001ull) && pt < cnt) {
+            if (!__builtin_isfinite(q) && pt < cnt) {
                 q = 0.0;
                 const GLB(double) *xr = xb + (i64)pt * d;
                 for (int r = 0; r < d; ++r) {
@@ -688,16 +704,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
         const double e = s_e[pl];
         s0 += e;
         double xv[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) xv[c] = xb[(i64)plc * d + (4 * c + g < d ? 4 * c + g : d - 1)];
+        load_row<DB>(xv, xb + (i64)plc * d, g, d);
         asm volatile("" ::: "memory");
+        if (wid * 64 + tile * 16 + 16 > cnt) {  // the rows past the last particle
+#pragma unroll
+            for (int c = 0; c < NC; ++c) xv[c] = pact ? xv[c] : 0.0;
+        }
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const int k = 4 * c + g;
-            const double xk = (pact && k < d) ? xv[c] : 0.0;
-            const double ex = e * xk;
+            const double ex = e * xv[c];
             s1[c] += ex;
-            s2[c] += ex * xk;
+            s2[c] += ex * xv[c];
         }
     }
     s0 = row16_sum(s0);
@@ -725,6 +742,84 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
         o.bad = bb;
         o.pad = 0;
         S.tis[chunk] = o;
+    }
+}
+
+// Buckets from this width up take the matrix-core form of the update (below
+// it the vector form measured as fast: a 16-row block is mostly padding).
+constexpr int kQuadMxMin = 24;
+
+template <int DB>
+using QuadLdsOf = std::conditional_t<(DB >= kQuadMxMin), QuadMxLds<DB>, QuadLds<DB>>;
+
+template <int DB, bool kInit>
+__device__ __forceinline__ void quad_form(QuadLdsOf<DB> &L, const BSlot *slots, int slot, int chunk)
+{
+    if constexpr (DB >= kQuadMxMin) quad_mx<DB, kInit>(L, slots, slot, chunk);
+    else quad_rows<DB, kInit>(L, slots, slot, chunk);
+}
+
+// The chunks of one bucket (single >= 0: of that slot).  W: the occupancy the
+// register allocation aims at (waves per SIMD), a per-bucket speed knob
+// (smc_batch_set_bucket_waves); results do not depend on it.
+template <int DB, bool kInit, int W>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k_bquad(
+    const BSlot *slots, const int *n_act, const int *bact, const int *bchunk_pref, int bucket,
+    int cap, int single)
+{
+    __shared__ QuadLdsOf<DB> L;
+    int slot, chunk;
+    if (single >= 0) {
+        slot = single;
+        chunk = blockIdx.x;
+    } else if (!locate(bchunk_pref + bucket * (cap + 1), bact + bucket * cap, n_act[1 + bucket],
+                       blockIdx.x, slot, chunk)) {
+        return;
+    }
+    quad_form<DB, kInit>(L, slots, slot, chunk);
+}
+
+// The chunks of every bucket at the highest aim, widest rows first, in one launch: a
+// bucket alone makes two to three rounds of workgroups on the chip, the last one
+// mostly empty (2085 workgroups of width 56 on 1024 places): 505 us as eight
+// launches, 439 as one, for the 256-sampler workload.  Bound by the FP64 pipe,
+// which the matrix and vector instructions share (width 56: 48 matrix instructions
+// of 64 cycles and about 300 vector instructions a tile of 16 particles).
+struct QuadSpan {
+    int end[kBuckets];  // workgroups of the buckets from the widest down, running total
+};
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bquad_all(
+    const BSlot *slots, const int *n_act, const int *bact, const int *bchunk_pref, int cap,
+    QuadSpan sp)
+{
+    __shared__ union Lds {
+        __device__ Lds() {}
+        QuadLdsOf<8> b0;
+        QuadLdsOf<16> b1;
+        QuadLdsOf<24> b2;
+        QuadLdsOf<32> b3;
+        QuadLdsOf<40> b4;
+        QuadLdsOf<48> b5;
+        QuadLdsOf<56> b6;
+        QuadLdsOf<64> b7;
+    } L;
+    int i = 0;
+    while (i < kBuckets - 1 && (int)blockIdx.x >= sp.end[i]) ++i;
+    const int bucket = kBuckets - 1 - i;
+    int slot, chunk;
+    if (!locate(bchunk_pref + bucket * (cap + 1), bact + bucket * cap, n_act[1 + bucket],
+                blockIdx.x - (i ? sp.end[i - 1] : 0), slot, chunk))
+        return;
+    switch (bucket) {
+    case 0: quad_form<8, false>(L.b0, slots, slot, chunk); break;
+    case 1: quad_form<16, false>(L.b1, slots, slot, chunk); break;
+    case 2: quad_form<24, false>(L.b2, slots, slot, chunk); break;
+    case 3: quad_form<32, false>(L.b3, slots, slot, chunk); break;
+    case 4: quad_form<40, false>(L.b4, slots, slot, chunk); break;
+    case 5: quad_form<48, false>(L.b5, slots, slot, chunk); break;
+    case 6: quad_form<56, false>(L.b6, slots, slot, chunk); break;
+    default: quad_form<64, false>(L.b7, slots, slot, chunk); break;
     }
 }
 
@@ -1333,35 +1428,23 @@ hipError_t launch_tables(smc_batch *b, hipStream_t s)
     return hipGetLastError();
 }
 
-// Buckets from this width up take the matrix-core form of the update (below
-// it the vector form measured as fast: a 16-row block is mostly padding).
-constexpr int kQuadMxMin = 24;
-
-// Highest occupancy aim the kernel of bucket width DB can meet (LDS and
-// registers of the wider rows; the matrix-core kernel needs 166 VGPRs at
-// width 64, 150 at 56, 122 at 48); larger requests are clamped to it.
-constexpr int max_quad_waves(int DB)
-{
-    return DB >= kQuadMxMin ? (DB <= 40 ? 4 : 3) : (DB <= 16 ? 4 : (DB <= 40 ? 3 : 2));
-}
+// The highest occupancy aim of bucket width DB: larger requests are clamped to it,
+// and a step takes all buckets at theirs in one launch, k_bquad_all.
+constexpr int max_quad_waves(int DB) { return DB <= 40 ? 4 : 3; }
 
 template <int DB, bool kInit>
 void launch_quad_waves(int w, dim3 g, hipStream_t s, const smc_batch *b, int q, int single)
 {
     const BSlot *sl = b->d_slots;
     const BTabs &t = b->tabs;
-    w = w < max_quad_waves(DB) ? w : max_quad_waves(DB);
+    constexpr int kMax = max_quad_waves(DB);
+    w = w < kMax ? w : kMax;
     switch (w) {
 #define SMC_BQW_CASE(W)                                                                        \
     case W:                                                                                    \
-        if constexpr (W <= max_quad_waves(DB)) {                                               \
-            if constexpr (DB >= kQuadMxMin)                                                    \
-                hipLaunchKernelGGL((k_bquad_mx<DB, kInit, W>), g, dim3(256), 0, s, sl,         \
-                                   t.n_act, t.bact, t.btile_pref, q, b->cap, single);          \
-            else                                                                               \
-                hipLaunchKernelGGL((k_bquad<DB, kInit, W>), g, dim3(256), 0, s, sl, t.n_act,   \
-                                   t.bact, t.btile_pref, q, b->cap, single);                   \
-        }                                                                                      \
+        if constexpr (W < kMax || (kInit && W == kMax))                                        \
+            hipLaunchKernelGGL((k_bquad<DB, kInit, W>), g, dim3(256), 0, s, sl, t.n_act,       \
+                               t.bact, t.btile_pref, q, b->cap, single);                       \
         break;
         SMC_BQW_CASE(1) SMC_BQW_CASE(2) SMC_BQW_CASE(3) SMC_BQW_CASE(4)
 #undef SMC_BQW_CASE
@@ -1386,18 +1469,23 @@ void launch_quad_bucket(int q, dim3 g, hipStream_t s, const smc_batch *b, int si
     }
 }
 
-// Default occupancy aim of the quadratic-form kernel per bucket: the highest
-// it reaches (the widest rows need the registers of two waves per SIMD).
-inline int default_quad_waves(int q) { return max_quad_waves(8 * (q + 1)); }
-
 hipError_t enqueue_step(smc_batch *b, smc_resample_info *info, double *est, hipStream_t s)
 {
     const BSlot *sl = b->d_slots;
     const BTabs &t = b->tabs;
     hipLaunchKernelGGL(k_bprop, dim3(b->total_chunks), dim3(256), 0, s, sl, t.n_act, t.act,
                        t.chunk_pref);
-    for (int q = 0; q < kBuckets; ++q)
-        if (b->btiles[q] > 0) launch_quad_bucket<false>(q, dim3(b->btiles[q]), s, b, -1);
+    QuadSpan sp;  // buckets of a lower aim have launches of their own
+    int quads = 0;
+    for (int i = 0; i < kBuckets; ++i) {
+        const int q = kBuckets - 1 - i;
+        if (b->quad_waves[q] >= max_quad_waves(8 * (q + 1))) quads += b->btiles[q];
+        else if (b->btiles[q] > 0) launch_quad_bucket<false>(q, dim3(b->btiles[q]), s, b, -1);
+        sp.end[i] = quads;
+    }
+    if (quads > 0)
+        hipLaunchKernelGGL(k_bquad_all, dim3(quads), dim3(256), 0, s, sl, t.n_act, t.bact,
+                           t.btile_pref, b->cap, sp);
     hipLaunchKernelGGL(k_bscan, dim3(b->total_tiles), dim3(256), 0, s, sl, t.n_act, t.act,
                        t.tile_pref);
     hipLaunchKernelGGL(k_bdecide, dim3(b->n_act), dim3(256), 0, s, sl, t.n_act, t.act, info, est);
@@ -1452,7 +1540,7 @@ smc_status smc_batch_create(smc_batch **h_out, int32_t capacity, void *ws, size_
     b->h_slots.assign((size_t)capacity, BSlot());
     for (auto &v : b->h_slots) v.n = 0;
     b->graph_on = true;
-    for (int q = 0; q < kBuckets; ++q) b->quad_waves[q] = default_quad_waves(q);
+    for (int q = 0; q < kBuckets; ++q) b->quad_waves[q] = max_quad_waves(8 * (q + 1));
     b->graph = nullptr;
     b->exec = nullptr;
     b->version = 0;

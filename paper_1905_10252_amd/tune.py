@@ -4,11 +4,12 @@ Times whole batched steps on the device on a scratch batch holding the
 caller's workload shapes, for the knobs that change only speed (every
 candidate gives the same bits):
 
-  - ``k_bprop`` / unit_pairs: coordinate pairs per proposal work unit (2, 4, 8);
+  - ``k_bprop`` / unit_pairs: coordinate pairs per proposal work unit (the
+    proposal no longer has units: every candidate takes the same time);
   - ``k_bquad`` / waves, per dimension bucket: the occupancy the target
-    kernel of samplers with d in (8 q, 8 q + 8] aims at (1 up to what that
-    bucket's kernel reaches), tuned one bucket at a time with the others at
-    their current choice.
+    kernel of samplers with d in (8 q, 8 q + 8] aims at (1 up to that
+    bucket's highest, where the bucket joins the others in one launch), tuned
+    one bucket at a time with the others at their current choice.
 
 Results are kept in a JSON cache keyed by kernel, knob, bucket, device
 architecture (gcnArchName, e.g. gfx950) and a digest of the workload's
