@@ -55,7 +55,7 @@ struct Work {
     double *epart;      // particle filter: [kEstCols][expand segments] row sums of the
                         // redistributed rows (NULL otherwise)
     // logistic regression (NULL otherwise)
-    unsigned short *xs;   // [mpad][dp] bf16 rows of X times (1 - 2 y)
+    unsigned short *xs;   // [mpad][dp] bf16 X times (1 - 2 y), in MFMA operand order
     unsigned short *thb;  // [npad][dp] bf16 copy of the particles times log2 e
     double *csum;         // [dp] column sums of X (1 - 2 y) (of xs for BF16)
     double *xf;           // FP64: [mpad / 16][64][lr_ks(d)] X (1 - 2 y) in MFMA operand order
