@@ -24,8 +24,6 @@
 // coarse index for the merge-path searches of the expand kernel.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 #include "../../include/smc.h"
 #include "afun.hpp"
 #include "common.hpp"
@@ -170,17 +168,19 @@ struct ScanArgs {
     const u64 *slots_p; // max slots of this call's parity (quantise mode)
     unsigned *uniform;  // lazy-reset flag to clear (nullable)
     int n_tiles;
-    StatsArgs tail;     // kTail: the filter iteration before
+    StatsArgs st;
+    int n_st;           // workgroups ahead of the tiles' that form st
 };
 
 // Four waves per SIMD: the LDS of a 4096-element tile allows no more.
-template <bool kQuant, int kItems, bool kTail = false>
+template <bool kQuant, int kItems, bool kStats = false>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
     ScanArgs a)
 {
     static_assert(kItems % 4 == 0 && 64 % kItems == 0 && kItems <= 16, "scan tile shape");
     constexpr int kTile = kScanThreads * kItems;
-    __shared__ u64 sq[kTile];
+    constexpr size_t kLds = kStats && sizeof(StatsLds) > 8 * kTile ? sizeof(StatsLds) : 8 * kTile;
+    __shared__ u64 sq[kLds / 8];
     __shared__ u64 s_wsum[kScanWaves];
     __shared__ double s_z[kScanWaves], s_z2[kScanWaves];
     __shared__ u64 s_q2lo[kScanWaves], s_q2hi[kScanWaves];
@@ -188,15 +188,18 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
 
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const i64 n = a.n;
-    if constexpr (kTail) {  // the first workgroup, so that it ends with the others
-        if (blockIdx.x == 0) {
-            filter_stats<kScanThreads>(a.ctrl, a.tail.is_part, a.tail.nblk, a.tail.d,
-                                       a.tail.rec_num, a.tail.est,
-                                       reinterpret_cast<smc_resample_info *>(a.tail.info));
+    if constexpr (kStats) {  // the first workgroups, so that they end with the others
+        if ((int)blockIdx.x < a.n_st) {
+            if (a.st.cols)
+                fold_columns<kScanThreads>(*reinterpret_cast<StatsLds *>(sq), a.st, blockIdx.x);
+            else
+                filter_stats<kScanThreads>(a.ctrl, a.st.is_part, a.st.nblk, a.st.d, a.st.rec_num,
+                                           a.st.est,
+                                           reinterpret_cast<smc_resample_info *>(a.st.info));
             return;
         }
     }
-    const unsigned tile = blockIdx.x - (kTail ? 1u : 0u);
+    const unsigned tile = blockIdx.x - (kStats ? a.n_st : 0);
     const i64 base = (i64)tile * kTile;
     const bool full = base + kTile <= n;
 
@@ -418,10 +421,11 @@ __global__ __launch_bounds__(1024) void k_tile_prefix(Ctrl *ctrl, u64 *tsum,
 // ---------------------------------------------------------------- decision
 // One workgroup: tile offsets; tile partials summed in a fixed order
 // (reproducible FP64); exact integer decision and offset; with kStats also a
-// sampler iteration's estimates, c_t and recycling.  Bound by latency, so the
-// independent chains (offsets, partials, max slots, block references, the
-// state of the recycling) all start at once and share three barriers: one
-// wavefront decides while the others fold the estimate columns.
+// sampler iteration's estimates, c_t and recycling from the columns folded beside
+// the scan (folded here, by one compute unit, 66 columns of 1024 rows took this
+// kernel from 5 to 14 us).  Bound by latency, so the
+// independent chains (offsets, partials, max slots, columns, the
+// state of the recycling) all start at once.
 template <bool kStats>
 __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par,
                                                  const TilePart *tpart, u64 *tsum,
@@ -433,13 +437,16 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
     __shared__ u64 s_lo[16], s_hi[16];
     __shared__ u64 s_w[16];
     __shared__ unsigned s_err;
-    __shared__ typename std::conditional<kStats, StatsLds, int>::type s_st;
+    __shared__ double s_bc[3];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const RecState rec(ctrl);
-    StepStats<1024> ss;
-    double rec_old = 0.0;
+    double rec_old = 0.0, sum = 0.0, weights = 1.0;
     if constexpr (kStats) {
-        if (tid < 2 * st.d) rec_old = st.rec_num[tid];
+        if (tid < 2 * st.d) {
+            rec_old = st.rec_num[tid];
+            sum = st.cols[2 + tid];
+            weights = st.cols[1];
+        }
     }
     u64 key = 0;
     unsigned badf = 0;
@@ -470,7 +477,6 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
     }
     TileOffsets to;
     to.begin(tsum, n_tiles, s_w);
-    if constexpr (kStats) ss.begin(s_st, st.is_part, st.nblk);
     z = wave_sum_f64(z);
     z2 = wave_sum_f64(z2);
     q2 = wave_sum_u128(q2);
@@ -482,10 +488,6 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
     }
     __syncthreads();
     const u64 S = to.finish(tsum, n_tiles, s_w);
-    if constexpr (kStats) {
-        ss.scale(s_st, st.nblk);
-        __syncthreads();
-    }
     if (wid == 0) {
         // the 16 wavefronts' partials, one a lane (entries 16.. are the identity)
         const bool in = lane < 16;
@@ -500,17 +502,23 @@ __global__ __launch_bounds__(1024) void k_decide(Ctrl *ctrl, u64 *slots, int par
             // all weights zero) leaves c_t, the recycling sums and the
             // estimates as they were, as it stops at the resampling step
             double logc = 0.0;
-            if constexpr (kStats)
-                if (!dec.err) logc = recycle(ctrl, rec, dec.logZ, dec.resample, s_st.bc);
+            if constexpr (kStats) {
+                if (!dec.err) {
+                    double bc[3];
+                    RecNext nx;
+                    logc = recycle_step(rec, dec.logZ, bc, nx);
+                    store_recycling(nx, logc, dec.logZ, dec.resample, ctrl);
+                    for (int i = 0; i < 3; ++i) s_bc[i] = bc[i];
+                }
+            }
             store_decision(dec, K, logc, ctrl, info);
             s_err = dec.err;
         }
     }
     if constexpr (kStats) {
-        ss.columns(s_st, st.is_part, st.nblk, 2 + 2 * st.d);
         __syncthreads();
         if (tid < 2 * st.d && !s_err)
-            write_estimates(s_st, tid, st.d, rec_old, st.rec_num, st.est);
+            write_estimate(tid, st.d, sum, weights, rec_old, s_bc, st.rec_num, st.est);
     }
 }
 
@@ -651,7 +659,7 @@ hipError_t launch_small_resample(const Work &w, const double *lw, int64_t n, int
 }
 
 hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, int par,
-                             hipStream_t s, bool clear_uniform, const StatsArgs &tail)
+                             hipStream_t s, bool clear_uniform, const StatsArgs &st)
 {
     ScanArgs a;
     a.uniform = clear_uniform ? &w.ctrl->uniform : nullptr;
@@ -667,11 +675,12 @@ hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, 
     a.out64 = w.pref64;
     a.slots_p = w.slots + (par & 1) * kSlots * kSlotStride;
     a.n_tiles = w.n_tiles;
-    a.tail = tail;
-    const bool big = w.tile_shift == kTileShift, stats = tail.is_part != nullptr;
-    auto kern = stats ? (big ? k_scan<true, 16, true> : k_scan<true, 4, true>)
-                      : (big ? k_scan<true, 16> : k_scan<true, 4>);
-    hipLaunchKernelGGL(kern, dim3(w.n_tiles + stats), dim3(kScanThreads), 0, s, a);
+    a.st = st;
+    a.n_st = !st.is_part ? 0 : (st.cols ? (1 + 2 * st.d + kScanWaves - 1) / kScanWaves : 1);
+    const bool big = w.tile_shift == kTileShift;
+    auto kern = a.n_st ? (big ? k_scan<true, 16, true> : k_scan<true, 4, true>)
+                       : (big ? k_scan<true, 16> : k_scan<true, 4>);
+    hipLaunchKernelGGL(kern, dim3(w.n_tiles + a.n_st), dim3(kScanThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -779,10 +779,9 @@ __global__ __launch_bounds__(1024) void k_init_stats(Ctrl *ctrl, const double *i
     __syncthreads();
     const double m = ss.scale(s_st, nblk);
     __syncthreads();
-    ss.columns(s_st, is_part, nblk, 2);
-    __syncthreads();
+    const double z = tid < 64 ? ss.column(s_st, is_part, nblk, 1) : 0.0;
     if (tid == 0) {
-        ctrl->logZ_prev = m + log(s_st.col[1]);
+        ctrl->logZ_prev = m + log(z);
         ctrl->lc_max = -__builtin_huge_val();
         ctrl->rec_den = 0.0;
         ctrl->rec_steps = 0;
@@ -1859,19 +1858,21 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     if (launch_is<false>(c, w, par, t, x, logw, s,
                          fwd ? kToCopy : keep ? kInPlace : kToBoth) != hipSuccess)
         return SMC_E_DEVICE;
-    if (launch_quant_scan(w, logw, n, K, par, s, c.lazy_reset != 0) != hipSuccess)
-        return SMC_E_DEVICE;
-    const uint64_t r = resample_word(c.seed, c.sampler_id, t);
-    // Alg 2 estimates come before resampling: the decision's workgroup forms
-    // them (the filter takes its mean after resampling, below)
+    // Alg 2 estimates come before resampling: their sums are folded beside the scan
+    // and finished by the decision's workgroup (the filter takes its mean after
+    // resampling, below)
     StatsArgs st;
     if (!pf) {
         st.is_part = w.is_part;
         st.nblk = w.is_grid;
         st.d = c.d;
+        st.cols = w.cols;
         st.rec_num = w.rec_num;
         st.est = est;
     }
+    if (launch_quant_scan(w, logw, n, K, par, s, c.lazy_reset != 0, st) != hipSuccess)
+        return SMC_E_DEVICE;
+    const uint64_t r = resample_word(c.seed, c.sampler_id, t);
     if (launch_decide(w, par, n, K, r, c.mode, c.ess_num, c.ess_den, info, s, st) != hipSuccess)
         return SMC_E_DEVICE;
     if (keep) return SMC_OK;

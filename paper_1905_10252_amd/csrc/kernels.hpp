@@ -51,6 +51,7 @@ struct Work {
     double *x_scr;      // [n * d] redistribute destination
     double *lp_scr;     // [n]
     double *is_part;    // [kIsBlocks * (2 + 2d)] per-block estimate sums
+    double *cols;       // [2 + 2d] the same, folded over the blocks
     double *rec_num;    // [2d] recycled estimate sums
     double *epart;      // particle filter: [kEstCols][expand segments] row sums of the
                         // redistributed rows (NULL otherwise)
@@ -88,23 +89,23 @@ hipError_t launch_init_ctrl(const Work &w, hipStream_t s);
 // Max pass into the slots of parity par, then the fold of those slots.
 hipError_t launch_max(const Work &w, const double *lw, int64_t n, int par, hipStream_t s);
 hipError_t launch_fold(const Work &w, int par, hipStream_t s);
-// A sampler iteration's statistics, computed by the decision's workgroup
-// right after the decision (is_part NULL: none).
+// A sampler iteration's statistics from its blocks' sums (is_part NULL: none).
 struct StatsArgs {
     const double *is_part = nullptr;
     int nblk = 0, d = 0;
+    double *cols = nullptr;  // NULL: a filter iteration, whose decision has been made
     double *rec_num = nullptr, *est = nullptr;
-    void *info = nullptr;  // a filter iteration's smc_resample_info
+    void *info = nullptr;    // a filter iteration's smc_resample_info
 };
 
 // Quantise + scan; reads the max slots of parity par.
 // clear_uniform: also clears the lazy-reset flag (an iteration's scan runs
-// after the kernels that read it).  tail: the statistics of the filter iteration
-// before, formed by a workgroup of their own beside the scan (6 us as a kernel
-// of its own).
+// after the kernels that read it).  st: statistics that workgroups of their own
+// form beside the scan: the fold of this iteration's sums over the blocks, for the
+// decision to finish, or all of the filter iteration before.
 hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, int par,
                              hipStream_t s, bool clear_uniform = false,
-                             const StatsArgs &tail = StatsArgs());
+                             const StatsArgs &st = StatsArgs());
 
 // Error and decision of the call from the max slots of parity par and the
 // scan; info is a device smc_resample_info (nullable).

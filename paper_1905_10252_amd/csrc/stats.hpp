@@ -1,6 +1,4 @@
-// The sampler's per-iteration statistics as steps of one workgroup, shared by
-// the statistics kernel and the decision kernel (which interleaves them with
-// its own steps, so that both wait for memory and barriers together).
+// The sampler's per-iteration statistics, by workgroups beside other work.
 //
 // Every block of the update leaves one row of partial sums, stored by columns
 // (column c of block b at part[c nblk + b]: the folding wavefronts read whole
@@ -20,10 +18,8 @@ constexpr int kStatsMaxDim = 64;
 
 // LDS of the statistics.
 struct StatsLds {
-    double sc[kIsBlocks];                 // scale of each block's sums
-    double col[2 + 2 * kStatsMaxDim];     // folded columns
+    double sc[kIsBlocks];  // scale of each block's sums
     double mk[16];
-    double bc[4];                         // scale and weight of eq. recycling, its denominator
 };
 
 template <int NT>
@@ -64,35 +60,48 @@ struct StepStats {
         return m;
     }
 
-    // After another barrier: column c is folded by one wavefront, lanes over
-    // the blocks (a fixed order), eight loads in flight.  Column 1 goes to the
-    // second wavefront: the first has other work in the decision kernel.
-    __device__ void columns(StatsLds &L, const double *part, int nblk, int ncol)
+    // After another barrier: column c by one wavefront, lanes over the blocks (a
+    // fixed order), 16 loads in flight; in every lane.
+    __device__ double column(const StatsLds &L, const double *part, int nblk, int c)
     {
-        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-        for (int c = 1 + (wid + NW - 1) % NW; c < ncol; c += NW) {
-            const double *pc = part + (i64)c * nblk;
-            double acc = 0.0;
-            constexpr int U = 8;
-            for (int b0 = lane; b0 < nblk; b0 += 64 * U) {
-                double v[U];
+        const int lane = threadIdx.x & 63;
+        const double *pc = part + (i64)c * nblk;
+        double acc = 0.0;
+        constexpr int U = 16;
+        for (int b0 = lane; b0 < nblk; b0 += 64 * U) {
+            double v[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int b = b0 + 64 * u;
-                    v[u] = pc[b < nblk ? b : b0];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int b = b0 + 64 * u;
-                    const double s = b < nblk ? L.sc[b] : 0.0;
-                    acc += s != 0.0 ? s * v[u] : 0.0;
-                }
+            for (int u = 0; u < U; ++u) {
+                const int b = b0 + 64 * u;
+                v[u] = pc[b < nblk ? b : b0];
             }
-            acc = wave_sum_f64(acc);
-            if (lane == 0) L.col[c] = acc;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int b = b0 + 64 * u;
+                const double s = b < nblk ? L.sc[b] : 0.0;
+                acc += s != 0.0 ? s * v[u] : 0.0;
+            }
         }
+        return wave_sum_f64(acc);
     }
 };
+
+// Workgroup `g` of the fold of an iteration's sums: columns 1 + NW g .. of `part`, a
+// wavefront each, into cols.
+template <int NT>
+__device__ inline void fold_columns(StatsLds &L, const StatsArgs &st, int g)
+{
+    StepStats<NT> ss;
+    ss.begin(L, st.is_part, st.nblk);
+    __syncthreads();
+    ss.scale(L, st.nblk);
+    __syncthreads();
+    const int c = 1 + StepStats<NT>::NW * g + (int)(threadIdx.x >> 6);
+    if (c < 2 + 2 * st.d) {
+        const double v = ss.column(L, st.is_part, st.nblk, c);
+        if ((threadIdx.x & 63) == 0) st.cols[c] = v;
+    }
+}
 
 // The control block's part of c_t and recycling, read before it is needed.
 struct RecState {
@@ -142,27 +151,17 @@ __device__ inline void store_recycling(const RecNext &nx, double logc, double lo
     ctrl->logZ_prev = resampled ? 0.0 : logZ;
 }
 
-// Both by one thread.
-__device__ inline double recycle(Ctrl *ctrl, const RecState &r, double logZ, bool resampled,
-                                 double *bc)
+// Estimate k < 2 d: f_t (eq. estimation_at_t) and the recycled one, from the
+// sums' columns (1: the weights), the recycling's bc and rec_old = rec_num[k].
+__device__ inline void write_estimate(int k, int d, double sum, double weights, double rec_old,
+                                      const double *bc, double *rec_num, double *est)
 {
-    RecNext nx;
-    const double logc = recycle_step(r, logZ, bc, nx);
-    store_recycling(nx, logc, logZ, resampled, ctrl);
-    return logc;
-}
-
-// Estimates f_t (eq. estimation_at_t) and the recycled ones; threads k < 2 d,
-// rec_old = rec_num[k].
-__device__ inline void write_estimates(const StatsLds &L, int k, int d, double rec_old,
-                                       double *rec_num, double *est)
-{
-    const double f = L.col[2 + k] / L.col[1];
-    const double num = rec_old * L.bc[0] + L.bc[1] * f;
+    const double f = sum / weights;
+    const double num = rec_old * bc[0] + bc[1] * f;
     rec_num[k] = num;
     if (est) {
         est[k] = f;
-        est[2 * d + k] = num / L.bc[2];
+        est[2 * d + k] = num / bc[2];
     }
 }
 
@@ -208,15 +207,8 @@ __device__ inline void filter_stats(Ctrl *ctrl, const double *part, int nblk, in
         for (int i = 0; i < 3; ++i) s_bc[i] = bc[i];
     }
     __syncthreads();
-    if (tid < 2 * d) {
-        const double f = s_col[2 + tid] / s_col[1];
-        const double num = rec_old * s_bc[0] + s_bc[1] * f;
-        rec_num[tid] = num;
-        if (est) {
-            est[tid] = f;
-            est[2 * d + tid] = num / s_bc[2];
-        }
-    }
+    if (tid < 2 * d)
+        write_estimate(tid, d, s_col[2 + tid], s_col[1], rec_old, s_bc, rec_num, est);
 }
 
 }  // namespace smc
