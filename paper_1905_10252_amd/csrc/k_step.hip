@@ -39,8 +39,6 @@
 #include "stats.hpp"
 #include "step.hpp"
 
-static_assert(smc::kStatsMaxDim == smc::kMaxDim, "statistics width");
-
 namespace smc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

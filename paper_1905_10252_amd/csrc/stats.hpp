@@ -14,8 +14,6 @@
 
 namespace smc {
 
-constexpr int kStatsMaxDim = 64;
-
 // LDS of the statistics.
 struct StatsLds {
     double sc[kIsBlocks];  // scale of each block's sums

@@ -84,7 +84,7 @@ def test_resample_size_edges(smc, dev, n, kind):
 
 # rows of 4 w bytes at an address `off` values past a 16-byte boundary; the
 # populations take segments of 256, 512, 1024 and 2048 merge steps
-@pytest.mark.parametrize("n", [1, 255, 262144, 524289, 1048577])
+@pytest.mark.parametrize("n", [1, 255, 262144, 262145, 524289, 1048577])
 @pytest.mark.parametrize("w,off", [(1, 0), (2, 1), (4, 1), (5, 0), (7, 3), (8, 2), (9, 0), (11, 1),
                                    (16, 0), (33, 0)])
 def test_redistribute_row_edges(smc, dev, n, w, off):
