@@ -47,7 +47,6 @@ struct Work {
     u64 *pref64;        // [n / 64 + 1] every 64th tile-local prefix value
     // sampler state (NULL when no target)
     double *lp;         // [n] cached log-target of the current particles
-    double *lp_new;     // [n] proposal log-target (costly targets)
     double *x_scr;      // [n * d] redistribute destination
     double *lp_scr;     // [n]
     double *is_part;    // [kIsBlocks * (2 + 2d)] per-block estimate sums
@@ -117,7 +116,7 @@ hipError_t launch_weights(const Work &w, const double *lw, int64_t n, double *ou
 // smc_resample in one launch, for n <= kSmallResample (one workgroup; above, the
 // separate passes spread over the chip); slots: also clears the max slots of
 // the parity after par.
-constexpr int64_t kSmallResample = 8192;
+constexpr int64_t kSmallResample = 6144;
 hipError_t launch_small_resample(const Work &w, const double *lw, int64_t n, int K, uint64_t r,
                                  int mode, int ess_num, int ess_den, int par, bool slots,
                                  int64_t *ncopies, void *info, hipStream_t s);

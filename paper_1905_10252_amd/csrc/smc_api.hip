@@ -49,7 +49,7 @@ namespace {
 
 struct Layout {
     size_t ctrl, slots, tsum, tpart, pref, pref64;
-    size_t lp, lp_new, x_scr, lp_scr, is_part, cols, rec_num, epart;
+    size_t lp, x_scr, lp_scr, is_part, cols, rec_num, epart;
     size_t xs, thb, csum, xf, etab, lpart;
     int64_t mpad, npad;
     int dp;
@@ -100,14 +100,13 @@ Layout layout_of(const smc_config *c)
     L.tpart = take(sizeof(TilePart) * nt);
     L.pref = take(8 * n);
     L.pref64 = take(8 * (n / 64 + 1));
-    L.lp = L.lp_new = L.x_scr = L.lp_scr = L.is_part = L.cols = L.rec_num = L.epart = 0;
+    L.lp = L.x_scr = L.lp_scr = L.is_part = L.cols = L.rec_num = L.epart = 0;
     L.xs = L.thb = L.csum = L.xf = L.etab = L.lpart = 0;
     L.dp = (int)((d + 15) / 16 * 16);
     L.mpad = (c->m_rows + 31) / 32 * 32;
     L.npad = (int64_t)((n + 31) / 32 * 32);
     if (c->target != SMC_TARGET_NONE) {
         L.lp = take(8 * n);
-        L.lp_new = take(8 * n);
         L.x_scr = take(8 * n * d);
         L.lp_scr = take(8 * n);
         L.is_part = take(8 * (size_t)kIsBlocks * (2 + 2 * d));
@@ -217,7 +216,6 @@ smc_status smc_init(smc_ctx **h_out, const smc_config *h_cfg, void *workspace,
     w.tile_shift = tile_shift_of(h_cfg->n);
     const bool samp = h_cfg->target != SMC_TARGET_NONE;
     w.lp = samp ? reinterpret_cast<double *>(b + L.lp) : nullptr;
-    w.lp_new = samp ? reinterpret_cast<double *>(b + L.lp_new) : nullptr;
     w.x_scr = samp ? reinterpret_cast<double *>(b + L.x_scr) : nullptr;
     w.lp_scr = samp ? reinterpret_cast<double *>(b + L.lp_scr) : nullptr;
     w.is_part = samp ? reinterpret_cast<double *>(b + L.is_part) : nullptr;

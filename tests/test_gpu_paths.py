@@ -52,9 +52,10 @@ def weights(kind, n, seed):
     return I.logw_normal(n, float(kind), seed)
 
 
-# one launch up to 8192 weights (512 and 1024 threads), the separate passes above;
+# one launch up to 6144 weights (four, then eight a thread), the separate passes above;
 # tiles of 1024 weights below 2^20, of 4096 from there on
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 2047, 4095, 4096, 4097, 8191, 8192, 8193,
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 2047, 4095, 4096, 4097, 6143, 6144, 6145,
+                               8192,
                                (1 << 20) - 1, 1 << 20])
 @pytest.mark.parametrize("kind", ["equal", "one", "0.7", "8"])
 def test_resample_size_edges(smc, dev, n, kind):
