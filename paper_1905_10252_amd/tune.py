@@ -149,7 +149,10 @@ def tune_buckets(specs, *, device=None, steps: int = 4, pairs: int | None = None
             for w in range(1, _max_waves(q) + 1):
                 b.set_bucket_waves(q, w)
                 times[w] = _time_steps(b, steps)
-            best[q] = min(times, key=times.get)
+            # a lower aim takes the bucket out of the common launch: only for a gain
+            # beyond what two timings of one choice differ by
+            w, top = min(times, key=times.get), _max_waves(q)
+            best[q] = w if times[w] < 0.98 * times[top] else top
             b.set_bucket_waves(q, best[q])
             ms[q] = times
         del b
