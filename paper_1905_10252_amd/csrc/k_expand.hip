@@ -46,36 +46,6 @@ struct VecT<4> {
     typedef unsigned T;
 };
 
-// Values of a filter row (four FP64 values) that the threads of the row-summing
-// copy add up: each thread's chunks of VEC bytes all sit in the same place of
-// a row (the lane stride is a multiple of the row's chunks), so it keeps the
-// sums and the sums of squares of that place, each weighted by w.
-template <int VEC>
-struct RowAcc {
-    static constexpr int NV = VEC / 8 > 0 ? VEC / 8 : 1;  // values a chunk
-    double s[NV], q[NV], e;
-    __device__ void init()
-    {
-        e = 0.0;
-        for (int i = 0; i < NV; ++i) s[i] = q[i] = 0.0;
-    }
-    __device__ void add(const u32x4 &v, double w)
-    {
-        one(0, __hiloint2double((int)v.y, (int)v.x), w);
-        one(NV - 1, __hiloint2double((int)v.w, (int)v.z), w);
-    }
-    __device__ void add(const u32x2 &v, double w)
-    {
-        one(0, __hiloint2double((int)v.y, (int)v.x), w);
-    }
-    __device__ void one(int i, double x, double w)
-    {
-        const double wx = w * x;
-        s[i] += wx;
-        q[i] += wx * x;
-    }
-};
-
 // Copies np rows [p0, p0 + np) of dst from rows sAnc[] of src, VEC bytes per
 // lane access; consecutive lanes write consecutive addresses.  A thread's
 // chunks are 256 apart, so its (row, column) moves by a constant step and one
@@ -91,17 +61,13 @@ struct RowAcc {
 // s = 0.5 (HBM read requests are whole 128-byte lines either way).  Where a
 // few sources fill many outputs (heavy degeneracy) the cached reads are
 // faster, the same lines serving the whole segment.
-// kSum (rows of four FP64 values): also adds up the rows; lw (nullable): each
-// row weighted by exp(lw - m), otherwise by one.
 // kPow2: a row's chunks are a power of two up to 256, so a thread's column is
 // fixed.
-template <int VEC, bool kPow2, bool kSum, bool kNtLoad, bool kNtStore>
+template <int VEC, bool kPow2, bool kNtLoad, bool kNtStore>
 __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
                                    unsigned char *__restrict__ dst, int row_bytes, int cpr,
-                                   const unsigned *sAnc, i64 p0, int total, RowAcc<VEC> *acc,
-                                   const double *lw, double m)
+                                   const unsigned *sAnc, i64 p0, int total)
 {
-    static_assert(!kSum || VEC >= 8, "row sums take FP64 values");
     typedef typename VecT<VEC>::T V;
     const int dr = kExpandThreads / cpr, dc = kExpandThreads - dr * cpr;
     int r = (int)threadIdx.x / cpr, col = (int)threadIdx.x - r * cpr;
@@ -120,31 +86,19 @@ __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
         }
         return v;
     };
-    auto store = [&](const V &v, int c, int row) {
+    auto store = [&](const V &v, int c) {
         if (kNtStore) __builtin_nontemporal_store(v, d + c);
         else d[c] = v;
-        if constexpr (kSum) {
-            const double w = lw ? det_exp(lw[p0 + row] - m) : 1.0;
-            if (threadIdx.x % (32 / VEC) == 0) acc->e += w;
-            acc->add(v, w);
-        }
     };
     int c = threadIdx.x;
     for (; c + (U - 1) * kExpandThreads < total; c += U * kExpandThreads) {
         V v[U];
-        int row[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            row[u] = r;
-            v[u] = load();
-        }
+        for (int u = 0; u < U; ++u) v[u] = load();
 #pragma unroll
-        for (int u = 0; u < U; ++u) store(v[u], c + u * kExpandThreads, row[u]);
+        for (int u = 0; u < U; ++u) store(v[u], c + u * kExpandThreads);
     }
-    for (; c < total; c += kExpandThreads) {
-        const int row = r;
-        store(load(), c, row);
-    }
+    for (; c < total; c += kExpandThreads) store(load(), c);
 }
 
 // Rows of at least 16 bytes whose size or address is no multiple of 16: 16-byte
@@ -204,54 +158,16 @@ __device__ inline void copy_ragged(const unsigned char *__restrict__ src,
     }
 }
 
-template <int VEC, bool kSum, bool kNtLoad, bool kNtStore>
+template <int VEC, bool kNtLoad, bool kNtStore>
 __device__ inline void copy_rows(const unsigned char *__restrict__ src,
                                  unsigned char *__restrict__ dst, int row_bytes,
-                                 const unsigned *sAnc, i64 p0, int np,
-                                 RowAcc<VEC> *acc = nullptr, const double *lw = nullptr,
-                                 double m = 0.0)
+                                 const unsigned *sAnc, i64 p0, int np)
 {
     const int cpr = row_bytes / VEC;
-    if (kSum || ((cpr & (cpr - 1)) == 0 && cpr <= kExpandThreads))
-        copy_chunks<VEC, true, kSum, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0,
-                                                        np * cpr, acc, lw, m);
+    if ((cpr & (cpr - 1)) == 0 && cpr <= kExpandThreads)
+        copy_chunks<VEC, true, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0, np * cpr);
     else
-        copy_chunks<VEC, false, kSum, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0,
-                                                         np * cpr, acc, lw, m);
-}
-
-// Sums of the rows one workgroup wrote: lanes of equal index modulo the row's
-// chunks hold the same place of a row; their sums are combined in a fixed order
-// and written in the filter's estimate columns (column c of this workgroup at
-// out[c stride]: 0 the reference weight, 1 the sum of the weights, 2 + k the
-// sum of value k, 6 + k the sum of its square).
-template <int VEC>
-__device__ inline void store_row_sums(RowAcc<VEC> &acc, double ref, double *out, i64 stride)
-{
-    constexpr int NC = 32 / VEC, NV = RowAcc<VEC>::NV, NW = kExpandThreads / 64;
-    __shared__ double s_acc[NW][NC][2 * NV + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    double v[2 * NV + 1];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        v[i] = acc.s[i];
-        v[NV + i] = acc.q[i];
-    }
-    v[2 * NV] = acc.e;
-#pragma unroll
-    for (int i = 0; i < 2 * NV + 1; ++i)
-        for (int o = NC; o < 64; o <<= 1) v[i] += __shfl_xor(v[i], o, 64);
-    if (lane < NC)
-        for (int i = 0; i < 2 * NV + 1; ++i) s_acc[wid][lane][i] = v[i];
-    __syncthreads();
-    if (tid < kEstCols) {
-        const int k = (tid - 2) & 3;  // value
-        const int ch = tid < 2 ? 0 : k / NV;
-        const int i = tid < 2 ? 2 * NV : (tid >= 6 ? NV : 0) + k % NV;
-        double t = s_acc[0][ch][i];
-        for (int w = 1; w < NW; ++w) t += s_acc[w][ch][i];
-        out[tid * stride] = tid == 0 ? ref : t;
-    }
+        copy_chunks<VEC, false, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0, np * cpr);
 }
 
 struct ExpandArgs {
@@ -272,7 +188,6 @@ struct ExpandArgs {
     double *logw;       // a resampling iteration's weights, set to `reset` (nullable) ...
     double reset;
     unsigned *uniform;  // ... or marked uniform here instead (lazy reset, nullable)
-    double *est_part;   // kSum: [kEstCols][segments] sums of the rows written
     int stream;         // the new rows are written past the caches
 };
 
@@ -282,20 +197,18 @@ struct ExpandArgs {
 // A, marks, copy; 5.8 us at N = 1000).
 // SEG: merge steps of one workgroup.
 // kRagged: rows for copy_ragged (VEC does not matter then).
-template <int VEC, int SEG, bool kSum, bool kRagged>
+template <int VEC, int SEG, bool kRagged>
 __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
 {
     __shared__ SegLds<SEG> s_seg;
     unsigned *const sAnc = s_seg.anc;
     const int tid = threadIdx.x;
     AFun f;
-    bool failed = false;
     if (!make_afun(a.ctrl, a.pref, a.tpre, a.tsh, a.n, a.count_mode, f,
                    blockIdx.x == 0 && tid == 0)) {
         // an iteration that found an error resamples nothing: its proposal
         // still has to reach the caller's array
         if (a.mode != ExpandMode::kForward) return;
-        failed = true;
         f.mode = 0;
     }
     if (a.mode == ExpandMode::kIfResampled && f.mode == 0) return;
@@ -321,22 +234,7 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
     if (a.anc_out)
         for (int r = tid; r < np; r += kExpandThreads) a.anc_out[p0 + r] = (i64)sAnc[r];
     const bool distinct = np < 2 * ns;  // fewer than two outputs per source in this segment
-    if constexpr (kSum) {
-        RowAcc<VEC> acc;
-        acc.init();
-        // the filter's mean of the new population: equal weights when it
-        // resampled, the current ones against the exact max otherwise
-        const double *lw = f.mode == 0 && !failed ? a.logw : nullptr;
-        const double m = lw ? a.ctrl->m : a.reset;
-        if (a.stream && distinct)
-            copy_rows<VEC, true, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
-        else if (a.stream)
-            copy_rows<VEC, true, false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
-        else
-            copy_rows<VEC, true, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np, &acc, lw, m);
-        store_row_sums(acc, failed ? -__builtin_huge_val() : m, a.est_part + blockIdx.x,
-                       gridDim.x);
-    } else if constexpr (kRagged) {
+    if constexpr (kRagged) {
         if (a.stream && distinct)
             copy_ragged<true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
         else if (a.stream)
@@ -344,24 +242,24 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
         else
             copy_ragged<false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream && distinct) {
-        copy_rows<VEC, false, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        copy_rows<VEC, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream) {
-        copy_rows<VEC, false, false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        copy_rows<VEC, false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else {
-        copy_rows<VEC, false, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        copy_rows<VEC, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     }
-    if (a.aux) copy_rows<8, false, false, false>(a.aux, a.auxo, 8, sAnc, p0, np);
+    if (a.aux) copy_rows<8, false, false>(a.aux, a.auxo, 8, sAnc, p0, np);
 }
 
-template <int VEC, bool kSum, bool kRagged = false>
+template <int VEC, bool kRagged = false>
 static void launch_expand_seg(int seg, int64_t n, hipStream_t s, const ExpandArgs &a)
 {
     const dim3 g((unsigned)((2 * n + seg - 1) / seg)), b(kExpandThreads);
     switch (seg) {
-    case 256: hipLaunchKernelGGL((k_expand<VEC, 256, kSum, kRagged>), g, b, 0, s, a); break;
-    case 512: hipLaunchKernelGGL((k_expand<VEC, 512, kSum, kRagged>), g, b, 0, s, a); break;
-    case 1024: hipLaunchKernelGGL((k_expand<VEC, 1024, kSum, kRagged>), g, b, 0, s, a); break;
-    default: hipLaunchKernelGGL((k_expand<VEC, kSegLen, kSum, kRagged>), g, b, 0, s, a); break;
+    case 256: hipLaunchKernelGGL((k_expand<VEC, 256, kRagged>), g, b, 0, s, a); break;
+    case 512: hipLaunchKernelGGL((k_expand<VEC, 512, kRagged>), g, b, 0, s, a); break;
+    case 1024: hipLaunchKernelGGL((k_expand<VEC, 1024, kRagged>), g, b, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_expand<VEC, kSegLen, kRagged>), g, b, 0, s, a); break;
     }
 }
 
@@ -387,23 +285,13 @@ hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x
     a.logw = o.logw;
     a.reset = o.reset;
     a.uniform = o.uniform;
-    a.est_part = o.est_part;
     a.stream = n * (int64_t)row_bytes >= kStreamBytes;
     const uintptr_t al = (uintptr_t)x | (uintptr_t)x_out | (uintptr_t)row_bytes;
     const int seg = expand_seg_len(n);
-    if (o.est_part) {
-        if ((al & 7) != 0 || row_bytes != 32) return hipErrorInvalidValue;
-        if ((al & 15) == 0) launch_expand_seg<16, true>(seg, n, s, a);
-        else launch_expand_seg<8, true>(seg, n, s, a);
-    } else if ((al & 15) == 0) {
-        launch_expand_seg<16, false>(seg, n, s, a);
-    } else if (row_bytes >= 16) {
-        launch_expand_seg<16, false, true>(seg, n, s, a);
-    } else if ((al & 7) == 0) {
-        launch_expand_seg<8, false>(seg, n, s, a);
-    } else {
-        launch_expand_seg<4, false>(seg, n, s, a);
-    }
+    if ((al & 15) == 0) launch_expand_seg<16>(seg, n, s, a);
+    else if (row_bytes >= 16) launch_expand_seg<16, true>(seg, n, s, a);
+    else if ((al & 7) == 0) launch_expand_seg<8>(seg, n, s, a);
+    else launch_expand_seg<4>(seg, n, s, a);
     return hipGetLastError();
 }
 

@@ -14,10 +14,10 @@
 //                       targets': k_decide).
 //   k_is<BEARING>       one SIR particle-filter update (Alg 1, Sec. 5.2.2):
 //                       constant-velocity transition as proposal, bearing
-//                       likelihood as weight; the expand then adds up the rows
-//                       it writes for the mean of the resampled population.
-//   k_filter_step       inside a call of several iterations: that expand and the
-//                       next update in one pass.
+//                       likelihood as weight.
+//   k_filter_step       its redistribution, with the mean of the resampled
+//                       population; inside a call of several iterations the
+//                       next update too, in the same pass.
 //   k_small_step        a whole iteration of a small population.
 //   k_logreg_f64 / k_logreg_bf16 + k_logreg_sum
 //                       Bayesian logistic regression log-likelihood
@@ -390,7 +390,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // of the one and the update of the next (step t) in one pass over the rows.  Each
 // workgroup takes a segment of the merge path; a particle is read from its
 // source's row, counted in the mean of the resampled population, moved, weighted
-// and written once.  The population in between is never stored: 64 bytes a
+// and written once (kMove false, the last iteration of a call: counted and written
+// as it is, with its reset weight).  The population in between is never stored: 64 bytes a
 // particle less, and a launch (35.0 us at N = 2^20; redistribution 21.6 us and
 // update 25.7 us as kernels of their own).  Bound by vector issue, the normals
 // foremost.  An iteration that kept its weights or found an error moves each
@@ -406,9 +407,10 @@ struct FilterArgs {
     double *logw;
     u64 *slots_p;
     double *est_part;  // [kEstCols][segments]
+    unsigned *uniform; // kMove false: the mark set instead of writing reset weights
 };
 
-template <int SEG>
+template <int SEG, bool kMove>
 __global__ __launch_bounds__(kExpandThreads) __attribute__((amdgpu_waves_per_eu(4))) void
 k_filter_step(TArgs a, FilterArgs g)
 {
@@ -448,11 +450,13 @@ k_filter_step(TArgs a, FilterArgs g)
         const double st[4] = {xs[0], xs[1], xs[2], xs[3]};
         double lw = kept && act ? g.logw[i] : a.reset;
         asm volatile("" ::: "memory");
-        const uint32_t idx[2] = {(uint32_t)i, (uint32_t)i}, pair[2] = {0u, 1u};
-        const bool act2[2] = {act, act};
         double z[4];
-        normal_pairs_wave<2>(a.seed, kTagPropose, a.sampler, g.t, idx, pair, 2, act2, z,
-                             L.m.xch[wid]);
+        if constexpr (kMove) {
+            const uint32_t idx[2] = {(uint32_t)i, (uint32_t)i}, pair[2] = {0u, 1u};
+            const bool act2[2] = {act, act};
+            normal_pairs_wave<2>(a.seed, kTagPropose, a.sampler, g.t, idx, pair, 2, act2, z,
+                                 L.m.xch[wid]);
+        }
         if (!act) continue;
         const double w = kept && !failed ? det_exp(lw - m) : 1.0;
         se += w;
@@ -462,13 +466,17 @@ k_filter_step(TArgs a, FilterArgs g)
             s1[k] += wx;
             s2[k] += wx * st[k];
         }
-        double nx[4];
-        lw = bearing_move(a, g.t, st, z, lw, nx);
+        double nx[4] = {st[0], st[1], st[2], st[3]};
+        if constexpr (kMove) lw = bearing_move(a, g.t, st, z, lw, nx);
         double *xw = g.xo + i * 4;
         xw[0] = nx[0];
         xw[1] = nx[1];
         xw[2] = nx[2];
         xw[3] = nx[3];
+        if constexpr (!kMove) {
+            if (!kept && !g.uniform) g.logw[i] = lw;
+            continue;
+        }
         g.logw[i] = lw;
         mx = fmax(mx, lw);
         if (!(lw < __builtin_huge_val())) {  // NaN or +inf
@@ -486,7 +494,8 @@ k_filter_step(TArgs a, FilterArgs g)
         L.red[k][tid] = s1[k];
         L.red[4 + k][tid] = s2[k];
     }
-    const u64 bk = block_max_key(key, bad);
+    u64 bk = 0;
+    if constexpr (kMove) bk = block_max_key(key, bad);
     __syncthreads();
     {
         const int c = tid >> 5, l = tid & 31;  // 32 threads a column
@@ -501,7 +510,8 @@ k_filter_step(TArgs a, FilterArgs g)
             out[gridDim.x] = (s_e[0] + s_e[1]) + (s_e[2] + s_e[3]);
         }
     }
-    slot_publish(g.slots_p, bk, bad);
+    if constexpr (kMove) slot_publish(g.slots_p, bk, bad);
+    else if (!kept && g.uniform && blockIdx.x == 0 && tid == 0) *g.uniform = 1u;
 }
 
 // ------------------------------------------------ rows of several coordinates
@@ -1723,10 +1733,11 @@ smc_status small_step(const smc_config &c, const Work &w, int K, int par, uint32
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
-// The filter's row sums of an iteration (nseg rows), in at most kIsBlocks rows.
-static StatsArgs filter_sums(const smc_config &c, const Work &w, int64_t nseg, double *est,
+// The filter's row sums of an iteration, in at most kIsBlocks rows.
+static StatsArgs filter_sums(const smc_config &c, const Work &w, double *est,
                              smc_resample_info *info, hipStream_t s)
 {
+    const int64_t nseg = filter_segments(c.n);
     const bool fold = nseg > kIsBlocks;
     if (fold)
         hipLaunchKernelGGL(k_fold_rows, dim3(kFoldBlocks), dim3(64), 0, s, w.epart, (i64)nseg,
@@ -1741,31 +1752,14 @@ static StatsArgs filter_sums(const smc_config &c, const Work &w, int64_t nseg, d
     return st;
 }
 
-// Where a resampling iteration's weights go.
-static void reset_weights(const smc_config &c, const Work &w, double *logw, ExpandOut &o)
+// Where a resampling iteration's weights go instead of logw (lazy reset);
+// populations of at most kSmallN particles always write them.
+static unsigned *uniform_mark(const smc_config &c, const Work &w)
 {
-    o.logw = logw;
-    o.reset = -std::log((double)c.n);
-    // populations of at most kSmallN particles always write their weights
-    o.uniform = c.lazy_reset && c.n > kSmallN ? &w.ctrl->uniform : nullptr;
+    return c.lazy_reset && c.n > kSmallN ? &w.ctrl->uniform : nullptr;
 }
 
-// The end of a filter iteration: the redistribution into x, and the mean, which
-// Alg 1 takes after resampling.
-static smc_status filter_finish(const smc_config &c, const Work &w, double *x, double *logw,
-                                double *est, smc_resample_info *info, hipStream_t s)
-{
-    ExpandOut o;
-    o.mode = ExpandMode::kForward;
-    reset_weights(c, w, logw, o);
-    o.est_part = w.epart;
-    if (launch_expand(w, c.n, 0, w.x_scr, x, c.d * 8, s, o) != hipSuccess) return SMC_E_DEVICE;
-    const StatsArgs st = filter_sums(c, w, expand_segments(c.n), est, info, s);
-    hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, st.is_part, st.nblk, c.d,
-                       w.rec_num, est, info);
-    return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
-}
-
+template <bool kMove>
 static hipError_t launch_filter_step(const smc_config &c, const Work &w, int par, uint32_t t,
                                      const double *x, double *xo, double *logw, hipStream_t s)
 {
@@ -1782,14 +1776,28 @@ static hipError_t launch_filter_step(const smc_config &c, const Work &w, int par
     g.logw = logw;
     g.slots_p = w.slots + (par & 1) * kSlots * kSlotStride;
     g.est_part = w.epart;
+    g.uniform = uniform_mark(c, w);
     const int seg = filter_seg_len(c.n);
-    auto kern = seg == 256    ? k_filter_step<256>
-                : seg == 512  ? k_filter_step<512>
-                : seg == 1024 ? k_filter_step<1024>
-                              : k_filter_step<kSegLen>;
+    auto kern = seg == 256    ? k_filter_step<256, kMove>
+                : seg == 512  ? k_filter_step<512, kMove>
+                : seg == 1024 ? k_filter_step<1024, kMove>
+                              : k_filter_step<kSegLen, kMove>;
     hipLaunchKernelGGL(kern, dim3((unsigned)filter_segments(c.n)), dim3(kExpandThreads), 0, s,
                        targs(c, w, false), g);
     return hipGetLastError();
+}
+
+// The end of a filter iteration: the redistribution into x, and the mean, which
+// Alg 1 takes after resampling (the same sums in the same order as inside a call).
+static smc_status filter_finish(const smc_config &c, const Work &w, double *x, double *logw,
+                                double *est, smc_resample_info *info, hipStream_t s)
+{
+    if (launch_filter_step<false>(c, w, 0, 0, w.x_scr, x, logw, s) != hipSuccess)
+        return SMC_E_DEVICE;
+    const StatsArgs st = filter_sums(c, w, est, info, s);
+    hipLaunchKernelGGL(k_step_stats, dim3(1), dim3(1024), 0, s, w.ctrl, st.is_part, st.nblk, c.d,
+                       w.rec_num, est, info);
+    return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
 }
 
 // Several iterations of the particle filter: the rows go back and forth between x
@@ -1810,9 +1818,9 @@ static smc_status filter_run_n(const smc_config &c, const Work &w, int K, int pa
                 return SMC_E_DEVICE;
         } else {
             double *from = to_copy ? x : w.x_scr, *to = to_copy ? w.x_scr : x;
-            if (launch_filter_step(c, w, par, t, from, to, logw, s) != hipSuccess)
+            if (launch_filter_step<true>(c, w, par, t, from, to, logw, s) != hipSuccess)
                 return SMC_E_DEVICE;
-            tail = filter_sums(c, w, filter_segments(c.n), est ? est + (int64_t)(i - 1) * 4 * c.d : nullptr,
+            tail = filter_sums(c, w, est ? est + (int64_t)(i - 1) * 4 * c.d : nullptr,
                                info ? info + (i - 1) : nullptr, s);
         }
         if (launch_quant_scan(w, logw, c.n, K, par, s, c.lazy_reset != 0, tail) != hipSuccess)
@@ -1879,7 +1887,9 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     if (pf) return filter_finish(c, w, x, logw, est, info, s);
     ExpandOut o;
     o.mode = fwd ? ExpandMode::kForward : ExpandMode::kIfResampled;
-    reset_weights(c, w, logw, o);
+    o.logw = logw;
+    o.reset = -std::log((double)n);
+    o.uniform = uniform_mark(c, w);
     // the 1-D Gaussian and Student-t samplers carry no cached log-target
     if (!(c.d == 1 && (c.target == SMC_TARGET_GAUSS || c.target == SMC_TARGET_STUDENT))) {
         o.aux = w.lp_scr;

@@ -52,7 +52,7 @@ struct Work {
     double *is_part;    // [kIsBlocks * (2 + 2d)] per-block estimate sums
     double *cols;       // [2 + 2d] the same, folded over the blocks
     double *rec_num;    // [2d] recycled estimate sums
-    double *epart;      // particle filter: [kEstCols][expand segments] row sums of the
+    double *epart;      // particle filter: [kEstCols][filter_segments] row sums of the
                         // redistributed rows (NULL otherwise)
     // logistic regression (NULL otherwise)
     unsigned short *xs;   // [mpad][dp] bf16 X times (1 - 2 y), in MFMA operand order
@@ -134,12 +134,6 @@ inline int expand_seg_len(int64_t n)
     while (seg < kSegLen && 2 * n > 2048ll * seg) seg <<= 1;
     return seg;
 }
-inline int64_t expand_segments(int64_t n)
-{
-    const int seg = expand_seg_len(n);
-    return (2 * n + seg - 1) / seg;
-}
-
 // The same for the filter's fused iteration, whose workgroups hold their CU longer:
 // four per CU (N = 2^20: 34.4 us with 2048 steps, 38.6 with 1024; N = 2^19: 24.6,
 // 22.7 with 1024, 25.3 with 512; N = 2^17: 13.0 with 512, 12.8 with 256).
@@ -149,7 +143,7 @@ inline int filter_seg_len(int64_t n)
     while (seg > 256 && 2 * n < 1024ll * seg) seg >>= 1;
     return seg;
 }
-inline int64_t filter_segments(int64_t n)  // at most expand_segments(n): they share epart
+inline int64_t filter_segments(int64_t n)
 {
     const int seg = filter_seg_len(n);
     return (2 * n + seg - 1) / seg;
@@ -170,9 +164,6 @@ struct ExpandOut {
     double *logw = nullptr;     // weights set to `reset` where the decision resampled,
     double reset = 0.0;         //   or the flag `uniform` set instead (lazy reset)
     unsigned *uniform = nullptr;
-    // rows of four FP64 values only: per workgroup the weighted sums of the
-    // rows it wrote, kEstCols columns of expand_segments(n)
-    double *est_part = nullptr;
 };
 hipError_t launch_expand(const Work &w, int64_t n, int count_mode, const void *x, void *x_out,
                          int row_bytes, hipStream_t s, const ExpandOut &o);

@@ -113,7 +113,7 @@ Layout layout_of(const smc_config *c)
         L.cols = take(8 * (2 + 2 * d));
         L.rec_num = take(8 * 2 * d);
         if (c->target == SMC_TARGET_BEARING)
-            L.epart = take(8 * (size_t)kEstCols * (size_t)expand_segments(c->n));
+            L.epart = take(8 * (size_t)kEstCols * (size_t)filter_segments(c->n));
         if (c->target == SMC_TARGET_LOGREG) {
             L.lpart = take(8 * (size_t)kLogregSplit * n);
             L.csum = take(8 * (size_t)L.dp);
