@@ -19,6 +19,8 @@
 // marks its first output, and a max-scan over the outputs carries the marks.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "../../include/smc.h"
 #include "afun.hpp"
 #include "common.hpp"
@@ -61,9 +63,15 @@ struct VecT<4> {
 // s = 0.5 (HBM read requests are whole 128-byte lines either way).  Where a
 // few sources fill many outputs (heavy degeneracy) the cached reads are
 // faster, the same lines serving the whole segment.
+// kNtTail: so are the rows at the end of the segment, past the last whole round
+// of loads.  The lines they lie in are shared with the next segment, whose
+// workgroup reads them at about the same time: through the caches they come
+// from HBM once (rows of 32 bytes, s = 2, N = 2^23: 110 us streamed, 104 cached).
+// Populations whose prefix fills the memory-side cache by itself (kTailStreamN)
+// take them streamed (N = 2^25: 413 us streamed, 421 cached).
 // kPow2: a row's chunks are a power of two up to 256, so a thread's column is
 // fixed.
-template <int VEC, bool kPow2, bool kNtLoad, bool kNtStore>
+template <int VEC, bool kPow2, bool kNtLoad, bool kNtStore, bool kNtTail>
 __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
                                    unsigned char *__restrict__ dst, int row_bytes, int cpr,
                                    const unsigned *sAnc, i64 p0, int total)
@@ -73,9 +81,9 @@ __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
     int r = (int)threadIdx.x / cpr, col = (int)threadIdx.x - r * cpr;
     constexpr int U = VEC == 4 ? 8 : 4;  // loads in flight a thread
     V *d = reinterpret_cast<V *>(dst + p0 * (i64)row_bytes);
-    auto load = [&]() {  // the chunk at (r, col), then on to the thread's next
+    auto load = [&](auto nt) {  // the chunk at (r, col), then on to the thread's next
         const V *sp = reinterpret_cast<const V *>(src + (i64)sAnc[r] * row_bytes) + col;
-        const V v = kNtLoad ? __builtin_nontemporal_load(sp) : *sp;
+        const V v = decltype(nt)::value ? __builtin_nontemporal_load(sp) : *sp;
         r += dr;
         if (!kPow2) {
             col += dc;
@@ -94,11 +102,11 @@ __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
     for (; c + (U - 1) * kExpandThreads < total; c += U * kExpandThreads) {
         V v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = load();
+        for (int u = 0; u < U; ++u) v[u] = load(std::bool_constant<kNtLoad>());
 #pragma unroll
         for (int u = 0; u < U; ++u) store(v[u], c + u * kExpandThreads);
     }
-    for (; c < total; c += kExpandThreads) store(load(), c);
+    for (; c < total; c += kExpandThreads) store(load(std::bool_constant<kNtTail>()), c);
 }
 
 // Rows of at least 16 bytes whose size or address is no multiple of 16: 16-byte
@@ -158,16 +166,18 @@ __device__ inline void copy_ragged(const unsigned char *__restrict__ src,
     }
 }
 
-template <int VEC, bool kNtLoad, bool kNtStore>
+template <int VEC, bool kNtLoad, bool kNtStore, bool kNtTail = false>
 __device__ inline void copy_rows(const unsigned char *__restrict__ src,
                                  unsigned char *__restrict__ dst, int row_bytes,
                                  const unsigned *sAnc, i64 p0, int np)
 {
     const int cpr = row_bytes / VEC;
     if ((cpr & (cpr - 1)) == 0 && cpr <= kExpandThreads)
-        copy_chunks<VEC, true, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0, np * cpr);
+        copy_chunks<VEC, true, kNtLoad, kNtStore, kNtTail>(src, dst, row_bytes, cpr, sAnc, p0,
+                                                           np * cpr);
     else
-        copy_chunks<VEC, false, kNtLoad, kNtStore>(src, dst, row_bytes, cpr, sAnc, p0, np * cpr);
+        copy_chunks<VEC, false, kNtLoad, kNtStore, kNtTail>(src, dst, row_bytes, cpr, sAnc, p0,
+                                                            np * cpr);
 }
 
 struct ExpandArgs {
@@ -227,7 +237,10 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
         }
     }
 
-    segment_map<SEG>(f, g, s_seg);
+    // the longest segments take several trips over their sources, each waiting for its
+    // prefix values if they are requested one at a time (rows of 32 bytes, s = 0.5,
+    // N = 2^23: 112 us, 107 now); the shorter ones, one or two trips, lose by it
+    segment_map<SEG, SEG == kSegLen ? 4 : 1>(f, g, s_seg);
     if (a.nc_out)
         for (int i = tid; i < ns; i += kExpandThreads)
             a.nc_out[g.j0 + i] = (i64)s_seg.A[i + 1] - (i64)s_seg.A[i];
@@ -241,6 +254,8 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
             copy_ragged<false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
         else
             copy_ragged<false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+    } else if (a.stream && distinct && SEG == kSegLen && a.n >= kTailStreamN) {
+        copy_rows<VEC, true, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream && distinct) {
         copy_rows<VEC, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream) {

@@ -103,8 +103,9 @@ __device__ inline Segment segment_cut(const AFun &f, const u64 *pref64, SegLds<S
 }
 
 // Into L.A: A of the sources before, between and in the segment; into L.anc: the
-// source of each output of the segment (any valid one past np).
-template <int SEG>
+// source of each output of the segment (any valid one past np).  U prefix values
+// are requested at a time.
+template <int SEG, int U = 1>
 __device__ inline void segment_map(const AFun &f, const Segment &g, SegLds<SEG> &L)
 {
     unsigned *const sA = L.A, *const sAnc = L.anc;
@@ -119,8 +120,25 @@ __device__ inline void segment_map(const AFun &f, const Segment &g, SegLds<SEG> 
         const int skip = j0 == 0 ? 1 : 0;  // A before the first source is 0
         const i64 jb = j0 - 1 + skip;
         if (skip && tid == 0) sA[0] = 0u;
-        for (int i = tid; i <= ns - skip; i += kExpandThreads)
-            sA[i + skip] = f.A_of(0, f.at(jb + i));
+        const int last = ns - skip;
+        if constexpr (U == 1) {
+            for (int i = tid; i <= last; i += kExpandThreads)
+                sA[i + skip] = f.A_of(0, f.at(jb + i));
+        } else {
+            for (int i0 = tid; i0 <= last; i0 += U * kExpandThreads) {
+                u64 s[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = i0 + u * kExpandThreads;
+                    s[u] = f.at(jb + (i <= last ? i : i0));
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = i0 + u * kExpandThreads;
+                    if (i <= last) sA[i + skip] = f.A_of(0, s[u]);
+                }
+            }
+        }
     }
     for (int r = tid; r < np; r += kExpandThreads) sAnc[r] = 0u;
     __syncthreads();

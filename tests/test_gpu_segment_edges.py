@@ -1,0 +1,38 @@
+"""Rows at the ends of the redistribution's segments, for the populations that are
+written past the caches: the rows past a segment's last whole round of loads take
+another route than the others, and a third one from 2^25 particles on."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def smc():
+    from paper_1905_10252_amd import smc
+    return smc
+
+
+@pytest.mark.parametrize("n,row_bytes", [
+    ((1 << 20) + 37, 128),     # whole 16-byte chunks, a power of two a row
+    (1398101 + 2, 96),         # six chunks a row
+    ((1 << 22) + 1, 32),       # two chunks a row
+    ((1 << 24) + 3, 8),        # 8-byte rows
+    ((1 << 25) - 1, 16),       # last size of the common route
+    (1 << 25, 16),             # first of the other
+    ((1 << 25) + 5, 16),
+])
+@pytest.mark.parametrize("s", [0.5, 2.0, 8.0])
+def test_streamed_rows(smc, dev, n, row_bytes, s):
+    import torch
+    print("streamed rows", n, row_bytes, s, flush=True)
+    g = torch.Generator(device=dev).manual_seed(n + row_bytes)
+    logw = s * torch.randn(n, generator=g, device=dev, dtype=torch.float64)
+    x = torch.randint(-2**31, 2**31 - 1, (n, row_bytes // 4), generator=g, device=dev,
+                      dtype=torch.int32)
+    R = smc.Resampler(n)
+    nc = torch.empty(n, dtype=torch.int64, device=dev)
+    R.resample(logw, 0x9E3779B97F4A7C15, smc.L.MODE_FORCE, ncopies=nc)
+    got = R.redistribute(x)
+    assert R.sync_error() == 0
+    assert int(nc.sum()) == n and int(nc.min()) >= 0
+    assert torch.equal(got, x.repeat_interleave(nc, 0))
