@@ -1,11 +1,11 @@
 // Sampler kernels of Alg 2 (SMC sampler with recycling), random-walk proposal
 // and backward kernel L = q (so the incremental weight is pi(x_t)/pi(x_{t-1}),
 // eq. smcs_drawing_weights):
-//   k_is<target, init>  one-coordinate particles: draws x0 ~ q0 or
+//   k_is<target, init>  particles of one or two coordinates: draws x0 ~ q0 or
 //                       x_t = x_{t-1} + rw_sd z, evaluates the target, updates
 //                       the log-weights, and leaves per block estimate sums
 //                       (against a block reference) and the grid max.
-//   k_rows              the same for rows of several coordinates, and the
+//   k_rows              the same for longer rows, and the
 //                       weight update of the logistic regression after its
 //                       proposal (k_propose) and likelihood kernels.
 //   k_step_stats        estimates f_t (eq. estimation_at_t), c_t
@@ -74,7 +74,7 @@ constexpr double kLog2e = 1.4426950408889634;
 constexpr double kLn2 = 0.6931471805599453;
 
 // ------------------------------------------------------------------ partials
-// Estimate sums of the 1-D updates, in one pass: each thread keeps
+// Estimate sums of k_is (D coordinates), in one pass: each thread keeps
 // a reference and sums e = exp(l - ref), so the rows are read once; blocks
 // combine the thread references by det_exp rescaling.  The reference is the
 // first finite weight and moves (rescaling the sums) only when a weight exceeds
@@ -83,68 +83,78 @@ constexpr double kLn2 = 0.6931471805599453;
 // maximum, which in a wave of 64 lanes happened on most iterations.
 constexpr double kOnlineSlack = 64.0;
 
+template <int D>
 struct Online {
-    double m, e0, e1, e2;
+    double m, e0, e1[D], e2[D];
     __device__ void init()
     {
         m = -__builtin_huge_val();
-        e0 = e1 = e2 = 0.0;
+        e0 = 0.0;
+        for (int k = 0; k < D; ++k) e1[k] = e2[k] = 0.0;
     }
-    __device__ void add(double lw, double xv)
+    __device__ void sum(double e, const double *xv)
+    {
+        e0 += e;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            const double ex = e * xv[k];
+            e1[k] += ex;
+            e2[k] += ex * xv[k];
+        }
+    }
+    __device__ void add(double lw, const double *xv)
     {
         if (!(lw > -__builtin_huge_val())) return;  // zero weight, or NaN (flagged elsewhere)
         if (lw > m + kOnlineSlack) {
             if (m > -__builtin_huge_val()) {
                 const double sc = det_exp(m - lw);
                 e0 *= sc;
-                e1 *= sc;
-                e2 *= sc;
+                for (int k = 0; k < D; ++k) {
+                    e1[k] *= sc;
+                    e2[k] *= sc;
+                }
             }
             m = lw;
         }
-        const double e = det_exp(lw - m);
-        e0 += e;
-        const double ex = e * xv;
-        e1 += ex;
-        e2 += ex * xv;
+        sum(det_exp(lw - m), xv);
     }
-    // Two particles: their exponentials share the polynomial's coefficients.
-    // A zero weight (or NaN) and a weight that moves the reference take the
-    // one-by-one form.
+    // Two particles of one coordinate: their exponentials share the polynomial's
+    // coefficients.  A zero weight (or NaN) and a weight that moves the reference
+    // take the one-by-one form.
     __device__ void add2(const double (&lw)[2], const double (&xv)[2])
     {
+        static_assert(D == 1, "one coordinate a particle");
         const double hi = m + kOnlineSlack;
         if (!(lw[0] > -__builtin_huge_val() && lw[1] > -__builtin_huge_val() && lw[0] <= hi &&
               lw[1] <= hi)) {
-            add(lw[0], xv[0]);
-            add(lw[1], xv[1]);
+            add(lw[0], xv);
+            add(lw[1], xv + 1);
             return;
         }
         const double a[2] = {lw[0] - m, lw[1] - m};
         double e[2];
         det_exp_w<2>(a, e);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            e0 += e[h];
-            const double ex = e[h] * xv[h];
-            e1 += ex;
-            e2 += ex * xv[h];
-        }
+        sum(e[0], xv);
+        sum(e[1], xv + 1);
     }
     // Block combine into the block's partial row (columns at stride gridDim.x).
     __device__ void finish(double *is_part)
     {
-        __shared__ double s_m[4], s_acc[4][3];
+        constexpr int C = 1 + 2 * D;
+        __shared__ double s_m[4], s_acc[4][C];
         const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
         const double mw = wave_max_f64(m);
         const double sc = m > -__builtin_huge_val() ? det_exp(m - mw) : 0.0;
-        const double a0 = wave_sum_f64(e0 * sc), a1 = wave_sum_f64(e1 * sc),
-                     a2 = wave_sum_f64(e2 * sc);
+        double a[C];
+        a[0] = wave_sum_f64(e0 * sc);
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            a[1 + k] = wave_sum_f64(e1[k] * sc);
+            a[1 + D + k] = wave_sum_f64(e2[k] * sc);
+        }
         if (lane == 0) {
             s_m[wid] = mw;
-            s_acc[wid][0] = a0;
-            s_acc[wid][1] = a1;
-            s_acc[wid][2] = a2;
+            for (int c = 0; c < C; ++c) s_acc[wid][c] = a[c];
         }
         __syncthreads();
         if (tid == 0) {
@@ -155,7 +165,7 @@ struct Online {
                 scw[w] = s_m[w] > -__builtin_huge_val() ? det_exp(s_m[w] - mb) : 0.0;
             double *part = is_part + blockIdx.x;
             part[0] = mb;
-            for (int c = 0; c < 3; ++c) {
+            for (int c = 0; c < C; ++c) {
                 double v = 0.0;
                 for (int w = 0; w < 4; ++w) v += scw[w] * s_acc[w][c];
                 part[(i64)(1 + c) * gridDim.x] = v;
@@ -166,9 +176,12 @@ struct Online {
 
 // ------------------------------------------------------- proposal + weights
 typedef double f64x2s __attribute__((ext_vector_type(2)));
-// The update of one-coordinate particles (Gaussian and Student-t targets, the
-// estimate sums in the same pass) and of the particle filter, which takes its
-// estimate after resampling.  k_rows below is the update of longer rows.
+// The update of particles of one or two coordinates (kD; Gaussian and Student-t
+// targets, the estimate sums in the same pass) and of the particle filter, which
+// takes its estimate after resampling.  k_rows below is the update of longer rows:
+// a particle that is one pair leaves it nothing to spread over the lanes, and its
+// LDS passes cost more than they save (N = 2^20, two coordinates: 39 us there, 25
+// here).
 // Where the proposal goes.  kToCopy: to the workspace copy xo; the
 // redistribution then maps it into x.  kToBoth: to x, and to xo as well, from
 // which a resampling redistribution writes x; an iteration that keeps its
@@ -197,10 +210,11 @@ __device__ inline double bearing_move(const TArgs &a, uint32_t t, const double (
     return lw + (a.obs_log_norm - 0.5 * ((e * e) * a.obs_prec));
 }
 
-template <int kKind, bool kInit, Dst kDst>
+template <int kKind, bool kInit, Dst kDst, int kD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_is(
     TArgs a, i64 n, uint32_t t, double *__restrict__ x, double *__restrict__ logw,
-    double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo)
+    double *__restrict__ lp, u64 *slots_p, double *is_part, double *__restrict__ xo,
+    double *__restrict__ lpo)
 {
     constexpr bool kFilter = kKind == SMC_TARGET_BEARING;
     __shared__ uint4 s_xch[4][64];  // normal generator exchange, one row per wave
@@ -212,7 +226,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     u64 key = 0;
     unsigned bad = 0;
     double mx = -__builtin_huge_val();  // largest weight seen
-    Online on;
+    Online<kD> on;
     on.init();
     // the largest weight, and a flag for NaN or +inf (never on a sound path)
     auto note = [&](double lw) {
@@ -249,7 +263,62 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             SMC_EACH lpv[w] = a.log_norm - a.hnu1 * lg[w];
         }
     };
-    if constexpr (!kFilter) {
+    if constexpr (kD == 2) {
+        // Two coordinates: one pair and one row of 16 bytes a particle.
+        static_assert(kKind == SMC_TARGET_GAUSS, "the only target of two coordinates here");
+        const bool v2 = (((uintptr_t)x | (uintptr_t)xo) & 15) == 0;
+        for (i64 base = gtid - (tid & 63); base < n; base += gsz) {
+            const i64 i = base + (tid & 63);
+            const bool act = i < n;
+            const i64 ic = act ? i : n - 1;
+            // requested before the normals are drawn, as below
+            double xk[2] = {a.init_mean, a.init_mean}, lw_old = a.reset, lp_old = 0.0;
+            if (!kInit) {
+                if (v2) {
+                    const f64x2s v = *reinterpret_cast<const f64x2s *>(x + 2 * ic);
+                    xk[0] = v[0];
+                    xk[1] = v[1];
+                } else {
+                    xk[0] = x[2 * ic];
+                    xk[1] = x[2 * ic + 1];
+                }
+                if (!uni) lw_old = logw[ic];
+                lp_old = lp[ic];
+            }
+            asm volatile("" ::: "memory");
+            double z[2];
+            normal_pair_wave(a.seed, tag, a.sampler, tt_, (uint32_t)i, 0u, act, z[0], z[1],
+                             s_xch[tid >> 6]);
+            if (!act) continue;
+            double acc = 0.0, acc0 = 0.0;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                xk[k] = xk[k] + (kInit ? a.init_sd : a.rw_sd) * z[k];
+                const double tt = xk[k] - a.mean[k], t0 = xk[k] - a.init_mean;
+                acc = acc + (tt * tt) * a.prec[k];
+                acc0 = acc0 + (t0 * t0) * a.init_prec;
+            }
+            const double lpn = a.log_norm - 0.5 * acc;
+            const double lw = kInit ? lpn - (a.init_log_norm - 0.5 * acc0) : lw_old + (lpn - lp_old);
+            if (v2) {
+                if (kDst != kToCopy)
+                    *reinterpret_cast<f64x2s *>(x + 2 * i) = f64x2s{xk[0], xk[1]};
+                if (kDst != kInPlace)
+                    *reinterpret_cast<f64x2s *>(xo + 2 * i) = f64x2s{xk[0], xk[1]};
+            } else {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    if (kDst != kToCopy) x[2 * i + k] = xk[k];
+                    if (kDst != kInPlace) xo[2 * i + k] = xk[k];
+                }
+            }
+            if (kDst != kToCopy) lp[i] = lpn;
+            if (kDst != kInPlace) lpo[i] = lpn;
+            logw[i] = lw;
+            note(lw);
+            on.add(lw, xk);
+        }
+    } else if constexpr (!kFilter) {
         // One coordinate a particle: particles 2p and 2p + 1 take the two
         // values of the pair drawn for index p, so each lane draws one pair
         // for two particles (a wave-uniform trip count over the pairs).  The
@@ -618,7 +687,7 @@ __device__ inline double logreg_lp_row(const double *row, int d, double lik, con
     return log_norm - 0.5 * lr.prior_prec * pr + (lik - lr.usc * su);
 }
 
-// The update of particles with d >= 2 coordinates (any d for the logistic
+// The update of particles with d >= 3 coordinates (any d for the logistic
 // regression): rows drawn (Gaussian) or read (logistic regression) into LDS by
 // the whole workgroup, then one thread per particle for the target and weight,
 // then the estimate sums with threads over (column, share of the particles).
@@ -1566,17 +1635,18 @@ hipError_t logreg_lik(const smc_config &c, const Work &w, const double *x, int64
     return hipGetLastError();
 }
 
-template <int kKind, bool kInit>
+template <int kKind, bool kInit, int kD = 1>
 void launch_is_k(dim3 g, hipStream_t s, const TArgs &a, i64 n, uint32_t t, double *x, double *logw,
                  const Work &w, u64 *sp, Dst dst)
 {
-    auto kern = k_is<kKind, kInit, kInPlace>;
+    auto kern = k_is<kKind, kInit, kInPlace, kD>;
     if constexpr (!kInit) {
-        if (dst == kToCopy) kern = k_is<kKind, false, kToCopy>;
+        if (dst == kToCopy) kern = k_is<kKind, false, kToCopy, kD>;
         if constexpr (kKind != SMC_TARGET_BEARING)
-            if (dst == kToBoth) kern = k_is<kKind, false, kToBoth>;
+            if (dst == kToBoth) kern = k_is<kKind, false, kToBoth, kD>;
     }
-    hipLaunchKernelGGL(kern, g, dim3(256), 0, s, a, n, t, x, logw, w.lp, sp, w.is_part, w.x_scr);
+    hipLaunchKernelGGL(kern, g, dim3(256), 0, s, a, n, t, x, logw, w.lp, sp, w.is_part, w.x_scr,
+                       w.lp_scr);
 }
 
 // The same for rows of several coordinates, with their log-targets.
@@ -1606,6 +1676,8 @@ hipError_t launch_is(const smc_config &c, const Work &w, int par, uint32_t t, do
     switch (c.target) {
     case SMC_TARGET_GAUSS:
         if (c.d == 1) launch_is_k<SMC_TARGET_GAUSS, kInit>(g, s, a, n, t, x, logw, w, sp, out);
+        else if (c.d == 2)
+            launch_is_k<SMC_TARGET_GAUSS, kInit, 2>(g, s, a, n, t, x, logw, w, sp, out);
         else launch_rows_k<SMC_TARGET_GAUSS, kInit>(g, s, a, n, t, x, logw, w, sp, out, LrArgs{});
         break;
     case SMC_TARGET_STUDENT:
@@ -1632,11 +1704,11 @@ hipError_t launch_is(const smc_config &c, const Work &w, int par, uint32_t t, do
     return kInit ? launch_fold(w, par, s) : hipSuccess;
 }
 
-template <int kKind>
+template <int kKind, int kD = 1>
 int resident_blocks()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_is<kKind, false, kInPlace>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_is<kKind, false, kInPlace, kD>, 256, 0) !=
         hipSuccess)
         return 0;
     return nb;
@@ -1646,8 +1718,8 @@ int resident_blocks()
 
 int sampler_grid(const smc_config &c)
 {
-    // rows of several coordinates: one workgroup per chunk of rows
-    if (c.target == SMC_TARGET_LOGREG || (c.target == SMC_TARGET_GAUSS && c.d > 1)) {
+    // k_rows: one workgroup per chunk of rows
+    if (c.target == SMC_TARGET_LOGREG || (c.target == SMC_TARGET_GAUSS && c.d > 2)) {
         const int64_t g = row_chunks(c.n, c.d);
         return (int)(g < kIsBlocks ? g : kIsBlocks);
     }
@@ -1657,7 +1729,10 @@ int sampler_grid(const smc_config &c)
         return 0;
     int per_cu = 0;
     switch (c.target) {
-    case SMC_TARGET_GAUSS: per_cu = resident_blocks<SMC_TARGET_GAUSS>(); break;
+    case SMC_TARGET_GAUSS:
+        per_cu = c.d == 1 ? resident_blocks<SMC_TARGET_GAUSS>()
+                          : resident_blocks<SMC_TARGET_GAUSS, 2>();
+        break;
     case SMC_TARGET_STUDENT: per_cu = resident_blocks<SMC_TARGET_STUDENT>(); break;
     case SMC_TARGET_BEARING: per_cu = resident_blocks<SMC_TARGET_BEARING>(); break;
     default: return 0;
