@@ -697,7 +697,12 @@ __global__ __launch_bounds__(256) void k_weights(const Ctrl *ctrl, const double 
     if (ctrl->err_call) return;
     const double m = ctrl->m, Z = ctrl->Z;
     const i64 gtid = (i64)blockIdx.x * 256 + threadIdx.x, gsz = (i64)gridDim.x * 256;
-    for (i64 i = gtid; i < n; i += gsz) w[i] = det_exp(lw[i] - m) / Z;
+    for (i64 i = gtid; i < n; i += gsz) {
+        // the caller's array need not be the one of that decision: a value far above
+        // m gives +inf, a NaN itself
+        const double v = lw[i] - m;
+        w[i] = (v <= 709.0 ? det_exp(v) : (v != v ? v : __builtin_huge_val())) / Z;
+    }
 }
 
 hipError_t launch_weights(const Work &w, const double *lw, int64_t n, double *out, hipStream_t s)
