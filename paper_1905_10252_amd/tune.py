@@ -12,9 +12,9 @@ candidate gives the same bits):
     one bucket at a time with the others at their current choice.
 
 Results are kept in a JSON cache keyed by kernel, knob, bucket, device
-architecture (gcnArchName, e.g. gfx950) and a digest of the workload's
-(N, d) shapes, so a later run on the same device and workload reuses them
-without timing.  The cache file is ``$SMC_TUNE_CACHE`` or
+architecture (gcnArchName, e.g. gfx950), a digest of the workload's (N, d)
+shapes and the version of what a choice means (``RULE``), so a later run on the
+same device and workload reuses them without timing.  The cache file is ``$SMC_TUNE_CACHE`` or
 ``~/.cache/paper_1905_10252_amd/tune.json``.
 """
 from __future__ import annotations
@@ -29,6 +29,10 @@ from . import smc
 
 GROUP_CANDIDATES = (2, 4, 5, 6, 8)
 BUCKETS = 8
+# What a cached choice means, raised with the kernels or the rule that picked it.
+# 2: an aim below the bucket's highest takes the bucket out of the common launch (the
+# entries before, without a version, chose among launches of the bucket's own).
+RULE = 2
 
 
 def _max_waves(bucket: int) -> int:
@@ -70,8 +74,8 @@ def workload_digest(specs) -> str:
 
 
 def key(kernel: str, knob: str, bucket, arch_name: str, digest: str) -> str:
-    return "%s|%s|%s|%s|%s" % (kernel, knob, "all" if bucket is None else bucket, arch_name,
-                               digest)
+    return "%s|%s|%s|%s|%s|rule%d" % (kernel, knob, "all" if bucket is None else bucket, arch_name,
+                                      digest, RULE)
 
 
 def _scratch_batch(specs, dev):
