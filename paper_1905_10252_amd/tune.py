@@ -9,7 +9,8 @@ candidate gives the same bits):
   - ``k_bquad`` / waves, per dimension bucket: the occupancy the target
     kernel of samplers with d in (8 q, 8 q + 8] aims at (1 up to that
     bucket's highest, where the bucket joins the others in one launch), tuned
-    one bucket at a time with the others at their current choice.
+    one bucket at a time with the others at their current choice, the
+    candidates timed in turn.
 
 Results are kept in a JSON cache keyed by kernel, knob, bucket, device
 architecture (gcnArchName, e.g. gfx950), a digest of the workload's (N, d)
@@ -22,6 +23,7 @@ from __future__ import annotations
 import hashlib
 import json
 import os
+import statistics
 
 import torch
 
@@ -29,6 +31,7 @@ from . import smc
 
 GROUP_CANDIDATES = (2, 4, 5, 6, 8)
 BUCKETS = 8
+ROUNDS = 4  # timings of a candidate
 # What a cached choice means, raised with the kernels or the rule that picked it.
 # 2: an aim below the bucket's highest takes the bucket out of the common launch (the
 # entries before, without a version, chose among launches of the bucket's own).
@@ -97,6 +100,29 @@ def _time_steps(b, steps: int) -> float:
     return e0.elapsed_time(e1) / steps
 
 
+def _in_turn(candidates, timing) -> dict:
+    """ROUNDS timings of every candidate, all of them in each round, every other round
+    backwards: the clock's drift over a run (9 % over five timings of one and the
+    same step) then falls on all alike."""
+    candidates = list(candidates)
+    times = {c: [] for c in candidates}
+    for r in range(ROUNDS):
+        for c in candidates if r % 2 == 0 else reversed(candidates):
+            times[c].append(timing(c))
+    return times
+
+
+def _faster_than(top, times: dict):
+    """The fastest candidate that beats `top` by 2 % in the mean of every pair of rounds,
+    forwards and backwards, else `top`.  A lower aim takes its bucket out of the
+    common launch: only for a gain that no drift or stray timing makes up."""
+    def pairs(c):
+        return [times[c][r] + times[c][r + 1] for r in range(0, ROUNDS, 2)]
+    ref = pairs(top)
+    sure = [c for c in times if all(a < 0.98 * b for a, b in zip(pairs(c), ref))]
+    return min(sure, key=lambda c: statistics.median(times[c])) if sure else top
+
+
 def tune_group(specs, *, device=None, steps: int = 3, candidates=GROUP_CANDIDATES,
                use_cache: bool = True) -> dict:
     """``specs``: sampler descriptions (dicts with n, d, mean, chol, seed,
@@ -149,16 +175,11 @@ def tune_buckets(specs, *, device=None, steps: int = 4, pairs: int | None = None
         for q in present:
             b.set_bucket_waves(q, best[q])
         for q in todo:
-            times = {}
-            for w in range(1, _max_waves(q) + 1):
-                b.set_bucket_waves(q, w)
-                times[w] = _time_steps(b, steps)
-            # a lower aim takes the bucket out of the common launch: only for a gain
-            # beyond what two timings of one choice differ by
-            w, top = min(times, key=times.get), _max_waves(q)
-            best[q] = w if times[w] < 0.98 * times[top] else top
+            times = _in_turn(range(1, _max_waves(q) + 1),
+                             lambda w: (b.set_bucket_waves(q, w), _time_steps(b, steps))[1])
+            best[q] = _faster_than(_max_waves(q), times)
             b.set_bucket_waves(q, best[q])
-            ms[q] = times
+            ms[q] = {w: statistics.median(t) for w, t in times.items()}
         del b
         if use_cache:
             data = _load(path)

@@ -51,3 +51,24 @@ def test_entries_of_an_earlier_rule_are_not_reused(clock):
     assert r["best"] == {q: tune._max_waves(q) for q in PRESENT}
     r2 = tune.tune_buckets(SPECS)
     assert r2["cached"] == PRESENT and r2["best"] == r["best"]
+
+
+@pytest.mark.parametrize("drift", [0.97, 0.995, 1.005, 1.03])
+def test_drift_of_the_clock_picks_no_aim(clock, drift):
+    """All aims equal, the step time falling or rising from timing to timing: every bucket
+    stays in the common launch."""
+    clock(lambda b, k: 1.3 * drift ** k)
+    assert tune.tune_buckets(SPECS)["best"] == {q: tune._max_waves(q) for q in PRESENT}
+
+
+def test_one_stray_timing_picks_no_aim(clock):
+    clock(lambda b, k: 0.9 if k % 7 == 3 else 1.0)
+    assert tune.tune_buckets(SPECS)["best"] == {q: tune._max_waves(q) for q in PRESENT}
+
+
+def test_a_faster_aim_is_picked(clock):
+    """Bucket 5 is 6 % faster at an aim of 2, under a drift."""
+    clock(lambda b, k: 1.3 * 1.01 ** k * (0.94 if b.waves.get(5) == 2 else 1.0))
+    r = tune.tune_buckets(SPECS)
+    assert r["best"] == {q: 2 if q == 5 else tune._max_waves(q) for q in PRESENT}
+    assert sorted(r["ms"][5]) == [1, 2, 3]
