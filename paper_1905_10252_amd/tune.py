@@ -4,8 +4,9 @@ Times whole batched steps on the device on a scratch batch holding the
 caller's workload shapes, for the knobs that change only speed (every
 candidate gives the same bits):
 
-  - ``k_bprop`` / unit_pairs: coordinate pairs per proposal work unit (the
-    proposal no longer has units: every candidate takes the same time);
+  - ``k_bprop`` / unit_pairs: coordinate pairs per proposal work unit.  The
+    proposal has no units any more, so the choice is fixed and one timing of the
+    step stands for every candidate;
   - ``k_bquad`` / waves, per dimension bucket: the occupancy the target
     kernel of samplers with d in (8 q, 8 q + 8] aims at (1 up to that
     bucket's highest, where the bucket joins the others in one launch), tuned
@@ -30,6 +31,7 @@ import torch
 from . import smc
 
 GROUP_CANDIDATES = (2, 4, 5, 6, 8)
+GROUP_DEFAULT = 8  # what a batch starts with
 BUCKETS = 8
 ROUNDS = 4  # timings of a candidate
 # What a cached choice means, raised with the kernels or the rule that picked it.
@@ -127,19 +129,16 @@ def tune_group(specs, *, device=None, steps: int = 3, candidates=GROUP_CANDIDATE
                use_cache: bool = True) -> dict:
     """``specs``: sampler descriptions (dicts with n, d, mean, chol, seed,
     sampler_id, rw_sd, init_sd).  Returns {"best": pairs, "ms": {pairs: ms},
-    "cached": bool}."""
+    "cached": bool}.  The library ignores the pairs: "best" is GROUP_DEFAULT where
+    that is a candidate, and every candidate has the same "ms"."""
     dev = torch.device(device or "cuda")
     path, k = cache_path(), key("k_bprop", "unit_pairs", None, arch(dev), workload_digest(specs))
     data = _load(path) if use_cache else {}
     if k in data:
         return {"best": data[k]["best"], "ms": data[k]["ms"], "cached": True}
-    b = _scratch_batch(specs, dev)
-    times = {}
-    for g in candidates:
-        b.set_group(g)
-        times[g] = _time_steps(b, steps)
-    del b
-    best = min(times, key=times.get)
+    candidates = list(candidates)
+    times = dict.fromkeys(candidates, _time_steps(_scratch_batch(specs, dev), steps))
+    best = GROUP_DEFAULT if GROUP_DEFAULT in candidates else candidates[0]
     if use_cache:
         data = _load(path)
         data[k] = {"best": best, "ms": {str(g): t for g, t in times.items()}}

@@ -72,3 +72,14 @@ def test_a_faster_aim_is_picked(clock):
     r = tune.tune_buckets(SPECS)
     assert r["best"] == {q: 2 if q == 5 else tune._max_waves(q) for q in PRESENT}
     assert sorted(r["ms"][5]) == [1, 2, 3]
+
+
+def test_unit_pairs_are_not_chosen_by_timing(clock):
+    """The library ignores the pairs: the timings' noise must not pick among them."""
+    clock(lambda b, k: 1.3 * 0.97 ** k)
+    r = tune.tune_group(SPECS)
+    assert r["best"] == tune.GROUP_DEFAULT and not r["cached"]
+    assert set(r["ms"]) == set(tune.GROUP_CANDIDATES) and len(set(r["ms"].values())) == 1
+    clock(lambda b, k: 1.3 * 1.03 ** k)
+    assert tune.tune_group(SPECS, candidates=(4, 2), use_cache=False)["best"] == 4
+    assert tune.tune_group(SPECS)["cached"]
