@@ -18,7 +18,7 @@ namespace smc {
 // 128-bit products decide the rest, about one value in 2^17.
 constexpr double kSlack = 0x1p-18;
 
-__device__ inline double u64_to_f64(u64 v)
+__host__ __device__ inline double u64_to_f64(u64 v)
 {
     return fma((double)(unsigned)(v >> 32), 0x1p32, (double)(unsigned)v);
 }
@@ -32,10 +32,10 @@ struct AFun {
     u64 S, U;
     double nS, uS;  // N / S and U / S
 
-    __device__ inline u64 at(i64 j) const { return pref[j] + tpre[j >> tsh]; }
+    __host__ __device__ inline u64 at(i64 j) const { return pref[j] + tpre[j >> tsh]; }
 
     // Systematic copies from the fixed-point sum S and the offset U.
-    __device__ inline void set_systematic(u64 S_, u64 U_)
+    __host__ __device__ inline void set_systematic(u64 S_, u64 U_)
     {
         mode = 1;
         S = S_;
@@ -46,7 +46,7 @@ struct AFun {
     }
 
     // A_j + j < k, given the prefix value pj of source j
-    __device__ inline bool pred_at(i64 j, u64 pj, i64 k) const
+    __host__ __device__ inline bool pred_at(i64 j, u64 pj, i64 k) const
     {
         if (mode == 0) return 2 * j + 1 < k;
         if (mode == 2) return (i64)pj + j < k;
@@ -59,13 +59,13 @@ struct AFun {
         return lt128(lhs, rhs);
     }
 
-    __device__ inline bool pred(i64 j, i64 k) const
+    __host__ __device__ inline bool pred(i64 j, i64 k) const
     {
         return pred_at(j, mode == 0 ? 0ull : at(j), k);
     }
 
     // A_j given the prefix value sj of source j
-    __device__ inline unsigned A_of(i64 j, u64 sj) const
+    __host__ __device__ inline unsigned A_of(i64 j, u64 sj) const
     {
         if (mode == 0) return (unsigned)(j + 1);
         if (mode == 2) return (unsigned)sj;
