@@ -167,7 +167,6 @@ struct ScanArgs {
     u64 *out64;         // [n / 64] every 64th tile-local prefix value
     const u64 *slots_p; // max slots of this call's parity (quantise mode)
     unsigned *uniform;  // lazy-reset flag to clear (nullable)
-    int n_tiles;
     StatsArgs st;
     int n_st;           // workgroups ahead of the tiles' that form st
 };
@@ -679,7 +678,6 @@ hipError_t launch_quant_scan(const Work &w, const double *lw, int64_t n, int K, 
     a.out = w.pref;
     a.out64 = w.pref64;
     a.slots_p = w.slots + (par & 1) * kSlots * kSlotStride;
-    a.n_tiles = w.n_tiles;
     a.st = st;
     a.n_st = !st.is_part ? 0 : (st.cols ? (1 + 2 * st.d + kScanWaves - 1) / kScanWaves : 1);
     const bool big = w.tile_shift == kTileShift;
@@ -728,7 +726,6 @@ hipError_t launch_count_scan(const Work &w, const int64_t *ncopies, int64_t n, h
     a.out = w.pref;
     a.out64 = w.pref64;
     a.slots_p = nullptr;
-    a.n_tiles = w.n_tiles;
     auto kern = w.tile_shift == kTileShift ? k_scan<false, 16> : k_scan<false, 4>;
     hipLaunchKernelGGL(kern, dim3(w.n_tiles), dim3(kScanThreads), 0, s, a);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;

@@ -890,13 +890,13 @@ __global__ __launch_bounds__(64) void k_fold_rows(const double *epart, i64 nseg,
 template <int DT>
 __global__ __launch_bounds__(256) void k_post_est(const Ctrl *ctrl, i64 n, int d,
                                                   const double *__restrict__ x,
-                                                  const double *__restrict__ logw, double reset,
+                                                  const double *__restrict__ logw,
                                                   double *is_part)
 {
     __shared__ double s_acc[4][1 + 2 * DT];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const i64 gtid = (i64)blockIdx.x * 256 + tid, gsz = (i64)gridDim.x * 256;
-    const double m = (ctrl->resample && !ctrl->err_call) ? reset : ctrl->m;
+    const double m = ctrl->m;
     double e0 = 0.0, e1[DT], e2[DT];
     for (int k = 0; k < DT; ++k) e1[k] = e2[k] = 0.0;
     for (i64 i = gtid; i < n; i += gsz) {
@@ -1769,7 +1769,7 @@ smc_status step_init(const smc_config &c, const Work &w, int par, double *x, dou
     if (launch_is<true>(c, w, par, 0u, x, logw, s) != hipSuccess) return SMC_E_DEVICE;
     if (c.target == SMC_TARGET_BEARING)  // equal initial weights: sums from the common reference
         hipLaunchKernelGGL(k_post_est<4>, dim3(w.is_grid), dim3(256), 0, s, w.ctrl, (i64)c.n,
-                           c.d, x, logw, -std::log((double)c.n), w.is_part);
+                           c.d, x, logw, w.is_part);
     hipLaunchKernelGGL(k_init_stats, dim3(1), dim3(1024), 0, s, w.ctrl, w.is_part, w.is_grid,
                        c.d, w.rec_num);
     return hipGetLastError() == hipSuccess ? SMC_OK : SMC_E_DEVICE;
