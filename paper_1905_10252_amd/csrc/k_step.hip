@@ -185,9 +185,10 @@ typedef double f64x2s __attribute__((ext_vector_type(2)));
 // Where the proposal goes.  kToCopy: to the workspace copy xo; the
 // redistribution then maps it into x.  kToBoth: to x, and to xo as well, from
 // which a resampling redistribution writes x; an iteration that keeps its
-// weights is then done (the second store rides under the arithmetic; mapping x
-// into a copy and back instead took another pass over the rows each way).
-// kInPlace: to x alone.
+// weights is then done.  The second store costs its bytes in large populations
+// (N = 2^24, one coordinate: 205 us an iteration that keeps its weights, 173 with
+// one store and no redistribution) and saves a resampling iteration two passes over
+// the rows (308 us; 389 with x mapped into a copy and back).  kInPlace: to x alone.
 enum Dst { kInPlace, kToCopy, kToBoth };
 
 // The particle filter's transition of one state and its weight.
@@ -1224,7 +1225,7 @@ typedef double f64x2v __attribute__((ext_vector_type(2)));
 // e^-a = 2^(-k / 2048) e^-r, |r| <= ln 2 / 4096, the first factor from a table of
 // 2048 values (exact to 0.5 ulp, in LDS) and an exponent shift in 32-bit
 // arithmetic, the second 1 - r + r^2 / 2 - r^3 / 6 with the r^4 term folded into
-// r^2 (off by at most 4.3e-18; the constant enters as 1 + e^-a, whose rounding
+// r^2 (off by at most 8.6e-18; the constant enters as 1 + e^-a, whose rounding
 // is 1.1e-16).  Nine FP64 instructions an element instead of nineteen.  The
 // clamp of a (in its high word: infinities and NaN too) keeps the exponent in
 // range; e^-700 adds nothing to 1.
@@ -1779,7 +1780,10 @@ smc_status step_init(const smc_config &c, const Work &w, int par, double *x, dou
 // kernels' 22.5 to 23.5 us (18.5 with one coordinate) at these sizes it takes
 // 6.1 us at N = 256, 7.2 at 1024 and 10.4 at 2048 with one coordinate, 14.8 at
 // N = 2048 with two, 19.2 at 1536 with four, 20.4 at 1024 with six, 20.6 at 512 and
-// 25.0 at 640 with eight; the draws of one compute unit set the line.
+// 25.0 at 640 with eight; the draws of one compute unit set the line.  Above eight
+// coordinates the separate kernels take 17.5 us whatever the few particles, and one
+// workgroup 16 to 17 up to 2 particles of nine or ten, 18 to 20 at 8, 21 to 27 at 64:
+// they go to the separate kernels at every size.
 bool small_path(const smc_config &c)
 {
     if (c.n > kSmallN) return false;
@@ -1930,8 +1934,8 @@ smc_status step_run(const smc_config &c, const Work &w, int K, int par, uint32_t
     const int64_t n = c.n;
     const bool pf = c.target == SMC_TARGET_BEARING;
     // Resampling forced every iteration, and the particle filter (its weights
-    // collapse almost every update, and the expand forms its post-resampling
-    // sums from the rows it writes): the proposal goes to the workspace copy
+    // collapse almost every update, and its redistribution adds up the rows that it
+    // writes): the proposal goes to the workspace copy
     // and the redistribution writes x (an identity copy if the step found an
     // error or kept the weights).  ESS rule: to both, and a resampling
     // redistribution overwrites x.  The logistic regression reads its proposal

@@ -178,12 +178,13 @@ __device__ const __attribute__((address_space(1))) f64x2r *vec_of(const gdouble 
 // 64 new ones at a time, leaves the accepted uniforms in their slots and queues
 // the others in LDS with their next attempt; a queue of 64 makes a trial of its
 // own, and the last ones share the wavefront, floor(64 / pending) lanes trying
-// consecutive attempts of each (the lowest accepted counts).  A block of 512
-// takes about 11 trials; resolving every 64 items at once took 16.5, with an
-// exchange of results each.  The logarithms and roots then run on whole
+// consecutive attempts of each (the lowest accepted counts).  For 64 items that is
+// 1.5 trials in blocks of 256 to 384, 1.9 in blocks of 128 and 2.1 in blocks of 64,
+// where nothing is queued together; resolving every 64 items at once also takes 2.1,
+// with an exchange of results each.  The logarithms and roots then run on whole
 // wavefronts, two items a lane, and rows are read and written in whole lines
 // (finishing each item where it was accepted scattered a fifth of the stores:
-// 630 us against 380 without them, 256-sampler workload).  Bound by vector
+// 630 us against 478, proposal of the 256-sampler workload).  Bound by vector
 // issue.
 constexpr int kDrawBlock = 256;  // where the items wait in a buffer of their own
 constexpr int kDrawQueue = 128;  // entries a wavefront: fewer than 64 before a trial
