@@ -321,7 +321,7 @@ __global__ __launch_bounds__(256) void k_bdraw0(const BSlot *slots, int slot)
 // The random-walk proposal in place, one workgroup per chunk of 256 particles of
 // every sampler in one launch (draw_rows: items spread over the lanes, rows
 // touched in whole lines).  The first workgroup of a tile also clears the
-// tile's lookback word.  Bound by vector issue (95 % busy, 260 vector
+// tile's lookback word.  Bound by vector issue (85 % busy, 260 vector
 // instructions per pair of normals and wavefront): 614 -> 478 us on the
 // 256-sampler workload against units of 256 particles times 8 pairs through an
 // LDS block, each pair's rejections resolved at once.  The same drawing inside
@@ -782,9 +782,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W))) void k
 // The chunks of every bucket at the highest aim, widest rows first, in one launch: a
 // bucket alone makes two to three rounds of workgroups on the chip, the last one
 // mostly empty (2085 workgroups of width 56 on 1024 places): 505 us as eight
-// launches, 439 as one, for the 256-sampler workload.  Bound by the FP64 pipe,
-// which the matrix and vector instructions share (width 56: 48 matrix instructions
-// of 64 cycles and about 300 vector instructions a tile of 16 particles).
+// launches, 439 as one, for the 256-sampler workload.  Matrix unit busy 36 %, vector
+// unit 26 % (the FP64 instructions of both share a pipe; width 56: 48 matrix
+// instructions of 64 cycles and about 300 vector ones a tile of 16 particles), the
+// waves waiting 47 % of their time on the rows.  Held to
+// the 128 VGPRs of four waves a SIMD the widest forms spill 24 bytes a lane.
 struct QuadSpan {
     int end[kBuckets];  // workgroups of the buckets from the widest down, running total
 };

@@ -463,8 +463,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // and written once (kMove false, the last iteration of a call: counted and written
 // as it is, with its reset weight).  The population in between is never stored: 64 bytes a
 // particle less, and a launch (35.0 us at N = 2^20; redistribution 21.6 us and
-// update 25.7 us as kernels of their own).  Bound by vector issue, the normals
-// foremost.  An iteration that kept its weights or found an error moves each
+// update 25.7 us as kernels of their own).  Vector unit busy 55 % of the time (the
+// normals foremost), the waves waiting 37 % of theirs on the segment's phases.  An iteration that kept its weights or found an error moves each
 // particle from its own row, as the separate kernels do.
 struct FilterArgs {
     i64 n;
@@ -632,7 +632,7 @@ inline int64_t row_chunks(int64_t n, int d)
 // the workspace copy.  With d = 1 particles 2p
 // and 2p + 1 take the pair drawn for index p: rows of two values.  65536 particles of
 // 32 coordinates: 16 us (46 with the weights' update in one kernel, pairs resolved one
-// by one), bound by vector issue.
+// by one), vector unit busy 37 % of them in a single round of workgroups.
 template <bool kInit>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_propose(
     TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x, double *__restrict__ xo)
@@ -696,7 +696,9 @@ __device__ inline double logreg_lp_row(const double *row, int d, double lik, con
 // moved only when a weight exceeds it by kOnlineSlack nats.  Rows are touched
 // once in memory; a second pass over the population for the estimates, with
 // the exponential formed again for every coordinate, took 30 of 50 us at
-// N = 300007, d = 10; one pass takes 28.  Bound by vector issue of the normals.
+// N = 300007, d = 10; one pass takes 28, vector unit busy 44 % and the waves waiting
+// 39 % of their time: fewer workgroups than the chip holds at once, so that their
+// phases hardly overlap.
 template <int kKind, bool kInit, Dst kDst>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rows(
     TArgs a, i64 n, uint32_t t, int P, double *__restrict__ x, double *__restrict__ logw,

@@ -184,8 +184,7 @@ __device__ const __attribute__((address_space(1))) f64x2r *vec_of(const gdouble 
 // with an exchange of results each.  The logarithms and roots then run on whole
 // wavefronts, two items a lane, and rows are read and written in whole lines
 // (finishing each item where it was accepted scattered a fifth of the stores:
-// 630 us against 478, proposal of the 256-sampler workload).  Bound by vector
-// issue.
+// 630 us against 478, proposal of the 256-sampler workload; vector unit busy 85 %).
 constexpr int kDrawBlock = 256;  // where the items wait in a buffer of their own
 constexpr int kDrawQueue = 128;  // entries a wavefront: fewer than 64 before a trial
 
