@@ -48,6 +48,9 @@ struct VecT<4> {
     typedef unsigned T;
 };
 
+// Which accesses at a segment's end go past the caches where the others do.
+enum class Tail { kCached, kCachedLoad, kStream };
+
 // Copies np rows [p0, p0 + np) of dst from rows sAnc[] of src, VEC bytes per
 // lane access; consecutive lanes write consecutive addresses.  A thread's
 // chunks are 256 apart, so its (row, column) moves by a constant step and one
@@ -63,15 +66,11 @@ struct VecT<4> {
 // s = 0.5 (HBM read requests are whole 128-byte lines either way).  Where a
 // few sources fill many outputs (heavy degeneracy) the cached reads are
 // faster, the same lines serving the whole segment.
-// kNtTail: so are the rows at the end of the segment, past the last whole round
-// of loads.  The lines they lie in are shared with the next segment, whose
-// workgroup reads them at about the same time: through the caches they come
-// from HBM once (rows of 32 bytes, s = 2, N = 2^23: 110 us streamed, 104 cached).
-// Populations whose prefix fills the memory-side cache by itself (kTailStreamN)
-// take them streamed (N = 2^25: 413 us streamed, 421 cached).
+// kTail: what of that holds for the rows at the end of the segment, past the last
+// whole round of loads (copy_streamed).
 // kPow2: a row's chunks are a power of two up to 256, so a thread's column is
 // fixed.
-template <int VEC, bool kPow2, bool kNtLoad, bool kNtStore, bool kNtTail>
+template <int VEC, bool kPow2, bool kNtLoad, bool kNtStore, Tail kTail>
 __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
                                    unsigned char *__restrict__ dst, int row_bytes, int cpr,
                                    const unsigned *sAnc, i64 p0, int total)
@@ -94,8 +93,8 @@ __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
         }
         return v;
     };
-    auto store = [&](const V &v, int c) {
-        if (kNtStore) __builtin_nontemporal_store(v, d + c);
+    auto store = [&](const V &v, int c, auto nt) {
+        if (decltype(nt)::value) __builtin_nontemporal_store(v, d + c);
         else d[c] = v;
     };
     int c = threadIdx.x;
@@ -104,9 +103,12 @@ __device__ inline void copy_chunks(const unsigned char *__restrict__ src,
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = load(std::bool_constant<kNtLoad>());
 #pragma unroll
-        for (int u = 0; u < U; ++u) store(v[u], c + u * kExpandThreads);
+        for (int u = 0; u < U; ++u)
+            store(v[u], c + u * kExpandThreads, std::bool_constant<kNtStore>());
     }
-    for (; c < total; c += kExpandThreads) store(load(std::bool_constant<kNtTail>()), c);
+    for (; c < total; c += kExpandThreads)
+        store(load(std::bool_constant<kNtLoad && kTail == Tail::kStream>()), c,
+              std::bool_constant<kNtStore && kTail != Tail::kCached>());
 }
 
 // Rows of at least 16 bytes whose size or address is no multiple of 16: 16-byte
@@ -166,18 +168,18 @@ __device__ inline void copy_ragged(const unsigned char *__restrict__ src,
     }
 }
 
-template <int VEC, bool kNtLoad, bool kNtStore, bool kNtTail = false>
+template <int VEC, bool kNtLoad, bool kNtStore, Tail kTail>
 __device__ inline void copy_rows(const unsigned char *__restrict__ src,
                                  unsigned char *__restrict__ dst, int row_bytes,
                                  const unsigned *sAnc, i64 p0, int np)
 {
     const int cpr = row_bytes / VEC;
     if ((cpr & (cpr - 1)) == 0 && cpr <= kExpandThreads)
-        copy_chunks<VEC, true, kNtLoad, kNtStore, kNtTail>(src, dst, row_bytes, cpr, sAnc, p0,
-                                                           np * cpr);
+        copy_chunks<VEC, true, kNtLoad, kNtStore, kTail>(src, dst, row_bytes, cpr, sAnc, p0,
+                                                         np * cpr);
     else
-        copy_chunks<VEC, false, kNtLoad, kNtStore, kNtTail>(src, dst, row_bytes, cpr, sAnc, p0,
-                                                            np * cpr);
+        copy_chunks<VEC, false, kNtLoad, kNtStore, kTail>(src, dst, row_bytes, cpr, sAnc, p0,
+                                                          np * cpr);
 }
 
 struct ExpandArgs {
@@ -200,6 +202,37 @@ struct ExpandArgs {
     unsigned *uniform;  // ... or marked uniform here instead (lazy reset, nullable)
     int stream;         // the new rows are written past the caches
 };
+
+// The rows at a segment's end lie in lines that the next segment's workgroup reads and
+// writes at about the same time, so both go through the caches.  Streamed, they cost up
+// to 9 % of a redistribution of rows of 32 to 96 bytes (rows of 32 bytes, s = 2,
+// N = 2^23: 110 us streamed, 104 read through the caches, 103 written through them
+// too).  That ends where the prefix and such rows no longer share the 256 MB
+// memory-side cache: from 13 to 14 million particles on (kTailStoreN) writing past the
+// caches is faster (the same rows: N = 12 x 10^6 138 us both ways, 15 x 10^6 178 cached
+// and 171 streamed, 2^24 203 and 190), and where the prefix fills that cache
+// (kTailLoadN) reading past them too (N = 2^25: 421 us and 413).
+template <int VEC, int SEG>
+__device__ inline void copy_streamed(const ExpandArgs &a, bool distinct, const unsigned *sAnc,
+                                     i64 p0, int np)
+{
+    auto copy = [&](auto nt, auto tail) {
+        copy_rows<VEC, decltype(nt)::value, true, decltype(tail)::value>(a.x, a.xo, a.row_bytes,
+                                                                         sAnc, p0, np);
+    };
+    const std::bool_constant<true> yes;
+    const std::bool_constant<false> no;
+    if (SEG < kSegLen || a.n < kTailStoreN) {
+        if (distinct) copy(yes, std::integral_constant<Tail, Tail::kCached>());
+        else copy(no, std::integral_constant<Tail, Tail::kCached>());
+    } else if (!distinct) {
+        copy(no, std::integral_constant<Tail, Tail::kCachedLoad>());
+    } else if (a.n < kTailLoadN) {
+        copy(yes, std::integral_constant<Tail, Tail::kCachedLoad>());
+    } else {
+        copy(yes, std::integral_constant<Tail, Tail::kStream>());
+    }
+}
 
 // Bound by HBM for large rows and populations (N = 2^24: 340 us for rows of 64
 // bytes, 351 with A in 128-bit integers; 127 to 133 for rows of 8 with the weights'
@@ -254,16 +287,12 @@ __global__ __launch_bounds__(kExpandThreads) void k_expand(ExpandArgs a)
             copy_ragged<false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
         else
             copy_ragged<false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
-    } else if (a.stream && distinct && SEG == kSegLen && a.n >= kTailStreamN) {
-        copy_rows<VEC, true, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
-    } else if (a.stream && distinct) {
-        copy_rows<VEC, true, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     } else if (a.stream) {
-        copy_rows<VEC, false, true>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        copy_streamed<VEC, SEG>(a, distinct, sAnc, p0, np);
     } else {
-        copy_rows<VEC, false, false>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
+        copy_rows<VEC, false, false, Tail::kCached>(a.x, a.xo, a.row_bytes, sAnc, p0, np);
     }
-    if (a.aux) copy_rows<8, false, false>(a.aux, a.auxo, 8, sAnc, p0, np);
+    if (a.aux) copy_rows<8, false, false, Tail::kCached>(a.aux, a.auxo, 8, sAnc, p0, np);
 }
 
 template <int VEC, bool kRagged = false>

@@ -1,6 +1,6 @@
 """Rows at the ends of the redistribution's segments, for the populations that are
 written past the caches: the rows past a segment's last whole round of loads take
-another route than the others, and a third one from 2^25 particles on."""
+another route than the others, one of three by the population's size."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -16,9 +16,12 @@ def smc():
     ((1 << 20) + 37, 128),     # whole 16-byte chunks, a power of two a row
     (1398101 + 2, 96),         # six chunks a row
     ((1 << 22) + 1, 32),       # two chunks a row
+    ((13 << 20) - 1, 32),      # last size of the cached ends, first of the next route
+    (13 << 20, 32),
+    ((13 << 20) + 7, 48),
     ((1 << 24) + 3, 8),        # 8-byte rows
-    ((1 << 25) - 1, 16),       # last size of the common route
-    (1 << 25, 16),             # first of the other
+    ((1 << 25) - 1, 16),       # last size of that route, first of the third
+    (1 << 25, 16),
     ((1 << 25) + 5, 16),
 ])
 @pytest.mark.parametrize("s", [0.5, 2.0, 8.0])
