@@ -207,11 +207,13 @@ struct ExpandArgs {
 // writes at about the same time, so both go through the caches.  Streamed, they cost up
 // to 9 % of a redistribution of rows of 32 to 96 bytes (rows of 32 bytes, s = 2,
 // N = 2^23: 110 us streamed, 104 read through the caches, 103 written through them
-// too).  That ends where the prefix and such rows no longer share the 256 MB
-// memory-side cache: from 13 to 14 million particles on (kTailStoreN) writing past the
-// caches is faster (the same rows: N = 12 x 10^6 138 us both ways, 15 x 10^6 178 cached
-// and 171 streamed, 2^24 203 and 190), and where the prefix fills that cache
-// (kTailLoadN) reading past them too (N = 2^25: 421 us and 413).
+// too).  That ends where such rows no longer share the 256 MB memory-side cache with the
+// prefix and the counts and ancestors that the call writes.  From two fifths of it on
+// (kTailStoreBytes) writing past the caches is faster (the same rows, no counts:
+// N = 12 x 10^6 138 us both ways, 15 x 10^6 178 cached and 171 streamed, 2^24 203 and
+// 190; with counts, N = 10^7: 164 and 150), and where they fill it (kTailLoadBytes)
+// reading past them too (no counts, N = 2^25: 421 us and 413; resampling and rows of 64
+// bytes with counts, N = 2^24: 454 and 442).
 template <int VEC, int SEG>
 __device__ inline void copy_streamed(const ExpandArgs &a, bool distinct, const unsigned *sAnc,
                                      i64 p0, int np)
@@ -222,12 +224,13 @@ __device__ inline void copy_streamed(const ExpandArgs &a, bool distinct, const u
     };
     const std::bool_constant<true> yes;
     const std::bool_constant<false> no;
-    if (SEG < kSegLen || a.n < kTailStoreN) {
+    const i64 kept = 8 * a.n * (1 + (a.nc_out ? 1 : 0) + (a.anc_out ? 1 : 0));
+    if (SEG < kSegLen || kept < kTailStoreBytes) {
         if (distinct) copy(yes, std::integral_constant<Tail, Tail::kCached>());
         else copy(no, std::integral_constant<Tail, Tail::kCached>());
     } else if (!distinct) {
         copy(no, std::integral_constant<Tail, Tail::kCachedLoad>());
-    } else if (a.n < kTailLoadN) {
+    } else if (kept < kTailLoadBytes) {
         copy(yes, std::integral_constant<Tail, Tail::kCachedLoad>());
     } else {
         copy(yes, std::integral_constant<Tail, Tail::kStream>());

@@ -25,9 +25,9 @@ constexpr int kSegLen = 2048;                     // most merge-path steps per e
 // Populations from this size on are written past the caches by the expand
 // (half of the 256 MB memory-side cache).
 constexpr int64_t kStreamBytes = 128ll << 20;
-// Populations whose prefix array (8 bytes each) takes two fifths of that cache, or all
-// of it (see copy_streamed).
-constexpr int64_t kTailStoreN = 13 << 20, kTailLoadN = 2 * kStreamBytes / 8;
+// What else the expand moves through that cache (its prefix, the counts and ancestors
+// it writes) taking two fifths of it, or all of it (see copy_streamed).
+constexpr int64_t kTailStoreBytes = 104ll << 20, kTailLoadBytes = 2 * kStreamBytes;
 // Largest row of smc_redistribute: a segment's 32-bit chunk count
 // (kSegLen rows of row_bytes / 4 chunks) then stays below 2^31.
 constexpr int kMaxRowBytes = 1 << 20;

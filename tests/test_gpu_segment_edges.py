@@ -26,8 +26,22 @@ def smc():
 ])
 @pytest.mark.parametrize("s", [0.5, 2.0, 8.0])
 def test_streamed_rows(smc, dev, n, row_bytes, s):
+    check(smc, dev, n, row_bytes, s, False)
+
+
+# counts and ancestors written too: three times the bytes, so the lines lie at a third of
+# the populations
+@pytest.mark.parametrize("n,row_bytes", [((1 << 22) + 3, 32), ((13 << 20) // 3, 48),
+                                         ((13 << 20) // 3 + 1, 48), ((1 << 25) // 3, 16),
+                                         ((1 << 25) // 3 + 1, 16)])
+@pytest.mark.parametrize("s", [0.5, 8.0])
+def test_streamed_rows_with_counts_and_ancestors(smc, dev, n, row_bytes, s):
+    check(smc, dev, n, row_bytes, s, True)
+
+
+def check(smc, dev, n, row_bytes, s, outputs):
     import torch
-    print("streamed rows", n, row_bytes, s, flush=True)
+    print("streamed rows", n, row_bytes, s, outputs, flush=True)
     g = torch.Generator(device=dev).manual_seed(n + row_bytes)
     logw = s * torch.randn(n, generator=g, device=dev, dtype=torch.float64)
     x = torch.randint(-2**31, 2**31 - 1, (n, row_bytes // 4), generator=g, device=dev,
@@ -35,7 +49,12 @@ def test_streamed_rows(smc, dev, n, row_bytes, s):
     R = smc.Resampler(n)
     nc = torch.empty(n, dtype=torch.int64, device=dev)
     R.resample(logw, 0x9E3779B97F4A7C15, smc.L.MODE_FORCE, ncopies=nc)
-    got = R.redistribute(x)
+    nco = torch.empty_like(nc) if outputs else None
+    anc = torch.empty_like(nc) if outputs else None
+    got = R.redistribute(x, ncopies_out=nco, anc=anc)
     assert R.sync_error() == 0
+    if outputs:
+        assert torch.equal(nco, nc)
+        assert torch.equal(anc, torch.arange(n, device=dev).repeat_interleave(nc))
     assert int(nc.sum()) == n and int(nc.min()) >= 0
     assert torch.equal(got, x.repeat_interleave(nc, 0))
